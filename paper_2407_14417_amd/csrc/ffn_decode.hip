@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void decode_up_kernel(DevExperts ex, const 
         __syncthreads();
         int sel[MOE_MAX_TOPK];
         float lsel[MOE_MAX_TOPK];
-        gate_select(logit_s, ga.E, k, sel, lsel);
+        gate_select(logit_s, ga.E, k, lane, sel, lsel);
 #pragma unroll
         for (int s = 0; s < MOE_MAX_TOPK; ++s)
             if (s < k) routed |= (uint64_t)(uint32_t)sel[s] << (5 * s);

@@ -72,10 +72,53 @@ __device__ __forceinline__ float gate_logit(const uint4_t (&xv)[NCHUNK], const h
     return wave_total(acc);
 }
 
-// Top-k by k selection passes over the E logits (strict ">" keeps the lower index among equal logits), in
-// descending order of the logit.  Every thread that calls it gets the same result.
-__device__ __forceinline__ void gate_select(const float* __restrict__ logit, int E, int k, int (&sel)[MOE_MAX_TOPK],
-                                            float (&lsel)[MOE_MAX_TOPK]) {
+// The logits of N experts e, e + step, ... (past the last one: e again): every row of the gate matrix is asked for
+// before the first is used, one trip to memory where N calls of gate_logit take N.  Bit for bit gate_logit's results.
+template <int N, int NCHUNK>
+__device__ __forceinline__ void gate_logits(const uint4_t (&xv)[NCHUNK], const half_t* __restrict__ wg, int e, int step,
+                                            int E, int d, int lane, float (&out)[N]) {
+    uint4_t wv[N][NCHUNK];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const int en = e + n * step < E ? e + n * step : e;
+        gate_load_row<NCHUNK>(wg + (size_t)en * d, d, lane, wv[n]);
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NCHUNK; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc = __builtin_amdgcn_fdot2(as_half2(xv[j][i]), as_half2(wv[n][j][i]), acc, false);
+        out[n] = wave_total(acc);
+    }
+}
+
+// Top-k in descending order of the logit, the lower index first among equal logits, by a whole wavefront: lane e
+// counts the experts that go before expert e, and the expert of rank s is found with a ballot.  Every lane of the
+// wavefront gets the same result.  (With one thread that makes k passes over the E logits in LDS, and one row of the
+// gate matrix per trip to memory, the gating kernel took 22.9 us for 500 tokens, E = 32, k = 8, d_model 2048; 9.9 us
+// now.)  A NaN has no rank: such logits take the passes, in which a NaN is chosen exactly when it is the first expert
+// left.
+__device__ __forceinline__ void gate_select(const float* __restrict__ logit, int E, int k, int lane,
+                                            int (&sel)[MOE_MAX_TOPK], float (&lsel)[MOE_MAX_TOPK]) {
+    const float l = lane < E ? logit[lane] : 0.0f;
+    if (!__ballot(l != l)) {
+        int rank = lane < E ? 0 : MOE_MAX_EXPERTS;
+        for (int e = 0; e < E; ++e) {
+            const float le = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), e));
+            rank += (le > l || (le == l && e < lane)) ? 1 : 0;
+        }
+#pragma unroll
+        for (int s = 0; s < MOE_MAX_TOPK; ++s) {
+            if (s < k) {
+                sel[s] = __builtin_ctzll(__ballot(rank == s));
+                lsel[s] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), sel[s]));
+            }
+        }
+        return;
+    }
     uint32_t taken = 0;
 #pragma unroll
     for (int s = 0; s < MOE_MAX_TOPK; ++s) {
@@ -84,8 +127,8 @@ __device__ __forceinline__ void gate_select(const float* __restrict__ logit, int
             float lb = 0.0f;
             for (int e = 0; e < E; ++e) {
                 if (taken & (1u << e)) continue;
-                const float l = logit[e];
-                if (best < 0 || l > lb) { best = e; lb = l; }
+                const float v = logit[e];
+                if (best < 0 || v > lb) { best = e; lb = v; }
             }
             taken |= 1u << best;
             sel[s] = best;

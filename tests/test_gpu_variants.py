@@ -62,3 +62,54 @@ def test_quantizer_wide_loads_equal_narrow_loads(orc, bits, shape):
             ref = orc.quantize_int4(w) if bits == 4 else orc.quantize_int8(w)
             assert np.array_equal(wide[0], ref.data)
             assert np.array_equal(wide[1], ref.scale.view(np.uint16)) and np.array_equal(wide[2], ref.zero.view(np.uint16))
+
+
+# ---------------------------------------------------------------- gating and grouping
+
+def _routing_layer(wg, k):
+    ex = [mm.Expert(mm.PREC_FP16, None, None, None, resident=False) for _ in range(wg.shape[0])]
+    return mm.Layer(wg.shape[1], 64, k, dev(wg), ex)
+
+
+@pytest.mark.parametrize("E,k,T", [(32, 8, 128), (32, 8, 129), (32, 1, 63), (1, 1, 65), (31, 7, 2341)])
+def test_permute_runs_of_every_length(orc, E, k, T):
+    """16 runs of whole groups of 64 pairs: exactly one group each, one more, a single ragged one, long runs."""
+    rng = np.random.default_rng(E * 100 + T)
+    idx = rng.integers(0, E, (T, k)).astype(np.int32) if T % 2 else np.sort(rng.integers(0, E, (T, k)), axis=0).astype(np.int32)
+    layer = _routing_layer(np.zeros((E, 64), np.float16), k)
+    ws = mm.alloc_workspace(layer, T)
+    counts, offsets, perm = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * k))
+    mm.moe_permute(layer, dev(idx), counts, offsets, perm, ws)
+    for got, ref in zip((counts, offsets, perm), orc.permute(idx, E)):
+        assert np.array_equal(got.cpu().numpy(), ref)
+    assert mm.moe_read_status(ws) == 0
+
+
+def _selection_passes(logits, k):
+    """k passes over the logits, each taking the first of the largest that are left; a NaN never compares larger, so
+    it is taken exactly when it is the first one left."""
+    left, out = list(range(len(logits))), []
+    for _ in range(k):
+        best = left[0]
+        for e in left[1:]:
+            if logits[e] > logits[best]:
+                best = e
+        left.remove(best)
+        out.append(best)
+    return out
+
+
+@pytest.mark.parametrize("T", [1, 3])
+@pytest.mark.parametrize("d,E,k", [(64, 32, 8), (2048, 8, 2), (4160, 5, 3), (8192, 13, 4)])
+def test_route_infinite_and_nan_logits(T, d, E, k):
+    """Router rows with one non-zero column, so that every logit is one product: infinities, NaN and ties."""
+    values = np.array([1.0, np.nan, -np.inf, 2.0, np.inf, 2.0, np.nan, -3.0], np.float16)
+    wg = np.zeros((E, d), np.float16)
+    wg[:, d - 1] = np.resize(values, E)
+    x = np.zeros((T, d), np.float16)
+    x[:, d - 1] = [1.0, -1.0, 0.5][:T]
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    gate = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    mm.moe_route(_routing_layer(wg, k), dev(x), idx, gate)
+    for t in range(T):
+        assert idx[t].tolist() == _selection_passes((x[t, d - 1].astype(np.float32) * wg[:, d - 1].astype(np.float32)).tolist(), k)
