@@ -12,8 +12,8 @@
 // mantissa of an fp16 constant, the constant subtracted, one packed fp16 multiply-add with the group's scale and
 // zero); 8-bit codes likewise, with a byte permute in place of the masks.
 // Four bodies, chosen per chunk:
-//   tile_body    launches with chunks of at most 64 rows, ranges with an odd number of 128-column steps, 8-bit
-//                experts, one-tile chunks.  Weights are read in whole 128-byte lines (8 lanes per row, 8 rows per
+//   tile_body    launches with chunks of at most 64 rows, ranges with an odd number of 128-column steps or half a
+//                step at the end, 8-bit experts, one-tile chunks.  Weights are read in whole 128-byte lines (8 lanes per row, 8 rows per
 //                load instruction, streamed) and turned into operand layout through a small wavefront-private LDS
 //                region; activations as a [16*CT, 128*SPB] tile per stage, double-buffered, one barrier per stage.
 //   direct_body  16-bit experts in launches with 128-row chunks: weights straight into operand registers, chunks of
@@ -77,6 +77,9 @@ __device__ __forceinline__ float4_t mfma16(half8_t a, half8_t b, float4_t c) {
 // Nothing moves across this point when the compiler schedules instructions: the pipelined bodies below lay out
 // their loads, LDS accesses and products by hand.
 __device__ __forceinline__ void pin_schedule() { __builtin_amdgcn_sched_barrier(0); }
+
+// Two neighbouring scales or zeros: rows of an odd number of them start on 2-byte boundaries.
+typedef uint32_t __attribute__((aligned(2))) uint32_half_aligned_t;
 
 // The same product with the accumulator tied to one register tuple by construction: in long straight-line loops the
 // compiler otherwise unties some products (writes the sum to a new tuple), leaves every accumulator somewhere else
@@ -144,7 +147,8 @@ struct TileCtx {
     int K, N;
     int begin, m0, rows;     // grouped rows [begin + m0, begin + m0 + rows)
     int n0;                  // first weight row of the workgroup
-    int k_begin, n_steps;    // contraction range [k_begin, k_begin + 128 n_steps)
+    int k_begin, n_steps;    // contraction range [k_begin, k_begin + 128 n_steps), up to the end of the rows
+    bool tail;               // the last step holds 64 columns: the range ends with rows of an odd multiple of 64
     int rot;                 // the workgroup walks the range from step rot on, wrapping around (a multiple of 4; see below)
     int mc;                  // rows per LDS buffer (16 * ct of the launch)
     int unit_bytes;          // LDS bytes per A operand of the weight staging regions (2048: 4-bit only, 4096)
@@ -195,7 +199,12 @@ __device__ __forceinline__ void store_results(const TileCtx& c, const float4_t (
 // NCT = 16-row activation tiles computed (exactly the tiles that hold rows), so the inner loops are
 // straight-line code.  SPB = 128-column steps per LDS stage (and per barrier): a launch with few activation
 // rows per chunk stages more columns at a time, so that the LDS buffers always hold 128 x 128 elements.
-template <bool UP, int PREC, int NCT, int SPB, int NA>   // PREC: moe_prec of the expert
+// HALF: rows of an odd multiple of 64 columns.  The last step of the row (c.tail) is half a step: activations past the
+// end are zero in LDS, loads past the end of a row repeat its last pieces, and the other operand of those products is
+// zero too (quantized weights: the scale and zero of the absent group are zero words out of the byte permute, which
+// costs nothing) or the products are left out (16-bit weights: the last two of four sub-steps), so that neither an
+// infinity next door nor one in the repeated piece reaches a sum.
+template <bool UP, int PREC, int NCT, int SPB, int NA, bool HALF = false>   // PREC: moe_prec of the expert
 __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee, void* out_base) {
     constexpr bool INT4 = PREC == MOE_PREC_INT4G64, INT8 = PREC == MOE_PREC_INT8G64, QUANT = INT4 || INT8;
     constexpr int NT = UP ? 32 * NA : 64 * NA;     // weight rows per workgroup: 16 NA / (matrices) per wavefront
@@ -223,19 +232,25 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         xoff[i] = src * (uint32_t)K * 2 + (pcol & 15) * 16;
     }
     uint4_t xr[NP];
+    const bool tail = HALF && c.tail;
+    bool xpast = false;                                // the pieces in xr lie past the end of the rows
     auto load_x = [&](int stage) {
         int step = stage * SPB + pstep;
         step = step < last ? step : last;
         step = step + c.rot < n_steps ? step + c.rot : step + c.rot - n_steps;
+        if (HALF) xpast = tail && step == last && (pcol & 8);
+        const int byte = step * (kKTile * 2) - (HALF && xpast ? kKTile : 0);
 #pragma unroll
-        for (int i = 0; i < NP; ++i)
-            xr[i] = *(const uint4_t MOEMIX_GLOBAL*)(xbase + step * (kKTile * 2) + fresh_offset(xoff[i]));
+        for (int i = 0; i < NP; ++i) {
+            if (HALF) xr[i] = *(const uint4_t MOEMIX_GLOBAL*)(xbase + fresh_offset(xoff[i] + byte));
+            else xr[i] = *(const uint4_t MOEMIX_GLOBAL*)(xbase + step * (kKTile * 2) + fresh_offset(xoff[i]));
+        }
     };
     auto store_x = [&](int buf) {
         uint8_t* base = c.lds + buf * buf_bytes + (tid / PPR) * kStride + pcol * 16;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            uint4_t v = xr[i];
+            uint4_t v = HALF && xpast ? uint4_t{0u, 0u, 0u, 0u} : xr[i];
             if (INT4) {   // element order (0,4,1,5,2,6,3,7) inside each group of 8, as expand_word delivers codes
                 const half8_t h = __builtin_bit_cast(half8_t, v);
                 v = __builtin_bit_cast(uint4_t, half8_t{h[0], h[4], h[1], h[5], h[2], h[6], h[3], h[7]});
@@ -283,13 +298,25 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     // scale loads and the place of the barriers are compile-time constants.
     constexpr int G = SPB > 4 ? SPB : 4;
     uint32_t sz_cur[NA][2], sz_next[NA][2];
-    const uint32_t sel = (c4 >> 1) ? 0x03020302u : 0x01000100u;   // which of the two groups of a 128-column step
+    const uint32_t sel_full = (c4 >> 1) ? 0x03020302u : 0x01000100u;   // which of the two groups of a 128-column step
+    // half a step: its group is the second of the two words fetched for it (load_sz), the other one is absent (the
+    // permute's selector 0x0C is a zero byte)
+    const uint32_t sel_tail = (c4 >> 1) ? 0x0C0C0C0Cu : 0x03020302u;
     const uint32_t m1024 = vreg_const(0x64006400u), m64 = vreg_const(INT8 ? 0x64646464u : 0x54005400u);
     // scales and zeros of four steps with one load: lane (r16, c4) fetches the pair of groups of step 4 S + c4
     auto load_sz = [&](uint32_t (&dst)[NA][2], int S) {
         int step = 4 * S + c4;
         step = step < last ? step : last;
         step = step + c.rot < n_steps ? step + c.rot : step + c.rot - n_steps;
+        if (HALF) {                                    // (the pair of half a step starts one group earlier)
+            const uint32_t byte = step * 4 - (tail && step == last ? 2 : 0);
+#pragma unroll
+            for (int t = 0; t < NA; ++t) {
+                dst[t][0] = *(const uint32_half_aligned_t MOEMIX_GLOBAL*)(sbase[t] + fresh_offset(soff[t] + byte));
+                dst[t][1] = *(const uint32_half_aligned_t MOEMIX_GLOBAL*)(zbase[t] + fresh_offset(soff[t] + byte));
+            }
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < NA; ++t) {
             dst[t][0] = *(const uint32_t MOEMIX_GLOBAL*)(sbase[t] + step * 4 + fresh_offset(soff[t]));
@@ -301,7 +328,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     // steps 16 S + 4 c4 .. + 3), so a row's 128-byte line of scales is asked for in two 64-byte requests instead of
     // eight of 16 bytes; with the narrow requests the lines left L2 between requests and a launch fetched 29 % more
     // than its algorithmic bytes.
-    constexpr bool kWideSz = INT4 && NA == kNASmall;
+    constexpr bool kWideSz = INT4 && NA == kNASmall && !HALF;
     const bool wide_sz = kWideSz && !(n_steps & 3) && sz_aligned16;
     uint4_t sq_cur[NA][2], sq_next[NA][2];
     auto load_sq = [&](uint4_t (&dst)[NA][2], int S) {
@@ -342,6 +369,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     const int w_wr = (lane >> 3) * UB + (((lane & 7) ^ (lane >> 3)) * 16);
     const int w_rd = r16 * UB;
     const int last_unit = INT4 ? (n_steps + 1) / 2 - 1 : n_steps - 1;
+    const int row_end = (INT4 ? (K - c.k_begin) >> 1 : INT8 ? K - c.k_begin : 2 * (K - c.k_begin)) - 16;   // the row's last piece
 #pragma unroll
     for (int t = 0; t < NA; ++t) {
         const int tile = UP ? (t >> 1) : t;
@@ -365,7 +393,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         }
         // 4-bit, odd number of steps: the last pair's second half would leave the row only in the last row of the
         // last split, so the pair is moved back by one step there (its second half is then never used)
-        const int byte0 = (!INT4 || 2 * unit + 2 <= n_steps) ? unit * UB : unit * UB - 64;
+        const int byte0 = (HALF || !INT4 || 2 * unit + 2 <= n_steps) ? unit * UB : unit * UB - 64;
 #pragma unroll
         for (int t = 0; t < NA; ++t)
 #pragma unroll
@@ -373,8 +401,11 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
 #pragma unroll
                 for (int q = 0; q < UL; ++q)
                 {
+                    // (HALF: pieces past the end of the row repeat its last one)
+                    const int lp = (lane & 7) * 16, at = byte0 + q * 128 + lp;
                     const uint4_t MOEMIX_GLOBAL* src =
-                        (const uint4_t MOEMIX_GLOBAL*)(cbase[t] + (byte0 + q * 128) + fresh_offset(goff[t][hb]));
+                        HALF ? (const uint4_t MOEMIX_GLOBAL*)(cbase[t] + fresh_offset(goff[t][hb] + (at < row_end ? at : row_end) - lp))
+                             : (const uint4_t MOEMIX_GLOBAL*)(cbase[t] + (byte0 + q * 128) + fresh_offset(goff[t][hb]));
                     // launches with many activation rows per expert run several chunks of one expert side by side on
                     // the same XCD: the second reader of a weight line should find it in L2, so the line is not
                     // marked as used once there
@@ -394,7 +425,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     };
     auto lds_to_operands = [&](int unit) {
         // (4-bit: for the moved-back last pair of an odd range the wanted step sits in the second half)
-        const int shift = (!INT4 || 2 * unit + 2 <= n_steps) ? 0 : 4;
+        const int shift = (HALF || !INT4 || 2 * unit + 2 <= n_steps) ? 0 : 4;
 #pragma unroll
         for (int t = 0; t < NA; ++t)
 #pragma unroll
@@ -421,6 +452,8 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         for (int g = 0; g < G; ++g) {
             const int step = base + g;
             if (step < n_steps) {                                   // uniform; false only in the last group
+                const bool half_step = HALF && tail && step == last;
+                const uint32_t sel = half_step ? sel_tail : sel_full;
                 const int stage = step / SPB;
                 const uint8_t* xb = c.lds + (stage & 1) * buf_bytes + b_lane + (g % SPB) * (kKTile * 2);
                 if (g % SPB == 0) {
@@ -522,6 +555,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
                     lds_to_operands(step);
 #pragma unroll
                     for (int sb = 0; sb < 4; ++sb) {
+                        if (HALF && sb == 2 && half_step) break;
 #pragma unroll
                         for (int j2 = 0; j2 < NCT; ++j2) {
                             const half8_t b = *(const half8_t*)(xb + j2 * 16 * kStride + sb * b_sub);
@@ -1209,7 +1243,11 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
 // WIDE: the block holds 8-bit experts as well.  The 8-bit body needs more registers than the other two, and a
 // kernel's register count is that of its largest body, so blocks without 8-bit experts get a kernel without it
 // (and keep four wavefronts per SIMD at few rows per expert).  The wide kernel has bodies for 1, 2, 4 and 8 tiles.
-template <bool UP, int CT, bool WIDE>
+// HALF: contraction lengths that are odd multiples of 64, tile_body only, all precisions.  (A wavefront per weight row
+// with scalar products, which is what such widths had, took 296 + 190 us for 33 tokens, 4 of 32 experts, d_model and
+// d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
+// a time and 4-bit rows whose 128-byte requests straddle two lines.)
+template <bool UP, int CT, bool WIDE, bool HALF>
 __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int MC = 16 * CT;                  // activation rows per chunk
     constexpr int NA = CT <= 2 ? kNASmall : 4;   // A operands per wavefront
@@ -1235,9 +1273,10 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
 
     // ---- which expert, which rows.  Chunks hold at most MC rows, those of 16-bit experts in launches with 128-row
     // chunks up to kDirectRows (direct_body), split evenly in whole tiles.
-    const int n_steps = a.k_per_split / kKTile;
+    const int k_begin = split_z * a.k_per_split;
+    const int n_steps = HALF ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
     // (launches with 128-row chunks have LDS for two 256-row stages)
-    const bool wide_ok = CT >= 8 && !(n_steps & 1);
+    const bool wide_ok = !HALF && CT >= 8 && !(n_steps & 1);
     // (4-bit chunks of more than 128 rows save compute-unit time, not latency: one expert alone whose launch does not
     // fill the chip twice over is faster with more, smaller workgroups side by side -- 148 rows: 73 us in chunks of
     // 128 + 20 rows, 89 us in one chunk)
@@ -1273,8 +1312,9 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     c.begin = begin;
     c.rows = min(per, cnt - c.m0);
     c.n0 = tile_x * NT;
-    c.k_begin = split_z * a.k_per_split;
+    c.k_begin = k_begin;
     c.n_steps = n_steps;
+    c.tail = HALF && k_begin + n_steps * kKTile > a.K;
     // Workgroups that work on different weight rows start at different places of the contraction range and wrap
     // around: walking it in step, every workgroup of the launch would ask for the same columns of rows that lie a
     // power of two apart at the same time, which lands on a fraction of the memory channels (measured with a bare
@@ -1285,7 +1325,7 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     // prone to the effect): one per expert and contraction split, so that the workgroups which share a slice of the
     // hidden rows walk it in step and find it in L2 (fetched bytes of the prefill down-projection: 1060 MB with one
     // starting place per tile, 781 MB per slice, 637 MB with the slice's workgroups on two XCDs as well).
-    c.rot = (c.n_steps & 3) ? 0 : 4 * ((UP ? tile_x * 5 : e * 3 + split_z * 5) % (c.n_steps >> 2));
+    c.rot = (HALF || (c.n_steps & 3)) ? 0 : 4 * ((UP ? tile_x * 5 : e * 3 + split_z * 5) % (c.n_steps >> 2));
     c.mc = MC;
     c.unit_bytes = a.unit_bytes;
     c.lds = lds;
@@ -1309,12 +1349,12 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     // the smaller launches from instantiating bodies they never run)
 #define MOEMIX_BODY(n)                                                                                          \
     do {                                                                                                        \
-        if (prec == MOE_PREC_INT4G64) tile_body<UP, MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA>(c, ee, out_base); \
-        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA>(c, ee, out_base); \
-        else tile_body<UP, MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA>(c, ee, out_base);                    \
+        if (prec == MOE_PREC_INT4G64) tile_body<UP, MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
+        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
+        else tile_body<UP, MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base);                    \
     } while (0)
-#define MOEMIX_DIRECT(n) direct_body<UP, CT >= 8 ? (n) : 8>(c, ee, out_base)
-    if (CT >= 8 && wide_ok && prec == MOE_PREC_FP16 && nct >= kDirectNCT) {
+#define MOEMIX_DIRECT(n) direct_body<UP, CT >= 8 && !HALF ? (n) : 8>(c, ee, out_base)
+    if (!HALF && CT >= 8 && wide_ok && prec == MOE_PREC_FP16 && nct >= kDirectNCT) {
         switch (nct) {
             case 5: MOEMIX_DIRECT(5); break;
             case 6: MOEMIX_DIRECT(6); break;
@@ -1332,9 +1372,9 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
         return;
     }
 #undef MOEMIX_DIRECT
-#define MOEMIX_QUANT4(n) quant4_body<UP, CT >= 8 ? (n) : 8>(c, ee, out_base)
-#define MOEMIX_QUANT4W(n) quant4_wide_body<UP, CT >= 8 ? (n) : 12>(c, ee, out_base)
-    if (quant4_ok && prec == MOE_PREC_INT4G64 && nct >= 2) {
+#define MOEMIX_QUANT4(n) quant4_body<UP, CT >= 8 && !HALF ? (n) : 8>(c, ee, out_base)
+#define MOEMIX_QUANT4W(n) quant4_wide_body<UP, CT >= 8 && !HALF ? (n) : 12>(c, ee, out_base)
+    if (!HALF && CT >= 8 && quant4_ok && prec == MOE_PREC_INT4G64 && nct >= 2) {
         switch (nct) {
             case 2: MOEMIX_QUANT4(2); break;
             case 3: MOEMIX_QUANT4(3); break;
@@ -1369,12 +1409,12 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
 #undef MOEMIX_BODY
 }
 
-template <bool UP, int CT, bool WIDE>
+template <bool UP, int CT, bool WIDE, bool HALF>
 void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr int NA = CT <= 2 ? kNASmall : 4;
     // activation stages + 4 wavefronts x NA operands of weight staging
     // (launches with 128-row chunks: at least two unpadded 256-row stages for the pipelined bodies)
-    constexpr size_t lds_wide = CT >= 8 ? 2u * kDirectRows * kKTile * 2 : 0;
+    constexpr size_t lds_wide = CT >= 8 && !HALF ? 2u * kDirectRows * kKTile * 2 : 0;
     const size_t lds_max = 2u * 16 * CT * (spb_for(CT) * kKTile * 2 + 16) + 4 * NA * 4096;
     const size_t lds_plain = 2u * 16 * CT * (spb_for(CT) * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
     const size_t lds_bytes = lds_plain > lds_wide ? lds_plain : lds_wide;
@@ -1385,20 +1425,20 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     (void)hipGetDevice(&dev);
     const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
     if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
-        (void)hipFuncSetAttribute((const void*)grouped_mfma_kernel<UP, CT, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds_max);
         configured.fetch_or(bit, std::memory_order_relaxed);
     }
-    grouped_mfma_kernel<UP, CT, WIDE><<<grid, 256, lds_bytes, st>>>(a);
+    grouped_mfma_kernel<UP, CT, WIDE, HALF><<<grid, 256, lds_bytes, st>>>(a);
 }
 
-template <bool UP, bool WIDE>
+template <bool UP, bool WIDE, bool HALF>
 void launch_ct_w(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
     switch (ct) {
-        case 1: launch_one<UP, 1, WIDE>(a, grid, st); break;
-        case 2: launch_one<UP, 2, WIDE>(a, grid, st); break;
-        case 4: launch_one<UP, 4, WIDE>(a, grid, st); break;
-        default: launch_one<UP, 8, WIDE>(a, grid, st); break;
+        case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
+        case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
+        case 4: launch_one<UP, 4, WIDE, HALF>(a, grid, st); break;
+        default: launch_one<UP, 8, WIDE, HALF>(a, grid, st); break;
     }
 }
 
@@ -1421,8 +1461,9 @@ bool any_int8(const DevExperts& ex, int E) {
 
 template <bool UP>
 void launch_ct(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
-    if (any_int8(a.ex, a.E)) launch_ct_w<UP, true>(a, ct, grid, st);
-    else launch_ct_w<UP, false>(a, ct, grid, st);
+    if (a.K % kKTile) launch_ct_w<UP, true, true>(a, ct, grid, st);
+    else if (any_int8(a.ex, a.E)) launch_ct_w<UP, true, false>(a, ct, grid, st);
+    else launch_ct_w<UP, false, false>(a, ct, grid, st);
 }
 
 // Weight staging needs 4 KB of LDS per A operand for 16-bit experts, 2 KB for 4-bit ones.
@@ -1446,7 +1487,7 @@ int chunk_slots(const RowMap& rows, int P, int E, int ct) {
 // every contraction range must hold at least two 128-column steps (4-bit codes are fetched in pairs of steps)
 // (and a weight matrix spans less than 4 GB: rows are addressed with 32-bit byte offsets from the matrix)
 bool mfma_shape_ok(int d, int f) {
-    return d % kKTile == 0 && f % kKTile == 0 && d >= 2 * kKTile && f >= 2 * kKTile && (uint64_t)d * (uint64_t)f * 2u < (1ull << 32);
+    return d % kGroup == 0 && f % kGroup == 0 && d >= 2 * kKTile && f >= 2 * kKTile && (uint64_t)d * (uint64_t)f * 2u < (1ull << 32);
 }
 
 // The kernels address the rows of their input (tokens, hidden rows) with 32-bit byte offsets from its start.
@@ -1459,12 +1500,15 @@ MfmaPlan plan_mfma(int P, int d, int f, int E) {
     const int avg = (P + E - 1) / E;              // rows per expert if the load were even
     p.ct = avg <= 16 ? 1 : avg <= 32 ? 2 : avg <= 64 ? 4 : 8;
     // down-projection: split the contraction until there are enough workgroups for 256 compute units
-    const int steps = f / kKTile;
+    const int steps = (f + kKTile - 1) / kKTile;
     const int down_rows = 64 * (p.ct <= 2 ? kNASmall : 4);
     const int base = ((d + down_rows - 1) / down_rows) * (P / (16 * p.ct) + 1);
     int best = 1, best4 = 0;
     for (int s = 1; s <= 16; ++s)
-        if (steps % s == 0 && steps / s >= 2 && base * s <= 640) {
+        // (widths that are no multiple of 128: no more scratch than fits the library's own, so that a block which fits
+        // with one range per row still does)
+        if (steps % s == 0 && steps / s >= 2 && base * s <= 640 &&
+            (s == 1 || !((d | f) % kKTile) || (size_t)P * ((size_t)4 * s * d + 2 * d + 2 * f + 64) + 4096 <= MOE_STATIC_SCRATCH_BYTES)) {
             best = s;
             if ((steps / s) % 4 == 0) best4 = s;
         }
@@ -1495,7 +1539,7 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     MfmaArgs a;
     a.ex = ex; a.offsets = rows.offsets; a.perm = nullptr; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
-    a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = f / splits; a.split_stride = split_stride;
+    a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = (f + kKTile - 1) / kKTile / splits * kKTile; a.split_stride = split_stride;
     a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     launch_order(ex, E, ct, a.order);

@@ -31,7 +31,7 @@ void launch_ffn_up(const DevExperts& ex, int E, const RowMap& rows, const half_t
 void launch_ffn_down(const DevExperts& ex, int E, const RowMap& rows, const half_t* h, int d, int f, float* y,
                      int32_t* status, hipStream_t st);
 
-// Matrix-core path for many rows (contraction lengths multiples of 128).  `ct` = 16-row activation tiles per
+// Matrix-core path for many rows (contraction lengths multiples of 64, at least 256).  `ct` = 16-row activation tiles per
 // chunk (1, 2, 4 or 8); the down-projection splits the contraction `splits` ways and writes one partial
 // y per split (`split_stride` elements apart), which launch_combine adds up.
 struct MfmaPlan {

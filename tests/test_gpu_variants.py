@@ -7,7 +7,9 @@ import pytest
 import torch
 
 from paper_2407_14417_amd import binding as mm, synth
-from tests.gpu_common import dev
+from tests import common
+from tests.common import assert_ffn_close, build_workload
+from tests.gpu_common import dev, device_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -113,3 +115,58 @@ def test_route_infinite_and_nan_logits(T, d, E, k):
     mm.moe_route(_routing_layer(wg, k), dev(x), idx, gate)
     for t in range(T):
         assert idx[t].tolist() == _selection_passes((x[t, d - 1].astype(np.float32) * wg[:, d - 1].astype(np.float32)).tolist(), k)
+
+
+# ---------------------------------------------------------------- blocks
+
+def _run_block(layer, x, k):
+    T, d = x.shape
+    out = torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda")
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    gate = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    ws = torch.full((mm.workspace_bytes(layer, T),), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever it is floats
+    mm.moe_layer_forward(layer, dev(x), out, ws, idx, gate)
+    assert mm.moe_read_status(ws) == 0
+    return out.cpu().numpy(), idx.cpu().numpy(), gate.cpu().numpy()
+
+
+def _check_block(orc, cfg):
+    print(cfg.name, flush=True)
+    wl = build_workload(cfg, orc)
+    out, idx, gate = _run_block(device_layer(wl), wl.x, cfg.k)
+    ref, ref_idx, ref_gate = orc.layer_forward(wl.x, wl.wg, wl.experts, cfg.k, bias=wl.bias)
+    assert np.array_equal(idx, ref_idx)
+    assert np.allclose(gate, ref_gate, rtol=0, atol=2e-6)
+    assert_ffn_close(out, ref, cfg.name)
+
+
+# Contractions that end with half a step of 128 columns (odd multiples of 64): in the up-projection, in the
+# down-projection (one range of an odd and of an even number of steps, several ranges of which the last ends early),
+# in both; 16, 32, 64 and 128 rows per chunk; every precision.
+@pytest.mark.parametrize("d,f", [(320, 512), (512, 320), (448, 960), (320, 1472), (832, 2752), (8128, 256), (256, 16320)])
+@pytest.mark.parametrize("T,zipf", [(2, None), (40, None), (75, 1.2), (150, None), (300, 2.0)])
+def test_block_widths_of_odd_multiples_of_64(orc, d, f, T, zipf):
+    if d * f > 500000 and T != 40:
+        return
+    _check_block(orc, common.Config(f"half_d{d}_f{f}_T{T}", d, f, 5, 2, T, (0, 3), zipf=zipf, int8_experts=(1, 4)))
+
+
+@pytest.mark.parametrize("bits", [4, 8, 16])
+def test_half_step_keeps_neighbours_apart(orc, bits):
+    """A row's end is the next row's start in memory: infinities at the start of a token, of a hidden row and of a
+    weight row stay with their token and their output column."""
+    d, f, T = 320, 448, 6
+    quant = {4: dict(int4_experts=(0,)), 8: dict(int4_experts=(), int8_experts=(0,)), 16: dict(int4_experts=())}[bits]
+    wl = build_workload(common.Config("half_inf", d, f, 1, 1, T, **quant), orc)
+    layer = device_layer(wl)
+    clean = _run_block(layer, wl.x, 1)[0]
+    x = wl.x.copy()
+    x[3, 0] = np.inf
+    got = _run_block(layer, x, 1)[0]
+    keep = np.arange(T) != 3
+    assert np.array_equal(got[keep], clean[keep]) and not np.isfinite(got[3]).all()
+    w2 = layer.experts[0].w2
+    (w2.data if bits == 16 else w2.scale)[7, 0] = float("inf")
+    got = _run_block(layer, wl.x, 1)[0]
+    cols = np.arange(d) != 7
+    assert np.array_equal(got[:, cols], clean[:, cols]) and not np.isfinite(got[:, 7]).any()
