@@ -11,9 +11,9 @@
 // 16-byte (fp32) pieces.  4-bit weights travel as codes and are expanded in registers (codes masked into the
 // mantissa of an fp16 constant, the constant subtracted, one packed fp16 multiply-add with the group's scale and
 // zero); 8-bit codes likewise, with a byte permute in place of the masks.
-// Four bodies, chosen per chunk:
+// Five bodies, chosen per chunk:
 //   tile_body    launches with chunks of at most 64 rows, ranges with an odd number of 128-column steps or half a
-//                step at the end, 8-bit experts, one-tile chunks.  Weights are read in whole 128-byte lines (8 lanes per row, 8 rows per
+//                step at the end, one-tile chunks.  Weights are read in whole 128-byte lines (8 lanes per row, 8 rows per
 //                load instruction, streamed) and turned into operand layout through a small wavefront-private LDS
 //                region; activations as a [16*CT, 128*SPB] tile per stage, double-buffered, one barrier per stage.
 //   direct_body  16-bit experts in launches with 128-row chunks: weights straight into operand registers, chunks of
@@ -21,6 +21,7 @@
 //   quant4_body  4-bit experts in those launches, chunks of 2 .. 8 tiles: the same schedule with the expansion of the
 //                codes folded in.
 //   quant4_wide_body  the same for chunks of 9 .. 12 tiles (a 4-bit expert's chunks hold up to 192 rows).
+//   quant8_body  8-bit experts in those launches, chunks of 2 .. 12 tiles.
 #include <atomic>
 
 #include "common.hpp"
@@ -1240,6 +1241,272 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
     store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
 }
 
+// 8-bit weights against chunks of 17 .. 192 activation rows (launches with 128-row chunks): the pinned schedule of
+// quant4_body (up to 8 tiles) and quant4_wide_body (9 .. 12 tiles: two units per sub-step, activations staged in two
+// batches), with the byte-permute expansion.  Lane (r16, c4) loads the 32 bytes that hold its 32 codes of a
+// 128-column step (two 128-bit loads); words 2 sb and 2 sb + 1 are its operand of sub-step sb, in column order, so the
+// staged activations keep theirs.  A step's codes are twice as many registers as a 4-bit step's, so the ring holds two
+// steps: a step of 8 tiles takes 1.9 us, and its codes are asked for one and a quarter steps ahead.
+// (tile_body, which staged codes through LDS behind a barrier per step and had 1, 2, 4 or 8 tiles: 1000 tokens, 8
+// experts, top-2, Mixtral shape, 801 us in the up-projection and 466 us in the down-projection; 710 and 349 us here.)
+// Two stages of activations under way up to 8 tiles: no gain (913 against 933 us for the block).
+// The number of steps is a multiple of 4 here.
+template <bool UP, int NCT>
+__device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& ee, void* out_base) {
+    static_assert(16 * NCT <= kQuantRows, "two units of at most 8 tiles");
+    constexpr int NA = 4;
+    constexpr int NT = UP ? 32 * NA : 64 * NA;
+    constexpr int R = 2;                               // ring slots = steps of codes in flight
+    constexpr int U = NCT > 8 ? 2 : 1;                 // units per sub-step
+    constexpr int NU0 = NCT > 8 ? 8 : NCT;             // tiles in a sub-step's first unit; the second holds the rest
+    constexpr int XB = NU0;                            // activation pieces per batch
+    constexpr int kRowBytes = kKTile * 2;              // one activation row of a stage: 256 bytes, 16 slots
+    constexpr int kStageBytes = kDirectRows * kRowBytes;
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, c4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int K = c.K, N = c.N, n_steps = c.n_steps;
+    const int last = n_steps - 1;
+    auto phys_step = [&](int step) {                   // steps past the end repeat the last one
+        step = step < last ? step : last;
+        return step + c.rot < n_steps ? step + c.rot : step + c.rot - n_steps;
+    };
+
+    // ---- activation pieces this thread stages (see direct_body), at most XB of them in registers at a time
+    const gptr_t xbase = scalar_ptr(c.in + c.k_begin);
+    uint32_t xoff[NCT];
+#pragma unroll
+    for (int i = 0; i < NCT; ++i) {
+        int rr = (tid >> 4) + 16 * i;
+        rr = rr < c.rows ? rr : c.rows - 1;
+        const int g = c.begin + c.m0 + rr;
+        const uint32_t src = (UP && c.perm) ? (uint32_t)(c.perm[g] / c.top_k) : (uint32_t)g;
+        xoff[i] = src * (uint32_t)K * 2 + (tid & 15) * 16;
+    }
+    uint4_t xr[XB];
+    uint8_t* const xst = c.lds + (tid >> 4) * kRowBytes + (((tid & 15) ^ (tid >> 4)) * 16);
+    auto load_x1 = [&](int i, int stage) {
+        xr[i % XB] = *(const uint4_t MOEMIX_GLOBAL*)(xbase + phys_step(stage) * kRowBytes + fresh_offset(xoff[i]));
+    };
+    auto store_x1 = [&](int i, int stage) {
+        *(uint4_t*)(xst + (stage & 1) * kStageBytes + i * (16 * kRowBytes)) = xr[i % XB];
+    };
+
+    // ---- weights: row r16 of each of the wavefront's NA tiles: codes, scales, zeros
+    gptr_t cbase[NA];
+    uint32_t doff[NA];
+    gptr_t sbase[NA], zbase[NA];                       // scales and zeros: uniform bases, one lane offset for both
+    uint32_t soff[NA];
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+        const int tile = UP ? (t >> 1) : t;                        // up: operands (w1 tile0, w3 tile0, w1 tile1, w3 tile1)
+        const DevMat& m = UP ? ((t & 1) ? ee.w3 : ee.w1) : ee.w2;
+        cbase[t] = scalar_ptr(m.data + c.k_begin);
+        int row = c.n0 + wave * (NT / 4) + tile * 16 + r16;
+        row = row < N ? row : N - 1;                               // rows past the end repeat the last row, never stored
+        doff[t] = (uint32_t)row * (uint32_t)K + c4 * 32;
+        sbase[t] = scalar_ptr(m.scale + (c.k_begin >> 6));
+        zbase[t] = scalar_ptr(m.zero + (c.k_begin >> 6));
+        soff[t] = (uint32_t)row * (uint32_t)(K >> 6) * 2;
+    }
+    uint4_t ar[R][NA][2];
+    auto load_a = [&](int slot, int step) {
+        const int ps = phys_step(step);
+#pragma unroll
+        for (int t = 0; t < NA; ++t) {
+            const uint32_t off = fresh_offset(doff[t]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) ar[slot][t][h] = *(const uint4_t MOEMIX_GLOBAL*)(cbase[t] + (ps * kKTile + 16 * h) + off);
+        }
+    };
+    uint32_t sz_a[NA][2], sz_b[NA][2];                 // scales / zeros of the four steps under way, of the next four
+    auto load_sz = [&](uint32_t (&dst)[NA][2], int S) {
+        const int ps = phys_step(4 * S + c4);          // (rotation and range are multiples of 4 steps: no wrap inside)
+#pragma unroll
+        for (int t = 0; t < NA; ++t) {
+            dst[t][0] = *(const uint32_t MOEMIX_GLOBAL*)(sbase[t] + ps * 4 + fresh_offset(soff[t]));
+            dst[t][1] = *(const uint32_t MOEMIX_GLOBAL*)(zbase[t] + ps * 4 + fresh_offset(soff[t]));
+        }
+    };
+    const uint32_t sel = (c4 >> 1) ? 0x03020302u : 0x01000100u;   // which of the two groups of a 128-column step
+    const uint32_t m1024 = vreg_const(0x64006400u), m64x4 = vreg_const(0x64646464u);
+    half2_t s2[NA], z2[NA];
+    uint32_t hs[NA], hz[NA];
+    auto hand_ask = [&](const uint32_t (&src)[NA][2], int g, int t0) {   // tiles t0, t0 + 1
+        const int from = (r16 + 16 * (g & 3)) * 4;
+#pragma unroll
+        for (int t = t0; t < t0 + 2; ++t) {
+            hs[t] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)src[t][0]);
+            hz[t] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)src[t][1]);
+        }
+    };
+    auto hand_take = [&](half2_t (&so)[NA], half2_t (&zo)[NA]) {
+#pragma unroll
+        for (int t = 0; t < NA; ++t) {
+            so[t] = as_half2(__builtin_amdgcn_perm(hs[t], hs[t], sel));
+            zo[t] = as_half2(__builtin_amdgcn_perm(hz[t], hz[t], sel));
+        }
+    };
+
+    float4_t acc[NA][NCT];
+#pragma unroll
+    for (int t = 0; t < NA; ++t)
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) acc[t][j] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // B operand of tile j, sub-step sb: row 16 j + r16, piece 4 c4 + sb, which sits in slot (4 c4 + sb) ^ r16
+    int b_off[4];
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb) b_off[sb] = r16 * kRowBytes + (((4 * c4 + sb) ^ r16) * 16);
+    half8_t bq[2][8];
+    uint32_t af[2][NA][4];                             // A operands as words: code pairs dequantized, in column order
+    // The expansion of a sub-step's NA operands as 48 single instructions, stage by stage over all tiles: 16 byte
+    // permutes that put a code under the high byte of fp16 1024, 16 subtractions of 1024, 16 multiply-adds with scale
+    // and zero; the intermediate values live in the destination registers.
+    constexpr int NX = 48;
+    auto expand_op = [&](int k, int slot, int sub, uint32_t (&dst)[NA][4], const half2_t (&sc)[NA], const half2_t (&ze)[NA]) {
+        const int t = (k & 15) >> 2, q = k & 3;
+        if (k < 16) {
+            const uint32_t w = ar[slot][t][sub >> 1][2 * (sub & 1) + (q >> 1)];
+            dst[t][q] = __builtin_amdgcn_perm(m64x4, w, (q & 1) ? 0x04030402u : 0x04010400u);
+        } else if (k < 32) {
+            dst[t][q] = __builtin_bit_cast(uint32_t, as_half2(dst[t][q]) - as_half2(m1024));
+        } else {
+            dst[t][q] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(as_half2(dst[t][q]), sc[t], ze[t]));
+        }
+    };
+
+    // Stage 0 goes to LDS here (two units: and the first batch of stage 1); the pieces in registers when the loop starts
+    // are stage 1's (two units: its second batch).  Scales of the first four steps; the ring.
+#pragma unroll
+    for (int i = 0; i < XB; ++i) load_x1(i, 0);
+    load_sz(sz_a, 0);
+    if (U == 1) {
+#pragma unroll
+        for (int i = 0; i < NCT; ++i) { store_x1(i, 0); load_x1(i, 1); }
+    } else {
+#pragma unroll
+        for (int i = 0; i < XB; ++i) { store_x1(i, 0); if (XB + i < NCT) load_x1(XB + i, 0); }
+#pragma unroll
+        for (int i = 0; i < XB; ++i) { if (XB + i < NCT) store_x1(XB + i, 0); load_x1(i, 1); }
+#pragma unroll
+        for (int i = 0; i < XB; ++i) { store_x1(i, 1); if (XB + i < NCT) load_x1(XB + i, 1); }
+    }
+    pin_schedule();
+#pragma unroll
+    for (int u = 0; u < R; ++u) load_a(u, u);
+    pin_schedule();
+    hand_ask(sz_a, 0, 0);
+    hand_ask(sz_a, 0, 2);
+    hand_take(s2, z2);
+#pragma unroll
+    for (int k = 0; k < NX; ++k) expand_op(k, 0, 0, af[0], s2, z2);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NU0; ++j) bq[0][j] = *(const half8_t*)(c.lds + b_off[0] + j * (16 * kRowBytes));
+    pin_schedule();
+
+    constexpr int PPS = (NCT + 2) / 3;                 // one unit: activation pieces staged per sub-step
+    for (int base = 0; base < n_steps; base += 4) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int step = base + g;
+            const uint8_t* const cur = c.lds + (step & 1) * kStageBytes;
+            const uint8_t* const nxt = c.lds + ((step + 1) & 1) * kStageBytes;
+            half2_t s2n[NA], z2n[NA];
+#pragma unroll
+            for (int sb = 0; sb < 4; ++sb) {
+                const int u = 4 * g + sb;                          // parity of the A register sets
+                // what the next sub-step multiplies: sub-step sb + 1 of this step's codes, or 0 of the next step's
+                const int nslot = sb < 3 ? g & 1 : (g + 1) & 1, nsub = (sb + 1) & 3;
+#pragma unroll
+                for (int h = 0; h < U; ++h) {
+                    const int v = U * sb + h;                      // unit of the step; B register set v & 1
+                    const bool last_unit = v == 4 * U - 1;
+                    // Before the step's last unit: every wavefront has read this stage out (its last reads were
+                    // issued a unit ago) and has written its pieces of the next one.
+                    if (last_unit) __syncthreads();
+                    const int nh = h + 1 < U ? h + 1 : 0;
+                    const int ntiles = h ? NCT - NU0 : NU0, next_tiles = nh ? NCT - NU0 : NU0;
+                    // the next unit's operands: the same sub-step's second unit, or the next sub-step's first
+                    const uint8_t* const nb =
+                        (last_unit ? nxt : cur) + b_off[h + 1 < U ? sb : nsub] + 8 * nh * (16 * kRowBytes);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        if (j < ntiles) {
+                            if (U == 1 && sb < 3 && j < PPS && sb * PPS + j < NCT) {   // staging, spread over three sub-steps
+                                store_x1(sb * PPS + j, step + 1);
+                                load_x1(sb * PPS + j, step + 2);
+                            }
+                            if (j < next_tiles) bq[(v + 1) & 1][j] = *(const half8_t*)(nb + j * (16 * kRowBytes));
+#pragma unroll
+                            for (int t = 0; t < NA; ++t) {
+                                mfma16_tied(acc[t][8 * h + j],
+                                            __builtin_bit_cast(half8_t, uint4_t{af[u & 1][t][0], af[u & 1][t][1],
+                                                                                af[u & 1][t][2], af[u & 1][t][3]}),
+                                            bq[v & 1][j]);
+                                constexpr int NM = 4 * NCT;         // products per sub-step
+                                const int m = 4 * (8 * h + j) + t;  // this one
+#pragma unroll
+                                for (int k = (m * NX + NM - 1) / NM; k < ((m + 1) * NX + NM - 1) / NM; ++k) {
+                                    if (sb < 3) expand_op(k, nslot, nsub, af[(u + 1) & 1], s2, z2);
+                                    else expand_op(k, nslot, nsub, af[(u + 1) & 1], s2n, z2n);
+                                }
+                                pin_schedule();
+                            }
+                            if (U == 2) {                          // direct_body's two-batch order
+                                if (v == 2 && XB + j < NCT) store_x1(XB + j, step + 1);
+                                if (v == 3) {
+#pragma unroll
+                                    for (int i = j; i < XB; i += ntiles) load_x1(i, step + 2);
+                                }
+                                if (last_unit) {
+#pragma unroll
+                                    for (int i = j; i < XB; i += ntiles) {
+                                        store_x1(i, step + 2);
+                                        if (XB + i < NCT) load_x1(XB + i, step + 2);
+                                    }
+                                }
+                            }
+                            pin_schedule();
+                        }
+                    }
+                    if (next_tiles > ntiles) {                     // operands of the next unit this one had no group for
+#pragma unroll
+                        for (int j = ntiles; j < next_tiles; ++j) bq[(v + 1) & 1][j] = *(const half8_t*)(nb + j * (16 * kRowBytes));
+                        pin_schedule();
+                    }
+                }
+                if (sb < 2) {                                      // the next step's scales and zeros: asked for ...
+                    if (g < 3) hand_ask(sz_a, g + 1, 2 * sb);
+                    else hand_ask(sz_b, 0, 2 * sb);
+                    pin_schedule();
+                }
+                if (sb == 2) {
+                    hand_take(s2n, z2n);                           // ... and picked up
+                    pin_schedule();
+                }
+                // This step's codes are used up after its third sub-step; those of two steps on take their place, right
+                // after the step's last activation loads (loads retire in the order of their issue).  Every fourth
+                // step the scales and zeros of the next four.
+                if (sb == (U == 1 ? 2 : 3)) {
+                    load_a(g & 1, step + R);
+                    if (g == 0) load_sz(sz_b, base / 4 + 1);
+                    pin_schedule();
+                }
+                if (sb == 3) {
+#pragma unroll
+                    for (int t = 0; t < NA; ++t) { s2[t] = s2n[t]; z2[t] = z2n[t]; }
+                    pin_schedule();
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NA; ++t) { sz_a[t][0] = sz_b[t][0]; sz_a[t][1] = sz_b[t][1]; }
+    }
+    mfma_settle();
+    store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
+}
+
 // WIDE: the block holds 8-bit experts as well.  The 8-bit body needs more registers than the other two, and a
 // kernel's register count is that of its largest body, so blocks without 8-bit experts get a kernel without it
 // (and keep four wavefronts per SIMD at few rows per expert).  The wide kernel has bodies for 1, 2, 4 and 8 tiles.
@@ -1280,12 +1547,12 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     // (4-bit chunks of more than 128 rows save compute-unit time, not latency: one expert alone whose launch does not
     // fill the chip twice over is faster with more, smaller workgroups side by side -- 148 rows: 73 us in chunks of
     // 128 + 20 rows, 89 us in one chunk)
-    const bool quant4_ok = wide_ok && !(n_steps & 3);
-    const bool wide4_ok = quant4_ok && (a.direct_expert < 0 || gridDim.x * gridDim.y >= 2 * kComputeUnits);
+    const bool quant_ok = wide_ok && !(n_steps & 3);
+    const bool wide_quant_ok = quant_ok && (a.direct_expert < 0 || gridDim.x * gridDim.y >= 2 * kComputeUnits);
     auto chunk_rows = [&](int expert, int n) {   // rows per chunk of an expert with n rows
         const int prec = a.ex.e[expert].prec;
         if (!((wide_ok && prec == MOE_PREC_FP16 && n > 16 * (kDirectNCT - 1)) ||
-              (wide4_ok && prec == MOE_PREC_INT4G64 && n > MC)))
+              (wide_quant_ok && prec != MOE_PREC_FP16 && n > MC)))
             return MC;
         const int cap = prec == MOE_PREC_FP16 ? kDirectRows : kQuantRows;
         const int nch = (n + cap - 1) / cap;
@@ -1374,7 +1641,7 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
 #undef MOEMIX_DIRECT
 #define MOEMIX_QUANT4(n) quant4_body<UP, CT >= 8 && !HALF ? (n) : 8>(c, ee, out_base)
 #define MOEMIX_QUANT4W(n) quant4_wide_body<UP, CT >= 8 && !HALF ? (n) : 12>(c, ee, out_base)
-    if (!HALF && CT >= 8 && quant4_ok && prec == MOE_PREC_INT4G64 && nct >= 2) {
+    if (!HALF && CT >= 8 && quant_ok && prec == MOE_PREC_INT4G64 && nct >= 2) {
         switch (nct) {
             case 2: MOEMIX_QUANT4(2); break;
             case 3: MOEMIX_QUANT4(3); break;
@@ -1392,6 +1659,24 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     }
 #undef MOEMIX_QUANT4
 #undef MOEMIX_QUANT4W
+#define MOEMIX_QUANT8(n) quant8_body<UP, WIDE && CT >= 8 && !HALF ? (n) : 8>(c, ee, out_base)
+    if (WIDE && !HALF && CT >= 8 && quant_ok && prec == MOE_PREC_INT8G64 && nct >= 2) {
+        switch (nct) {
+            case 2: MOEMIX_QUANT8(2); break;
+            case 3: MOEMIX_QUANT8(3); break;
+            case 4: MOEMIX_QUANT8(4); break;
+            case 5: MOEMIX_QUANT8(5); break;
+            case 6: MOEMIX_QUANT8(6); break;
+            case 7: MOEMIX_QUANT8(7); break;
+            case 8: MOEMIX_QUANT8(8); break;
+            case 9: MOEMIX_QUANT8(9); break;
+            case 10: MOEMIX_QUANT8(10); break;
+            case 11: MOEMIX_QUANT8(11); break;
+            default: MOEMIX_QUANT8(12); break;
+        }
+        return;
+    }
+#undef MOEMIX_QUANT8
     if (WIDE) {
         if (CT >= 8 && nct > 4) MOEMIX_BODY(8);
         else if (CT >= 4 && nct > 2) MOEMIX_BODY(4);

@@ -170,3 +170,25 @@ def test_half_step_keeps_neighbours_apart(orc, bits):
     got = _run_block(layer, wl.x, 1)[0]
     cols = np.arange(d) != 7
     assert np.array_equal(got[:, cols], clean[:, cols]) and not np.isfinite(got[:, 7]).any()
+
+
+# 8-bit experts in launches with 128-row chunks: every number of 16-row tiles the pipelined body has (2 .. 8 in one
+# unit, 9 .. 12 in two; a lone expert's chunks stay at 128 rows, so those come from blocks), ragged last tiles, the
+# one-tile rest, ranges of 8 steps (up) and of splits of 4 steps (down).
+@pytest.mark.parametrize("n", [70, 81, 96, 100, 128, 129, 150, 170, 185, 200, 225, 250, 257])
+def test_expert_ffn_8bit_pipelined_body(orc, n):
+    cfg = common.Config("steps4_8bit", 1024, 2048, 2, 1, 4, (), int8_experts=(0, 1))
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    x = synth.normal_f16((n, cfg.d), 1.0, 9, 77)
+    y = torch.full((n, cfg.d), float("nan"), dtype=torch.float32, device="cuda")
+    ws = mm.alloc_workspace(layer, n)
+    mm.moe_expert_ffn_mixed(layer, 1, dev(x), y, ws)
+    assert mm.moe_read_status(ws) == 0
+    assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[1], x), f"n={n}")
+
+
+@pytest.mark.parametrize("T", [139, 150, 170, 185, 230])
+def test_block_8bit_chunks_of_more_than_128_rows(orc, T):
+    """One expert takes every token: chunks of 9, 10, 11 and 12 tiles, then two of 8."""
+    _check_block(orc, common.Config(f"steps4_8bit_T{T}", 1024, 2048, 2, 2, T, (), int8_experts=(0, 1)))
