@@ -64,7 +64,10 @@ constexpr int kDecodeUpBlocks = 1024;
 
 // Which kernels serve T tokens of a block: T == 1 the batch-1 kernels, otherwise the matrix-core path when
 // the shape allows it, else the shape-agnostic kernels.
-bool use_decode(const moe_layer* L, int T) { return T == 1 && decode_shape_ok(L->d_model, L->d_ff); }
+bool use_decode(int T) { return T == 1; }
+// The expert-miss path adds the experts it brings in to an fp16 output at one token.  It keeps the multi-token kernels,
+// which add every expert before the one rounding, for the widths that had them before the one-token kernels took any.
+bool use_decode_swap(const moe_layer* L, int T) { return T == 1 && decode_shape_ok(L->d_model, L->d_ff); }
 bool use_mfma(const moe_layer* L, int rows) {
     return rows > 1 && mfma_shape_ok(L->d_model, L->d_ff) && mfma_rows_ok(rows, L->d_model, L->d_ff);
 }
@@ -109,7 +112,7 @@ int layer_body(const moe_layer* L, const DevExperts& table, const half_t* x, int
                const half_t* residual, half_t* out, int32_t* idx_out, float* gate_out, const Workspace& w,
                bool reset_status, hipStream_t st) {
     const int d = L->d_model, f = L->d_ff, E = L->n_experts, k = L->top_k;
-    if (use_decode(L, T)) {
+    if (use_decode(T)) {
         // batch-1 decode: two launches.  The gating network (and the RMSNorm of the chain) runs inside the
         // up-projection launch, no grouping is needed, the weighted average is fused into the down-projection.
         // The up-projection launch clears the word it is given: the status word for the first block of a call, a
@@ -223,7 +226,7 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
     RowMap rows{nullptr, nullptr, layer->top_k, expert, n};
     const int d = layer->d_model, f = layer->d_ff;
     launch_zero_words(w.status, 1, st);   // the status word describes this call
-    if (use_decode(layer, n)) {
+    if (use_decode(n)) {
         // one row: the batch-1 kernels, with the routing result "this expert, weight 1" written to the workspace
         launch_single_route(w.idx, w.gate, expert, st);
         launch_decode_up(table, w.idx, (const half_t*)x_rows, d, f, 1, w.h, w.status, kDecodeUpBlocks, st);
@@ -356,7 +359,7 @@ hipError_t copy_mat(const moe_mat& src, const MatBytes& b, char*& cursor, DevMat
 void run_experts(const moe_layer* L, const DevExperts& table, const half_t* x, int T, const Workspace& w,
                  const half_t* decode_residual, half_t* out, hipStream_t st) {
     const int d = L->d_model, f = L->d_ff, E = L->n_experts, k = L->top_k;
-    if (use_decode(L, T)) {
+    if (use_decode_swap(L, T)) {
         launch_decode_up(table, w.idx, x, d, f, k, w.h, w.status, kDecodeUpBlocks, st);
         launch_decode_down(table, w.idx, w.gate, w.h, d, f, k, decode_residual, out, w.status, st);
         return;
@@ -429,7 +432,7 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
     // pass over the resident experts; the missed ones wait for their copies
     DevExperts table = device_table(layer);
     for (int i = 0; i < n_miss; ++i) table.e[missed[i]].resident = kDeferred;
-    const bool decode = use_decode(layer, T);
+    const bool decode = use_decode_swap(layer, T);
     if (!decode) launch_permute(w.idx, T * k, E, w.counts, w.offsets, w.perm, w.inv, w.status, st);
     run_experts(layer, table, xin, T, w, nullptr, (half_t*)out, st);
 

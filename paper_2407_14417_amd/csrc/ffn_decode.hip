@@ -523,6 +523,7 @@ __global__ __launch_bounds__(256, 2) void decode_up_kernel(DevExperts ex, const 
 // Partial sums meet in LDS and are added in wavefront order: the result does not depend on scheduling.
 constexpr int kDownRows = 16;
 constexpr int kDownBatch = 4;
+constexpr int kDownAnyWideRows = 2048;   // d_model up to which the kernel for any width gives an output row a whole wavefront
 
 template <bool WIDE>   // WIDE: with the branch for 8-bit experts
 __global__ __launch_bounds__(512) void decode_down_kernel(DevExperts ex, const int32_t* __restrict__ idx,
@@ -694,6 +695,313 @@ __global__ __launch_bounds__(512) void decode_down_kernel(DevExperts ex, const i
     }
 }
 
+// ---------------------------------------------------------------- one token, any width
+
+// The same two launches for widths that are no multiple of 2048 (any multiple of 64): what was the five-launch
+// multi-token path.  Small experts are what such blocks are about: a launch is a chain of latencies with a few
+// microseconds of loads at its end, so the chip is filled with short shares instead of long register pipelines.  The
+// token (or the hidden row) lies in LDS, from where a lane picks the activations of whatever 16-byte piece of a row it
+// has loaded; the last pieces of a row are masked lane by lane.  Whole blocks, graph replays over a pool of layers, five
+// launches -> these two: d_model 1024, d_ff 2816, 4- and 16-bit 29.0 -> 15.2 us; 256 x 512 18.0 -> 10.2; 32 experts of
+// 2048 x 1408, eight slots 61.8 -> 44.7; 2880 x 2880, four slots, 4-bit 73.4 -> 49.8; 4096 x 11008, 4- and 16-bit 94 -> 69
+// (5.0 TB/s); 7360 x 10624, 8-bit 279 -> 115.
+//   up  : a wavefront takes one row of w1 (lanes 0 .. 31) and the same row of w3 (lanes 32 .. 63) at a time
+//   down: LPR lanes per output row (64 where d_model is small, so that there are enough workgroups for the chip)
+// 16-byte pieces of the activations are stored at swizzled places: lanes that read every fourth piece (4-bit rows: 32
+// columns per lane), every second one (8-bit) or consecutive ones (16-bit) then hit different banks.
+__device__ __forceinline__ int act_slot(int piece) { return piece ^ ((piece >> 3) & 3); }
+
+// Activations of one row in LDS: natural order for 16-bit and 8-bit weights; for 4-bit weights the order (0,4,1,5,2,6,3,7)
+// of the code pairs inside each eight; sums for the factored forms (per 32 columns c1 and c2 of ActI4, per 16 columns
+// the two of ActI8).
+struct ActLds {
+    half8_t* nat;
+    half8_t* perm4;
+    float2* sum4;    // [K / 32]
+    float2* sum8;    // [K / 16]
+};
+
+// The byte sizes behind an ActLds for rows of K columns.
+__host__ __device__ constexpr size_t act_lds_bytes(int K, bool natural, bool bits4, bool bits8) {
+    return (size_t)K * 2 * ((natural ? 1 : 0) + (bits4 ? 1 : 0)) + (bits4 ? (size_t)K / 4 : 0) + (bits8 ? (size_t)K / 2 : 0);
+}
+
+// Thread's share of the 4-bit form: 32 columns per turn, read from four 16-byte pieces with `get`.
+template <typename Get>
+__device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get) {
+    for (int p = tid; p < K / 32; p += n_threads) {
+        float se = 0.0f, so = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const half8_t v = get(4 * p + j);
+            a.perm4[act_slot(4 * p + j)] = half8_t{v[0], v[4], v[1], v[5], v[2], v[6], v[3], v[7]};
+            se += ((float)v[0] + (float)v[2]) + ((float)v[4] + (float)v[6]);
+            so += ((float)v[1] + (float)v[3]) + ((float)v[5] + (float)v[7]);
+        }
+        a.sum4[p] = float2{1024.0f * se + 64.0f * so, se + so};
+    }
+}
+
+template <typename Get>
+__device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get) {
+    for (int p = tid; p < K / 16; p += n_threads) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const half8_t v = get(2 * p + j);
+            sum += (((float)v[0] + (float)v[1]) + ((float)v[2] + (float)v[3])) +
+                   (((float)v[4] + (float)v[5]) + ((float)v[6] + (float)v[7]));
+        }
+        a.sum8[p] = float2{1024.0f * sum, sum};
+    }
+}
+
+// One precision's pieces of a row: how many, and the dot product of one with its activations.
+template <int PREC>
+struct RowPiece {
+    static constexpr int kCols = PREC == MOE_PREC_INT4G64 ? 32 : PREC == MOE_PREC_INT8G64 ? 16 : 8;   // per 16 bytes
+    uint4_t v;
+    half_t s, z;
+    __device__ __forceinline__ void load(const DevMat& m, int row, int K, int piece) {
+        const int pieces = K / kCols;
+        piece = piece < pieces ? piece : pieces - 1;
+        v = load_stream((gptr_t)(m.data + ((size_t)row * pieces + piece) * 16));
+        if (PREC != MOE_PREC_FP16) {
+            const size_t g = (size_t)row * (K >> 6) + (piece * kCols >> 6);
+            s = load_half((gptr_t)(m.scale + g));
+            z = load_half((gptr_t)(m.zero + g));
+        }
+    }
+    __device__ __forceinline__ float dot(const ActLds& a, int K, int piece) const {
+        const int pieces = K / kCols;
+        const int at = piece < pieces ? piece : pieces - 1;
+        float r;
+        if (PREC == MOE_PREC_INT4G64) {
+            ActI4 act;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const half8_t x = a.perm4[act_slot(4 * at + j)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) act.p[j][q] = half2_t{x[2 * q], x[2 * q + 1]};
+            }
+            const float2 c = a.sum4[at];
+            act.c1 = c.x;
+            act.c2 = c.y;
+            r = dot_i4(v, act, (float)s, (float)z);
+        } else if (PREC == MOE_PREC_INT8G64) {
+            ActI8 act;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const half8_t x = a.nat[act_slot(2 * at + j)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) act.p[4 * j + q] = half2_t{x[2 * q], x[2 * q + 1]};
+            }
+            const float2 c = a.sum8[at];
+            act.k1 = c.x;
+            act.sx = c.y;
+            r = dot_i8(v, act, (float)s, (float)z);
+        } else {
+            const half8_t x = a.nat[act_slot(at)];
+            ActF16 act;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) act.p[q] = half2_t{x[2 * q], x[2 * q + 1]};
+            r = dot_f16(v, act, 0.0f);
+        }
+        return piece < pieces ? r : 0.0f;      // (a select, not a product: the repeated piece may hold anything)
+    }
+};
+
+// Walks the 16-byte pieces of a share's rows, kAtOnce of them per trip to memory, across the ends of rows (with 16
+// wavefronts per compute unit that is 64 KB under way).  row_at(i): the i-th row of the share; mat: the lane's matrix;
+// done(row, sum): the lane's partial sum of a row.
+template <int PREC, int LPR, typename RowAt, typename Done>
+__device__ __forceinline__ void walk_rows(const DevMat& mat, int n_rows, int K, const ActLds& act, int l, RowAt row_at, Done done) {
+    constexpr int kAtOnce = 4;
+    const int per_lane = (K / RowPiece<PREC>::kCols + LPR - 1) / LPR;   // pieces of a row per lane
+    const int items = n_rows * per_lane;
+    int lr = 0, lc = 0, ur = 0, uc = 0;        // row and piece of the next load and of the next use
+    float sum = 0.0f;
+    for (int i = 0; i < items; i += kAtOnce) {
+        RowPiece<PREC> p[kAtOnce];
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {
+            p[j].load(mat, row_at(lr), K, l + LPR * lc);
+            if (i + j + 1 < items && ++lc == per_lane) { lc = 0; ++lr; }   // (past the end the last piece is repeated)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {
+            if (i + j < items) {
+                sum += p[j].dot(act, K, l + LPR * uc);
+                if (++uc == per_lane) {
+                    done(row_at(ur), sum);
+                    sum = 0.0f;
+                    uc = 0;
+                    ++ur;
+                }
+            }
+        }
+    }
+}
+
+// Sums over lanes 0 .. 31 and over lanes 32 .. 63.
+__device__ __forceinline__ void half_totals(float v, float& lo, float& hi) {
+    v += dpp_move<0xB1>(v);
+    v += dpp_move<0x4E>(v);
+    v += dpp_move<0x141>(v);
+    v += dpp_move<0x140>(v);
+    v += dpp_move<0x142, 0xA>(v);
+    lo = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 31));
+    hi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+template <int NCHUNK, bool ROUTE>   // NCHUNK: 512-column chunks of the token per lane of the gating network
+__global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel(DevExperts ex, const int32_t* __restrict__ idx,
+                                                             const half_t* __restrict__ x, int d, int f, int k,
+                                                             half_t* __restrict__ h, int32_t* status, const GateArgs ga) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ float logit_s[MOE_MAX_EXPERTS];
+    const ActLds act{(half8_t*)lds, (half8_t*)(lds + d * 2), (float2*)(lds + d * 4), (float2*)(lds + d * 4 + d / 4)};
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = wave_index();
+    uint64_t routed = 0;                               // 5 bits per slot
+    if (ROUTE) {
+        // (nothing of this launch raises status bits, see decode_up_kernel)
+        if (blockIdx.x == 0 && tid == 0) *status = 0;
+        uint4_t xv[NCHUNK];
+        gate_load_row<NCHUNK>(x, d, lane, xv);
+        if (ga.rms_gain) gate_rmsnorm<NCHUNK>(xv, ga.rms_gain, d, ga.eps, lane);
+        if (wave == 0) {
+#pragma unroll
+            for (int j = 0; j < NCHUNK; ++j)
+                if ((lane + 64 * j) * 8 < d) act.nat[act_slot(lane + 64 * j)] = __builtin_bit_cast(half8_t, xv[j]);
+        }
+        constexpr int kAtOnce = NCHUNK <= 4 ? 2 : 1;
+#pragma unroll 1
+        for (int e = wave; e < ga.E; e += 4 * kAtOnce) {
+            float l[kAtOnce];
+            gate_logits<kAtOnce, NCHUNK>(xv, ga.wg, e, 4, ga.E, d, lane, l);
+            if (lane == 0) {
+#pragma unroll
+                for (int n = 0; n < kAtOnce; ++n)
+                    if (e + 4 * n < ga.E) logit_s[e + 4 * n] = l[n] + (ga.bias ? ga.bias[e + 4 * n] : 0.0f);
+            }
+        }
+        __syncthreads();
+        int sel[MOE_MAX_TOPK];
+        float lsel[MOE_MAX_TOPK];
+        gate_select(logit_s, ga.E, k, lane, sel, lsel);
+#pragma unroll
+        for (int s = 0; s < MOE_MAX_TOPK; ++s)
+            if (s < k) routed |= (uint64_t)(uint32_t)sel[s] << (5 * s);
+        if (blockIdx.x == 0 && tid == 0) {
+            float g[MOE_MAX_TOPK];
+            gate_weights(lsel, k, g);
+#pragma unroll
+            for (int s = 0; s < MOE_MAX_TOPK; ++s) {
+                if (s < k) {
+                    ga.idx_ws[s] = sel[s];
+                    ga.gate_ws[s] = g[s];
+                    if (ga.idx_out) ga.idx_out[s] = sel[s];
+                    if (ga.gate_out) ga.gate_out[s] = g[s];
+                }
+            }
+        }
+    } else {
+        for (int s = 0; s < k; ++s) routed |= (uint64_t)(uint32_t)idx[s] << (5 * s);
+        for (int p = tid; p < d / 8; p += 256) act.nat[act_slot(p)] = *(const half8_t*)(x + p * 8);
+        __syncthreads();
+    }
+    routed = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(routed >> 32)) << 32) |
+             (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)routed);
+    bool bits4 = false, bits8 = false;
+    for (int s = 0; s < k; ++s) {
+        const int prec = ex.e[(routed >> (5 * s)) & 31u].prec;
+        bits4 |= prec == MOE_PREC_INT4G64;
+        bits8 |= prec == MOE_PREC_INT8G64;
+    }
+    auto get = [&](int piece) { return act.nat[act_slot(piece)]; };
+    if (bits4) act_pair_up(act, d, tid, 256, get);
+    if (bits8) act_sum_bytes(act, d, tid, 256, get);
+    if (bits4 || bits8) __syncthreads();
+    // Rows of all slots, dealt to the launch's wavefronts in turn: every share has its part of each slot.
+    const int n_waves = gridDim.x * 4, gw = blockIdx.x * 4 + wave;
+    for (int s = 0; s < k; ++s) {
+        const DevExpert& ee = ex.e[(routed >> (5 * s)) & 31u];
+        if (ee.resident != 1 || !ee.w1.data) continue;   // reported by the down-projection launch
+        // first row of slot s in this wavefront's share: the smallest r >= 0 with (s f + r) % n_waves == gw
+        const int first = __builtin_amdgcn_readfirstlane((gw - (int)((unsigned)(s * f) % (unsigned)n_waves) + n_waves) % n_waves);
+        const int rows = first < f ? (f - first + n_waves - 1) / n_waves : 0;
+        half_t* const hs = h + (size_t)s * f;
+        auto row_at = [&](int i) { return first + i * n_waves; };
+        auto done = [&](int row, float sum) {
+            float a, b;
+            half_totals(sum, a, b);
+            if (lane == 0) hs[row] = (half_t)silu_mul(a, b);
+        };
+        const DevMat mat = lane < 32 ? ee.w1 : ee.w3;
+        const int l = lane & 31;
+        if (ee.prec == MOE_PREC_INT4G64) walk_rows<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
+        else if (ee.prec == MOE_PREC_INT8G64) walk_rows<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
+        else walk_rows<MOE_PREC_FP16, 32>(mat, rows, d, act, l, row_at, done);
+    }
+}
+
+// One workgroup: 256 / LPR output rows at a time, every slot of them in turn, its hidden row in LDS.
+template <int LPR>
+__global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, const int32_t* __restrict__ idx,
+                                                               const float* __restrict__ gate,
+                                                               const half_t* __restrict__ h, int d, int f, int k,
+                                                               const half_t* __restrict__ residual,
+                                                               half_t* __restrict__ out, float* __restrict__ out32,
+                                                               int32_t* status) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    // (one precision at a time: the natural order and the 4-bit order share their place)
+    const ActLds act{(half8_t*)lds, (half8_t*)lds, (float2*)(lds + f * 2), (float2*)(lds + f * 2)};
+    constexpr int kRows = 256 / LPR;
+    const int tid = threadIdx.x, lane = tid & 63, l = tid & (LPR - 1);
+    const int row = blockIdx.x * kRows + tid / LPR;
+    const int row_safe = row < d ? row : d - 1;        // (lanes past the last row repeat it and store nothing)
+    float acc = 0.0f;
+    for (int s = 0; s < k; ++s) {
+        const DevExpert& ee = ex.e[__builtin_amdgcn_readfirstlane(idx[s])];
+        if (ee.resident == kDeferred) continue;
+        if (!ee.resident || !ee.w2.data) {
+            if (tid == 0 && blockIdx.x == 0) atomicOr(status, kStatusNotResident);
+            continue;
+        }
+        const float g = gate[s];
+        const half_t* const hs = h + (size_t)s * f;
+        auto get = [&](int piece) { return *(const half8_t*)(hs + piece * 8); };
+        __syncthreads();                               // the last slot's hidden row has been read
+        if (ee.prec == MOE_PREC_INT4G64) {
+            act_pair_up(act, f, tid, 256, get);
+        } else {
+            for (int p = tid; p < f / 8; p += 256) act.nat[act_slot(p)] = get(p);
+            if (ee.prec == MOE_PREC_INT8G64) act_sum_bytes(act, f, tid, 256, get);
+        }
+        __syncthreads();
+        auto row_at = [&](int) { return row_safe; };
+        auto done = [&](int, float sum) { acc = fmaf(g, sum, acc); };
+        if (ee.prec == MOE_PREC_INT4G64) walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        else if (ee.prec == MOE_PREC_INT8G64) walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
+    }
+    float total;
+    if (LPR == 64) {
+        total = wave_total(acc);
+    } else {
+        float lo, hi;
+        half_totals(acc, lo, hi);
+        total = lane < 32 ? lo : hi;
+    }
+    if (l == 0 && row < d) {
+        const float t = residual ? (float)residual[row] : 0.0f;
+        if (out32) out32[row] = t + total;
+        else out[row] = (half_t)(t + total);
+    }
+}
+
 // Routing result "this one expert with weight 1", for a single expert run through the batch-1 kernels.
 __global__ void single_route_kernel(int32_t* idx, float* gate, int expert) {
     idx[0] = expert;
@@ -721,9 +1029,33 @@ static void launch_up(const DevExperts& ex, const int32_t* idx, const half_t* x,
     }
 }
 
+template <int NCHUNK>
+static void launch_up_any(const DevExperts& ex, const int32_t* idx, const half_t* x, int d, int f, int k, half_t* h,
+                          int32_t* status, int E, const GateArgs* gating, hipStream_t st) {
+    // Workgroups of four wavefronts, a row pair each at most.  Every one of them reads the gate matrix (E rows of d) out
+    // of L2, so no more than leave that traffic a few times the weights' (a row of w1 and w3
+    // per workgroup and expert), but enough to fill the chip.
+    const int rows = k * f;
+    int blocks = (rows + 3) / 4;
+    const int by_gate = gating ? rows / E : rows;
+    if (blocks > by_gate) blocks = by_gate;
+    if (blocks < 256) blocks = (rows + 3) / 4 < 256 ? (rows + 3) / 4 : 256;
+    if (blocks > 1024) blocks = 1024;
+    const size_t lds = act_lds_bytes(d, true, true, true);
+    if (gating) decode_up_any_kernel<NCHUNK, true><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, *gating);
+    else decode_up_any_kernel<NCHUNK, false><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, GateArgs{});
+}
+
 void launch_decode_up(const DevExperts& ex, const int32_t* idx, const half_t* x, int d, int f, int k, half_t* h,
                       int32_t* status, int blocks, hipStream_t st, const GateArgs* gating) {
     TraceScope trace(kKernelUp, st);
+    if (!decode_shape_ok(d, f)) {
+        const int E = gating ? gating->E : 0;
+        // (no variant for 4096 columns in between: it came out of the compiler with its token spilled to scratch)
+        if (d <= 2048) launch_up_any<4>(ex, idx, x, d, f, k, h, status, E, gating, st);
+        else launch_up_any<kGateMaxChunks>(ex, idx, x, d, f, k, h, status, E, gating, st);
+        return;
+    }
     const bool wide = any_int8(ex);
     if (gating) {
         if (wide) launch_up<true, true>(ex, idx, x, d, f, k, h, status, blocks, *gating, st);
@@ -737,6 +1069,12 @@ void launch_decode_up(const DevExperts& ex, const int32_t* idx, const half_t* x,
 void launch_decode_down(const DevExperts& ex, const int32_t* idx, const float* gate, const half_t* h, int d, int f,
                         int k, const half_t* residual, half_t* out, int32_t* status, hipStream_t st, float* out32) {
     TraceScope trace(kKernelDown, st);
+    if (!decode_shape_ok(d, f)) {
+        const size_t lds = act_lds_bytes(f, true, false, false) + (size_t)f / 2;   // one order and the larger of the sums
+        if (d <= kDownAnyWideRows) decode_down_any_kernel<64><<<(d + 3) / 4, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, status);
+        else decode_down_any_kernel<32><<<(d + 7) / 8, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, status);
+        return;
+    }
     if (any_int8(ex))
         decode_down_kernel<true><<<d / kDownRows, (f / 2048) * 64, 0, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, status);
     else

@@ -192,3 +192,62 @@ def test_expert_ffn_8bit_pipelined_body(orc, n):
 def test_block_8bit_chunks_of_more_than_128_rows(orc, T):
     """One expert takes every token: chunks of 9, 10, 11 and 12 tiles, then two of 8."""
     _check_block(orc, common.Config(f"steps4_8bit_T{T}", 1024, 2048, 2, 2, T, (), int8_experts=(0, 1)))
+
+
+# One token at widths that are no multiple of 2048: rows shorter than a wavefront's loads, one load per lane exactly,
+# ragged last ones, up to the limits; one, two, three and four or more loads per lane and row in both kernels; few and
+# many experts and slots; every precision; the RMSNorm of the chain; one expert alone.
+@pytest.mark.parametrize("d,f,E,k", [(64, 64, 3, 2), (192, 320, 4, 2), (1024, 2816, 8, 2), (1088, 3008, 5, 3), (512, 1536, 1, 1),
+                                     (2048, 1408, 32, 8), (2112, 960, 6, 4), (4160, 1024, 3, 2), (8192, 192, 2, 1),
+                                     (128, 16320, 2, 2), (2880, 2880, 4, 2)])
+def test_one_token_any_width(orc, d, f, E, k):
+    for seed in range(3):
+        low = tuple(range(seed, E, 3))
+        _check_block(orc, common.Config(f"one_token_d{d}_f{f}_E{E}_k{k}_{seed}", d, f, E, k, 1, low, seed=seed,
+                                        int8_experts=tuple(range((seed + 1) % 3, E, 3)), zipf=1.2 if seed == 1 else None))
+
+
+@pytest.mark.parametrize("d,f", [(192, 320), (1088, 3008), (2880, 960)])
+@pytest.mark.parametrize("bits", [4, 8, 16])
+def test_one_row_any_width(orc, d, f, bits):
+    """One expert alone; the 16-bit one with most of w2 subnormal (sums of products that are not flushed)."""
+    quant = {4: dict(int4_experts=(0,)), 8: dict(int4_experts=(), int8_experts=(0,)), 16: dict(int4_experts=())}[bits]
+    wl = build_workload(common.Config(f"one_row_{bits}", d, f, 1, 1, 1, **quant), orc)
+    if bits == 16:
+        wl.experts[0].w2.data[:] = (wl.experts[0].w2.data.astype(np.float32) * 1e-3).astype(np.float16)
+    layer = device_layer(wl)
+    y = torch.full((1, d), float("nan"), dtype=torch.float32, device="cuda")
+    ws = mm.alloc_workspace(layer, 1)
+    mm.moe_expert_ffn_mixed(layer, 0, dev(wl.x), y, ws)
+    assert mm.moe_read_status(ws) == 0
+    assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[0], wl.x), f"d={d} f={f} bits={bits}")
+
+
+def test_one_token_any_width_non_resident_and_chain(orc):
+    cfg = common.Config("one_token_chain", 1088, 1472, 6, 2, 1, (0, 3), int8_experts=(1,))
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    gain = synth.uniform_f16((cfg.d,), 1.0, 3, 90)
+    h = synth.normal_f16((1, cfg.d), 1.0, 3, 91)
+    got = dev(h).clone()
+    idx = torch.empty((2, 1, 2), dtype=torch.int32, device="cuda")
+    ws = mm.alloc_workspace(layer, 1)
+    mm.moe_chain_forward(mm.Chain([layer, layer], [dev(gain), dev(gain)]), 1e-5, got, ws, idx)
+    ref = h
+    for l in range(2):
+        ref, ref_idx = orc.chain_layer(ref, gain, 1e-5, wl.wg, wl.experts, cfg.k)[:2]
+        assert np.array_equal(idx[l].cpu().numpy(), ref_idx)
+        ref = ref.astype(np.float16)
+    assert_ffn_close(got.cpu().numpy(), ref, "chain")
+    assert mm.moe_read_status(ws) == 0
+    first = int(idx[0, 0, 0])
+    x = wl.x
+    _, ref_idx, ref_gate = orc.layer_forward(x, wl.wg, wl.experts, cfg.k)
+    gone, kept = int(ref_idx[0, 0]), int(ref_idx[0, 1])
+    experts = list(layer.experts)
+    experts[gone] = mm.Expert(experts[gone].prec, None, None, None, resident=False)
+    part = mm.Layer(cfg.d, cfg.f, cfg.k, layer.w_gate, experts)
+    out = torch.empty((1, cfg.d), dtype=torch.float16, device="cuda")
+    mm.moe_layer_forward(part, dev(x), out, ws)
+    assert mm.moe_read_status(ws) == mm.STATUS_NOT_RESIDENT
+    assert_ffn_close(out.cpu().numpy(), ref_gate[0, 1] * orc.expert_ffn(wl.experts[kept], x), "non-resident")
