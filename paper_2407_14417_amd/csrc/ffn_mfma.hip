@@ -20,8 +20,8 @@
 //                up to 256 rows, the order of loads, LDS reads and products pinned by hand.
 //   quant4_body  4-bit experts in those launches, chunks of 2 .. 8 tiles: the same schedule with the expansion of the
 //                codes folded in.
-//   quant4_wide_body  the same for chunks of 9 .. 12 tiles (a 4-bit expert's chunks hold up to 192 rows).
-//   quant8_body  8-bit experts in those launches, chunks of 2 .. 12 tiles.
+//   quant4_wide_body  the same for chunks of 9 .. 16 tiles.
+//   quant8_body  8-bit experts in those launches, chunks of 2 .. 16 tiles.
 #include <atomic>
 
 #include "common.hpp"
@@ -42,7 +42,7 @@ constexpr int spb_for(int ct) { return (8 / ct) < kSPBMax ? (8 / ct) : kSPBMax; 
 constexpr int kKTile = 128;                 // contraction elements per LDS tile
 constexpr int kDirectRows = 256;            // most activation rows of a chunk of a 16-bit expert (direct_body)
 constexpr unsigned kComputeUnits = 256;     // of the MI355X
-constexpr int kQuantRows = 192;             // ... of a 4-bit expert (quant4_wide_body: 12 tiles leave it the registers it needs)
+constexpr int kQuantRows = 256;             // ... of a 4-bit or 8-bit expert (quant4_wide_body, quant8_body)
 
 struct MfmaArgs {
     DevExperts ex;
@@ -997,10 +997,11 @@ __device__ __forceinline__ void quant4_body(const TileCtx& c, const DevExpert& e
     store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
 }
 
-// 4-bit weights against chunks of 129 .. 192 activation rows (9 .. 12 tiles): quant4_body's expansion and scale
+// 4-bit weights against chunks of 129 .. 256 activation rows (9 .. 16 tiles): quant4_body's expansion and scale
 // hand-out in direct_body's two-unit schedule.  A workgroup's time is 35 us for expanding its 256 x 4096 codes plus
 // 6 us per tile of 16 rows (prefill workload, per-workgroup device clock stamps), so one chunk of 9 tiles costs 89 us
-// where chunks of 8 tiles and 1 tile cost 87 + 49 us.  A sub-step's products run in two units (tiles 0 .. 7, then the
+// where chunks of 8 tiles and 1 tile cost 87 + 49 us.  (8 experts with 200 rows each: two chunks of 7 tiles 578 + 275 us in
+// the two projections, one of 13 tiles 517 + 227 us; with 256 rows, two of 8 or one of 16: 636 + 300, 625 + 274 us.)  A sub-step's products run in two units (tiles 0 .. 7, then the
 // rest), each with its own B register set; the 52 instructions that expand the next sub-step's A operands are spread
 // over the products of both.  Activations are staged in two batches of at most 8 pieces per thread, as in direct_body.
 // Codes and scales of later steps are asked for at the end of a step, right after its last activation loads (loads
@@ -1010,7 +1011,9 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
     static_assert(NCT > 8 && 16 * NCT <= kQuantRows, "two units of at most 8 tiles");
     constexpr int NA = 4;
     constexpr int NT = UP ? 32 * NA : 64 * NA;
-    constexpr int R = 4;                               // ring slots = steps of codes in flight
+    // ring slots = steps of codes in flight.  Above 12 tiles the accumulators take the accumulation registers the ring
+    // would spill to, and a step is long enough (2.5 us and more) for two steps of codes to cover the trip to memory.
+    constexpr int R = NCT > 12 ? 2 : 4;
     constexpr int NU0 = 8;                             // tiles in a sub-step's first unit; the second holds the rest
     constexpr int XB = 8;                              // activation pieces per batch (the second holds the rest)
     static_assert(NCT - XB <= XB, "two batches");
@@ -1158,7 +1161,7 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
             for (int sb = 0; sb < 4; ++sb) {
                 const int u = 4 * g + sb;                          // parity of the A register sets
                 // what the next sub-step multiplies: word sb + 1 of this step's codes, or word 0 of the next step's
-                const int nslot = sb < 3 ? g : (g + 1) & 3, nword = (sb + 1) & 3;
+                const int nslot = (sb < 3 ? g : g + 1) % R, nword = (sb + 1) & 3;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int v = 2 * sb + h;                      // unit of the step; B register set v & 1
@@ -1226,7 +1229,7 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
                 if (sb == 3) {
                     // the codes of four steps on, into the slot this step has used up; every fourth step the scales
                     // and zeros of the next four
-                    load_a(g, step + R);
+                    load_a(g % R, step + R);
                     if (g == 0) load_sz(sz_b, base / 4 + 1);
 #pragma unroll
                     for (int t = 0; t < NA; ++t) { s2[t] = s2n[t]; z2[t] = z2n[t]; }
@@ -1241,15 +1244,16 @@ __device__ __forceinline__ void quant4_wide_body(const TileCtx& c, const DevExpe
     store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
 }
 
-// 8-bit weights against chunks of 17 .. 192 activation rows (launches with 128-row chunks): the pinned schedule of
-// quant4_body (up to 8 tiles) and quant4_wide_body (9 .. 12 tiles: two units per sub-step, activations staged in two
+// 8-bit weights against chunks of 17 .. 256 activation rows (launches with 128-row chunks): the pinned schedule of
+// quant4_body (up to 8 tiles) and quant4_wide_body (9 .. 16 tiles: two units per sub-step, activations staged in two
 // batches), with the byte-permute expansion.  Lane (r16, c4) loads the 32 bytes that hold its 32 codes of a
 // 128-column step (two 128-bit loads); words 2 sb and 2 sb + 1 are its operand of sub-step sb, in column order, so the
 // staged activations keep theirs.  A step's codes are twice as many registers as a 4-bit step's, so the ring holds two
 // steps: a step of 8 tiles takes 1.9 us, and its codes are asked for one and a quarter steps ahead.
 // (tile_body, which staged codes through LDS behind a barrier per step and had 1, 2, 4 or 8 tiles: 1000 tokens, 8
 // experts, top-2, Mixtral shape, 801 us in the up-projection and 466 us in the down-projection; 710 and 349 us here.)
-// Two stages of activations under way up to 8 tiles: no gain (913 against 933 us for the block).
+// Chunks of up to 256 instead of 192 rows: block 913 -> 891 us.  Two stages of activations under way up to 8 tiles, and
+// codes of 64 contiguous bytes per row and load instruction: no gain (933 us, + 2 %).
 // The number of steps is a multiple of 4 here.
 template <bool UP, int NCT>
 __device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& ee, void* out_base) {
@@ -1640,7 +1644,7 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     }
 #undef MOEMIX_DIRECT
 #define MOEMIX_QUANT4(n) quant4_body<UP, CT >= 8 && !HALF ? (n) : 8>(c, ee, out_base)
-#define MOEMIX_QUANT4W(n) quant4_wide_body<UP, CT >= 8 && !HALF ? (n) : 12>(c, ee, out_base)
+#define MOEMIX_QUANT4W(n) quant4_wide_body<UP, CT >= 8 && !HALF ? (n) : 9>(c, ee, out_base)
     if (!HALF && CT >= 8 && quant_ok && prec == MOE_PREC_INT4G64 && nct >= 2) {
         switch (nct) {
             case 2: MOEMIX_QUANT4(2); break;
@@ -1653,7 +1657,11 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
             case 9: MOEMIX_QUANT4W(9); break;
             case 10: MOEMIX_QUANT4W(10); break;
             case 11: MOEMIX_QUANT4W(11); break;
-            default: MOEMIX_QUANT4W(12); break;
+            case 12: MOEMIX_QUANT4W(12); break;
+            case 13: MOEMIX_QUANT4W(13); break;
+            case 14: MOEMIX_QUANT4W(14); break;
+            case 15: MOEMIX_QUANT4W(15); break;
+            default: MOEMIX_QUANT4W(16); break;
         }
         return;
     }
@@ -1672,7 +1680,11 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
             case 9: MOEMIX_QUANT8(9); break;
             case 10: MOEMIX_QUANT8(10); break;
             case 11: MOEMIX_QUANT8(11); break;
-            default: MOEMIX_QUANT8(12); break;
+            case 12: MOEMIX_QUANT8(12); break;
+            case 13: MOEMIX_QUANT8(13); break;
+            case 14: MOEMIX_QUANT8(14); break;
+            case 15: MOEMIX_QUANT8(15); break;
+            default: MOEMIX_QUANT8(16); break;
         }
         return;
     }
@@ -1769,6 +1781,10 @@ int chunk_slots(const RowMap& rows, int P, int E, int ct) {
 
 }  // namespace
 
+// The two projections are separate instantiations of everything above; the build compiles one object for each
+// (MOEMIX_MFMA_UP, MOEMIX_MFMA_DOWN; neither: both in one).
+#if !defined(MOEMIX_MFMA_DOWN)
+
 // every contraction range must hold at least two 128-column steps (4-bit codes are fetched in pairs of steps)
 // (and a weight matrix spans less than 4 GB: rows are addressed with 32-bit byte offsets from the matrix)
 bool mfma_shape_ok(int d, int f) {
@@ -1818,6 +1834,9 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     launch_ct<true>(a, ct, grid, st);
 }
 
+#endif
+#if !defined(MOEMIX_MFMA_UP)
+
 void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,
                           int ct, int splits, size_t split_stride, int32_t* status, hipStream_t st) {
     TraceScope trace(kKernelDown, st);
@@ -1833,5 +1852,7 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     dim3 grid(a.tiles * splits, chunk_slots(rows, P, E, ct), 1);
     launch_ct<false>(a, ct, grid, st);
 }
+
+#endif
 
 }  // namespace moemix

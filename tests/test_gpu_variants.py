@@ -188,10 +188,12 @@ def test_expert_ffn_8bit_pipelined_body(orc, n):
     assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[1], x), f"n={n}")
 
 
-@pytest.mark.parametrize("T", [139, 150, 170, 185, 230])
-def test_block_8bit_chunks_of_more_than_128_rows(orc, T):
-    """One expert takes every token: chunks of 9, 10, 11 and 12 tiles, then two of 8."""
-    _check_block(orc, common.Config(f"steps4_8bit_T{T}", 1024, 2048, 2, 2, T, (), int8_experts=(0, 1)))
+@pytest.mark.parametrize("T", [139, 150, 170, 185, 200, 215, 230, 256, 257])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_block_quantized_chunks_of_more_than_128_rows(orc, T, bits):
+    """Both experts take every token: chunks of 9 to 16 tiles, then two of 9."""
+    _check_block(orc, common.Config(f"steps4_{bits}bit_T{T}", 1024, 2048, 2, 2, T, (0, 1) if bits == 4 else (),
+                                    int8_experts=(0, 1) if bits == 8 else ()))
 
 
 # One token at widths that are no multiple of 2048: rows shorter than a wavefront's loads, one load per lane exactly,
