@@ -125,14 +125,20 @@ int layer_body(const moe_layer* L, const DevExperts& table, const half_t* x, int
     launch_route(x, (const half_t*)L->w_gate, L->gate_bias, T, d, E, k, w.idx, w.gate, idx_out, gate_out,
                  reset_status ? w.status : nullptr, st, rms_gain, eps, w.xn);
     if (rms_gain) x = w.xn;
-    launch_permute(w.idx, T * k, E, w.counts, w.offsets, w.perm, w.inv, w.status, st);
-    RowMap rows{w.offsets, w.perm, k, -1, 0};
     const size_t split_stride = (size_t)T * k * d;
-    if (use_mfma(L, T * k)) {
-        const MfmaPlan p = plan_for(L, T * k);
+    const bool mfma = use_mfma(L, T * k);
+    MfmaPlan p{1, 1};
+    if (mfma) p = plan_for(L, T * k);
+    // few pairs: no launch for the grouping, unless that is the kernel the caller wants to measure
+    const bool inline_groups = mfma && group_inline_ok(T * k, p.ct) && !trace_armed(kKernelPermute);
+    if (!inline_groups) launch_permute(w.idx, T * k, E, w.counts, w.offsets, w.perm, w.inv, w.status, st);
+    RowMap rows{w.offsets, w.perm, k, -1, 0};
+    if (inline_groups) rows.idx = w.idx;
+    if (mfma) {
         launch_ffn_up_mfma(table, E, rows, T * k, x, d, f, w.h, p.ct, w.status, st);
         launch_ffn_down_mfma(table, E, rows, T * k, w.h, d, f, w.y, p.ct, p.down_splits, split_stride, w.status, st);
-        launch_combine(w.y, p.down_splits, split_stride, w.gate, w.inv, T, d, k, residual, out, st);
+        launch_combine(w.y, p.down_splits, split_stride, w.gate, inline_groups ? nullptr : w.inv, T, d, k, residual, out, st,
+                       w.idx);
     } else {
         launch_ffn_up(table, E, rows, x, d, f, w.h, w.status, st);
         launch_ffn_down(table, E, rows, w.h, d, f, w.y, w.status, st);
@@ -155,6 +161,7 @@ thread_local Trace g_trace[kKernelCount];   // one slot per kernel id: several k
 
 void trace_arm(int kernel, hipEvent_t start, hipEvent_t stop) { g_trace[kernel] = Trace{true, start, stop}; }
 void trace_disarm(int kernel) { g_trace[kernel] = Trace{}; }
+bool trace_armed(int kernel) { return g_trace[kernel].armed; }
 
 TraceScope::TraceScope(int kernel_, hipStream_t st_) : kernel(kernel_), st(st_) {
     if (g_trace[kernel].armed) (void)hipEventRecord(g_trace[kernel].start, st);

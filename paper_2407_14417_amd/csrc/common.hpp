@@ -124,6 +124,13 @@ __device__ __forceinline__ void wave_lds_handover() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The expert indices of at most 64 N pairs, pair 64 q + lane in v[q] (-1 past the end), for groupings by ballot.
+template <int N>
+__device__ __forceinline__ void load_pairs(const int32_t* __restrict__ idx, int P, int lane, int (&v)[N]) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] = 64 * q + lane < P ? idx[64 * q + lane] : -1;
+}
+
 // Reinterpret a 32-bit word as two halves.  The argument is taken by value on purpose: the bit-cast
 // builtin applied directly to an element of a vector lvalue (v[j]) reads element 0 whatever j is.
 __device__ __forceinline__ half2_t as_half2(uint32_t v) { return __builtin_bit_cast(half2_t, v); }

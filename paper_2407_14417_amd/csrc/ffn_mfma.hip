@@ -48,6 +48,8 @@ struct MfmaArgs {
     DevExperts ex;
     const int32_t* offsets;   // [E+1] grouped rows per expert, or null in direct mode
     const int32_t* perm;      // up, grouped: grouped row -> flat pair (token = pair / top_k); null: rows in order
+    const int32_t* idx;       // [P] the routing result, if the grouping is worked out from it (offsets, perm unused)
+    int P;
     int top_k;
     int direct_expert, direct_n;
     const half_t* in;         // up: x [T, K]; down: h [rows, K]
@@ -144,6 +146,7 @@ __device__ __forceinline__ half8_t expand_bytes(uint32_t w0, uint32_t w1, half2_
 struct TileCtx {
     const half_t* in;        // activations
     const int32_t* perm;     // up, grouped: grouped row -> flat pair; else null
+    const uint16_t* tokens;  // up, grouping worked out by the workgroup: the chunk's rows -> tokens (LDS); else null
     int top_k;
     int K, N;
     int begin, m0, rows;     // grouped rows [begin + m0, begin + m0 + rows)
@@ -229,7 +232,8 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         int rr = tid / PPR + RPP * i;
         rr = rr < c.rows ? rr : c.rows - 1;
         const int g = c.begin + c.m0 + rr;
-        const uint32_t src = (UP && c.perm) ? (uint32_t)(c.perm[g] / c.top_k) : (uint32_t)g;
+        const uint32_t src = (UP && NA == kNASmall && c.tokens) ? (uint32_t)c.tokens[rr]
+                           : (UP && c.perm) ? (uint32_t)(c.perm[g] / c.top_k) : (uint32_t)g;
         xoff[i] = src * (uint32_t)K * 2 + (pcol & 15) * 16;
     }
     uint4_t xr[NP];
@@ -1563,7 +1567,40 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
         return (((n + nch - 1) / nch) + 15) & ~15;
     };
     int e, begin, cnt, per, chunk = blockIdx.y;
-    if (a.direct_expert >= 0) {
+    TileCtx c;
+    c.tokens = nullptr;
+    if (CT <= 2 && a.idx) {
+        // few pairs: the expert's rows by ballots over the routing result, every wavefront for itself; grouped rows keep
+        // increasing pair order, as the grouping kernel has them
+        constexpr int NQ = kInlinePairs / 64;
+        __shared__ uint16_t tokens[4][MC];
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        int v[NQ];
+        load_pairs(a.idx, a.P, lane, v);
+        e = -1; begin = 0; cnt = 0; per = MC;
+        for (int i = 0; i < a.E; ++i) {
+            int n = 0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) n += __popcll(__ballot(v[q] == i));
+            const int nch = (n + MC - 1) / MC;
+            if (chunk < nch) { e = i; cnt = n; break; }
+            chunk -= nch;
+            begin += n;
+        }
+        if (e < 0) return;
+        if (UP) {
+            int row = -chunk * MC;                         // of the chunk
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const unsigned long long m = __ballot(v[q] == e);
+                const int r = row + __popcll(m & ((1ull << lane) - 1ull));
+                if (v[q] == e && r >= 0 && r < MC) tokens[wave][r] = (uint16_t)((64 * q + lane) / a.top_k);
+                row += __popcll(m);
+            }
+            wave_lds_handover();
+            c.tokens = tokens[wave];
+        }
+    } else if (a.direct_expert >= 0) {
         e = a.direct_expert; begin = 0; cnt = a.direct_n; per = chunk_rows(e, cnt);
     } else {
         // Chunks are handed out expert by expert in the order the host has put the experts in (launch_order)
@@ -1576,7 +1613,6 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
         }
         if (e < 0) return;
     }
-    TileCtx c;
     c.m0 = chunk * per;
     if (c.m0 >= cnt) return;
     c.in = a.in; c.perm = a.perm; c.top_k = a.top_k; c.K = a.K; c.N = a.N;
@@ -1825,6 +1861,7 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     MfmaArgs a;
     a.ex = ex; a.offsets = rows.offsets; a.perm = rows.perm; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
+    a.idx = rows.idx; a.P = P;
     a.in = x; a.out = h; a.K = d; a.N = f; a.E = E; a.k_per_split = d; a.split_stride = 0; a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     launch_order(ex, E, ct, a.order);
@@ -1843,6 +1880,7 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     MfmaArgs a;
     a.ex = ex; a.offsets = rows.offsets; a.perm = nullptr; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
+    a.idx = rows.idx; a.P = P;
     a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = (f + kKTile - 1) / kKTile / splits * kKTile; a.split_stride = split_stride;
     a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);

@@ -6,23 +6,56 @@
 
 namespace moemix {
 
+// v += y[p] for p = 1 .. splits - 1, in order, up to seven of them asked for per trip to memory (added one load at a
+// time, the 14 partial results of 5 tokens in the Mixtral shape took 10.2 us; 5.7 us here).
+__device__ __forceinline__ void add_splits(const float* __restrict__ y, int splits, size_t split_stride, float4_t& v) {
+    for (int p0 = 1; p0 < splits; p0 += 7) {
+        float4_t part[7];
+#pragma unroll
+        for (int p = 0; p < 7; ++p) {
+            const int at = p0 + p < splits ? p0 + p : splits - 1;
+            part[p] = *(const float4_t*)(y + at * split_stride);
+        }
+#pragma unroll
+        for (int p = 0; p < 7; ++p)
+            if (p0 + p < splits) v += part[p];
+    }
+}
+
 // out[t, c] = fp16( residual[t, c] + sum_s gate[t, s] * sum_p y[p][inv[t*k+s], c] ), slots and partials added in order.
+// INLINE: the grouped row of a pair is the number of pairs of lower experts and of earlier pairs of its own, counted
+// by ballots over all of them.
+template <bool INLINE>
 __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ y, int splits, size_t split_stride,
                                                        const float* __restrict__ gate, const int32_t* __restrict__ inv,
-                                                       int d, int k, const half_t* __restrict__ residual,
-                                                       half_t* __restrict__ out) {
+                                                       const int32_t* __restrict__ idx, int P, int d, int k,
+                                                       const half_t* __restrict__ residual, half_t* __restrict__ out) {
     const int t = blockIdx.y;
-    const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (c >= d) return;
+    int pairs[INLINE ? kInlinePairs / 64 : 1];
+    if (INLINE) load_pairs(idx, P, threadIdx.x & 63, pairs);
+    const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
+    if (!INLINE && c >= d) return;                     // (the ballots want every lane)
     float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int s = 0; s < k; ++s) {
-        const int r = inv[t * k + s];
-        if (r < 0) continue;
+        int r;
+        if (INLINE) {
+            const int me = t * k + s, e = idx[me], lane = threadIdx.x & 63;
+            r = 0;
+#pragma unroll
+            for (int q = 0; q < kInlinePairs / 64; ++q)
+                r += __popcll(__ballot(pairs[q] >= 0 && (pairs[q] < e || (pairs[q] == e && 64 * q + lane < me))));
+        } else {
+            r = inv[t * k + s];
+            if (r < 0) continue;
+        }
+        if (INLINE && c >= d) continue;
         const float g = gate[t * k + s];
-        float4_t v = *(const float4_t*)(y + (size_t)r * d + c);
-        for (int p = 1; p < splits; ++p) v += *(const float4_t*)(y + p * split_stride + (size_t)r * d + c);
+        const float* const row = y + (size_t)r * d + c;
+        float4_t v = *(const float4_t*)row;
+        add_splits(row, splits, split_stride, v);
         acc += g * v;
     }
+    if (INLINE && c >= d) return;
     if (residual) {
         const half4_t rv = *(const half4_t*)(residual + (size_t)t * d + c);
 #pragma unroll
@@ -35,10 +68,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 }
 
 void launch_combine(const float* y, int splits, size_t split_stride, const float* gate, const int32_t* inv, int T, int d,
-                    int k, const half_t* residual, half_t* out, hipStream_t st) {
+                    int k, const half_t* residual, half_t* out, hipStream_t st, const int32_t* idx) {
     TraceScope trace(kKernelCombine, st);
-    dim3 grid((d / 4 + 255) / 256, T);
-    combine_kernel<<<grid, 256, 0, st>>>(y, splits, split_stride, gate, inv, d, k, residual, out);
+    // few tokens: one wavefront per workgroup, or there are no more workgroups than a quarter of the compute units
+    const int threads = (size_t)T * d <= 64 * 4096 ? 64 : 256;
+    dim3 grid((d / 4 + threads - 1) / threads, T);
+    if (inv) combine_kernel<false><<<grid, threads, 0, st>>>(y, splits, split_stride, gate, inv, nullptr, 0, d, k, residual, out);
+    else combine_kernel<true><<<grid, threads, 0, st>>>(y, splits, split_stride, gate, nullptr, idx, T * k, d, k, residual, out);
 }
 
 // dst[i] = sum_p y[p][i], partials added in order
@@ -46,7 +82,7 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
                                                              size_t n4, float* __restrict__ dst) {
     for (size_t i = blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
         float4_t v = ((const float4_t*)y)[i];
-        for (int p = 1; p < splits; ++p) v += *(const float4_t*)(y + p * split_stride + i * 4);
+        add_splits(y + i * 4, splits, split_stride, v);
         ((float4_t*)dst)[i] = v;
     }
 }

@@ -15,7 +15,16 @@ struct RowMap {
     int top_k;
     int direct_expert;       // >= 0: direct mode
     int direct_n;
+    // few pairs (group_inline_ok): the routing result [P] itself, from which every workgroup works out the grouping
+    // that offsets and perm would tell it (those are not read then)
+    const int32_t* idx = nullptr;
 };
+
+// Up to kInlinePairs pairs in launches with at most 32 rows per chunk, the kernels that need the grouping work it out
+// from the routing result with ballots, four per 64-lane register of expert indices: a fraction of a microsecond in
+// each of three launches in place of a launch of its own, 2.2 - 4.7 us.
+constexpr int kInlinePairs = 256;
+inline bool group_inline_ok(int P, int ct) { return P <= kInlinePairs && ct <= 2; }
 
 // rms_gain != null: the gating input is RMSNorm(x) * rms_gain (fp16), which is also written to xn [T, d].
 void launch_route(const half_t* x, const half_t* wg, const float* bias, int T, int d, int E, int k, int32_t* idx,
@@ -74,8 +83,9 @@ void launch_single_route(int32_t* idx, float* gate, int expert, hipStream_t st);
 
 // out[t, :] = fp16( (residual ? residual[t, :] : 0) + sum_s gate[t, s] * sum_p y[p][inv[t*k + s], :] ),
 // p over the `splits` partial results, `split_stride` elements apart.
+// inv == null: at most kInlinePairs pairs, their places are worked out from the routing result idx [T, k].
 void launch_combine(const float* y, int splits, size_t split_stride, const float* gate, const int32_t* inv, int T, int d,
-                    int k, const half_t* residual, half_t* out, hipStream_t st);
+                    int k, const half_t* residual, half_t* out, hipStream_t st, const int32_t* idx = nullptr);
 // dst[i] = sum_p y[p][i] for i < n (n a multiple of 4), p over the `splits` partial results `split_stride` elements apart
 void launch_reduce_splits(const float* y, int splits, size_t split_stride, size_t n, float* dst, hipStream_t st);
 void launch_zero_words(int32_t* p, int n, hipStream_t st);
@@ -101,6 +111,7 @@ enum KernelId { kKernelRoute = 0, kKernelPermute = 1, kKernelUp = 2, kKernelDown
 // One-shot event bracket around the next launch of a given kernel on this thread.
 void trace_arm(int kernel, hipEvent_t start, hipEvent_t stop);
 void trace_disarm(int kernel);
+bool trace_armed(int kernel);
 struct TraceScope {
     int kernel;
     hipStream_t st;

@@ -253,3 +253,27 @@ def test_one_token_any_width_non_resident_and_chain(orc):
     mm.moe_layer_forward(part, dev(x), out, ws)
     assert mm.moe_read_status(ws) == mm.STATUS_NOT_RESIDENT
     assert_ffn_close(out.cpu().numpy(), ref_gate[0, 1] * orc.expert_ffn(wl.experts[kept], x), "non-resident")
+
+
+# Few pairs: the grouping worked out inside the launches against the grouping launch (which runs when its kernel is to be
+# measured): one, two and four registers of pairs, all full or ragged, one and two tiles per chunk, several chunks per
+# expert, experts without tokens.
+@pytest.mark.parametrize("T,E,k,zipf,d,f", [(2, 8, 2, None, 256, 384), (32, 8, 2, None, 512, 1408), (33, 8, 2, 2.0, 512, 1408),
+                                            (64, 16, 4, 1.2, 256, 512), (128, 8, 2, 1.2, 384, 640), (33, 9, 7, None, 320, 448),
+                                            (29, 32, 8, 1.2, 256, 2816), (5, 8, 2, None, 1024, 14336)])
+def test_grouping_inside_the_launches(orc, T, E, k, zipf, d, f):
+    cfg = common.Config(f"inline_T{T}_E{E}_k{k}", d, f, E, k, T, tuple(range(0, E, 2)), zipf=zipf, int8_experts=(1,))
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    inside = _run_block(layer, wl.x, k)
+    start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record(), stop.record()
+    mm.moe_trace_kernel(mm.KERNEL_PERMUTE, start.cuda_event, stop.cuda_event)
+    apart = _run_block(layer, wl.x, k)
+    torch.cuda.synchronize()
+    assert start.elapsed_time(stop) > 0
+    for a, b in zip(inside, apart):
+        assert np.array_equal(a, b)
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, k, bias=wl.bias)
+    assert np.array_equal(inside[1], ref_idx)
+    assert_ffn_close(inside[0], ref, cfg.name)
