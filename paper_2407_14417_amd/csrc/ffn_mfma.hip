@@ -59,7 +59,7 @@ struct MfmaArgs {
     int tiles;                // tiles of weight rows (grid.x = tiles * splits)
     size_t split_stride;      // elements of y between two splits
     int unit_bytes;           // LDS bytes per A operand for weight staging: 4096 if any expert is 16-bit, else 2048
-    uint8_t order[MOE_MAX_EXPERTS];   // the experts in the order their chunks are handed out
+    uint32_t prec16, prec8;   // the experts held in 16 and in 8 bits, one bit each
     int32_t* status;
 };
 
@@ -1533,8 +1533,7 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int SPB = spb_for(CT);          // 128-column steps per LDS stage
     extern __shared__ __align__(16) uint8_t lds[];   // [2][MC][SPB * 256 + 16]
     const int tid = threadIdx.x;
-    // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by
-    // chunk, in expert order
+    // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk
     // Workgroups go to the 8 XCDs (each with an L2 of its own) in turn, in launch order: with 2, 4 or 8 contraction
     // splits those of one chunk and split, which read the same slice of the activations, get the indices that
     // land on the same 4, 2 or 1 XCDs.
@@ -1560,8 +1559,13 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     // 128 + 20 rows, 89 us in one chunk)
     const bool quant_ok = wide_ok && !(n_steps & 3);
     const bool wide_quant_ok = quant_ok && (a.direct_expert < 0 || gridDim.x * gridDim.y >= 2 * kComputeUnits);
+    // (the precisions as two words: read lane by lane out of the expert table they would be vector loads from the
+    // kernel's arguments)
+    auto prec_of = [&](int expert) {
+        return (a.prec16 >> expert) & 1u ? MOE_PREC_FP16 : (a.prec8 >> expert) & 1u ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64;
+    };
     auto chunk_rows = [&](int expert, int n) {   // rows per chunk of an expert with n rows
-        const int prec = a.ex.e[expert].prec;
+        const int prec = prec_of(expert);
         if (!((wide_ok && prec == MOE_PREC_FP16 && n > 16 * (kDirectNCT - 1)) ||
               (wide_quant_ok && prec != MOE_PREC_FP16 && n > MC)))
             return MC;
@@ -1572,7 +1576,9 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
     int e, begin, cnt, per, chunk = blockIdx.y;
     TileCtx c;
     c.tokens = nullptr;
-    if (CT <= 2 && a.idx) {
+    if (a.direct_expert >= 0) {
+        e = a.direct_expert; begin = 0; cnt = a.direct_n; per = chunk_rows(e, cnt);
+    } else if (CT <= 2 && a.idx) {
         // few pairs: the expert's rows by ballots over the routing result, every wavefront for itself; grouped rows keep
         // increasing pair order, as the grouping kernel has them
         constexpr int NQ = kInlinePairs / 64;
@@ -1603,18 +1609,47 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
             wave_lds_handover();
             c.tokens = tokens[wave];
         }
-    } else if (a.direct_expert >= 0) {
-        e = a.direct_expert; begin = 0; cnt = a.direct_n; per = chunk_rows(e, cnt);
-    } else {
-        // Chunks are handed out expert by expert in the order the host has put the experts in (launch_order)
+    } else if (CT < 8) {
         e = -1; begin = 0; cnt = 0; per = MC;
-        for (int j = 0; j < a.E; ++j) {
-            const int i = a.order[j];
-            const int b = a.offsets[i], n = a.offsets[i + 1] - b, pr = chunk_rows(i, n), nch = (n + pr - 1) / pr;
-            if (chunk < nch) { e = i; begin = b; cnt = n; per = pr; break; }
+        for (int i = 0; i < a.E; ++i) {
+            const int b = a.offsets[i], n = a.offsets[i + 1] - b, nch = (n + MC - 1) / MC;
+            if (chunk < nch) { e = i; begin = b; cnt = n; break; }
             chunk -= nch;
         }
         if (e < 0) return;
+    } else {
+        // Chunks are handed out expert by expert, those whose workgroups run longest first: a launch ends when its last
+        // workgroup does, so the long ones must not start last.  Microseconds of a workgroup with 4096 columns in
+        // the prefill workload: 16-bit 118 - 132 (11 - 14 tiles; bound by its weight stream), 8-bit 99 and 155 (8 and
+        // 16), 4-bit 35 + 7 per tile.  16-bit experts go by their rows, so that those with two chunks come first: the
+        // chunks run side by side then and the second finds its weights in L2 (prefill workload by chunk length: + 2 %).
+        // Lane i of every wavefront looks after expert i.  (Against the 16-bit experts
+        // first and expert order otherwise, blocks: 1000 tokens, all 8-bit, 893 -> 858 us; 500 tokens, 32 experts, eight
+        // slots 207 -> 196; 1500 tokens, 16 experts, four slots 548 -> 540.  Launches of smaller chunks have more and shorter workgroups
+        // and lose 3 % to this search.)
+        const int lane = tid & 63;
+        const bool mine = lane < a.E;
+        int n = 0, b = 0;
+        if (mine) {
+            b = a.offsets[lane];
+            n = a.offsets[lane + 1] - b;
+        }
+        const int pr = chunk_rows(lane & 31, n), nch = (n + pr - 1) / pr;
+        const int tiles = (min(n, pr) + 15) >> 4, prec = prec_of(lane & 31);
+        const int cost = prec == MOE_PREC_FP16 ? 1000 + n : (prec == MOE_PREC_INT8G64 ? 45 : 35) + 7 * tiles;
+        int first = 0;                                     // chunks handed out before this expert's
+        for (int i = 0; i < a.E; ++i) {
+            const int ci = __builtin_amdgcn_readlane(cost, i);
+            const int ni = __builtin_amdgcn_readlane(nch, i);
+            first += (ci > cost || (ci == cost && i < lane)) ? ni : 0;
+        }
+        const unsigned long long owner = __ballot(mine && chunk >= first && chunk < first + nch);
+        if (!owner) return;
+        e = __builtin_ctzll(owner);
+        begin = __builtin_amdgcn_readlane(b, e);
+        cnt = __builtin_amdgcn_readlane(n, e);
+        per = __builtin_amdgcn_readlane(pr, e);
+        chunk -= __builtin_amdgcn_readlane(first, e);
     }
     c.m0 = chunk * per;
     if (c.m0 >= cnt) return;
@@ -1778,15 +1813,10 @@ void launch_ct_w(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
     }
 }
 
-// Launches with 128-row chunks hand out the chunks of the 16-bit experts first, then the others, each in expert
-// order: a 16-bit workgroup runs 110-130 us (bound by its weight stream) against 45-100 us for a 4-bit one, and the
-// launch ends when the last workgroup does, so the long ones must not start last.
-void launch_order(const DevExperts& ex, int E, int ct, uint8_t (&order)[MOE_MAX_EXPERTS]) {
-    int n = 0;
-    for (int pass = 0; pass < 2; ++pass)
-        for (int e = 0; e < E; ++e)
-            if (ct >= 8 ? (ex.e[e].prec == MOE_PREC_FP16) == (pass == 0) : pass == 0) order[n++] = (uint8_t)e;
-    for (; n < MOE_MAX_EXPERTS; ++n) order[n] = 0;
+uint32_t prec_mask(const DevExperts& ex, int E, int prec) {
+    uint32_t m = 0;
+    for (int e = 0; e < E; ++e) m |= (uint32_t)(ex.e[e].prec == prec) << e;
+    return m;
 }
 
 bool any_int8(const DevExperts& ex, int E) {
@@ -1810,12 +1840,16 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
     return 2048;
 }
 
-int chunk_slots(const RowMap& rows, int P, int E, int ct) {
-    const int mc = 16 * ct;
+// Chunks of a launch whose contraction ranges have n_steps steps of 128 columns.
+int chunk_slots(const RowMap& rows, int P, int E, int ct, int n_steps) {
+    int mc = 16 * ct;
     if (rows.direct_expert >= 0) return (rows.direct_n + mc - 1) / mc;
+    // the pipelined bodies, where the ranges allow them, take chunks of up to twice as many rows of every precision
+    // (a workgroup that finds no chunk costs some 3 us, at the launch's end)
+    static_assert(kDirectRows == 256 && kQuantRows == 256, "rows per chunk of the pipelined bodies");
+    if (ct == 8 && n_steps % 4 == 0) mc = 256;
     // every expert may end with one ragged chunk
-    const int full = P / mc + E;
-    return full;
+    return P / mc + E;
 }
 
 }  // namespace
@@ -1867,10 +1901,11 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     a.idx = rows.idx; a.P = P;
     a.in = x; a.out = h; a.K = d; a.N = f; a.E = E; a.k_per_split = d; a.split_stride = 0; a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
-    launch_order(ex, E, ct, a.order);
+    a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
+    a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
     const int up_rows = 32 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (f + up_rows - 1) / up_rows;
-    dim3 grid(a.tiles, chunk_slots(rows, P, E, ct), 1);
+    dim3 grid(a.tiles, chunk_slots(rows, P, E, ct, d % kKTile ? 1 : d / kKTile), 1);
     launch_ct<true>(a, ct, grid, st);
 }
 
@@ -1887,10 +1922,11 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = (f + kKTile - 1) / kKTile / splits * kKTile; a.split_stride = split_stride;
     a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
-    launch_order(ex, E, ct, a.order);
+    a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
+    a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
     const int down_rows = 64 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (d + down_rows - 1) / down_rows;
-    dim3 grid(a.tiles * splits, chunk_slots(rows, P, E, ct), 1);
+    dim3 grid(a.tiles * splits, chunk_slots(rows, P, E, ct, f % kKTile ? 1 : a.k_per_split / kKTile), 1);
     launch_ct<false>(a, ct, grid, st);
 }
 

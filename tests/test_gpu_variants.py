@@ -277,3 +277,21 @@ def test_grouping_inside_the_launches(orc, T, E, k, zipf, d, f):
     ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, k, bias=wl.bias)
     assert np.array_equal(inside[1], ref_idx)
     assert_ffn_close(inside[0], ref, cfg.name)
+
+
+# Launches with 128-row chunks hand out the longest workgroups first: experts with no, few, equal and most rows in an
+# order of sizes and precisions that is not the order of their indices, every chunk found exactly once.
+@pytest.mark.parametrize("E,k,T,bias", [(8, 2, 600, [0, 3, -9, 1, 3, 0, -9, 2]), (32, 8, 300, list(range(32))), (3, 3, 200, [0, 0, 0]),
+                                        (5, 1, 700, [-9, 4, -9, 4, 0])])
+@pytest.mark.parametrize("d,f", [(1024, 2048), (384, 640)])
+def test_chunks_handed_out_by_length(orc, E, k, T, bias, d, f):
+    cfg = common.Config(f"lpt_E{E}_T{T}_d{d}", d, f, E, k, T, tuple(range(0, E, 3)), int8_experts=tuple(range(2, E, 3)))
+    wg = common.gate_matrix(cfg)
+    gate_bias = np.array(bias, np.float32)
+    x = common.tokens_with_margin(cfg, wg, gate_bias)
+    wl = build_workload(cfg, orc)
+    wl.x, wl.bias = x, gate_bias
+    out, idx, _ = _run_block(device_layer(wl), x, k)
+    ref, ref_idx, _ = orc.layer_forward(x, wg, wl.experts, k, bias=gate_bias)
+    assert np.array_equal(idx, ref_idx)
+    assert_ffn_close(out, ref, cfg.name)
