@@ -703,10 +703,8 @@ __global__ __launch_bounds__(512) void decode_down_kernel(DevExperts ex, const i
 // token (or the hidden row) lies in LDS, from where a lane picks the activations of whatever 16-byte piece of a row it
 // has loaded; the last pieces of a row are masked lane by lane.  Whole blocks, graph replays over a pool of layers, five
 // launches -> these two: d_model 1024, d_ff 2816, 4- and 16-bit 29.0 -> 15.2 us; 256 x 512 18.0 -> 10.2; 32 experts of
-// 2048 x 1408, eight slots 61.8 -> 44.7; 2880 x 2880, four slots, 4-bit 73.4 -> 49.8; 4096 x 11008, 4- and 16-bit 94 -> 69
-// (5.0 TB/s); 7360 x 10624, 8-bit 279 -> 115.
-//   up  : a wavefront takes one row of w1 (lanes 0 .. 31) and the same row of w3 (lanes 32 .. 63) at a time
-//   down: LPR lanes per output row (64 where d_model is small, so that there are enough workgroups for the chip)
+// 2048 x 1408, eight slots 61.8 -> 40.4; 2880 x 2880, four slots, 4-bit 73.4 -> 45.6; 4096 x 11008, 4- and 16-bit 94 -> 62
+// (5.6 TB/s); 7360 x 10624, 8-bit 279 -> 102.
 // 16-byte pieces of the activations are stored at swizzled places: lanes that read every fourth piece (4-bit rows: 32
 // columns per lane), every second one (8-bit) or consecutive ones (16-bit) then hit different banks.
 __device__ __forceinline__ int act_slot(int piece) { return piece ^ ((piece >> 3) & 3); }
@@ -1033,14 +1031,16 @@ template <int NCHUNK>
 static void launch_up_any(const DevExperts& ex, const int32_t* idx, const half_t* x, int d, int f, int k, half_t* h,
                           int32_t* status, int E, const GateArgs* gating, hipStream_t st) {
     // Workgroups of four wavefronts, a row pair each at most.  Every one of them reads the gate matrix (E rows of d) out
-    // of L2, so no more than leave that traffic a few times the weights' (a row of w1 and w3
-    // per workgroup and expert), but enough to fill the chip.
+    // of L2, so no more than leave that traffic at the weights' own (two workgroups per row pair and expert), but
+    // enough to fill the chip, and all of them resident at once: a second generation would evaluate the gating network
+    // again (four per compute unit at d_model up to 2048, three above).  Block at E = 32, four slots, 2880 x 2880, 4-bit:
+    // 360 workgroups 50.4 us, 720 44.8, 1024 54.9; E = 32, eight slots, 2048 x 1408: 352 44.9 us, 704 40.6, 1024 40.5.
     const int rows = k * f;
     int blocks = (rows + 3) / 4;
-    const int by_gate = gating ? rows / E : rows;
+    const int by_gate = gating ? 2 * rows / E : rows, resident = NCHUNK <= 4 ? 1024 : 768;
     if (blocks > by_gate) blocks = by_gate;
     if (blocks < 256) blocks = (rows + 3) / 4 < 256 ? (rows + 3) / 4 : 256;
-    if (blocks > 1024) blocks = 1024;
+    if (blocks > resident) blocks = resident;
     const size_t lds = act_lds_bytes(d, true, true, true);
     if (gating) decode_up_any_kernel<NCHUNK, true><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, *gating);
     else decode_up_any_kernel<NCHUNK, false><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, GateArgs{});
