@@ -1525,12 +1525,16 @@ __device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& e
 // with scalar products, which is what such widths had, took 296 + 190 us for 33 tokens, 4 of 32 experts, d_model and
 // d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
 // a time and 4-bit rows whose 128-byte requests straddle two lines.)
-template <bool UP, int CT, bool WIDE, bool HALF>
-__global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
+// SPB: 128-column steps per LDS stage.  Launches with 64-row chunks of blocks without 16-bit experts take one instead of
+// two: their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two wavefronts per SIMD
+// are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 364 -> 320 us, 8-bit 412 -> 378;
+// 4-bit 2048 x 5632, 160 tokens 116 -> 99.  With 16-bit experts (99 KB) there is no second workgroup and one step per
+// stage loses up to 4 %; contractions that end with half a step lose 7 %.
+template <bool UP, int CT, bool WIDE, bool HALF, int SPB>
+__global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int MC = 16 * CT;                  // activation rows per chunk
     constexpr int NA = CT <= 2 ? kNASmall : 4;   // A operands per wavefront
     constexpr int NT = UP ? 32 * NA : 64 * NA;   // weight rows per workgroup
-    constexpr int SPB = spb_for(CT);          // 128-column steps per LDS stage
     extern __shared__ __align__(16) uint8_t lds[];   // [2][MC][SPB * 256 + 16]
     const int tid = threadIdx.x;
     // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk
@@ -1780,14 +1784,14 @@ __global__ __launch_bounds__(256) void grouped_mfma_kernel(const MfmaArgs a) {
 #undef MOEMIX_BODY
 }
 
-template <bool UP, int CT, bool WIDE, bool HALF>
+template <bool UP, int CT, bool WIDE, bool HALF, int SPB = spb_for(CT)>
 void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr int NA = CT <= 2 ? kNASmall : 4;
     // activation stages + 4 wavefronts x NA operands of weight staging
     // (launches with 128-row chunks: at least two unpadded 256-row stages for the pipelined bodies)
     constexpr size_t lds_wide = CT >= 8 && !HALF ? 2u * kDirectRows * kKTile * 2 : 0;
-    const size_t lds_max = 2u * 16 * CT * (spb_for(CT) * kKTile * 2 + 16) + 4 * NA * 4096;
-    const size_t lds_plain = 2u * 16 * CT * (spb_for(CT) * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
+    const size_t lds_max = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * 4096;
+    const size_t lds_plain = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
     const size_t lds_bytes = lds_plain > lds_wide ? lds_plain : lds_wide;
     // the attribute belongs to (kernel, device): set it once per device of the process (bit d of the mask; devices
     // past the 64th set it on every launch)
@@ -1796,11 +1800,11 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     (void)hipGetDevice(&dev);
     const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
     if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
-        (void)hipFuncSetAttribute((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds_max);
         configured.fetch_or(bit, std::memory_order_relaxed);
     }
-    grouped_mfma_kernel<UP, CT, WIDE, HALF><<<grid, 256, lds_bytes, st>>>(a);
+    grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
 }
 
 template <bool UP, bool WIDE, bool HALF>
@@ -1808,7 +1812,10 @@ void launch_ct_w(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
     switch (ct) {
         case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
         case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
-        case 4: launch_one<UP, 4, WIDE, HALF>(a, grid, st); break;
+        case 4:
+            if (!HALF && a.unit_bytes == 2048) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
+            else launch_one<UP, 4, WIDE, HALF>(a, grid, st);
+            break;
         default: launch_one<UP, 8, WIDE, HALF>(a, grid, st); break;
     }
 }

@@ -295,3 +295,23 @@ def test_chunks_handed_out_by_length(orc, E, k, T, bias, d, f):
     ref, ref_idx, _ = orc.layer_forward(x, wg, wl.experts, k, bias=gate_bias)
     assert np.array_equal(idx, ref_idx)
     assert_ffn_close(out, ref, cfg.name)
+
+
+# 64-row chunks of blocks without 16-bit experts: one step per LDS stage (odd and even numbers of steps, ragged and full
+# chunks), the same bits as beside a 16-bit expert that no token reaches (two steps per stage).
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("d,f,T", [(640, 896, 140), (1024, 2048, 200), (384, 1536, 256)])
+def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
+    every = tuple(range(8))
+    cfg = common.Config(f"rows64_{bits}_{d}_{T}", d, f, 8, 2, T, every if bits == 4 else (), int8_experts=every if bits == 8 else ())
+    wl = build_workload(cfg, orc)
+    wl.bias = np.array([0, 0, 0, 0, 0, 0, 0, -50.0], np.float32)
+    wl.x = common.tokens_with_margin(cfg, wl.wg, wl.bias)
+    layer = device_layer(wl)
+    out, idx, _ = _run_block(layer, wl.x, 2)
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2, bias=wl.bias)
+    assert np.array_equal(idx, ref_idx) and not (idx == 7).any()
+    assert_ffn_close(out, ref, cfg.name)
+    w1, w3, w2 = (mm.Mat(dev(w)) for w in common.expert_weights_f16(cfg, 7))
+    beside = mm.Layer(d, f, 2, layer.w_gate, [*layer.experts[:7], mm.Expert(mm.PREC_FP16, w1, w3, w2)], layer.gate_bias)
+    assert np.array_equal(out, _run_block(beside, wl.x, 2)[0])
