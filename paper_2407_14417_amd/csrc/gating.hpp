@@ -103,12 +103,15 @@ __device__ __forceinline__ void gate_logits(const uint4_t (&xv)[NCHUNK], const h
 // left.
 __device__ __forceinline__ void gate_select(const float* __restrict__ logit, int E, int k, int lane,
                                             int (&sel)[MOE_MAX_TOPK], float (&lsel)[MOE_MAX_TOPK]) {
-    const float l = lane < E ? logit[lane] : 0.0f;
+    const float l = lane < E ? logit[lane] : -__builtin_inff();   // (lanes past the last expert go before none)
     if (!__ballot(l != l)) {
         int rank = lane < E ? 0 : MOE_MAX_EXPERTS;
-        for (int e = 0; e < E; ++e) {
-            const float le = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), e));
-            rank += (le > l || (le == l && e < lane)) ? 1 : 0;
+        for (int e0 = 0; e0 < E; e0 += 4) {
+#pragma unroll
+            for (int e = e0; e < e0 + 4; ++e) {
+                const float le = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), e));
+                rank += (le > l || (le == l && e < lane)) ? 1 : 0;
+            }
         }
 #pragma unroll
         for (int s = 0; s < MOE_MAX_TOPK; ++s) {
