@@ -104,7 +104,7 @@ __device__ __forceinline__ void gate_logits(const uint4_t (&xv)[NCHUNK], const h
 __device__ __forceinline__ void gate_select(const float* __restrict__ logit, int E, int k, int lane,
                                             int (&sel)[MOE_MAX_TOPK], float (&lsel)[MOE_MAX_TOPK]) {
     const float l = lane < E ? logit[lane] : -__builtin_inff();   // (lanes past the last expert go before none)
-    if (!__ballot(l != l)) {
+    if (k > 1 && !__ballot(l != l)) {                             // (one pass is cheaper than the ranking)
         int rank = lane < E ? 0 : MOE_MAX_EXPERTS;
         for (int e0 = 0; e0 < E; e0 += 4) {
 #pragma unroll
