@@ -724,9 +724,10 @@ __host__ __device__ constexpr size_t act_lds_bytes(int K, bool natural, bool bit
     return (size_t)K * 2 * ((natural ? 1 : 0) + (bits4 ? 1 : 0)) + (bits4 ? (size_t)K / 4 : 0) + (bits8 ? (size_t)K / 2 : 0);
 }
 
-// Thread's share of the 4-bit form: 32 columns per turn, read from four 16-byte pieces with `get`.
+// Thread's share of the 4-bit form: 32 columns per turn, read from four 16-byte pieces with `get`.  *unbounded is set
+// where a sum is not finite, that is, where an activation is not.
 template <typename Get>
-__device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get) {
+__device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
     for (int p = tid; p < K / 32; p += n_threads) {
         float se = 0.0f, so = 0.0f;
 #pragma unroll
@@ -737,11 +738,12 @@ __device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int
             so += ((float)v[1] + (float)v[3]) + ((float)v[5] + (float)v[7]);
         }
         a.sum4[p] = float2{1024.0f * se + 64.0f * so, se + so};
+        if (!__builtin_isfinite(se + so)) *unbounded = 1;
     }
 }
 
 template <typename Get>
-__device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get) {
+__device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
     for (int p = tid; p < K / 16; p += n_threads) {
         float sum = 0.0f;
 #pragma unroll
@@ -751,6 +753,7 @@ __device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, i
                    (((float)v[4] + (float)v[5]) + ((float)v[6] + (float)v[7]));
         }
         a.sum8[p] = float2{1024.0f * sum, sum};
+        if (!__builtin_isfinite(sum)) *unbounded = 1;
     }
 }
 
@@ -769,6 +772,23 @@ struct RowPiece {
             s = load_half((gptr_t)(m.scale + g));
             z = load_half((gptr_t)(m.zero + g));
         }
+    }
+    // the dequantized weights of piece `at`, one by one, against activations of any kind
+    __device__ __forceinline__ float dot_by_weight(const ActLds& a, int at) const {
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int j = 0; j < kCols / 8; ++j) {
+            const half8_t x = PREC == MOE_PREC_INT4G64 ? a.perm4[act_slot(4 * at + j)] : a.nat[act_slot(2 * at + j)];
+            const uint32_t w0 = PREC == MOE_PREC_INT4G64 ? (j & 2 ? (j & 1 ? v[3] : v[2]) : (j & 1 ? v[1] : v[0])) : (j ? v[2] : v[0]);
+            const uint32_t w1 = j ? v[3] : v[1];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {              // (4-bit: element c of the paired order is column c / 2 + 4 (c % 2))
+                const uint32_t code = PREC == MOE_PREC_INT4G64 ? (w0 >> (4 * (c / 2 + 4 * (c & 1)))) & 15u
+                                                               : ((c < 4 ? w0 : w1) >> (8 * (c & 3))) & 255u;
+                sum = fmaf((float)(half_t)fmaf((float)code, (float)s, (float)z), (float)x[c], sum);
+            }
+        }
+        return sum;
     }
     __device__ __forceinline__ float dot(const ActLds& a, int K, int piece) const {
         const int pieces = K / kCols;
@@ -842,6 +862,25 @@ __device__ __forceinline__ void walk_rows(const DevMat& mat, int n_rows, int K, 
     }
 }
 
+// The same for activations that are not all finite, with every weight dequantized.  The factored forms would turn an
+// infinite activation (a hidden value past 65504) into a NaN: they subtract 1024 times the sum of the activations, and
+// their terms of scale and zero may differ in sign.  Here the sum is the infinity that the products give, as in the
+// multi-token kernels.
+template <int PREC, int LPR, typename RowAt, typename Done>
+__device__ __forceinline__ void walk_rows_by_weight(const DevMat& mat, int n_rows, int K, const ActLds& act, int l, RowAt row_at, Done done) {
+#pragma unroll 1
+    for (int i = 0; i < n_rows; ++i) {
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int piece = l; piece < K / RowPiece<PREC>::kCols; piece += LPR) {
+            RowPiece<PREC> p;
+            p.load(mat, row_at(i), K, piece);
+            sum += p.dot_by_weight(act, piece);
+        }
+        done(row_at(i), sum);
+    }
+}
+
 // Sums over lanes 0 .. 31 and over lanes 32 .. 63.
 __device__ __forceinline__ void half_totals(float v, float& lo, float& hi) {
     v += dpp_move<0xB1>(v);
@@ -859,10 +898,12 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
                                                              half_t* __restrict__ h, int32_t* status, const GateArgs ga) {
     extern __shared__ __align__(16) uint8_t lds[];
     __shared__ float logit_s[MOE_MAX_EXPERTS];
+    __shared__ int unbounded;                          // an activation is not finite
     const ActLds act{(half8_t*)lds, (half8_t*)(lds + d * 2), (float2*)(lds + d * 4), (float2*)(lds + d * 4 + d / 4)};
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = wave_index();
     uint64_t routed = 0;                               // 5 bits per slot
+    if (tid == 0) unbounded = 0;
     if (ROUTE) {
         // (nothing of this launch raises status bits, see decode_up_kernel)
         if (blockIdx.x == 0 && tid == 0) *status = 0;
@@ -919,9 +960,10 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
         bits8 |= prec == MOE_PREC_INT8G64;
     }
     auto get = [&](int piece) { return act.nat[act_slot(piece)]; };
-    if (bits4) act_pair_up(act, d, tid, 256, get);
-    if (bits8) act_sum_bytes(act, d, tid, 256, get);
+    if (bits4) act_pair_up(act, d, tid, 256, get, &unbounded);
+    if (bits8) act_sum_bytes(act, d, tid, 256, get, &unbounded);
     if (bits4 || bits8) __syncthreads();
+    const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded);
     // Rows of all slots, dealt to the launch's wavefronts in turn: every share has its part of each slot.
     const int n_waves = gridDim.x * 4, gw = blockIdx.x * 4 + wave;
     for (int s = 0; s < k; ++s) {
@@ -939,9 +981,13 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
         };
         const DevMat mat = lane < 32 ? ee.w1 : ee.w3;
         const int l = lane & 31;
-        if (ee.prec == MOE_PREC_INT4G64) walk_rows<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
-        else if (ee.prec == MOE_PREC_INT8G64) walk_rows<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
-        else walk_rows<MOE_PREC_FP16, 32>(mat, rows, d, act, l, row_at, done);
+        if (ee.prec == MOE_PREC_INT4G64) {
+            if (by_weight) walk_rows_by_weight<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
+            else walk_rows<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
+        } else if (ee.prec == MOE_PREC_INT8G64) {
+            if (by_weight) walk_rows_by_weight<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
+            else walk_rows<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
+        } else walk_rows<MOE_PREC_FP16, 32>(mat, rows, d, act, l, row_at, done);
     }
 }
 
@@ -956,10 +1002,12 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
     extern __shared__ __align__(16) uint8_t lds[];
     // (one precision at a time: the natural order and the 4-bit order share their place)
     const ActLds act{(half8_t*)lds, (half8_t*)lds, (float2*)(lds + f * 2), (float2*)(lds + f * 2)};
+    __shared__ int unbounded[MOE_MAX_TOPK];            // slots whose hidden row is not all finite
     constexpr int kRows = 256 / LPR;
     const int tid = threadIdx.x, lane = tid & 63, l = tid & (LPR - 1);
     const int row = blockIdx.x * kRows + tid / LPR;
     const int row_safe = row < d ? row : d - 1;        // (lanes past the last row repeat it and store nothing)
+    if (tid < MOE_MAX_TOPK) unbounded[tid] = 0;
     float acc = 0.0f;
     for (int s = 0; s < k; ++s) {
         const DevExpert& ee = ex.e[__builtin_amdgcn_readfirstlane(idx[s])];
@@ -973,17 +1021,22 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
         auto get = [&](int piece) { return *(const half8_t*)(hs + piece * 8); };
         __syncthreads();                               // the last slot's hidden row has been read
         if (ee.prec == MOE_PREC_INT4G64) {
-            act_pair_up(act, f, tid, 256, get);
+            act_pair_up(act, f, tid, 256, get, &unbounded[s]);
         } else {
             for (int p = tid; p < f / 8; p += 256) act.nat[act_slot(p)] = get(p);
-            if (ee.prec == MOE_PREC_INT8G64) act_sum_bytes(act, f, tid, 256, get);
+            if (ee.prec == MOE_PREC_INT8G64) act_sum_bytes(act, f, tid, 256, get, &unbounded[s]);
         }
         __syncthreads();
+        const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded[s]);
         auto row_at = [&](int) { return row_safe; };
         auto done = [&](int, float sum) { acc = fmaf(g, sum, acc); };
-        if (ee.prec == MOE_PREC_INT4G64) walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-        else if (ee.prec == MOE_PREC_INT8G64) walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-        else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        if (ee.prec == MOE_PREC_INT4G64) {
+            if (by_weight) walk_rows_by_weight<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+            else walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        } else if (ee.prec == MOE_PREC_INT8G64) {
+            if (by_weight) walk_rows_by_weight<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+            else walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        } else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
     }
     float total;
     if (LPR == 64) {

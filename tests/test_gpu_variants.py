@@ -225,6 +225,28 @@ def test_one_row_any_width(orc, d, f, bits):
     assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[0], wl.x), f"d={d} f={f} bits={bits}")
 
 
+@pytest.mark.parametrize("d,f", [(192, 320), (1024, 2816), (2880, 960)])
+@pytest.mark.parametrize("bits", [4, 8, 16])
+def test_one_token_hidden_value_past_the_fp16_range(orc, d, f, bits):
+    """One hidden value beyond 65504 is an infinity: every output is that infinity with the sign of its weight, as in
+    the multi-token kernels, and no NaN."""
+    cfg = common.Config("overflow", d, f, 1, 1, 1, ())
+    wl = build_workload(cfg, orc)
+    w1, w3, w2 = common.expert_weights_f16(cfg, 0)
+    big = f - 5                                                   # in the last pieces of a hidden row
+    w1[big] = w3[big] = np.where(wl.x[0] < 0, -4, 4)
+    w2[:, big] = np.where(np.arange(d) % 3 == 0, -0.05, 0.05)     # (no dequantized weight there is zero)
+    stored = {4: orc.quantize_int4, 8: orc.quantize_int8, 16: orc.Mat}[bits]
+    wl.experts[0] = orc.Expert(stored(w1), stored(w3), stored(w2))
+    layer = device_layer(wl)
+    want = np.where(np.arange(d) % 3 == 0, -np.inf, np.inf)
+    assert np.array_equal(_run_block(layer, wl.x, 1)[0][0].astype(np.float64), want)
+    y = torch.empty((1, d), dtype=torch.float32, device="cuda")
+    mm.moe_expert_ffn_mixed(layer, 0, dev(wl.x), y, mm.alloc_workspace(layer, 1))
+    assert np.array_equal(y.cpu().numpy()[0].astype(np.float64), want)
+    assert np.array_equal(_run_block(layer, np.repeat(wl.x, 2, axis=0), 1)[0][0].astype(np.float64), want)   # two tokens
+
+
 def test_one_token_any_width_non_resident_and_chain(orc):
     cfg = common.Config("one_token_chain", 1088, 1472, 6, 2, 1, (0, 3), int8_experts=(1,))
     wl = build_workload(cfg, orc)
