@@ -166,8 +166,8 @@ int moe_layer_forward_static(const moe_layer* layer, const void* x, int T, void*
  * host memory; when the gating network routes a token to one of them it is copied into a slot of a device-side
  * swap space on `copy_stream` while the resident experts of the same call already compute on `stream`, then the
  * swapped-in experts run and their contribution is added.  The result equals moe_layer_forward on the same
- * layer with every expert resident (T > 1: bit for bit; T == 1: the output is rounded to fp16 once more between
- * the two passes).
+ * layer with every expert resident, bit for bit, except at T == 1 with d_model and d_ff both multiples of 2048, where
+ * the output is rounded to fp16 once more between the two passes.
  *   host_experts: HOST array [n_experts]; entry e is read only if layer->experts[e].resident == 0 and then
  *                 names the expert's matrices (same layouts, `prec` as in the layer) in pinned host memory;
  *                 a missed expert whose entry has no data keeps the behaviour of moe_layer_forward (left out,

@@ -65,9 +65,6 @@ constexpr int kDecodeUpBlocks = 1024;
 // Which kernels serve T tokens of a block: T == 1 the batch-1 kernels, otherwise the matrix-core path when
 // the shape allows it, else the shape-agnostic kernels.
 bool use_decode(int T) { return T == 1; }
-// The expert-miss path adds the experts it brings in to an fp16 output at one token.  It keeps the multi-token kernels,
-// which add every expert before the one rounding, for the widths that had them before the one-token kernels took any.
-bool use_decode_swap(const moe_layer* L, int T) { return T == 1 && decode_shape_ok(L->d_model, L->d_ff); }
 bool use_mfma(const moe_layer* L, int rows) {
     return rows > 1 && mfma_shape_ok(L->d_model, L->d_ff) && mfma_rows_ok(rows, L->d_model, L->d_ff);
 }
@@ -362,13 +359,15 @@ hipError_t copy_mat(const moe_mat& src, const MatBytes& b, char*& cursor, DevMat
     return e;
 }
 
-// Up- and down-projection of every expert the table marks runnable (deferred ones are skipped silently).
+// Up- and down-projection of every expert the table marks runnable (deferred ones are skipped silently).  At one token
+// the pass adds to the output (widths that are multiples of 2048) or leaves its slots' sums in w.y (the others).
 void run_experts(const moe_layer* L, const DevExperts& table, const half_t* x, int T, const Workspace& w,
                  const half_t* decode_residual, half_t* out, hipStream_t st) {
     const int d = L->d_model, f = L->d_ff, E = L->n_experts, k = L->top_k;
-    if (use_decode_swap(L, T)) {
+    if (use_decode(T)) {
         launch_decode_up(table, w.idx, x, d, f, k, w.h, w.status, kDecodeUpBlocks, st);
-        launch_decode_down(table, w.idx, w.gate, w.h, d, f, k, decode_residual, out, w.status, st);
+        if (decode_shape_ok(d, f)) launch_decode_down(table, w.idx, w.gate, w.h, d, f, k, decode_residual, out, w.status, st);
+        else launch_decode_down_slots(table, w.idx, w.h, d, f, k, w.y, w.status, st);
         return;
     }
     RowMap rows{w.offsets, w.perm, k, -1, 0};
@@ -439,7 +438,7 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
     // pass over the resident experts; the missed ones wait for their copies
     DevExperts table = device_table(layer);
     for (int i = 0; i < n_miss; ++i) table.e[missed[i]].resident = kDeferred;
-    const bool decode = use_decode_swap(layer, T);
+    const bool decode = use_decode(T);
     if (!decode) launch_permute(w.idx, T * k, E, w.counts, w.offsets, w.perm, w.inv, w.status, st);
     run_experts(layer, table, xin, T, w, nullptr, (half_t*)out, st);
 
@@ -468,7 +467,8 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
         e = hipEventRecord((hipEvent_t)swap->copied_event, cst);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, (hipEvent_t)swap->copied_event, 0);
         if (e != hipSuccess) return fail(MOE_EHIP, "HIP: %s", hipGetErrorString(e));
-        // at one token the weighted average is fused into the down-projection: this pass adds to the last one's output
+        // (one token, widths of multiples of 2048: the weighted average is fused into the down-projection, so this pass
+        // adds to the last one's output)
         run_experts(layer, round, xin, T, w, (const half_t*)out, (half_t*)out, st);
         e = hipEventRecord((hipEvent_t)swap->computed_event, st);
         if (e != hipSuccess) return fail(MOE_EHIP, "HIP: %s", hipGetErrorString(e));
@@ -476,6 +476,10 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
     if (!decode) {
         const int splits = use_mfma(layer, T * k) ? plan_for(layer, T * k).down_splits : 1;
         launch_combine(w.y, splits, (size_t)T * k * d, w.gate, w.inv, T, d, k, nullptr, (half_t*)out, st);
+    } else if (!decode_shape_ok(d, f)) {
+        uint32_t ran = 0;
+        for (int i = 0; i < E; ++i) ran |= (uint32_t)(table.e[i].resident == 1 || table.e[i].resident == kDeferred) << i;
+        launch_average_slots(w.y, w.idx, w.gate, ran, d, k, (half_t*)out, st);
     }
     return check_hip(st);
 }

@@ -991,14 +991,16 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
     }
 }
 
-// One workgroup: 256 / LPR output rows at a time, every slot of them in turn, its hidden row in LDS.
+// One workgroup: 256 / LPR output rows at a time, every slot of them in turn, its hidden row in LDS.  The slots' sums are
+// complete before they are weighted and added, in slot order: the expert-miss path, which runs the slots in more than
+// one launch, has them written to slot_sums [k, d] instead and gets the same bits from average_slots_kernel.
 template <int LPR>
 __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, const int32_t* __restrict__ idx,
                                                                const float* __restrict__ gate,
                                                                const half_t* __restrict__ h, int d, int f, int k,
                                                                const half_t* __restrict__ residual,
                                                                half_t* __restrict__ out, float* __restrict__ out32,
-                                                               int32_t* status) {
+                                                               float* __restrict__ slot_sums, int32_t* status) {
     extern __shared__ __align__(16) uint8_t lds[];
     // (one precision at a time: the natural order and the 4-bit order share their place)
     const ActLds act{(half8_t*)lds, (half8_t*)lds, (float2*)(lds + f * 2), (float2*)(lds + f * 2)};
@@ -1016,7 +1018,6 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
             if (tid == 0 && blockIdx.x == 0) atomicOr(status, kStatusNotResident);
             continue;
         }
-        const float g = gate[s];
         const half_t* const hs = h + (size_t)s * f;
         auto get = [&](int piece) { return *(const half8_t*)(hs + piece * 8); };
         __syncthreads();                               // the last slot's hidden row has been read
@@ -1029,7 +1030,8 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
         __syncthreads();
         const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded[s]);
         auto row_at = [&](int) { return row_safe; };
-        auto done = [&](int, float sum) { acc = fmaf(g, sum, acc); };
+        float sum = 0.0f;
+        auto done = [&](int, float v) { sum = v; };
         if (ee.prec == MOE_PREC_INT4G64) {
             if (by_weight) walk_rows_by_weight<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
             else walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
@@ -1037,19 +1039,21 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
             if (by_weight) walk_rows_by_weight<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
             else walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
         } else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        float total;
+        if (LPR == 64) {
+            total = wave_total(sum);
+        } else {
+            float lo, hi;
+            half_totals(sum, lo, hi);
+            total = lane < 32 ? lo : hi;
+        }
+        if (!slot_sums) acc = fmaf(gate[s], total, acc);
+        else if (l == 0 && row < d) slot_sums[(size_t)s * d + row] = total;
     }
-    float total;
-    if (LPR == 64) {
-        total = wave_total(acc);
-    } else {
-        float lo, hi;
-        half_totals(acc, lo, hi);
-        total = lane < 32 ? lo : hi;
-    }
-    if (l == 0 && row < d) {
+    if (!slot_sums && l == 0 && row < d) {
         const float t = residual ? (float)residual[row] : 0.0f;
-        if (out32) out32[row] = t + total;
-        else out[row] = (half_t)(t + total);
+        if (out32) out32[row] = t + acc;
+        else out[row] = (half_t)(t + acc);
     }
 }
 
@@ -1119,13 +1123,24 @@ void launch_decode_up(const DevExperts& ex, const int32_t* idx, const half_t* x,
     }
 }
 
+static void launch_down_any(const DevExperts& ex, const int32_t* idx, const float* gate, const half_t* h, int d, int f, int k,
+                            const half_t* residual, half_t* out, float* out32, float* slot_sums, int32_t* status, hipStream_t st) {
+    const size_t lds = act_lds_bytes(f, true, false, false) + (size_t)f / 2;   // one order and the larger of the sums
+    if (d <= kDownAnyWideRows) decode_down_any_kernel<64><<<(d + 3) / 4, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, slot_sums, status);
+    else decode_down_any_kernel<32><<<(d + 7) / 8, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, slot_sums, status);
+}
+
+void launch_decode_down_slots(const DevExperts& ex, const int32_t* idx, const half_t* h, int d, int f, int k, float* slot_sums,
+                              int32_t* status, hipStream_t st) {
+    TraceScope trace(kKernelDown, st);
+    launch_down_any(ex, idx, nullptr, h, d, f, k, nullptr, nullptr, nullptr, slot_sums, status, st);
+}
+
 void launch_decode_down(const DevExperts& ex, const int32_t* idx, const float* gate, const half_t* h, int d, int f,
                         int k, const half_t* residual, half_t* out, int32_t* status, hipStream_t st, float* out32) {
     TraceScope trace(kKernelDown, st);
     if (!decode_shape_ok(d, f)) {
-        const size_t lds = act_lds_bytes(f, true, false, false) + (size_t)f / 2;   // one order and the larger of the sums
-        if (d <= kDownAnyWideRows) decode_down_any_kernel<64><<<(d + 3) / 4, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, status);
-        else decode_down_any_kernel<32><<<(d + 7) / 8, 256, lds, st>>>(ex, idx, gate, h, d, f, k, residual, out, out32, status);
+        launch_down_any(ex, idx, gate, h, d, f, k, residual, out, out32, nullptr, status, st);
         return;
     }
     if (any_int8(ex))

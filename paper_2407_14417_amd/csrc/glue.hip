@@ -77,6 +77,24 @@ void launch_combine(const float* y, int splits, size_t split_stride, const float
     else combine_kernel<true><<<grid, threads, 0, st>>>(y, splits, split_stride, gate, nullptr, idx, T * k, d, k, residual, out);
 }
 
+// out[c] = fp16( sum_s gate[s] * slot_sums[s, c] ) over the slots whose expert ran, in slot order.
+__global__ __launch_bounds__(256) void average_slots_kernel(const float* __restrict__ slot_sums, const int32_t* __restrict__ idx,
+                                                             const float* __restrict__ gate, uint32_t ran, int d, int k,
+                                                             half_t* __restrict__ out) {
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= d) return;
+    float acc = 0.0f;
+    for (int s = 0; s < k; ++s)
+        if ((ran >> idx[s]) & 1u) acc = fmaf(gate[s], slot_sums[(size_t)s * d + c], acc);
+    out[c] = (half_t)(0.0f + acc);
+}
+
+void launch_average_slots(const float* slot_sums, const int32_t* idx, const float* gate, uint32_t ran, int d, int k, half_t* out,
+                          hipStream_t st) {
+    TraceScope trace(kKernelCombine, st);
+    average_slots_kernel<<<(d + 255) / 256, 256, 0, st>>>(slot_sums, idx, gate, ran, d, k, out);
+}
+
 // dst[i] = sum_p y[p][i], partials added in order
 __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restrict__ y, int splits, size_t split_stride,
                                                              size_t n4, float* __restrict__ dst) {

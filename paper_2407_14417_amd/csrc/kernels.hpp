@@ -78,6 +78,13 @@ void launch_decode_up(const DevExperts& ex, const int32_t* idx, const half_t* x,
 void launch_decode_down(const DevExperts& ex, const int32_t* idx, const float* gate, const half_t* h, int d, int f,
                         int k, const half_t* residual, half_t* out, int32_t* status, hipStream_t st,
                         float* out32 = nullptr);
+// Widths that are no multiple of 2048, a slot at a time: slot_sums[s, :] = W2_s h_s for the slots whose expert the table
+// marks runnable.  launch_average_slots then gives launch_decode_down's output, bit for bit, from the slots whose
+// expert is in `ran` (bit e: expert e).
+void launch_decode_down_slots(const DevExperts& ex, const int32_t* idx, const half_t* h, int d, int f, int k, float* slot_sums,
+                              int32_t* status, hipStream_t st);
+void launch_average_slots(const float* slot_sums, const int32_t* idx, const float* gate, uint32_t ran, int d, int k, half_t* out,
+                          hipStream_t st);
 // idx[0] = expert, gate[0] = 1: one expert alone through the batch-1 kernels.
 void launch_single_route(int32_t* idx, float* gate, int expert, hipStream_t st);
 

@@ -77,6 +77,41 @@ def test_swap_one_token_decode_kernels(orc, which, n_slots):
     assert_ffn_close(got, ref, f"swap decode {which}")
 
 
+# Widths that are no multiple of 2048: up to and above 2048 columns in the down-projection, one to three slots, every
+# precision, an odd multiple of 64; one token, and two through the multi-token kernels.
+@pytest.mark.parametrize("d,f,E,k", [(1024, 2816, 8, 2), (320, 448, 4, 3), (192, 320, 3, 1), (2112, 960, 6, 2)])
+@pytest.mark.parametrize("T", [1, 2])
+def test_swap_any_width_equals_all_resident_bit_for_bit(orc, d, f, E, k, T):
+    cfg = common.Config(f"swap_d{d}_f{f}_T{T}", d, f, E, k, T, tuple(range(0, E, 3)), int8_experts=tuple(range(1, E, 3)))
+    wl = build_workload(cfg, orc)
+    x = dev(wl.x)
+    want, want_idx = _forward(device_layer(wl), x, cfg)
+    routed = [int(e) for e in want_idx[0]]
+    for offloaded in (set(), {routed[0]}, {routed[-1]}, set(routed), set(range(E))):
+        for n_slots in (1, 2):
+            layer, hosts = device_layer_with_offloaded(wl, offloaded)
+            swap = mm.Swap(layer, hosts, n_slots, T)
+            ws = mm.alloc_workspace(layer, T)
+            ws.fill_(0xFF)                                        # NaN wherever it is floats
+            out = torch.full_like(x, float("nan"))
+            _say(f"swap {cfg.name} slots={n_slots} routed={routed} offloaded={sorted(offloaded)}")
+            missed = mm.moe_layer_forward_swap(layer, swap, x, out, ws)
+            assert mm.moe_read_status(ws) == 0
+            assert missed == len({int(e) for e in want_idx.reshape(-1)} & offloaded)
+            assert np.array_equal(out.cpu().numpy().view(np.uint16), want.view(np.uint16))
+    if T == 1 and k > 1:                                          # nothing to copy from: left out, reported
+        layer, hosts = device_layer_with_offloaded(wl, {routed[0]})
+        hosts[routed[0]] = None
+        swap = mm.Swap(layer, hosts, 1, 1)
+        out = torch.full_like(x, float("nan"))
+        part = torch.full_like(x, float("nan"))
+        assert mm.moe_layer_forward_swap(layer, swap, x, out, ws) == 0
+        assert mm.moe_read_status(ws) == mm.STATUS_NOT_RESIDENT
+        mm.moe_layer_forward(layer, x, part, ws)
+        assert mm.moe_read_status(ws) == mm.STATUS_NOT_RESIDENT
+        assert torch.equal(out, part) and bool(torch.isfinite(out).all())
+
+
 def test_swap_missed_expert_without_host_copy_keeps_the_status_bit(orc):
     wl = build_workload(TINY, orc)
     ref_idx, _ = orc.route(wl.x, wl.wg, TINY.k)
