@@ -728,6 +728,7 @@ __host__ __device__ constexpr size_t act_lds_bytes(int K, bool natural, bool bit
 // where a sum is not finite, that is, where an activation is not.
 template <typename Get>
 __device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
+    bool past = false;
     for (int p = tid; p < K / 32; p += n_threads) {
         float se = 0.0f, so = 0.0f;
 #pragma unroll
@@ -738,12 +739,14 @@ __device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int
             so += ((float)v[1] + (float)v[3]) + ((float)v[5] + (float)v[7]);
         }
         a.sum4[p] = float2{1024.0f * se + 64.0f * so, se + so};
-        if (!__builtin_isfinite(se + so)) *unbounded = 1;
+        past |= !__builtin_isfinite(se + so);
     }
+    if (past) *unbounded = 1;
 }
 
 template <typename Get>
 __device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
+    bool past = false;
     for (int p = tid; p < K / 16; p += n_threads) {
         float sum = 0.0f;
 #pragma unroll
@@ -753,8 +756,9 @@ __device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, i
                    (((float)v[4] + (float)v[5]) + ((float)v[6] + (float)v[7]));
         }
         a.sum8[p] = float2{1024.0f * sum, sum};
-        if (!__builtin_isfinite(sum)) *unbounded = 1;
+        past |= !__builtin_isfinite(sum);
     }
+    if (past) *unbounded = 1;
 }
 
 // One precision's pieces of a row: how many, and the dot product of one with its activations.
@@ -1023,9 +1027,11 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
         __syncthreads();                               // the last slot's hidden row has been read
         if (ee.prec == MOE_PREC_INT4G64) {
             act_pair_up(act, f, tid, 256, get, &unbounded[s]);
+        } else if (ee.prec == MOE_PREC_INT8G64) {
+            auto get_and_keep = [&](int piece) { return act.nat[act_slot(piece)] = get(piece); };
+            act_sum_bytes(act, f, tid, 256, get_and_keep, &unbounded[s]);
         } else {
             for (int p = tid; p < f / 8; p += 256) act.nat[act_slot(p)] = get(p);
-            if (ee.prec == MOE_PREC_INT8G64) act_sum_bytes(act, f, tid, 256, get, &unbounded[s]);
         }
         __syncthreads();
         const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded[s]);
