@@ -93,7 +93,11 @@ typedef void* moe_stream_t; /* hipStream_t; NULL = the default stream */
 
 /* Bytes of scratch that the calls below need for `n_tokens` tokens of `layer`.  Host-only arithmetic.
  * The caller allocates that many bytes of device memory (256-byte aligned) and passes them as `ws`;
- * one workspace must not be used by two calls that may overlap in time.  Returns 0 on bad arguments. */
+ * one workspace must not be used by two calls that may overlap in time.  Returns 0 on bad arguments.
+ * d_model or d_ff an odd multiple of 64: the bytes include partial results of a split contraction as long as the whole
+ * stays within MOE_STATIC_SCRATCH_BYTES (so they may fall where T grows past that).  A smaller workspace that holds the
+ * unsplit call is accepted as well and split less, so that one sized for more tokens always serves fewer; the fp32 sums
+ * are then added in another order. */
 size_t moe_workspace_bytes(const moe_layer* layer, int n_tokens);
 
 /*

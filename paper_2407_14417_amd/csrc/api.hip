@@ -76,6 +76,10 @@ int y_splits_for(const moe_layer* L, int T) {
     return plan_for(L, T * L->top_k).down_splits;
 }
 
+// Splits that moe_workspace_bytes asks for.  The one-token kernels write no partial results; the widths of whole steps ask
+// for them all the same, for moe_expert_ffn_mixed with a few rows.
+int asked_splits(const moe_layer* L, int T) { return T == 1 && half_step_width(L->d_model, L->d_ff) ? 1 : y_splits_for(L, T); }
+
 bool expert_resident(const moe_expert& x) { return x.resident && x.w1.data && x.w3.data && x.w2.data; }
 
 DevExperts device_table(const moe_layer* L) {
@@ -97,7 +101,13 @@ DevExperts device_table(const moe_layer* L) {
 int check_ws(const moe_layer* L, int T, void* ws, size_t ws_bytes, Workspace* out) {
     if (!ws) return fail(MOE_EWORKSPACE, "workspace is NULL");
     if ((uintptr_t)ws % 256) return fail(MOE_EWORKSPACE, "workspace must be 256-byte aligned");
-    *out = carve_workspace(ws, T, L->d_model, L->d_ff, L->n_experts, L->top_k, y_splits_for(L, T));
+    int splits = y_splits_for(L, T);
+    *out = carve_workspace(ws, T, L->d_model, L->d_ff, L->n_experts, L->top_k, splits);
+    // (at these widths every workspace that holds the unsplit call has always been enough)
+    while (out->bytes > ws_bytes && splits > 1 && half_step_width(L->d_model, L->d_ff)) {
+        splits = fewer_splits(L->d_ff, splits);
+        *out = carve_workspace(ws, T, L->d_model, L->d_ff, L->n_experts, L->top_k, splits);
+    }
     if (ws_bytes < out->bytes)
         return fail(MOE_EWORKSPACE, "workspace has %zu bytes, %zu needed", ws_bytes, out->bytes);
     return MOE_OK;
@@ -133,8 +143,8 @@ int layer_body(const moe_layer* L, const DevExperts& table, const half_t* x, int
     if (inline_groups) rows.idx = w.idx;
     if (mfma) {
         launch_ffn_up_mfma(table, E, rows, T * k, x, d, f, w.h, p.ct, w.status, st);
-        launch_ffn_down_mfma(table, E, rows, T * k, w.h, d, f, w.y, p.ct, p.down_splits, split_stride, w.status, st);
-        launch_combine(w.y, p.down_splits, split_stride, w.gate, inline_groups ? nullptr : w.inv, T, d, k, residual, out, st,
+        launch_ffn_down_mfma(table, E, rows, T * k, w.h, d, f, w.y, p.ct, w.y_splits, split_stride, w.status, st);
+        launch_combine(w.y, w.y_splits, split_stride, w.gate, inline_groups ? nullptr : w.inv, T, d, k, residual, out, st,
                        w.idx);
     } else {
         launch_ffn_up(table, E, rows, x, d, f, w.h, w.status, st);
@@ -189,7 +199,7 @@ int moe_trace_kernel(int kernel, void* start_event, void* stop_event) {
 size_t moe_workspace_bytes(const moe_layer* layer, int n_tokens) {
     if (!layer || n_tokens < 1 || layer->d_model < 1 || layer->d_ff < 1 || layer->n_experts < 1 || layer->top_k < 1)
         return 0;
-    return carve_workspace(nullptr, n_tokens, layer->d_model, layer->d_ff, layer->n_experts, layer->top_k, y_splits_for(layer, n_tokens)).bytes;
+    return carve_workspace(nullptr, n_tokens, layer->d_model, layer->d_ff, layer->n_experts, layer->top_k, asked_splits(layer, n_tokens)).bytes;
 }
 
 int moe_route(const moe_layer* layer, const void* x, int T, int32_t* topk_idx, float* topk_gate, moe_stream_t stream) {
@@ -375,7 +385,7 @@ void run_experts(const moe_layer* L, const DevExperts& table, const half_t* x, i
     if (use_mfma(L, T * k)) {
         const MfmaPlan p = plan_for(L, T * k);
         launch_ffn_up_mfma(table, E, rows, T * k, x, d, f, w.h, p.ct, w.status, st);
-        launch_ffn_down_mfma(table, E, rows, T * k, w.h, d, f, w.y, p.ct, p.down_splits, split_stride, w.status, st);
+        launch_ffn_down_mfma(table, E, rows, T * k, w.h, d, f, w.y, p.ct, w.y_splits, split_stride, w.status, st);
     } else {
         launch_ffn_up(table, E, rows, x, d, f, w.h, w.status, st);
         launch_ffn_down(table, E, rows, w.h, d, f, w.y, w.status, st);
@@ -474,8 +484,7 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
         if (e != hipSuccess) return fail(MOE_EHIP, "HIP: %s", hipGetErrorString(e));
     }
     if (!decode) {
-        const int splits = use_mfma(layer, T * k) ? plan_for(layer, T * k).down_splits : 1;
-        launch_combine(w.y, splits, (size_t)T * k * d, w.gate, w.inv, T, d, k, nullptr, (half_t*)out, st);
+        launch_combine(w.y, w.y_splits, (size_t)T * k * d, w.gate, w.inv, T, d, k, nullptr, (half_t*)out, st);
     } else if (!decode_shape_ok(d, f)) {
         uint32_t ran = 0;
         for (int i = 0; i < E; ++i) ran |= (uint32_t)(table.e[i].resident == 1 || table.e[i].resident == kDeferred) << i;

@@ -1889,7 +1889,7 @@ MfmaPlan plan_mfma(int P, int d, int f, int E) {
         // (widths that are no multiple of 128: no more scratch than fits the library's own, so that a block which fits
         // with one range per row still does)
         if (steps % s == 0 && steps / s >= 2 && base * s <= 640 &&
-            (s == 1 || !((d | f) % kKTile) || (size_t)P * ((size_t)4 * s * d + 2 * d + 2 * f + 64) + 4096 <= MOE_STATIC_SCRATCH_BYTES)) {
+            (s == 1 || !half_step_width(d, f) || (size_t)P * ((size_t)4 * s * d + 2 * d + 2 * f + 64) + 4096 <= MOE_STATIC_SCRATCH_BYTES)) {
             best = s;
             if ((steps / s) % 4 == 0) best4 = s;
         }
@@ -1897,6 +1897,13 @@ MfmaPlan plan_mfma(int P, int d, int f, int E) {
     // such ranges is preferred if it keeps at least half the workgroups
     p.down_splits = (p.ct == 8 && best4 * 2 >= best) ? best4 : best;
     return p;
+}
+
+int fewer_splits(int f, int splits) {
+    const int steps = (f + kKTile - 1) / kKTile;
+    do --splits;
+    while (splits > 1 && steps % splits);
+    return splits;
 }
 
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,

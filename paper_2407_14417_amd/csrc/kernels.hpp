@@ -43,6 +43,8 @@ void launch_ffn_down(const DevExperts& ex, int E, const RowMap& rows, const half
 // Matrix-core path for many rows (contraction lengths multiples of 64, at least 256).  `ct` = 16-row activation tiles per
 // chunk (1, 2, 4 or 8); the down-projection splits the contraction `splits` ways and writes one partial
 // y per split (`split_stride` elements apart), which launch_combine adds up.
+// Widths of odd multiples of 64 (half_step_width) take fewer splits where the workspace at hand has no room for the
+// plan's: fewer_splits gives the next smaller number that divides the contraction evenly.
 struct MfmaPlan {
     int ct;
     int down_splits;
@@ -50,6 +52,8 @@ struct MfmaPlan {
 bool mfma_shape_ok(int d, int f);
 bool mfma_rows_ok(int rows, int d, int f);
 MfmaPlan plan_mfma(int P, int d, int f, int E);
+inline bool half_step_width(int d, int f) { return (d | f) % 128 != 0; }
+int fewer_splits(int f, int splits);
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
                         int ct, int32_t* status, hipStream_t st);
 void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,

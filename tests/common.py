@@ -171,6 +171,13 @@ def tokens_with_margin(cfg: Config, wg: np.ndarray, bias: Optional[np.ndarray], 
     raise RuntimeError("could not separate top-k logits")
 
 
+def unsplit_workspace_bytes(d: int, f: int, E: int, k: int, T: int) -> int:
+    """Status, routing, grouping, normed tokens, hidden rows and one fp32 output row per pair, each on 256 bytes."""
+    P = T * k
+    parts = [256, 4 * P, 4 * P, 4 * E, 4 * (E + 1), 4 * P, 4 * P, 256, 2 * T * d, 2 * P * f, 4 * P * d]
+    return sum((n + 255) // 256 * 256 for n in parts)
+
+
 @dataclass
 class Workload:
     cfg: Config

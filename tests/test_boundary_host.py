@@ -7,6 +7,7 @@ from pathlib import Path
 import pytest
 
 from paper_2407_14417_amd import binding as mm
+from tests.common import unsplit_workspace_bytes
 
 ROOT = Path(__file__).resolve().parent.parent
 
@@ -43,6 +44,17 @@ def test_workspace_bytes_is_monotone_and_rejects_nonsense(L):
     assert b >= 16 * 2 * 512 * 2 + 16 * 2 * 256 * 4
     assert L.moe_workspace_bytes(ctypes.byref(lay), 0) == 0
     assert L.moe_workspace_bytes(None, 4) == 0
+
+
+def test_workspace_of_odd_multiples_of_64(L):
+    """Never less than the unsplit call needs, exactly that at one token, and partial results of split contractions
+    only within the library's own scratch: what fits there unsplit still does."""
+    own = L.moe_static_scratch_bytes()
+    for d, f, E, k in [(1088, 3008, 8, 2), (832, 2752, 8, 2), (320, 512, 32, 8), (512, 320, 5, 1), (64, 64, 4, 2)]:
+        lay, _ = _layer(d=d, f=f, E=E, k=k)
+        for T in [*range(1, 130), 500, 2000]:
+            need, unsplit = L.moe_workspace_bytes(ctypes.byref(lay), T), unsplit_workspace_bytes(d, f, E, k, T)
+            assert unsplit <= need and (need == unsplit or (T > 1 and need <= own)), (d, f, T)
 
 
 @pytest.mark.parametrize("kwargs,code", [

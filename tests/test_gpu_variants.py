@@ -151,6 +151,54 @@ def test_block_widths_of_odd_multiples_of_64(orc, d, f, T, zipf):
     _check_block(orc, common.Config(f"half_d{d}_f{f}_T{T}", d, f, 5, 2, T, (0, 3), zipf=zipf, int8_experts=(1, 4)))
 
 
+# One workspace for several numbers of tokens: sized for more tokens than the call has, and exactly the unsplit call's
+# bytes; nothing is written past either, and a byte less than that is refused.
+@pytest.mark.parametrize("d,f,E,k,T,T_sized", [(1088, 3008, 8, 2, 39, 40), (832, 2752, 8, 2, 95, 96), (320, 512, 5, 2, 7, 40),
+                                               (512, 2880, 4, 2, 1, 2)])
+def test_workspace_sized_for_more_tokens(orc, d, f, E, k, T, T_sized):
+    cfg = common.Config(f"ws_d{d}_f{f}_T{T}", d, f, E, k, T, tuple(range(0, E, 3)), int8_experts=tuple(range(1, E, 3)))
+    wl = build_workload(cfg, orc)
+    layer, x = device_layer(wl), dev(wl.x)
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, k)
+    least = common.unsplit_workspace_bytes(d, f, E, k, T)
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    for n in sorted({least, mm.workspace_bytes(layer, T_sized)}):
+        room = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda")
+        mm.moe_layer_forward(layer, x, out, room[:n], idx)
+        assert mm.moe_read_status(room) == 0 and bool((room[n:] == 0xFF).all())
+        assert np.array_equal(idx.cpu().numpy(), ref_idx)
+        assert_ffn_close(out.cpu().numpy(), ref, f"{cfg.name} ws={n}")
+        swap, swapped = mm.Swap(layer, [None] * E, 1, T), torch.full_like(out, float("nan"))
+        assert mm.moe_layer_forward_swap(layer, swap, x, swapped, room[:n]) == 0
+        assert torch.equal(swapped, out) and bool((room[n:] == 0xFF).all())
+        h = torch.zeros_like(out)
+        mm.moe_chain_forward(mm.Chain([layer], [torch.ones(d, dtype=torch.float16, device="cuda")]), 1e-5, h.copy_(x), room[:n])
+        assert bool(torch.isfinite(h).all()) and bool((room[n:] == 0xFF).all())
+    with pytest.raises(mm.MoeError) as refused:
+        mm.moe_layer_forward(layer, x, out, room[:least - 1], idx)
+    assert refused.value.code == mm.MOE_EWORKSPACE
+
+
+def test_static_scratch_at_its_limit_odd_multiples_of_64(orc):
+    """As many tokens as the library's own scratch holds unsplit, and where splits still fit: the same bits as with a
+    workspace; one token more is refused."""
+    d, f, E, k = 832, 2752, 8, 2
+    most = max(T for T in range(1, 1000) if common.unsplit_workspace_bytes(d, f, E, k, T) <= mm.moe_static_scratch_bytes())
+    cfg = common.Config("static_limit", d, f, E, k, most, (0, 3, 6), int8_experts=(1, 4, 7))
+    wl = build_workload(cfg, orc)
+    layer, x = device_layer(wl), dev(wl.x)
+    for T in (most, 95, 96, 30):
+        own, with_ws = (torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+        mm.moe_layer_forward_static(layer, x[:T], own)
+        mm.moe_layer_forward(layer, x[:T], with_ws, mm.alloc_workspace(layer, T))
+        assert torch.equal(own, with_ws) and bool(torch.isfinite(own).all())
+    more = torch.cat([x, x[:1]])
+    with pytest.raises(mm.MoeError) as refused:
+        mm.moe_layer_forward_static(layer, more, torch.empty_like(more))
+    assert refused.value.code == mm.MOE_EWORKSPACE
+
+
 @pytest.mark.parametrize("bits", [4, 8, 16])
 def test_half_step_keeps_neighbours_apart(orc, bits):
     """A row's end is the next row's start in memory: infinities at the start of a token, of a hidden row and of a
