@@ -16,28 +16,30 @@ pytestmark = pytest.mark.gpu
 
 # ---------------------------------------------------------------- quantizer: 128-bit loads against 2-byte loads
 
-def _quantized(w, bits, shift):
-    """Codes, scales and zeros of `w`, read from an address `shift` halves past an aligned one."""
+def _quantized(w, bits, shift=0, code_shift=0):
+    """Codes, scales and zeros of `w`, read from an address `shift` halves past an aligned one; codes written
+    `code_shift` bytes past one."""
     out, inn = w.shape
     buf = torch.zeros(out * inn + 8, dtype=torch.float16, device="cuda")
     src = buf[shift:shift + out * inn].view(out, inn)
     src.copy_(w)
-    codes = torch.zeros((out, inn * bits // 8), dtype=torch.uint8, device="cuda")
+    n = out * inn * bits // 8
+    codes = torch.zeros(n + 8, dtype=torch.uint8, device="cuda")[code_shift:code_shift + n].view(out, -1)
     scale, zero = (torch.zeros((out, inn // 64), dtype=torch.float16, device="cuda") for _ in range(2))
     (mm.moe_quantize_int4 if bits == 4 else mm.moe_quantize_int8)(src, codes, scale, zero)
     return codes.cpu().numpy(), scale.cpu().numpy().view(np.uint16), zero.cpu().numpy().view(np.uint16)
 
 
 def _grid_weights(out, inn):
-    """Every group on a grid of half steps of its own scale (quotients that are ties), other groups constant, with
-    both zeros, subnormal, at the edge of fp16 or holding infinities and NaN."""
+    """Groups on a grid of half steps of their own scale (quotients that are ties: kind 1 for 4 bits, kind 7 for 8),
+    with both zeros, subnormal, at the edge of fp16 or holding infinities and NaN."""
     rng = np.random.default_rng(5)
     w = synth.normal_f16((out, inn), 0.02, 4, 61).astype(np.float32).reshape(-1, 64)
     n = w.shape[0]
     for g in range(n):
         kind = g % 8
         if kind == 1:
-            w[g] = (rng.integers(0, 31, 64) * 0.5 - 3) * 2.0 ** rng.integers(-8, 3)
+            w[g] = (np.append(rng.integers(0, 31, 62), [0, 30]) * 0.5 - 3) * 2.0 ** rng.integers(-8, 3)
         elif kind == 2:
             w[g] = rng.choice([0.0, -0.0], 64)
         elif kind == 3:
@@ -49,7 +51,7 @@ def _grid_weights(out, inn):
         elif kind == 6:
             w[g, rng.integers(0, 64, 3)] = np.nan
         elif kind == 7:
-            w[g] = (rng.integers(0, 511, 64) * 0.5) * 2.0 ** -10
+            w[g] = (np.append(rng.integers(0, 511, 62), [0, 510]) * 0.5) * 2.0 ** -10
     return w.astype(np.float16).reshape(out, inn)
 
 
@@ -57,13 +59,19 @@ def _grid_weights(out, inn):
 @pytest.mark.parametrize("shape", [(1, 64), (3, 64), (33, 2048), (8, 1024), (301, 1088)])
 def test_quantizer_wide_loads_equal_narrow_loads(orc, bits, shape):
     for w in (synth.normal_f16(shape, 0.02, 4, 60), _grid_weights(*shape)):
-        wide, narrow = _quantized(dev(w), bits, 0), _quantized(dev(w), bits, 1)
-        for a, b in zip(wide, narrow):
-            assert np.array_equal(a, b)
-        if np.isfinite(w.astype(np.float32)).all() and not (w == 0).any():
-            ref = orc.quantize_int4(w) if bits == 4 else orc.quantize_int8(w)
-            assert np.array_equal(wide[0], ref.data)
-            assert np.array_equal(wide[1], ref.scale.view(np.uint16)) and np.array_equal(wide[2], ref.zero.view(np.uint16))
+        wide = _quantized(dev(w), bits)
+        for narrow in (_quantized(dev(w), bits, shift=1), _quantized(dev(w), bits, code_shift=1),
+                       _quantized(dev(w), bits, code_shift=bits // 2)):
+            for a, b in zip(wide, narrow):
+                assert np.array_equal(a, b)
+        # against the definition: every group but those with infinities or NaN, or with both zeros (whose minimum is either)
+        g = w.reshape(-1, 64)
+        told = np.isfinite(g.astype(np.float32)).all(1) & ~((g.view(np.uint16) == 0).any(1) & (g.view(np.uint16) == 0x8000).any(1))
+        assert told.sum() > told.size // 2
+        tame = np.where(np.repeat(told, 64).reshape(shape), w, np.float16(1))
+        ref = orc.quantize_int4(tame) if bits == 4 else orc.quantize_int8(tame)
+        for a, b in zip(wide, (ref.data, ref.scale.view(np.uint16), ref.zero.view(np.uint16))):
+            assert np.array_equal(a.reshape(told.size, -1)[told], np.asarray(b).reshape(told.size, -1)[told])
 
 
 # ---------------------------------------------------------------- gating and grouping
