@@ -255,8 +255,12 @@ int moe_read_status(void* ws, moe_stream_t stream, int* status_bits);
  * hipEventRecord(start_event) / hipEventRecord(stop_event) on the stream it is launched on (one shot;
  * arm again for the next launch).  Events are hipEvent_t created by the caller with timing enabled.
  * Both events NULL: a bracket that has been armed and not used yet is dropped.  A call on one token launches no
- * separate gating kernel (the gating network runs inside the up-projection launch): MOE_KERNEL_ROUTE then never
- * fires.  An armed bracket must not meet a launch that is being captured into a graph.
+ * separate gating, grouping or averaging kernel (they run inside the two projections' launches): MOE_KERNEL_ROUTE,
+ * MOE_KERNEL_PERMUTE and MOE_KERNEL_COMBINE then never fire (nor do they drop: they stay armed for a later call).
+ * A call with few (token, slot) pairs works out the grouping inside the other launches.  Arming MOE_KERNEL_PERMUTE makes
+ * it launch the grouping kernel all the same, and the projections and the weighted average then read its result: the
+ * outputs are the same bits, but brackets around those kernels in the same call time the variants that go with a
+ * grouping launch.  An armed bracket must not meet a launch that is being captured into a graph.
  */
 enum { MOE_KERNEL_ROUTE = 0,   /* gating (with the RMSNorm of the chained configuration) */
        MOE_KERNEL_PERMUTE = 1, /* grouping */

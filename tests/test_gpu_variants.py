@@ -127,12 +127,13 @@ def test_route_infinite_and_nan_logits(T, d, E, k):
 
 # ---------------------------------------------------------------- blocks
 
-def _run_block(layer, x, k):
+def _run_block(layer, x, k, ws=None):
     T, d = x.shape
     out = torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda")
     idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
     gate = torch.empty((T, k), dtype=torch.float32, device="cuda")
-    ws = torch.full((mm.workspace_bytes(layer, T),), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever it is floats
+    ws = mm.alloc_workspace(layer, T) if ws is None else ws
+    ws.fill_(0xFF)                                                # NaN wherever it is floats
     mm.moe_layer_forward(layer, dev(x), out, ws, idx, gate)
     assert mm.moe_read_status(ws) == 0
     return out.cpu().numpy(), idx.cpu().numpy(), gate.cpu().numpy()
@@ -343,13 +344,17 @@ def test_grouping_inside_the_launches(orc, T, E, k, zipf, d, f):
     cfg = common.Config(f"inline_T{T}_E{E}_k{k}", d, f, E, k, T, tuple(range(0, E, 2)), zipf=zipf, int8_experts=(1,))
     wl = build_workload(cfg, orc)
     layer = device_layer(wl)
-    inside = _run_block(layer, wl.x, k)
+    ws = mm.alloc_workspace(layer, T)
+    routing = 256 + 2 * ((4 * T * k + 255) // 256 * 256)         # status word, experts, weights; then what the launch groups into
+    grouped = ws[routing:routing + 2 * 256 + (4 * T * k + 255) // 256 * 256]
+    inside = _run_block(layer, wl.x, k, ws)
+    assert bool((grouped == 0xFF).all())                          # no grouping launch has run
     start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
     start.record(), stop.record()
     mm.moe_trace_kernel(mm.KERNEL_PERMUTE, start.cuda_event, stop.cuda_event)
-    apart = _run_block(layer, wl.x, k)
+    apart = _run_block(layer, wl.x, k, ws)
     torch.cuda.synchronize()
-    assert start.elapsed_time(stop) > 0
+    assert start.elapsed_time(stop) > 0 and not bool((grouped == 0xFF).all())
     for a, b in zip(inside, apart):
         assert np.array_equal(a, b)
     ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, k, bias=wl.bias)
