@@ -211,7 +211,7 @@ def test_expert_ffn_pipelined_bodies(orc, n):
     A 16-bit expert's chunks hold up to 256 rows, split evenly (70 .. 256 rows: one chunk of 5 .. 16 tiles; 257, 300,
     400: two chunks; 520: three); a 4-bit expert alone, in a launch this small, runs in chunks of 128 rows (bodies for
     2 .. 8 tiles: 148 = 128 + 20 rows, 188 = 128 + 60, 90, 200 = 128 + 72, ...; a last chunk of one tile runs the plain
-    body); its chunks of up to 192 rows are covered by test_layer_forward_4bit_chunks_of_9_to_12_tiles."""
+    body); its chunks of up to 256 rows are covered by test_layer_forward_4bit_chunks_of_more_than_8_tiles."""
     cfg = STEPS4
     wl = build_workload(cfg, orc, experts_needed=(0, 1))
     assert not wl.experts[0].int4 and wl.experts[1].int4
@@ -302,9 +302,9 @@ def test_layer_forward(orc, cfg):
     assert_ffn_close(out, ref, cfg.name)
 
 
-@pytest.mark.parametrize("T,tiles", [(288, (9, 8, 11)), (320, (10, 9, 12)), (360, (11, 10, 7, 7))])
-def test_layer_forward_4bit_chunks_of_9_to_12_tiles(orc, T, tiles):
-    """The busiest 4-bit experts get between 129 and 384 rows: chunks of up to 192 rows, split evenly, on the two-unit
+@pytest.mark.parametrize("T,tiles", [(288, (9, 8, 11)), (320, (10, 9, 12)), (360, (11, 10, 14))])
+def test_layer_forward_4bit_chunks_of_more_than_8_tiles(orc, T, tiles):
+    """The busiest 4-bit experts get between 129 and 384 rows: chunks of up to 256 rows, split evenly, on the two-unit
     body (``tiles``: 16-row tiles of the chunks of experts 0 and 1, as the row counts asserted below imply)."""
     cfg = common.Config(f"steps4_zipf_4bit_heavy_T{T}", 1024, 2048, 8, 2, T, STEPS4_ZIPF_Q.int4_experts, zipf=1.2)
     wl = build_workload(cfg, orc)
@@ -315,7 +315,7 @@ def test_layer_forward_4bit_chunks_of_9_to_12_tiles(orc, T, tiles):
     _say(f"rows per expert: {counts.tolist()}")
 
     def chunk_tiles(n):          # the library's rule for a 4-bit expert with more than 128 rows
-        nch = -(-n // 192)
+        nch = -(-n // 256)
         per = (-(-n // nch) + 15) // 16 * 16
         return tuple((min(per, n - i * per) + 15) // 16 for i in range(nch))
     assert chunk_tiles(int(counts[0])) + chunk_tiles(int(counts[1])) == tiles

@@ -230,7 +230,7 @@ def test_half_step_keeps_neighbours_apart(orc, bits):
 
 
 # 8-bit experts in launches with 128-row chunks: every number of 16-row tiles the pipelined body has (2 .. 8 in one
-# unit, 9 .. 12 in two; a lone expert's chunks stay at 128 rows, so those come from blocks), ragged last tiles, the
+# unit, 9 .. 16 in two; a lone expert's chunks stay at 128 rows, so those come from blocks), ragged last tiles, the
 # one-tile rest, ranges of 8 steps (up) and of splits of 4 steps (down).
 @pytest.mark.parametrize("n", [70, 81, 96, 100, 128, 129, 150, 170, 185, 200, 225, 250, 257])
 def test_expert_ffn_8bit_pipelined_body(orc, n):
