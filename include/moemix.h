@@ -130,8 +130,8 @@ int moe_permute(const moe_layer* layer, const int32_t* topk_idx, int T, int32_t*
  * x_rows: device fp16 [n, d_model]; y: device fp32 [n, d_model] (overwritten).
  * ws: at least moe_workspace_bytes(layer, ceil(n / top_k)) bytes (the hidden rows live there).
  * Fails with MOE_ENOTRESIDENT on the host if the expert is not resident.
- * n == 1 runs the same one-token kernels as moe_layer_forward with T == 1 (when the shape is one they
- * take), n > 1 the multi-token kernels, so each can be checked alone, before gating and weighted average.
+ * n == 1 runs the same one-token kernels as moe_layer_forward with T == 1, n > 1 the multi-token kernels, so
+ * each can be checked alone, before gating and weighted average.
  */
 int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows, int n, float* y, void* ws,
                          size_t ws_bytes, moe_stream_t stream);
