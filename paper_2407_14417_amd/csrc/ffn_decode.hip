@@ -523,7 +523,11 @@ __global__ __launch_bounds__(256, 2) void decode_up_kernel(DevExperts ex, const 
 // Partial sums meet in LDS and are added in wavefront order: the result does not depend on scheduling.
 constexpr int kDownRows = 16;
 constexpr int kDownBatch = 4;
-constexpr int kDownAnyWideRows = 2048;   // d_model up to which the kernel for any width gives an output row a whole wavefront
+// d_model up to which the kernel for any width gives an output row a whole wavefront, half of one above: few output rows
+// leave the chip idle otherwise, with many of them the shorter share of a row costs more.  Block, half and whole
+// wavefront: 1024 x 2816 14.8, 14.4 us; 1920 x 4992 21.4, 20.2; 2048 x 5632 30.6, 27.9; 2880 x 2880, four slots, 29.6, 30.2;
+// 4096 x 11008 58.4, 59.5; 7360 x 10624, 8-bit, 96.7, 97.4.  (The line is on the safe side: 2112 x 5632 34.1, 31.4.)
+constexpr int kDownAnyWideRows = 2048;
 
 template <bool WIDE>   // WIDE: with the branch for 8-bit experts
 __global__ __launch_bounds__(512) void decode_down_kernel(DevExperts ex, const int32_t* __restrict__ idx,
@@ -1095,15 +1099,20 @@ static void launch_up_any(const DevExperts& ex, const int32_t* idx, const half_t
                           int32_t* status, int E, const GateArgs* gating, hipStream_t st) {
     // Workgroups of four wavefronts, a row pair each at most.  Every one of them reads the gate matrix (E rows of d) out
     // of L2, so no more than leave that traffic at the weights' own (two workgroups per row pair and expert), but
-    // enough to fill the chip, and all of them resident at once: a second generation would evaluate the gating network
-    // again (four per compute unit at d_model up to 2048, three above).  Block at E = 32, four slots, 2880 x 2880, 4-bit:
-    // 360 workgroups 50.4 us, 720 44.8, 1024 54.9; E = 32, eight slots, 2048 x 1408: 352 44.9 us, 704 40.6, 1024 40.5.
+    // enough to fill the chip.  Block at E = 32, four slots, 2880 x 2880, 4-bit: 360 workgroups 50.4 us, 720 44.8, 1024
+    // 54.9; E = 32, eight slots, 2048 x 1408: 352 44.9 us, 704 40.6, 1024 40.5.
+    // And no more than `most`.  d_model above 2048: three per compute unit are resident (133 registers), a fourth
+    // would evaluate the gating network in a second generation; 512, 768, 1024, 1536 workgroups: 4096 x 11008 62.0, 58.5,
+    // 67.5, 63.4 us; 2880 x 2880 20.3, 19.8, 24.7, 25.0.  Up to 2048: eight would be resident, but every further workgroup's
+    // own evaluation of the gating network costs more than its share of the rows saves; 512, 768, 1024, 1408, 2048:
+    // 1024 x 2816 15.2, 15.2, 15.2, 16.7, 16.7 us; 1024 x 14208 25.9, 25.5, 24.0, 25.3, 27.0; 2048 x 5632 20.6, 19.4, 20.0,
+    // 22.0, 22.5; 1920 x 7680, 16-bit, 40.3, 37.7, 37.4, 37.1, 38.1.  (E = 8, two slots, 4-bit where nothing else is said.)
     const int rows = k * f;
     int blocks = (rows + 3) / 4;
-    const int by_gate = gating ? 2 * rows / E : rows, resident = NCHUNK <= 4 ? 1024 : 768;
+    const int by_gate = gating ? 2 * rows / E : rows, most = NCHUNK <= 4 ? 1024 : 768;
     if (blocks > by_gate) blocks = by_gate;
     if (blocks < 256) blocks = (rows + 3) / 4 < 256 ? (rows + 3) / 4 : 256;
-    if (blocks > resident) blocks = resident;
+    if (blocks > most) blocks = most;
     const size_t lds = act_lds_bytes(d, true, true, true);
     if (gating) decode_up_any_kernel<NCHUNK, true><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, *gating);
     else decode_up_any_kernel<NCHUNK, false><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, GateArgs{});

@@ -1,7 +1,7 @@
 // Expert feed-forward layer, any number of rows per expert (paper §1: experts are parallel FF
 // layers; §3: each is 16-bit or 4-bit).  One wavefront per weight row; activations of up to NT
 // rows are staged in LDS and every weight is dequantized to its exact fp16 value in registers.
-// This is the shape-agnostic path, for more than one token at widths below 256.
+// This is the shape-agnostic path, for more than one row where d_model or d_ff is below 256 (or the rows span 4 GB).
 #include "common.hpp"
 #include "kernels.hpp"
 

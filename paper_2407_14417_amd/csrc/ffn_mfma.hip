@@ -1520,7 +1520,8 @@ __device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& e
 
 // WIDE: the block holds 8-bit experts as well.  The 8-bit body needs more registers than the other two, and a
 // kernel's register count is that of its largest body, so blocks without 8-bit experts get a kernel without it
-// (and keep four wavefronts per SIMD at few rows per expert).  The wide kernel has bodies for 1, 2, 4 and 8 tiles.
+// (and keep four wavefronts per SIMD at few rows per expert).  In the wide kernel tile_body has variants for 1, 2, 4 and 8
+// tiles only; the pipelined bodies have all of theirs.
 // HALF: contraction lengths that are odd multiples of 64, tile_body only, all precisions.  (A wavefront per weight row
 // with scalar products, which is what such widths had, took 296 + 190 us for 33 tokens, 4 of 32 experts, d_model and
 // d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
@@ -1631,6 +1632,10 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
         // first and expert order otherwise, blocks: 1000 tokens, all 8-bit, 893 -> 858 us; 500 tokens, 32 experts, eight
         // slots 207 -> 196; 1500 tokens, 16 experts, four slots 548 -> 540.  Launches of smaller chunks have more and shorter workgroups
         // and lose 3 % to this search.)
+        // The costs are those of the pipelined bodies.  Where the ranges are no multiple of four steps and other bodies
+        // run, this order and expert order take turns: 1000 tokens, zipf load, 8 experts of 2816 x 2816 (22 steps), half
+        // 16-bit, 222 and 229 us, two of them 16-bit 225 and 237; 32 experts of 1408 x 2048 304 and 310; but 500 tokens, 32
+        // of 2048 x 1408 (11 steps) 192 and 187, 1000 tokens, 16 of 2880 x 2880 428 and 420.  One order for all of them.
         const int lane = tid & 63;
         const bool mine = lane < a.E;
         int n = 0, b = 0;

@@ -104,7 +104,10 @@ __device__ __forceinline__ void gate_logits(const uint4_t (&xv)[NCHUNK], const h
 __device__ __forceinline__ void gate_select(const float* __restrict__ logit, int E, int k, int lane,
                                             int (&sel)[MOE_MAX_TOPK], float (&lsel)[MOE_MAX_TOPK]) {
     const float l = lane < E ? logit[lane] : -__builtin_inff();   // (lanes past the last expert go before none)
-    if (k > 1 && !__ballot(l != l)) {                             // (one pass is cheaper than the ranking)
+    // One slot: the one pass is cheaper than the ranking (one token, 32 experts of 2048 x 4096, top-1: block 16.0 and 16.3 us;
+    // of 1024 x 2816 12.1 and 12.3; three alternating runs each within 0.1).  Experts are ranked four a round: eight
+    // slots 47.5 us, one a round 48.1, two slots the same.
+    if (k > 1 && !__ballot(l != l)) {
         int rank = lane < E ? 0 : MOE_MAX_EXPERTS;
         for (int e0 = 0; e0 < E; e0 += 4) {
 #pragma unroll

@@ -71,6 +71,8 @@ void launch_combine(const float* y, int splits, size_t split_stride, const float
                     int k, const half_t* residual, half_t* out, hipStream_t st, const int32_t* idx) {
     TraceScope trace(kKernelCombine, st);
     // few tokens: one wavefront per workgroup, or there are no more workgroups than a quarter of the compute units
+    // (block, 64 and 256 threads: 2 tokens of the Mixtral shape, 4-bit, 95.7, 97.0 us; 5 tokens, three precisions, 229.4,
+    // 230.5; 5 tokens, 1024 x 2816, 29.1, 29.6; no difference at 16 to 500 tokens, so the line may lie anywhere there)
     const int threads = (size_t)T * d <= 64 * 4096 ? 64 : 256;
     dim3 grid((d / 4 + threads - 1) / threads, T);
     if (inv) combine_kernel<false><<<grid, threads, 0, st>>>(y, splits, split_stride, gate, inv, nullptr, 0, d, k, residual, out);

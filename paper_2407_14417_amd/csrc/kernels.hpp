@@ -21,8 +21,11 @@ struct RowMap {
 };
 
 // Up to kInlinePairs pairs in launches with at most 32 rows per chunk, the kernels that need the grouping work it out
-// from the routing result with ballots, four per 64-lane register of expert indices: a fraction of a microsecond in
-// each of three launches in place of a launch of its own, 2.2 - 4.7 us.
+// from the routing result with ballots over up to four 64-lane registers of expert indices: a fraction of a microsecond in
+// each of three launches in place of a launch of its own, 2.2 - 4.7 us.  Block with the grouping inside and launched:
+// 32 pairs, 1024 x 2816, 30.6, 32.9 us; 128 pairs, 32 experts of 2048 x 1408, 85.0, 86.1; 256 pairs, 8 experts of 1024 x 2816,
+// 47.8, 49.5.  The line lies where the gain ends: 256 pairs over 32 experts, a ballot per register and expert in every
+// workgroup, 86.7, 86.9 (2048 x 1408) and 32.7, 32.4 (256 x 512).
 constexpr int kInlinePairs = 256;
 inline bool group_inline_ok(int P, int ct) { return P <= kInlinePairs && ct <= 2; }
 
