@@ -1115,7 +1115,7 @@ static void launch_up_any(const DevExperts& ex, const int32_t* idx, const half_t
     if (blocks > most) blocks = most;
     const size_t lds = act_lds_bytes(d, true, true, true);
     if (gating) decode_up_any_kernel<NCHUNK, true><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, *gating);
-    else decode_up_any_kernel<NCHUNK, false><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, GateArgs{});
+    else decode_up_any_kernel<4, false><<<blocks, 256, lds, st>>>(ex, idx, x, d, f, k, h, status, GateArgs{});   // (4: no part in it)
 }
 
 void launch_decode_up(const DevExperts& ex, const int32_t* idx, const half_t* x, int d, int f, int k, half_t* h,
