@@ -33,6 +33,8 @@
  *     weight: the multi-token kernels with one fp16 multiply-add (a single rounding), the one-token kernels
  *     in the factored form scale * sum(code * x) + zero * sum(x) in fp32 (no rounding of the weight); both
  *     stay within the tolerance stated for the block outputs, not bit-exact per weight.
+ *   - The hidden rows are fp16: a hidden value past 65504 is an infinity, and so are the outputs its products reach.  One
+ *     token with d_model and d_ff both multiples of 2048: a 4-bit or 8-bit expert gives NaN there instead.
  *   - 8-bit (the precision of the paper's homogeneous 8-bit comparison model, §4 Table 1) follows the same scheme:
  *     asymmetric uint8, groups of 64 columns with an fp16 scale and an fp16 zero, one code per byte;
  *     dequantized weight = fp16_rne( fp32(code) * fp32(scale) + fp32(zero) ).

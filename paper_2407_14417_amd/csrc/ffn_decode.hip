@@ -706,9 +706,9 @@ __global__ __launch_bounds__(512) void decode_down_kernel(DevExperts ex, const i
 // microseconds of loads at its end, so the chip is filled with short shares instead of long register pipelines.  The
 // token (or the hidden row) lies in LDS, from where a lane picks the activations of whatever 16-byte piece of a row it
 // has loaded; the last pieces of a row are masked lane by lane.  Whole blocks, graph replays over a pool of layers, five
-// launches -> these two: d_model 1024, d_ff 2816, 4- and 16-bit 29.0 -> 15.2 us; 256 x 512 18.0 -> 10.2; 32 experts of
-// 2048 x 1408, eight slots 61.8 -> 40.4; 2880 x 2880, four slots, 4-bit 73.4 -> 45.6; 4096 x 11008, 4- and 16-bit 94 -> 62
-// (5.6 TB/s); 7360 x 10624, 8-bit 279 -> 102.
+// launches -> these two: d_model 1024, d_ff 2816, 4- and 16-bit 29.3 -> 15.2 us; 256 x 512 17.2 -> 9.8; 32 experts of
+// 2048 x 1408, eight slots 61.7 -> 38.9; 2880 x 2880, four slots, 4-bit 73.4 -> 45.6; 4096 x 11008, 4- and 16-bit 94 -> 58
+// (5.9 TB/s); 7360 x 10624, 8-bit 278 -> 97.
 // 16-byte pieces of the activations are stored at swizzled places: lanes that read every fourth piece (4-bit rows: 32
 // columns per lane), every second one (8-bit) or consecutive ones (16-bit) then hit different banks.
 __device__ __forceinline__ int act_slot(int piece) { return piece ^ ((piece >> 3) & 3); }
@@ -873,7 +873,7 @@ __device__ __forceinline__ void walk_rows(const DevMat& mat, int n_rows, int K, 
 // The same for activations that are not all finite, with every weight dequantized.  The factored forms would turn an
 // infinite activation (a hidden value past 65504) into a NaN: they subtract 1024 times the sum of the activations, and
 // their terms of scale and zero may differ in sign.  Here the sum is the infinity that the products give, as in the
-// multi-token kernels.
+// multi-token kernels.  (Asked once per workgroup; asked per piece inside the factored form it cost 1 - 3 % of a block.)
 template <int PREC, int LPR, typename RowAt, typename Done>
 __device__ __forceinline__ void walk_rows_by_weight(const DevMat& mat, int n_rows, int K, const ActLds& act, int l, RowAt row_at, Done done) {
 #pragma unroll 1
