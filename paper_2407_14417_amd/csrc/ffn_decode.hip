@@ -7,6 +7,8 @@
 // with fp32 accumulation.  4-bit rows use the factored form of the group-wise dequantization,
 //   sum_c (q_c*s + z) x_c = s * sum_c q_c x_c + z * sum_c x_c,
 // with the per-lane sums of x precomputed once, so a weight costs about 1.3 vector instructions.
+#include <type_traits>
+
 #include "common.hpp"
 #include "gating.hpp"
 #include "kernels.hpp"
@@ -728,11 +730,9 @@ __host__ __device__ constexpr size_t act_lds_bytes(int K, bool natural, bool bit
     return (size_t)K * 2 * ((natural ? 1 : 0) + (bits4 ? 1 : 0)) + (bits4 ? (size_t)K / 4 : 0) + (bits8 ? (size_t)K / 2 : 0);
 }
 
-// Thread's share of the 4-bit form: 32 columns per turn, read from four 16-byte pieces with `get`.  *unbounded is set
-// where a sum is not finite, that is, where an activation is not.
+// Thread's share of the 4-bit form: 32 columns per turn, read from four 16-byte pieces with `get`.
 template <typename Get>
-__device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
-    bool past = false;
+__device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int n_threads, Get get) {
     for (int p = tid; p < K / 32; p += n_threads) {
         float se = 0.0f, so = 0.0f;
 #pragma unroll
@@ -743,14 +743,11 @@ __device__ __forceinline__ void act_pair_up(const ActLds& a, int K, int tid, int
             so += ((float)v[1] + (float)v[3]) + ((float)v[5] + (float)v[7]);
         }
         a.sum4[p] = float2{1024.0f * se + 64.0f * so, se + so};
-        past |= !__builtin_isfinite(se + so);
     }
-    if (past) *unbounded = 1;
 }
 
 template <typename Get>
-__device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get, int* unbounded) {
-    bool past = false;
+__device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, int n_threads, Get get) {
     for (int p = tid; p < K / 16; p += n_threads) {
         float sum = 0.0f;
 #pragma unroll
@@ -760,9 +757,7 @@ __device__ __forceinline__ void act_sum_bytes(const ActLds& a, int K, int tid, i
                    (((float)v[4] + (float)v[5]) + ((float)v[6] + (float)v[7]));
         }
         a.sum8[p] = float2{1024.0f * sum, sum};
-        past |= !__builtin_isfinite(sum);
     }
-    if (past) *unbounded = 1;
 }
 
 // One precision's pieces of a row: how many, and the dot product of one with its activations.
@@ -870,22 +865,20 @@ __device__ __forceinline__ void walk_rows(const DevMat& mat, int n_rows, int K, 
     }
 }
 
-// The same for activations that are not all finite, with every weight dequantized.  The factored forms would turn an
-// infinite activation (a hidden value past 65504) into a NaN: they subtract 1024 times the sum of the activations, and
-// their terms of scale and zero may differ in sign.  Here the sum is the infinity that the products give, as in the
-// multi-token kernels.  (Asked once per workgroup; asked per piece inside the factored form it cost 1 - 3 % of a block.)
-template <int PREC, int LPR, typename RowAt, typename Done>
-__device__ __forceinline__ void walk_rows_by_weight(const DevMat& mat, int n_rows, int K, const ActLds& act, int l, RowAt row_at, Done done) {
+// A lane's partial sum of one row in two ways: as walk_rows has it, bit for bit, and with every weight dequantized.  For rows
+// whose total is not finite.  The factored forms make NaN of an infinite activation (a hidden value past 65504), because they
+// subtract 1024 times the sum of the activations and their terms of scale and zero may differ in sign, and infinities
+// of what should be NaN under an infinite scale; the second sum is what the products give, as in the multi-token
+// kernels.  (Asked of every row's total.  Asked of every piece inside the factored form it cost 1 - 3 % of a block.)
+template <int PREC, int LPR>
+__device__ __forceinline__ void row_both_ways(const DevMat& mat, int row, int K, const ActLds& act, int l, float& factored, float& by_weight) {
+    factored = by_weight = 0.0f;
 #pragma unroll 1
-    for (int i = 0; i < n_rows; ++i) {
-        float sum = 0.0f;
-#pragma unroll 1
-        for (int piece = l; piece < K / RowPiece<PREC>::kCols; piece += LPR) {
-            RowPiece<PREC> p;
-            p.load(mat, row_at(i), K, piece);
-            sum += p.dot_by_weight(act, piece);
-        }
-        done(row_at(i), sum);
+    for (int piece = l; piece < K / RowPiece<PREC>::kCols; piece += LPR) {
+        RowPiece<PREC> p;
+        p.load(mat, row, K, piece);
+        factored += p.dot(act, K, piece);
+        by_weight += p.dot_by_weight(act, piece);
     }
 }
 
@@ -906,12 +899,10 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
                                                              half_t* __restrict__ h, int32_t* status, const GateArgs ga) {
     extern __shared__ __align__(16) uint8_t lds[];
     __shared__ float logit_s[MOE_MAX_EXPERTS];
-    __shared__ int unbounded;                          // an activation is not finite
     const ActLds act{(half8_t*)lds, (half8_t*)(lds + d * 2), (float2*)(lds + d * 4), (float2*)(lds + d * 4 + d / 4)};
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = wave_index();
     uint64_t routed = 0;                               // 5 bits per slot
-    if (tid == 0) unbounded = 0;
     if (ROUTE) {
         // (nothing of this launch raises status bits, see decode_up_kernel)
         if (blockIdx.x == 0 && tid == 0) *status = 0;
@@ -968,10 +959,9 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
         bits8 |= prec == MOE_PREC_INT8G64;
     }
     auto get = [&](int piece) { return act.nat[act_slot(piece)]; };
-    if (bits4) act_pair_up(act, d, tid, 256, get, &unbounded);
-    if (bits8) act_sum_bytes(act, d, tid, 256, get, &unbounded);
+    if (bits4) act_pair_up(act, d, tid, 256, get);
+    if (bits8) act_sum_bytes(act, d, tid, 256, get);
     if (bits4 || bits8) __syncthreads();
-    const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded);
     // Rows of all slots, dealt to the launch's wavefronts in turn: every share has its part of each slot.
     const int n_waves = gridDim.x * 4, gw = blockIdx.x * 4 + wave;
     for (int s = 0; s < k; ++s) {
@@ -982,20 +972,34 @@ __global__ __launch_bounds__(256, NCHUNK <= 4 ? 4 : 3) void decode_up_any_kernel
         const int rows = first < f ? (f - first + n_waves - 1) / n_waves : 0;
         half_t* const hs = h + (size_t)s * f;
         auto row_at = [&](int i) { return first + i * n_waves; };
+        bool past = false;                             // a row's total is not finite
         auto done = [&](int row, float sum) {
             float a, b;
             half_totals(sum, a, b);
+            past |= !__builtin_isfinite(a + b);
             if (lane == 0) hs[row] = (half_t)silu_mul(a, b);
         };
         const DevMat mat = lane < 32 ? ee.w1 : ee.w3;
         const int l = lane & 31;
+        auto again = [&](auto prec) {
+#pragma unroll 1
+            for (int i = 0; i < rows; ++i) {
+                float sum, sum_w, a, b, a_w, b_w;
+                row_both_ways<prec, 32>(mat, row_at(i), d, act, l, sum, sum_w);
+                half_totals(sum, a, b);
+                half_totals(sum_w, a_w, b_w);
+                if (lane == 0) hs[row_at(i)] = (half_t)silu_mul(__builtin_isfinite(a) ? a : a_w, __builtin_isfinite(b) ? b : b_w);
+            }
+        };
         if (ee.prec == MOE_PREC_INT4G64) {
-            if (by_weight) walk_rows_by_weight<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
-            else walk_rows<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
+            walk_rows<MOE_PREC_INT4G64, 32>(mat, rows, d, act, l, row_at, done);
+            if (past) again(std::integral_constant<int, MOE_PREC_INT4G64>());
         } else if (ee.prec == MOE_PREC_INT8G64) {
-            if (by_weight) walk_rows_by_weight<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
-            else walk_rows<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
-        } else walk_rows<MOE_PREC_FP16, 32>(mat, rows, d, act, l, row_at, done);
+            walk_rows<MOE_PREC_INT8G64, 32>(mat, rows, d, act, l, row_at, done);
+            if (past) again(std::integral_constant<int, MOE_PREC_INT8G64>());
+        } else {
+            walk_rows<MOE_PREC_FP16, 32>(mat, rows, d, act, l, row_at, done);
+        }
     }
 }
 
@@ -1012,12 +1016,10 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
     extern __shared__ __align__(16) uint8_t lds[];
     // (one precision at a time: the natural order and the 4-bit order share their place)
     const ActLds act{(half8_t*)lds, (half8_t*)lds, (float2*)(lds + f * 2), (float2*)(lds + f * 2)};
-    __shared__ int unbounded[MOE_MAX_TOPK];            // slots whose hidden row is not all finite
     constexpr int kRows = 256 / LPR;
     const int tid = threadIdx.x, lane = tid & 63, l = tid & (LPR - 1);
     const int row = blockIdx.x * kRows + tid / LPR;
     const int row_safe = row < d ? row : d - 1;        // (lanes past the last row repeat it and store nothing)
-    if (tid < MOE_MAX_TOPK) unbounded[tid] = 0;
     float acc = 0.0f;
     for (int s = 0; s < k; ++s) {
         const DevExpert& ee = ex.e[__builtin_amdgcn_readfirstlane(idx[s])];
@@ -1030,32 +1032,33 @@ __global__ __launch_bounds__(256, 4) void decode_down_any_kernel(DevExperts ex, 
         auto get = [&](int piece) { return *(const half8_t*)(hs + piece * 8); };
         __syncthreads();                               // the last slot's hidden row has been read
         if (ee.prec == MOE_PREC_INT4G64) {
-            act_pair_up(act, f, tid, 256, get, &unbounded[s]);
+            act_pair_up(act, f, tid, 256, get);
         } else if (ee.prec == MOE_PREC_INT8G64) {
             auto get_and_keep = [&](int piece) { return act.nat[act_slot(piece)] = get(piece); };
-            act_sum_bytes(act, f, tid, 256, get_and_keep, &unbounded[s]);
+            act_sum_bytes(act, f, tid, 256, get_and_keep);
         } else {
             for (int p = tid; p < f / 8; p += 256) act.nat[act_slot(p)] = get(p);
         }
         __syncthreads();
-        const bool by_weight = __builtin_amdgcn_readfirstlane(unbounded[s]);
         auto row_at = [&](int) { return row_safe; };
         float sum = 0.0f;
         auto done = [&](int, float v) { sum = v; };
-        if (ee.prec == MOE_PREC_INT4G64) {
-            if (by_weight) walk_rows_by_weight<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-            else walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-        } else if (ee.prec == MOE_PREC_INT8G64) {
-            if (by_weight) walk_rows_by_weight<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-            else walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
-        } else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
-        float total;
-        if (LPR == 64) {
-            total = wave_total(sum);
-        } else {
+        if (ee.prec == MOE_PREC_INT4G64) walk_rows<MOE_PREC_INT4G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        else if (ee.prec == MOE_PREC_INT8G64) walk_rows<MOE_PREC_INT8G64, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        else walk_rows<MOE_PREC_FP16, LPR>(ee.w2, 1, f, act, l, row_at, done);
+        auto row_total = [&](float v) {
+            if (LPR == 64) return wave_total(v);
             float lo, hi;
-            half_totals(sum, lo, hi);
-            total = lane < 32 ? lo : hi;
+            half_totals(v, lo, hi);
+            return lane < 32 ? lo : hi;
+        };
+        float total = row_total(sum);
+        if (ee.prec != MOE_PREC_FP16 && __ballot(!__builtin_isfinite(total))) {
+            float same, by_weight;
+            if (ee.prec == MOE_PREC_INT4G64) row_both_ways<MOE_PREC_INT4G64, LPR>(ee.w2, row_safe, f, act, l, same, by_weight);
+            else row_both_ways<MOE_PREC_INT8G64, LPR>(ee.w2, row_safe, f, act, l, same, by_weight);
+            by_weight = row_total(by_weight);
+            if (!__builtin_isfinite(total)) total = by_weight;
         }
         if (!slot_sums) acc = fmaf(gate[s], total, acc);
         else if (l == 0 && row < d) slot_sums[(size_t)s * d + row] = total;

@@ -304,6 +304,26 @@ def test_one_token_hidden_value_past_the_fp16_range(orc, d, f, bits):
     assert np.array_equal(_run_block(layer, np.repeat(wl.x, 2, axis=0), 1)[0][0].astype(np.float64), want)   # two tokens
 
 
+@pytest.mark.parametrize("d,f", [(192, 320), (1024, 2816), (2880, 960)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_one_token_infinite_scale_or_zero(orc, d, f, bits):
+    """A group whose scale or zero is not finite: one token gives infinities and NaN where the multi-token kernels give
+    them, and leaves the other outputs' bits alone."""
+    every = dict(int4_experts=(0,)) if bits == 4 else dict(int4_experts=(), int8_experts=(0,))
+    wl = build_workload(common.Config("inf_group", d, f, 1, 1, 1, **every), orc)
+    layer = device_layer(wl)
+    clean = _run_block(layer, wl.x, 1)[0]
+    for mat, what, row, value in [("w2", "scale", 7, np.inf), ("w2", "zero", 7, np.nan), ("w2", "zero", 7, -np.inf),
+                                  ("w1", "scale", f - 1, np.inf), ("w3", "scale", 0, np.inf)]:
+        t = getattr(getattr(layer.experts[0], mat), what)
+        kept, t[row, -1] = t[row, -1].clone(), float(value)
+        one, two = _run_block(layer, wl.x, 1)[0][0], _run_block(layer, np.repeat(wl.x, 2, axis=0), 1)[0][0]
+        t[row, -1] = kept
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(kind(one), kind(two)), (mat, what, value)
+        assert not np.isfinite(one[7]) and np.array_equal(one[np.isfinite(one)], clean[0][np.isfinite(one)])
+
+
 def test_one_token_any_width_non_resident_and_chain(orc):
     cfg = common.Config("one_token_chain", 1088, 1472, 6, 2, 1, (0, 3), int8_experts=(1,))
     wl = build_workload(cfg, orc)
