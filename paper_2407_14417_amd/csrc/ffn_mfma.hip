@@ -60,6 +60,7 @@ struct MfmaArgs {
     size_t split_stride;      // elements of y between two splits
     int unit_bytes;           // LDS bytes per A operand for weight staging: 4096 if any expert is 16-bit, else 2048
     uint32_t prec16, prec8;   // the experts held in 16 and in 8 bits, one bit each
+    int quant_rows;           // most rows of a chunk of a 4-bit or 8-bit expert on the pipelined bodies (quant_chunk_rows)
     int32_t* status;
 };
 
@@ -1559,11 +1560,7 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     const int n_steps = HALF ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
     // (launches with 128-row chunks have LDS for two 256-row stages)
     const bool wide_ok = !HALF && CT >= 8 && !(n_steps & 1);
-    // (4-bit chunks of more than 128 rows save compute-unit time, not latency: one expert alone whose launch does not
-    // fill the chip twice over is faster with more, smaller workgroups side by side -- 148 rows: 73 us in chunks of
-    // 128 + 20 rows, 89 us in one chunk)
     const bool quant_ok = wide_ok && !(n_steps & 3);
-    const bool wide_quant_ok = quant_ok && (a.direct_expert < 0 || gridDim.x * gridDim.y >= 2 * kComputeUnits);
     // (the precisions as two words: read lane by lane out of the expert table they would be vector loads from the
     // kernel's arguments)
     auto prec_of = [&](int expert) {
@@ -1572,9 +1569,9 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     auto chunk_rows = [&](int expert, int n) {   // rows per chunk of an expert with n rows
         const int prec = prec_of(expert);
         if (!((wide_ok && prec == MOE_PREC_FP16 && n > 16 * (kDirectNCT - 1)) ||
-              (wide_quant_ok && prec != MOE_PREC_FP16 && n > MC)))
+              (quant_ok && prec != MOE_PREC_FP16 && n > MC && a.quant_rows)))
             return MC;
-        const int cap = prec == MOE_PREC_FP16 ? kDirectRows : kQuantRows;
+        const int cap = prec == MOE_PREC_FP16 ? kDirectRows : a.quant_rows;
         const int nch = (n + cap - 1) / cap;
         return (((n + nch - 1) / nch) + 15) & ~15;
     };
@@ -1852,16 +1849,38 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
     return 2048;
 }
 
-// Chunks of a launch whose contraction ranges have n_steps steps of 128 columns.
-int chunk_slots(const RowMap& rows, int P, int E, int ct, int n_steps) {
-    int mc = 16 * ct;
+// Most rows of a 4-bit or 8-bit expert's chunks on the pipelined bodies, 0: 128 and no even split (also where the bodies are
+// not run), for a launch of `columns` workgroups per chunk whose contraction ranges have n_steps steps of 128 columns.
+// Longer chunks save compute-unit time (a workgroup of 4096 columns takes some 40 us for its codes plus 7 per tile of 16
+// rows), not latency.  So 128 where such chunks all run side by side; else the length for which rounds of workgroups
+// times the time of one come out least, every expert at the mean load, the longer one if they tie.
+// Blocks with 256 rows throughout, and as it is: 8-bit, 2 experts of 1024 x 2048, both slots, 150 tokens 63.4, 46.8 us, 600
+// tokens 79.6, 63.8; 4-bit, 3 experts of 4096 x 4096, two slots, 300 tokens 175.9, 139.8, 1200 tokens (192 rows) 328, 299;
+// 4 experts of 2048 x 2048, one slot, 600 tokens 90.7, 70.0.  Launches of many workgroups keep 256 rows.
+// One expert alone: 256 from two rounds on (148 rows: 73 us in chunks of 128 + 20 rows, 89 us in one chunk).
+int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int ct, int columns, int n_steps) {
+    if (ct != 8 || n_steps % 4) return 0;
+    const auto chunks = [](int n, int cap) { return (n + cap - 1) / cap; };
+    const int units = kComputeUnits;
+    if (rows.direct_expert >= 0) return columns * chunks(rows.direct_n, 128) >= 2 * units ? kQuantRows : 0;
+    if (columns * (P / 128 + a.E / 2) <= units) return 128;
+    const int n = chunks(P, a.E), n16 = __builtin_popcount(a.prec16);
+    int best = 0, least = 0;
+    for (int cap = kQuantRows; cap >= 128; cap -= 64) {
+        const int tiles = chunks(chunks(n, chunks(n, cap)), 16);
+        const int cost = chunks(columns * (n16 * chunks(n, kDirectRows) + (a.E - n16) * chunks(n, cap)), units) * (40 + 7 * tiles);
+        if (!best || cost < least) { best = cap; least = cost; }
+    }
+    return best;
+}
+
+int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
+    const int mc = 16 * ct;
     if (rows.direct_expert >= 0) return (rows.direct_n + mc - 1) / mc;
-    // the pipelined bodies, where the ranges allow them, take chunks of up to twice as many rows of every precision
-    // (a workgroup that finds no chunk costs some 3 us, at the launch's end)
-    static_assert(kDirectRows == 256 && kQuantRows == 256, "rows per chunk of the pipelined bodies");
-    if (ct == 8 && n_steps % 4 == 0) mc = 256;
-    // every expert may end with one ragged chunk
-    return P / mc + E;
+    // every expert may end with one ragged chunk; where the ranges allow the pipelined bodies, chunks of 16-bit experts are
+    // never shorter than those of the others (a workgroup that finds no chunk costs some 3 us, at the launch's end)
+    static_assert(kDirectRows >= kQuantRows, "rows per chunk of the pipelined bodies");
+    return P / (a.quant_rows ? a.quant_rows : mc) + a.E;
 }
 
 }  // namespace
@@ -1924,7 +1943,8 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
     const int up_rows = 32 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (f + up_rows - 1) / up_rows;
-    dim3 grid(a.tiles, chunk_slots(rows, P, E, ct, d % kKTile ? 1 : d / kKTile), 1);
+    a.quant_rows = quant_chunk_rows(rows, a, P, ct, a.tiles, d % kKTile ? 1 : d / kKTile);
+    dim3 grid(a.tiles, chunk_slots(rows, a, P, ct), 1);
     launch_ct<true>(a, ct, grid, st);
 }
 
@@ -1945,7 +1965,8 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
     const int down_rows = 64 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (d + down_rows - 1) / down_rows;
-    dim3 grid(a.tiles * splits, chunk_slots(rows, P, E, ct, f % kKTile ? 1 : a.k_per_split / kKTile), 1);
+    a.quant_rows = quant_chunk_rows(rows, a, P, ct, a.tiles * splits, f % kKTile ? 1 : a.k_per_split / kKTile);
+    dim3 grid(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
     launch_ct<false>(a, ct, grid, st);
 }
 

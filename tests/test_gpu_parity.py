@@ -305,8 +305,9 @@ def test_layer_forward(orc, cfg):
 @pytest.mark.parametrize("T,tiles", [(288, (9, 8, 11)), (320, (10, 9, 12)), (360, (11, 10, 14))])
 def test_layer_forward_4bit_chunks_of_more_than_8_tiles(orc, T, tiles):
     """The busiest 4-bit experts get between 129 and 384 rows: chunks of up to 256 rows, split evenly, on the two-unit
-    body (``tiles``: 16-row tiles of the chunks of experts 0 and 1, as the row counts asserted below imply)."""
-    cfg = common.Config(f"steps4_zipf_4bit_heavy_T{T}", 1024, 2048, 8, 2, T, STEPS4_ZIPF_Q.int4_experts, zipf=1.2)
+    body (``tiles``: 16-row tiles of the chunks of experts 0 and 1, as the row counts asserted below imply).  With 40
+    workgroups per chunk in both projections the launches are past the size below which chunks keep to 128 rows."""
+    cfg = common.Config(f"steps4_zipf_4bit_heavy_T{T}", 1024, 5120, 8, 2, T, STEPS4_ZIPF_Q.int4_experts, zipf=1.2)
     wl = build_workload(cfg, orc)
     _say(f"layer_forward cfg={cfg.name}")
     out, idx, gate, status = _run_layer(device_layer(wl), wl.x, cfg)

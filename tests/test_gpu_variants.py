@@ -247,10 +247,52 @@ def test_expert_ffn_8bit_pipelined_body(orc, n):
 
 @pytest.mark.parametrize("T", [139, 150, 170, 185, 200, 215, 230, 256, 257])
 @pytest.mark.parametrize("bits", [4, 8])
-def test_block_quantized_chunks_of_more_than_128_rows(orc, T, bits):
-    """Both experts take every token: chunks of 9 to 16 tiles, then two of 9."""
+def test_block_quantized_chunks_in_small_launches(orc, T, bits):
+    """Both experts take every token; 16 workgroups per chunk: chunks of up to 128 rows, split evenly (5 .. 8 tiles)."""
     _check_block(orc, common.Config(f"steps4_{bits}bit_T{T}", 1024, 2048, 2, 2, T, (0, 1) if bits == 4 else (),
                                     int8_experts=(0, 1) if bits == 8 else ()))
+
+
+def _rows_per_chunk(n, E, columns):
+    """The library's rule for blocks of quantized experts with n rows each and `columns` workgroups per chunk."""
+    up = lambda a, b: -(-a // b)
+    if columns * (n * E // 128 + E // 2) <= 256:
+        return 128
+    return min((256, 192, 128), key=lambda cap: up(columns * E * up(n, cap), 256) * (40 + 7 * up(up(n, up(n, cap)), 16)))
+
+
+# Launches of more workgroups (in both projections): one chunk of 9 to 16 tiles, two of 9, and five of 10.
+@pytest.mark.parametrize("d,f,T,rows", [*((2048, 11264, T, 256) for T in (139, 150, 170, 185, 200, 215, 230, 256, 257)),
+                                        (1024, 5120, 800, 192)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_block_quantized_chunks_of_more_than_128_rows(d, f, T, rows, bits):
+    """Both experts take every token.  Weights are drawn and quantized on the device; the reference is a float64 product
+    with the dequantized ones."""
+    splits = 11 if f == 11264 else 10
+    assert _rows_per_chunk(T, 2, f // 128) == _rows_per_chunk(T, 2, d // 256 * splits) == rows
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    draw = lambda shape, sigma: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(0.0, sigma, generator=gen)
+    experts, dense = [], []
+    for _ in range(2):
+        mats = []
+        for o, i in ((f, d), (f, d), (d, f)):
+            codes = torch.empty((o, i * bits // 8), dtype=torch.uint8, device="cuda")
+            scale, zero = (torch.empty((o, i // 64), dtype=torch.float16, device="cuda") for _ in range(2))
+            w = draw((o, i), 0.02)
+            (mm.moe_quantize_int4 if bits == 4 else mm.moe_quantize_int8)(w, codes, scale, zero)
+            mats.append(mm.Mat(codes, scale, zero))
+            (mm.moe_dequant_int4 if bits == 4 else mm.moe_dequant_int8)(mats[-1], o, i, w)
+            dense.append(w)
+        experts.append(mm.Expert(mm.PREC_INT4G64 if bits == 4 else mm.PREC_INT8G64, *mats))
+    x = draw((T, d), 1.0)
+    out, idx, gate = _run_block(mm.Layer(d, f, 2, draw((2, d), 0.02), experts), x.cpu().numpy(), 2)
+    ref = np.zeros((T, d))
+    for e in range(2):
+        w1, w3, w2 = (w.double() for w in dense[3 * e:3 * e + 3])
+        a = x.double() @ w1.t()
+        y = (torch.nn.functional.silu(a) * (x.double() @ w3.t())) @ w2.t()
+        ref += (gate * (idx == e)).sum(1, dtype=np.float64)[:, None] * y.cpu().numpy()
+    assert_ffn_close(out, ref, f"{bits}-bit T={T}")
 
 
 # One token at widths that are no multiple of 2048: rows shorter than a wavefront's loads, one load per lane exactly,
