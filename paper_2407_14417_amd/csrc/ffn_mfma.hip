@@ -1529,8 +1529,9 @@ __device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& e
 // a time and 4-bit rows whose 128-byte requests straddle two lines.)
 // SPB: 128-column steps per LDS stage.  Launches with 64-row chunks of blocks without 16-bit experts take one instead of
 // two: their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two wavefronts per SIMD
-// are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 364 -> 320 us, 8-bit 412 -> 378;
-// 4-bit 2048 x 5632, 160 tokens 116 -> 99.  With 16-bit experts (99 KB) there is no second workgroup and one step per
+// are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us, 8-bit 408 -> 372;
+// 4-bit 2048 x 5632, 160 tokens 117 -> 95.  (Not everywhere: 150 tokens, 4 experts of 2048 x 2048, one slot, 52.7 us with two
+// steps and 54.7 with one; 200 tokens, 1408 x 1408 60.2 and 63.1; 12 of 16 shapes between 512 and 4096 columns gain.)  With 16-bit experts (99 KB) there is no second workgroup and one step per
 // stage loses up to 4 %; contractions that end with half a step lose 7 %.
 template <bool UP, int CT, bool WIDE, bool HALF, int SPB>
 __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
