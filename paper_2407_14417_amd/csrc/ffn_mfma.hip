@@ -1858,18 +1858,21 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 // Blocks with 256 rows throughout, and as it is: 8-bit, 2 experts of 1024 x 2048, both slots, 150 tokens 63.4, 46.8 us, 600
 // tokens 79.6, 63.8; 4-bit, 3 experts of 4096 x 4096, two slots, 300 tokens 175.9, 139.8, 1200 tokens (192 rows) 328, 299;
 // 4 experts of 2048 x 2048, one slot, 600 tokens 90.7, 70.0.  Launches of many workgroups keep 256 rows.
-// One expert alone: 256 from two rounds on (148 rows: 73 us in chunks of 128 + 20 rows, 89 us in one chunk).
+// One expert alone: the same from two rounds on (148 rows: 73 us in chunks of 128 + 20 rows, 89 us in one chunk; 1917 rows,
+// 1536 x 5632, 4-bit, 182.5 us in chunks of up to 256, 171 in chunks of up to 192).
 int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int ct, int columns, int n_steps) {
     if (ct != 8 || n_steps % 4) return 0;
     const auto chunks = [](int n, int cap) { return (n + cap - 1) / cap; };
     const int units = kComputeUnits;
-    if (rows.direct_expert >= 0) return columns * chunks(rows.direct_n, 128) >= 2 * units ? kQuantRows : 0;
-    if (columns * (P / 128 + a.E / 2) <= units) return 128;
-    const int n = chunks(P, a.E), n16 = __builtin_popcount(a.prec16);
+    const bool alone = rows.direct_expert >= 0;
+    if (alone && columns * chunks(P, 128) < 2 * units) return 0;
+    if (!alone && columns * (P / 128 + a.E / 2) <= units) return 128;
+    const int E = alone ? 1 : a.E, n16 = alone ? 0 : __builtin_popcount(a.prec16);
+    const int n = chunks(P, E);
     int best = 0, least = 0;
     for (int cap = kQuantRows; cap >= 128; cap -= 64) {
         const int tiles = chunks(chunks(n, chunks(n, cap)), 16);
-        const int cost = chunks(columns * (n16 * chunks(n, kDirectRows) + (a.E - n16) * chunks(n, cap)), units) * (40 + 7 * tiles);
+        const int cost = chunks(columns * (n16 * chunks(n, kDirectRows) + (E - n16) * chunks(n, cap)), units) * (40 + 7 * tiles);
         if (!best || cost < least) { best = cap; least = cost; }
     }
     return best;
