@@ -22,6 +22,7 @@
 //                codes folded in.
 //   quant4_wide_body  the same for chunks of 9 .. 16 tiles.
 //   quant8_body  8-bit experts in those launches, chunks of 2 .. 16 tiles.
+#include <algorithm>
 #include <atomic>
 
 #include "common.hpp"
@@ -1884,7 +1885,8 @@ int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
     // every expert may end with one ragged chunk; where the ranges allow the pipelined bodies, chunks of 16-bit experts are
     // never shorter than those of the others (a workgroup that finds no chunk costs some 3 us, at the launch's end)
     static_assert(kDirectRows >= kQuantRows, "rows per chunk of the pipelined bodies");
-    return P / (a.quant_rows ? a.quant_rows : mc) + a.E;
+    // (and no chunk is empty: 4 pairs, 32 experts of 1024 x 2816, 16-bit: block 44.8 -> 32.3 us)
+    return std::min(P, P / (a.quant_rows ? a.quant_rows : mc) + a.E);
 }
 
 }  // namespace
