@@ -1559,7 +1559,8 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     // ---- which expert, which rows.  Chunks hold at most MC rows, those of 16-bit experts in launches with 128-row
     // chunks up to kDirectRows (direct_body), split evenly in whole tiles.
     const int k_begin = split_z * a.k_per_split;
-    const int n_steps = HALF ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
+    // (the last range of uneven splits is shorter; launches of few pairs only)
+    const int n_steps = HALF || CT == 1 ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
     // (launches with 128-row chunks have LDS for two 256-row stages)
     const bool wide_ok = !HALF && CT >= 8 && !(n_steps & 1);
     const bool quant_ok = wide_ok && !(n_steps & 3);
@@ -1889,6 +1890,12 @@ int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
     return std::min(P, P / (a.quant_rows ? a.quant_rows : mc) + a.E);
 }
 
+// Splits of a contraction of `f` columns into ranges of whole steps, all of one length but the last, which may be shorter.
+int contraction_steps(int f) { return (f + kKTile - 1) / kKTile; }
+int steps_per_split(int steps, int splits) { return (steps + splits - 1) / splits; }
+// every range holds two steps at least, the last one included
+bool splits_ok(int steps, int splits) { return steps - (splits - 1) * steps_per_split(steps, splits) >= 2; }
+
 }  // namespace
 
 // The two projections are separate instantiations of everything above; the build compiles one object for each
@@ -1906,19 +1913,28 @@ bool mfma_rows_ok(int rows, int d, int f) {
     return (uint64_t)rows * (uint64_t)(d > f ? d : f) * 2u < (1ull << 32);
 }
 
+// Up to so many pairs the widths of odd multiples of 64 are split into ranges of unequal length where the number of steps
+// has no divisor: unsplit, a few workgroups walk the whole contraction one step after another, longer than a
+// wavefront per output row takes (two tokens, top-1, 16-bit: 960 x 4672 40.1 us with the shape-agnostic kernels, 53.5
+// unsplit, 27.4 here; 320 x 9280 49.6, 79.7, 24.5; 704 x 2432 30.9, 35.1, 23.9).  Every pair counts as a chunk there, up to the number
+// of experts: with the splits of one chunk, 10 pairs over 32 experts of 2880 x 2880, 4-bit, took 83 us, unsplit 59, with
+// those of ten 57.
+constexpr int kUnevenPairs = 16;   // (no more than a launch of 16-row chunks has)
+
 MfmaPlan plan_mfma(int P, int d, int f, int E) {
     MfmaPlan p;
     const int avg = (P + E - 1) / E;              // rows per expert if the load were even
     p.ct = avg <= 16 ? 1 : avg <= 32 ? 2 : avg <= 64 ? 4 : 8;
     // down-projection: split the contraction until there are enough workgroups for 256 compute units
-    const int steps = (f + kKTile - 1) / kKTile;
+    const int steps = contraction_steps(f);
     const int down_rows = 64 * (p.ct <= 2 ? kNASmall : 4);
-    const int base = ((d + down_rows - 1) / down_rows) * (P / (16 * p.ct) + 1);
+    const int tiles = (d + down_rows - 1) / down_rows, base = tiles * (P / (16 * p.ct) + 1);
     int best = 1, best4 = 0;
     for (int s = 1; s <= 16; ++s)
         // (widths that are no multiple of 128: no more scratch than fits the library's own, so that a block which fits
         // with one range per row still does)
-        if (steps % s == 0 && steps / s >= 2 && base * s <= 640 &&
+        if (splits_ok(steps, s) && base * s <= 640 &&
+            (steps % s == 0 || (half_step_width(d, f) && P <= kUnevenPairs && tiles * std::min(P, E) * s <= 640)) &&
             (s == 1 || !half_step_width(d, f) || (size_t)P * ((size_t)4 * s * d + 2 * d + 2 * f + 64) + 4096 <= MOE_STATIC_SCRATCH_BYTES)) {
             best = s;
             if ((steps / s) % 4 == 0) best4 = s;
@@ -1930,9 +1946,8 @@ MfmaPlan plan_mfma(int P, int d, int f, int E) {
 }
 
 int fewer_splits(int f, int splits) {
-    const int steps = (f + kKTile - 1) / kKTile;
     do --splits;
-    while (splits > 1 && steps % splits);
+    while (splits > 1 && !splits_ok(contraction_steps(f), splits));
     return splits;
 }
 
@@ -1964,7 +1979,7 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     a.ex = ex; a.offsets = rows.offsets; a.perm = nullptr; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
     a.idx = rows.idx; a.P = P;
-    a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = (f + kKTile - 1) / kKTile / splits * kKTile; a.split_stride = split_stride;
+    a.in = h; a.out = y; a.K = f; a.N = d; a.E = E; a.k_per_split = steps_per_split(contraction_steps(f), splits) * kKTile; a.split_stride = split_stride;
     a.status = status;
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);

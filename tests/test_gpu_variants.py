@@ -208,6 +208,30 @@ def test_static_scratch_at_its_limit_odd_multiples_of_64(orc):
     assert refused.value.code == mm.MOE_EWORKSPACE
 
 
+# Up to 16 pairs: ranges of unequal length where the number of steps has no divisor (17, 19, 23, 67 steps, with and without
+# half a step at the end, the last range of two and three steps), the same with a workspace for fewer splits and through
+# one expert alone.
+@pytest.mark.parametrize("d,f", [(704, 2112), (320, 2432), (512, 2880), (320, 8512), (448, 4672)])
+@pytest.mark.parametrize("T", [2, 5, 8])
+def test_uneven_splits(orc, d, f, T):
+    cfg = common.Config(f"uneven_d{d}_f{f}_T{T}", d, f, 3, 2, T, (0,), int8_experts=(1,))
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    least, full = common.unsplit_workspace_bytes(d, f, 3, 2, T), mm.workspace_bytes(layer, T)
+    assert full > least
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2)
+    for n in (full, full - 256, (least + full) // 2, least):
+        room = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        out, idx, _ = _run_block(layer, wl.x, 2, room[:n])
+        assert bool((room[n:] == 0xFF).all())
+        assert np.array_equal(idx, ref_idx)
+        assert_ffn_close(out, ref, f"{cfg.name} ws={n}")
+    for e in range(3):
+        y = torch.full((T, d), float("nan"), dtype=torch.float32, device="cuda")
+        mm.moe_expert_ffn_mixed(layer, e, dev(wl.x), y, mm.alloc_workspace(layer, T))
+        assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[e], wl.x), f"{cfg.name} expert {e}")
+
+
 @pytest.mark.parametrize("bits", [4, 8, 16])
 def test_half_step_keeps_neighbours_apart(orc, bits):
     """A row's end is the next row's start in memory: infinities at the start of a token, of a hidden row and of a
