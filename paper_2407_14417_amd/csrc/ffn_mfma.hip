@@ -1529,11 +1529,10 @@ __device__ __forceinline__ void quant8_body(const TileCtx& c, const DevExpert& e
 // d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
 // a time and 4-bit rows whose 128-byte requests straddle two lines.)
 // SPB: 128-column steps per LDS stage.  Launches with 64-row chunks of blocks without 16-bit experts take one instead of
-// two: their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two wavefronts per SIMD
-// are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us, 8-bit 408 -> 372;
-// 4-bit 2048 x 5632, 160 tokens 117 -> 95.  (Not everywhere: 150 tokens, 4 experts of 2048 x 2048, one slot, 52.7 us with two
-// steps and 54.7 with one; 200 tokens, 1408 x 1408 60.2 and 63.1; 12 of 16 shapes between 512 and 4096 columns gain.)  With 16-bit experts (99 KB) there is no second workgroup and one step per
-// stage loses up to 4 %; contractions that end with half a step lose 7 %.
+// two (one_step_per_stage): their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two
+// wavefronts per SIMD are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us,
+// 8-bit 408 -> 372; 4-bit 2048 x 5632, 160 tokens 117 -> 95.  With 16-bit experts (99 KB) there is no second workgroup and
+// one step per stage loses up to 4 %; contractions that end with half a step lose 7 %.
 template <bool UP, int CT, bool WIDE, bool HALF, int SPB>
 __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int MC = 16 * CT;                  // activation rows per chunk
@@ -1812,13 +1811,24 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
 }
 
+// One step per LDS stage lets a second workgroup share a compute unit and fills the first stage sooner; two halve the
+// barriers.  So two steps where every workgroup has a compute unit to itself and its range is long.  Launches, one and two
+// steps: 79 columns of workgroups x 4 chunks, 12 steps 43.0, 54.7 us; 6 x 4, 79 steps 142.5, 123.6; 32 x 4, 32 steps 55.9, 51.9;
+// 11 x 10, 11 steps 27.1, 26.7; 10 x 2, 19 steps 34.2, 31.8; 38 x 2, 9 steps 20.6, 21.7; 8 x 10, 4 steps 14.4, 15.7; of 52
+// launches of 60 to 240 tokens the faster one is taken in all but two, where they differ by 1 %.
+bool one_step_per_stage(const MfmaArgs& a, dim3 grid) {
+    if (a.unit_bytes != 2048) return false;
+    const int chunks = a.direct_expert >= 0 ? (int)grid.y : std::min(a.P, a.P / 64 + a.E / 2);
+    return grid.x * chunks > kComputeUnits || a.k_per_split / kKTile <= 10;
+}
+
 template <bool UP, bool WIDE, bool HALF>
 void launch_ct_w(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
     switch (ct) {
         case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
         case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
         case 4:
-            if (!HALF && a.unit_bytes == 2048) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
+            if (!HALF && one_step_per_stage(a, grid)) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
             else launch_one<UP, 4, WIDE, HALF>(a, grid, st);
             break;
         default: launch_one<UP, 8, WIDE, HALF>(a, grid, st); break;

@@ -467,9 +467,9 @@ def test_chunks_handed_out_by_length(orc, E, k, T, bias, d, f):
 
 
 # 64-row chunks of blocks without 16-bit experts: one step per LDS stage (odd and even numbers of steps, ragged and full
-# chunks), the same bits as beside a 16-bit expert that no token reaches (two steps per stage).
+# chunks; two in the few workgroups of 1408 x 1536, one in the many of 1408 x 5632), the same bits as beside a 16-bit expert that no token reaches (two steps per stage).
 @pytest.mark.parametrize("bits", [4, 8])
-@pytest.mark.parametrize("d,f,T", [(640, 896, 140), (1024, 2048, 200), (384, 1536, 256)])
+@pytest.mark.parametrize("d,f,T", [(640, 896, 140), (1024, 2048, 200), (384, 1536, 256), (1408, 1536, 140), (1408, 5632, 140)])
 def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
     every = tuple(range(8))
     cfg = common.Config(f"rows64_{bits}_{d}_{T}", d, f, 8, 2, T, every if bits == 4 else (), int8_experts=every if bits == 8 else ())
