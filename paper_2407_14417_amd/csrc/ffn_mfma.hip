@@ -1811,6 +1811,9 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
 }
 
+// Chunks of at most `cap` rows that P pairs over E experts make: half a chunk more per expert than full ones would be.
+int likely_chunks(int P, int E, int cap) { return (2 * P / cap + E + 1) / 2; }
+
 // One step per LDS stage lets a second workgroup share a compute unit and fills the first stage sooner; two halve the
 // barriers.  So two steps where every workgroup has a compute unit to itself and its range is long.  Launches, one and two
 // steps: 79 columns of workgroups x 4 chunks, 12 steps 43.0, 54.7 us; 6 x 4, 79 steps 142.5, 123.6; 32 x 4, 32 steps 55.9, 51.9;
@@ -1818,7 +1821,7 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
 // launches of 60 to 240 tokens the faster one is taken in all but two, where they differ by 1 %.
 bool one_step_per_stage(const MfmaArgs& a, dim3 grid) {
     if (a.unit_bytes != 2048) return false;
-    const int chunks = a.direct_expert >= 0 ? (int)grid.y : std::min(a.P, a.P / 64 + a.E / 2);
+    const int chunks = a.direct_expert >= 0 ? (int)grid.y : std::min(a.P, likely_chunks(a.P, a.E, 64));
     return grid.x * chunks > kComputeUnits || a.k_per_split / kKTile <= 10;
 }
 
@@ -1878,7 +1881,7 @@ int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int ct, int c
     const int units = kComputeUnits;
     const bool alone = rows.direct_expert >= 0;
     if (alone && columns * chunks(P, 128) < 2 * units) return 0;
-    if (!alone && columns * (P / 128 + a.E / 2) <= units) return 128;
+    if (!alone && columns * likely_chunks(P, a.E, 128) <= units) return 128;
     const int E = alone ? 1 : a.E, n16 = alone ? 0 : __builtin_popcount(a.prec16);
     const int n = chunks(P, E);
     int best = 0, least = 0;

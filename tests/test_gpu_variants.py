@@ -280,7 +280,7 @@ def test_block_quantized_chunks_in_small_launches(orc, T, bits):
 def _rows_per_chunk(n, E, columns):
     """The library's rule for blocks of quantized experts with n rows each and `columns` workgroups per chunk."""
     up = lambda a, b: -(-a // b)
-    if columns * (n * E // 128 + E // 2) <= 256:
+    if columns * ((2 * n * E // 128 + E + 1) // 2) <= 256:
         return 128
     return min((256, 192, 128), key=lambda cap: up(columns * E * up(n, cap), 256) * (40 + 7 * up(up(n, up(n, cap)), 16)))
 
