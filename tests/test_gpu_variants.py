@@ -278,11 +278,17 @@ def test_block_quantized_chunks_in_small_launches(orc, T, bits):
 
 
 def _rows_per_chunk(n, E, columns):
-    """The library's rule for blocks of quantized experts with n rows each and `columns` workgroups per chunk."""
+    """The library's rule for blocks in which every token reaches all E quantized experts (n rows each), with `columns`
+    workgroups per chunk."""
     up = lambda a, b: -(-a // b)
-    if columns * ((2 * n * E // 128 + E + 1) // 2) <= 256:
+    if columns * E * up(n, 128) <= 256:
         return 128
-    return min((256, 192, 128), key=lambda cap: up(columns * E * up(n, cap), 256) * (40 + 7 * up(up(n, up(n, cap)), 16)))
+    best = None
+    for cap in (256, 192, 128):
+        cost = up(columns * E * up(n, cap), 256) * (40 + 7 * up(n // up(n, cap), 16))
+        if best is None or 20 * cost < 19 * best[1]:
+            best = cap, cost
+    return best[0]
 
 
 # Launches of more workgroups (in both projections): one chunk of 9 to 16 tiles, two of 9, and five of 10.
