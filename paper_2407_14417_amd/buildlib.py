@@ -15,8 +15,8 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
-# the matrix-core kernels of the two projections are compiled side by side: minutes each
-PARTS = {"ffn_mfma.hip": (["-DMOEMIX_MFMA_UP"], ["-DMOEMIX_MFMA_DOWN"])}
+# the matrix-core kernels of the two projections are compiled side by side
+PARTS = {s: (["-DMOEMIX_MFMA_UP"], ["-DMOEMIX_MFMA_DOWN"]) for s in ("ffn_mfma.hip", "ffn_prefill.hip")}
 
 
 def sources():

@@ -490,3 +490,33 @@ def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
     w1, w3, w2 = (mm.Mat(dev(w)) for w in common.expert_weights_f16(cfg, 7))
     beside = mm.Layer(d, f, 2, layer.w_gate, [*layer.experts[:7], mm.Expert(mm.PREC_FP16, w1, w3, w2)], layer.gate_bias)
     assert np.array_equal(out, _run_block(beside, wl.x, 2)[0])
+
+
+# ---------------------------------------------------------------- prefill launches
+
+# Every number of 16-row tiles of a chunk with its ragged last one, one-tile rests, tiles of weight rows that end past the
+# matrix, contractions from two steps (shorter than the LDS rings are deep) to eleven, several splits; every token reaches
+# an expert of each precision, and chunks of 16-bit experts hold up to 256 rows.
+@pytest.mark.parametrize("T", [65, 80, 81, 97, 113, 127, 128, 129, 145, 161, 177, 193, 209, 225, 241, 256, 257])
+@pytest.mark.parametrize("d,f", [(256, 384), (640, 256), (384, 1408)])
+def test_prefill_tiles_and_steps(orc, d, f, T):
+    _check_block(orc, common.Config(f"prefill_{d}_{f}_{T}", d, f, 3, 3, T, (0,), int8_experts=(1,)))
+
+
+@pytest.mark.parametrize("shift", [1, 4])
+def test_prefill_tokens_off_16_byte_boundaries(orc, shift):
+    """Tokens may lie anywhere: those that no 16-byte transfer can fetch take the launch that loads them into registers."""
+    cfg = common.Config(f"prefill_shift{shift}", 512, 896, 3, 2, 150, (0,), int8_experts=(1,))
+    wl = build_workload(cfg, orc)
+    layer, n = device_layer(wl), cfg.T * cfg.d
+    x = torch.empty(n + 8, dtype=torch.float16, device="cuda")[shift:shift + n].view(cfg.T, cfg.d)
+    x.copy_(dev(wl.x))
+    out = torch.empty((cfg.T, cfg.d), dtype=torch.float16, device="cuda")
+    idx = torch.empty((cfg.T, 2), dtype=torch.int32, device="cuda")
+    gate = torch.empty((cfg.T, 2), dtype=torch.float32, device="cuda")
+    ws = mm.alloc_workspace(layer, cfg.T)
+    mm.moe_layer_forward(layer, x, out, ws, idx, gate)
+    assert mm.moe_read_status(ws) == 0
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2)
+    assert np.array_equal(idx.cpu().numpy(), ref_idx)
+    assert_ffn_close(out.cpu().numpy(), ref, cfg.name)
