@@ -69,7 +69,9 @@ bool use_mfma(const moe_layer* L, int rows) {
     return rows > 1 && mfma_shape_ok(L->d_model, L->d_ff) && mfma_rows_ok(rows, L->d_model, L->d_ff);
 }
 
-MfmaPlan plan_for(const moe_layer* L, int rows) { return plan_mfma(rows, L->d_model, L->d_ff, L->n_experts); }
+MfmaPlan plan_for(const moe_layer* L, int rows) {
+    return plan_mfma(rows, L->d_model, L->d_ff, L->n_experts, L->top_k == L->n_experts);
+}
 
 int y_splits_for(const moe_layer* L, int T) {
     if (!use_mfma(L, T * L->top_k)) return 1;
@@ -246,7 +248,7 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
         launch_decode_up(table, w.idx, (const half_t*)x_rows, d, f, 1, w.h, w.status, kDecodeUpBlocks, st);
         launch_decode_down(table, w.idx, w.gate, w.h, d, f, 1, nullptr, nullptr, w.status, st, y);
     } else if (use_mfma(layer, n)) {
-        MfmaPlan p = plan_mfma(n, d, f, 1);       // all n rows belong to the one expert
+        MfmaPlan p = plan_mfma(n, d, f, 1, true); // all n rows belong to the one expert
         launch_ffn_up_mfma(table, layer->n_experts, rows, n, (const half_t*)x_rows, d, f, w.h, p.ct, w.status, st);
         // few rows: the contraction of the down-projection is split over as many workgroups as the workspace's
         // partial-result region was sized for, and the partials are added in order

@@ -750,7 +750,7 @@ bool mfma_rows_ok(int rows, int d, int f) {
 // those of ten 57.
 constexpr int kUnevenPairs = 16;   // (no more than a launch of 16-row chunks has)
 
-MfmaPlan plan_mfma(int P, int d, int f, int E) {
+MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
     MfmaPlan p;
     const int avg = (P + E - 1) / E;              // rows per expert if the load were even
     p.ct = avg <= 16 ? 1 : avg <= 32 ? 2 : avg <= 64 ? 4 : 8;
@@ -771,6 +771,12 @@ MfmaPlan plan_mfma(int P, int d, int f, int E) {
     // launches with 128-row chunks: ranges of a multiple of 4 steps can be walked from different places (TileCtx::rot), so a
     // split that gives such ranges is preferred if it keeps at least half the workgroups
     p.down_splits = (p.ct == 8 && best4 * 2 >= best) ? best4 : best;
+    // Loads spread about their mean: from a mean of 13 rows on so many experts have more than 16 that two tiles per chunk
+    // cost less than their second chunks (64 tokens, Mixtral shape, 4-bit 236 -> 199 us, 8-bit 357 -> 276, 16-bit 596 -> 447;
+    // 52 tokens 200 -> 188, 314 -> 270, 500 -> 446; 40 tokens 177, 180; 268, 265; 429, 439), from 15 on where all chunks run side
+    // by side (8 experts of 1024 x 2816: 52 tokens 39.4, 41.3, 64 tokens 44.3 -> 42.0).  (The splits, and with them the
+    // workspace, stay those of one tile.)
+    if (p.ct == 1 && !even && avg > ((f + 63) / 64 * E <= 512 ? 14 : 12)) p.ct = 2;
     return p;
 }
 

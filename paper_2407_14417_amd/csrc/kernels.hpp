@@ -54,7 +54,8 @@ struct MfmaPlan {
 };
 bool mfma_shape_ok(int d, int f);
 bool mfma_rows_ok(int rows, int d, int f);
-MfmaPlan plan_mfma(int P, int d, int f, int E);
+// `even`: every expert gets the same number of the P pairs.
+MfmaPlan plan_mfma(int P, int d, int f, int E, bool even);
 inline bool half_step_width(int d, int f) { return (d | f) % 128 != 0; }
 int fewer_splits(int f, int splits);
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
