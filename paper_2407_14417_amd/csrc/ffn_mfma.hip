@@ -668,10 +668,25 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
     return 2048;
 }
 
-// Launches for ffn_prefill.hip: 128-row chunks, contractions of whole steps, input rows that start on 16-byte boundaries (its
+// Wavefronts per workgroup of ffn_prefill.hip for a launch of plan `ct` with `columns` tiles of 128 (down: 256) weight rows and
+// splits, 0: not for that kernel.  It takes contractions of whole steps, input rows that start on 16-byte boundaries (its
 // transfers into LDS are of 16 bytes; tokens may lie anywhere) and end a little before the reach of a 32-bit byte offset.
-bool prefill_ok(const MfmaArgs& a, int ct) {
-    return ct == 8 && a.K % kKTile == 0 && (uintptr_t)a.in % 16 == 0 && (uint64_t)a.P * a.K * 2 + 8192 < (1ull << 32);
+//   8: chunks of up to 256 rows, one workgroup per compute unit.
+//   4: chunks of up to 128 rows, two workgroups per compute unit with half the weight rows each: they hide each other's
+//      beginning and end, and there are more of them; activations go into LDS twice.  Where 8 wavefronts would not give every
+//      compute unit a workgroup (600 tokens, 4 experts of 2048 x 2048, top-1, 4-bit 65 -> 60 us; 80 tokens on each of 4 experts
+//      of 1024 x 2816, 4-bit 45.7 -> 42.6, 16-bit 50.7 -> 47.9), not where they would (512 tokens, Mixtral shape, 505, 579).
+//      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64 and about half of the experts need two from
+//      some 52 on: 250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415, 16-bit 662 -> 557; 140 tokens 289, 290, 371 ->
+//      363, 552 -> 524; 200 tokens, 32 experts of 2048 x 1408, 4-bit 104 -> 98.5.  Quantized experts alone, long
+//      contractions and fewer rows stay there: 200 tokens, Mixtral shape, 4-bit 312, 321, 8-bit 373, 389.
+int prefill_waves(const MfmaArgs& a, int ct, int columns) {
+    if (ct < 4 || a.K % kKTile || (uintptr_t)a.in % 16 || (uint64_t)a.P * a.K * 2 + 8192 >= (1ull << 32)) return 0;
+    const int E = a.direct_expert >= 0 ? 1 : a.E, rows = (a.P + E - 1) / E;
+    // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
+    const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
+    if (ct == 4) return any16 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
+    return columns * E * ((rows + 127) / 128) <= (int)kComputeUnits ? 4 : 8;
 }
 
 // Most rows of a 4-bit or 8-bit expert's chunks in ffn_prefill.hip, 0: 128 and no even split (also where that kernel is not
@@ -681,8 +696,8 @@ bool prefill_ok(const MfmaArgs& a, int ct) {
 // times the time of one come out least, the longer one unless a shorter one saves 5 %.  Loads spread around their mean:
 // half of the experts are taken to have an eighth more, half an eighth less (none where every token reaches every expert).
 // One expert alone: the same from two rounds on.
-int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int ct, int columns) {
-    if (!prefill_ok(a, ct)) return 0;
+int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int columns) {
+    if (a.waves != 8) return 0;
     const auto chunks = [](int n, int cap) { return (n + cap - 1) / cap; };
     const int units = kComputeUnits;
     const bool alone = rows.direct_expert >= 0, exact = alone || rows.top_k == a.E;
@@ -703,7 +718,7 @@ int quant_chunk_rows(const RowMap& rows, const MfmaArgs& a, int P, int ct, int c
 }
 
 int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
-    const int mc = 16 * ct;
+    const int mc = a.waves ? 128 : 16 * ct;
     if (rows.direct_expert >= 0) return (rows.direct_n + mc - 1) / mc;
     // every expert may end with one ragged chunk; those of 16-bit experts in ffn_prefill.hip are never shorter than those of
     // the others (a workgroup that finds no chunk costs some 3 us, at the launch's end)
@@ -713,7 +728,7 @@ int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
 
 template <bool UP>
 void launch_ct(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
-    if (prefill_ok(a, ct)) launch_prefill<UP>(a, grid, st);
+    if (a.waves) launch_prefill<UP>(a, grid, st);
     else if (a.K % kKTile || ct == 8) launch_ct_w<UP, true, true>(a, ct, grid, st);
     else if (any_int8(a.ex, a.E)) launch_ct_w<UP, true, false>(a, ct, grid, st);
     else launch_ct_w<UP, false, false>(a, ct, grid, st);
@@ -797,9 +812,10 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
-    const int up_rows = 32 * (ct <= 2 ? kNASmall : 4);
+    a.waves = prefill_waves(a, ct, (f + 127) / 128);
+    const int up_rows = a.waves ? 16 * a.waves : 32 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (f + up_rows - 1) / up_rows;
-    a.quant_rows = quant_chunk_rows(rows, a, P, ct, a.tiles);
+    a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles);
     dim3 grid(a.tiles, chunk_slots(rows, a, P, ct), 1);
     launch_ct<true>(a, ct, grid, st);
 }
@@ -819,9 +835,10 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
-    const int down_rows = 64 * (ct <= 2 ? kNASmall : 4);
+    a.waves = prefill_waves(a, ct, (d + 255) / 256 * splits);
+    const int down_rows = a.waves ? 32 * a.waves : 64 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (d + down_rows - 1) / down_rows;
-    a.quant_rows = quant_chunk_rows(rows, a, P, ct, a.tiles * splits);
+    a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles * splits);
     dim3 grid(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
     launch_ct<false>(a, ct, grid, st);
 }

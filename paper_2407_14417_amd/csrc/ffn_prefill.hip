@@ -30,8 +30,7 @@ namespace moemix {
 
 namespace {
 
-constexpr int kThreads = 512;
-constexpr int kLdsBytes = 163840;                          // all of a compute unit
+constexpr int kLdsBytes = 163840;                          // of a compute unit
 
 // ---- device memory straight into LDS
 
@@ -71,10 +70,10 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) 
 constexpr int min_of(int a, int b) { return a < b ? a : b; }
 
 // LDS rings of a chunk of N tiles: stages of activations, slabs of weights (4-bit: of two stages), in KB
-template <int PREC, int N>
+template <int WAVES, int PREC, int N>
 struct Rings {
-    static constexpr int kScales = PREC == MOE_PREC_FP16 ? 0 : 16, kRoom = kLdsBytes / 1024 - kScales;
-    static constexpr int kX = 2 * N, kSlab = PREC == MOE_PREC_FP16 ? 32 : 16;
+    static constexpr int kScales = PREC == MOE_PREC_FP16 ? 0 : 2 * WAVES, kRoom = kLdsBytes / 1024 * WAVES / 8 - kScales;
+    static constexpr int kX = 2 * N, kSlab = PREC == MOE_PREC_FP16 ? 4 * WAVES : 2 * WAVES;
     static constexpr int slabs(int d) { return PREC == MOE_PREC_INT4G64 ? (d + 4) / 2 : d; }
     static constexpr bool fits(int d) { return d * kX + slabs(d) * kSlab <= kRoom; }
     static constexpr int kDepth = fits(6) ? 6 : fits(5) ? 5 : fits(4) ? 4 : 3;
@@ -86,13 +85,13 @@ struct Rings {
 // One workgroup's chunk of N tiles of 16 rows.  Rings: stage i's activations in slot i mod XR, weights of slab u in slot
 // u mod R (a slab is a stage's weights, for 4-bit ones two stages').  What stage i asks for overwrites what stage i - 1 read
 // last (its reads are done when the wavefronts have met in stage i - 1) and is there when they meet XR - 2 stages later.
-template <bool UP, int PREC, int N>
+template <int WAVES, bool UP, int PREC, int N>
 __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee, void* out_base) {
     constexpr bool INT4 = PREC == MOE_PREC_INT4G64, INT8 = PREC == MOE_PREC_INT8G64, QUANT = INT4 || INT8;
-    typedef Rings<PREC, N> L;
-    constexpr int XR = L::kStages, R = L::kSlabs, XSTAGE = L::kX * 1024, SLAB = L::kSlab * 1024, WSLAB = SLAB / 8;
+    typedef Rings<WAVES, PREC, N> L;
+    constexpr int XR = L::kStages, R = L::kSlabs, XSTAGE = L::kX * 1024, SLAB = L::kSlab * 1024, WSLAB = SLAB / WAVES;
     constexpr int kSlabs = XR * XSTAGE, kScales = kSlabs + R * SLAB;
-    constexpr int NX = (2 * N + 7) / 8, XREM = 2 * N % 8;  // 1 KB runs of a stage's activations per wavefront; the first
+    constexpr int NX = (2 * N + WAVES - 1) / WAVES, XREM = 2 * N % WAVES;  // 1 KB runs of a stage's activations per wavefront; the first
                                                            // XREM wavefronts (0: all) have the last one
     constexpr int SPW = QUANT ? 2 : 4;                     // ... of a slab's weights
     constexpr int NS = INT4 ? 1 : SPW;                     // ... per stage
@@ -142,7 +141,7 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
         int s = 4 * q + c4;
         s = s < n_steps ? s : n_steps - 1;
         s = s + c.rot < n_steps ? s + c.rot : s + c.rot - n_steps;
-        const uint32_t d = lds0 + kScales + (q & 1) * 8192 + wave * 1024;
+        const uint32_t d = lds0 + kScales + (q & 1) * (1024 * WAVES) + wave * 1024;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             bring_words(d + t * 512, sb[t], sv[t] + s * 4);
@@ -223,7 +222,7 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
         }
     };
     auto read_sz = [&](uint32_t (&sz)[2][2], int step) {   // the two groups of a step: scales, zeros
-        const uint32_t at = s_off + ((step >> 2) & 1) * 8192 + (step & 3) * 64;
+        const uint32_t at = s_off + ((step >> 2) & 1) * (1024 * WAVES) + (step & 3) * 64;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -315,7 +314,7 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
             }
             // Of the two wavefronts of a SIMD the one further behind goes first: left to themselves the older one does, waits
             // for the younger at every meeting, and each alone cannot keep the matrix cores busy.
-            if constexpr (k == 0 || 4 * k / NU != 4 * (k - 1) / NU) __builtin_amdgcn_s_setprio(3 - 4 * k / NU);
+            if constexpr (WAVES == 8 && (k == 0 || 4 * k / NU != 4 * (k - 1) / NU)) __builtin_amdgcn_s_setprio(3 - 4 * k / NU);
             // next unit's operands
             constexpr int nk = (k + 1) % NU, nsub = nk / UPS, nu = nk % UPS;
             const uint8_t* const nbase = (k + 1 < NU ? xb : xn) + b_off[nsub] + first_tile(nu) * 2048;
@@ -388,10 +387,10 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
     }
 }
 
-template <bool UP, int PREC>
+template <int WAVES, bool UP, int PREC>
 __device__ __forceinline__ void run_chunk(const TileCtx& c, const DevExpert& ee, void* out_base) {
     const int nct = (c.rows + 15) >> 4;
-#define MOEMIX_CASE(n) case n: chunk_body<UP, PREC, n>(c, ee, out_base); break;
+#define MOEMIX_CASE(n) case n: chunk_body<WAVES, UP, PREC, (n) <= WAVES * 2 ? (n) : WAVES * 2>(c, ee, out_base); break;
     switch (nct) {
         MOEMIX_CASE(1) MOEMIX_CASE(2) MOEMIX_CASE(3) MOEMIX_CASE(4) MOEMIX_CASE(5) MOEMIX_CASE(6) MOEMIX_CASE(7) MOEMIX_CASE(8)
         MOEMIX_CASE(9) MOEMIX_CASE(10) MOEMIX_CASE(11) MOEMIX_CASE(12) MOEMIX_CASE(13) MOEMIX_CASE(14) MOEMIX_CASE(15) MOEMIX_CASE(16)
@@ -400,9 +399,9 @@ __device__ __forceinline__ void run_chunk(const TileCtx& c, const DevExpert& ee,
 }
 
 // WIDE: the block holds 8-bit experts as well.
-template <bool UP, bool WIDE>
-__global__ __launch_bounds__(kThreads) void prefill_kernel(const MfmaArgs a) {
-    constexpr int NT = UP ? 128 : 256;           // weight rows per workgroup
+template <int WAVES, bool UP, bool WIDE>
+__global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a) {
+    constexpr int kThreads = 64 * WAVES, NT = (UP ? 16 : 32) * WAVES;   // weight rows per workgroup
     extern __shared__ __align__(16) uint8_t lds[];
     const int tid = threadIdx.x;
     // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk.
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(const MfmaArgs a) {
     };
     auto chunk_rows = [&](int expert, int n) {   // rows per chunk of an expert with n rows, split evenly in whole tiles
         const int prec = prec_of(expert);
-        if (n <= 128 || (prec != MOE_PREC_FP16 && !a.quant_rows)) return 128;
+        if (n <= 128 || WAVES == 4 || (prec != MOE_PREC_FP16 && !a.quant_rows)) return 128;
         const int cap = prec == MOE_PREC_FP16 ? kChunkRows : a.quant_rows;
         const int nch = (n + cap - 1) / cap;
         return (((n + nch - 1) / nch) + 15) & ~15;
@@ -500,14 +499,14 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(const MfmaArgs a) {
         return;
     }
     const int prec = ee.prec;
-    if (prec == MOE_PREC_INT4G64) run_chunk<UP, MOE_PREC_INT4G64>(c, ee, out_base);
-    else if (WIDE && prec == MOE_PREC_INT8G64) run_chunk<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64>(c, ee, out_base);
-    else run_chunk<UP, MOE_PREC_FP16>(c, ee, out_base);
+    if (prec == MOE_PREC_INT4G64) run_chunk<WAVES, UP, MOE_PREC_INT4G64>(c, ee, out_base);
+    else if (WIDE && prec == MOE_PREC_INT8G64) run_chunk<WAVES, UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64>(c, ee, out_base);
+    else run_chunk<WAVES, UP, MOE_PREC_FP16>(c, ee, out_base);
 }
 
-template <bool UP, bool WIDE>
+template <int WAVES, bool UP, bool WIDE>
 void launch_prefill_w(const MfmaArgs& a, dim3 grid, hipStream_t st) {
-    constexpr size_t lds_bytes = kLdsBytes;
+    constexpr size_t lds_bytes = kLdsBytes * WAVES / 8;
     // the attribute belongs to (kernel, device): set it once per device of the process (bit d of the mask; devices
     // past the 64th set it on every launch)
     static std::atomic<unsigned long long> configured{0};
@@ -515,18 +514,23 @@ void launch_prefill_w(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     (void)hipGetDevice(&dev);
     const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
     if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
-        (void)hipFuncSetAttribute((const void*)prefill_kernel<UP, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        (void)hipFuncSetAttribute((const void*)prefill_kernel<WAVES, UP, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         configured.fetch_or(bit, std::memory_order_relaxed);
     }
-    prefill_kernel<UP, WIDE><<<grid, kThreads, lds_bytes, st>>>(a);
+    prefill_kernel<WAVES, UP, WIDE><<<grid, 64 * WAVES, lds_bytes, st>>>(a);
 }
 
 }  // namespace
 
 template <bool UP>
 void launch_prefill(const MfmaArgs& a, dim3 grid, hipStream_t st) {
-    if (a.prec8) launch_prefill_w<UP, true>(a, grid, st);
-    else launch_prefill_w<UP, false>(a, grid, st);
+    if (a.waves == 4) {
+        if (a.prec8) launch_prefill_w<4, UP, true>(a, grid, st);
+        else launch_prefill_w<4, UP, false>(a, grid, st);
+    } else {
+        if (a.prec8) launch_prefill_w<8, UP, true>(a, grid, st);
+        else launch_prefill_w<8, UP, false>(a, grid, st);
+    }
 }
 
 #if !defined(MOEMIX_MFMA_DOWN)

@@ -26,7 +26,8 @@ struct MfmaArgs {
     size_t split_stride;      // elements of y between two splits
     int unit_bytes;           // LDS bytes per A operand for weight staging: 4096 if any expert is 16-bit, else 2048
     uint32_t prec16, prec8;   // the experts held in 16 and in 8 bits, one bit each
-    int quant_rows;           // most rows of a chunk of a 4-bit or 8-bit expert in ffn_prefill.hip (quant_chunk_rows)
+    int waves;                // ffn_prefill.hip: wavefronts per workgroup (prefill_waves); else 0
+    int quant_rows;           // its 8-wavefront form: most rows of a chunk of a 4-bit or 8-bit expert (quant_chunk_rows)
     int32_t* status;
 };
 
@@ -116,7 +117,7 @@ struct TileCtx {
     uint32_t lds_base;       // the same as an LDS byte address
 };
 
-// Launches with 128-row chunks, contraction lengths of whole steps (ffn_prefill.hip).
+// Launches with a.waves != 0 (ffn_prefill.hip).
 template <bool UP>
 void launch_prefill(const MfmaArgs& a, dim3 grid, hipStream_t st);
 
