@@ -685,7 +685,7 @@ int prefill_waves(const MfmaArgs& a, int ct, int columns) {
     const int E = a.direct_expert >= 0 ? 1 : a.E, rows = (a.P + E - 1) / E;
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
     const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
-    if (ct == 4) return any16 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
+    if (ct == 4) return any16 || rows <= 32 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
     return columns * E * ((rows + 127) / 128) <= (int)kComputeUnits ? 4 : 8;
 }
 
@@ -791,6 +791,10 @@ MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
     // 52 tokens 200 -> 188, 314 -> 270, 500 -> 446; 40 tokens 177, 180; 268, 265; 429, 439), from 15 on where all chunks run side
     // by side (8 experts of 1024 x 2816: 52 tokens 39.4, 41.3, 64 tokens 44.3 -> 42.0).  (The splits, and with them the
     // workspace, stay those of one tile.)
+    // Likewise the launches of 33 to 64 rows from a mean of 27 on, unless all chunks run side by side (Mixtral shape, 110 tokens,
+    // 4-bit 266 -> 260, 8-bit 357 -> 348, 16-bit 581 -> 505; 126 tokens 287 -> 268, 380 -> 352, 629 -> 507; 8 experts of 1024 x 2816
+    // 46.1, 51.3 and 47.6, 48.8).
+    if (p.ct == 2 && !even && avg > 26 && (f + 63) / 64 * E > 512 && !half_step_width(d, f)) p.ct = 4;
     if (p.ct == 1 && !even && avg > ((f + 63) / 64 * E <= 512 ? 14 : 12)) p.ct = 2;
     return p;
 }
