@@ -76,7 +76,10 @@ struct Rings {
     static constexpr int kX = 2 * N, kSlab = PREC == MOE_PREC_FP16 ? 4 * WAVES : 2 * WAVES;
     static constexpr int slabs(int d) { return PREC == MOE_PREC_INT4G64 ? (d + 4) / 2 : d; }
     static constexpr bool fits(int d) { return d * kX + slabs(d) * kSlab <= kRoom; }
-    static constexpr int kDepth = fits(6) ? 6 : fits(5) ? 5 : fits(4) ? 4 : 3;
+    // As deep as LDS allows up to six stages; 4-bit four, whose stages need fewer bytes than the rings take to fill (80 tokens
+    // on every expert, Mixtral shape, 4-bit with up to six, four and three 357, 351, 369 us; 8-bit 416, 425, 426).
+    static constexpr int kMost = PREC == MOE_PREC_INT4G64 ? 4 : 6;
+    static constexpr int kDepth = kMost == 6 && fits(6) ? 6 : kMost == 6 && fits(5) ? 5 : fits(4) ? 4 : 3;
     static constexpr int kStages = fits(kDepth) ? kDepth : 2;         // (16-bit, more than 10 tiles: two stages, three slabs)
     static constexpr int kSlabs = slabs(kDepth);
     static_assert(kStages * kX + kSlabs * kSlab <= kRoom, "LDS");
@@ -100,6 +103,27 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
     const int K = c.K, Nw = c.N, n_steps = c.n_steps, nb = 2 * n_steps;
     const bool more_x = !XREM || wave < XREM;
     const uint32_t lds0 = c.lds_base;
+
+    // ---- the tokens of the rows it brings.  (Asked for and turned into offsets before anything else is on its way: transfers end
+    // in order, so tokens that are asked for behind weights come when those have come, 2 to 3 us later.)
+    const int run0 = XREM ? wave * (NX - 1) + (wave < XREM ? wave : XREM) : wave * NX;
+    uint32_t xv[NX];
+    {
+        const uint32_t rcp = UP && c.perm && c.top_k > 1 ? 0xFFFFFFFFu / (uint32_t)c.top_k + 1 : 0;   // (pairs: less than 2^24)
+        uint32_t pair[NX];
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const int row = (run0 + k) * 8 + (lane >> 3);
+            const int g = c.begin + c.m0 + (row < c.rows ? row : c.rows - 1);
+            pair[k] = UP && c.perm ? (uint32_t)c.perm[g] : (uint32_t)g;
+        }
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const uint32_t src = rcp ? __umulhi(pair[k], rcp) : pair[k];
+            xv[k] = src * (uint32_t)K * 2 + (((lane & 7) ^ swizzle128(((run0 + k) * 8 + (lane >> 3)) & 15)) * 16) + (kBack - 1024 * k);
+        }
+        pin_schedule();
+    }
 
     // ---- weights, scales and zeros: every wavefront brings its own
     const int row0 = c.n0 + wave * (UP ? 16 : 32);
@@ -150,9 +174,7 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
     };
 
     // ---- activations: an eighth each
-    const int run0 = XREM ? wave * (NX - 1) + (wave < XREM ? wave : XREM) : wave * NX;
     const gptr_t xb0 = scalar_ptr(c.in + c.k_begin - kBack / 2);
-    uint32_t xv[NX];
     const uint32_t x_end = n_steps * 256;
     uint32_t x_at = c.rot * 256, x_dst = lds0 + run0 * 1024;
     auto bring_x = [&](auto kc) {                          // run k of the next stage
@@ -261,17 +283,6 @@ __device__ __forceinline__ void chunk_body(const TileCtx& c, const DevExpert& ee
     if (QUANT) bring_scales(0);
     unrolled(std::make_integer_sequence<int, kAhead>{}, [&](auto ic) {
         constexpr int i = decltype(ic)::value - kAhead;    // stage
-        if constexpr (i == -(XR - 1)) {
-            // (weights are on their way: the tokens of the rows)
-#pragma unroll
-            for (int k = 0; k < NX; ++k) {
-                const int row = (run0 + k) * 8 + (lane >> 3);
-                const int rr = row < c.rows ? row : c.rows - 1;
-                const int g = c.begin + c.m0 + rr;
-                const uint32_t src = (UP && c.perm) ? (uint32_t)(c.perm[g] / c.top_k) : (uint32_t)g;
-                xv[k] = src * (uint32_t)K * 2 + (((lane & 7) ^ swizzle128(row & 15)) * 16) + (kBack - 1024 * k);
-            }
-        }
         const bool x = i >= -(XR - 1) && asks_x(i), w = asks_w(i);
         unrolled(std::make_integer_sequence<int, NX + NS>{}, [&](auto oc) { ask(oc, x, w, std::integral_constant<int, (i & 1)>{}); });
     });
@@ -425,18 +436,23 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a
     auto prec_of = [&](int expert) {
         return (a.prec16 >> expert) & 1u ? MOE_PREC_FP16 : (a.prec8 >> expert) & 1u ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64;
     };
-    auto chunk_rows = [&](int expert, int n) {   // rows per chunk of an expert with n rows, split evenly in whole tiles
+    // chunks of an expert with n rows, split evenly in whole tiles; rows per chunk
+    auto split = [&](int expert, int n, int& per) {
         const int prec = prec_of(expert);
-        if (n <= 128 || WAVES == 4 || (prec != MOE_PREC_FP16 && !a.quant_rows)) return 128;
-        const int cap = prec == MOE_PREC_FP16 ? kChunkRows : a.quant_rows;
-        const int nch = (n + cap - 1) / cap;
-        return (((n + nch - 1) / nch) + 15) & ~15;
+        per = 128;
+        const int cap = WAVES == 4 || n <= 128 ? 128 : prec == MOE_PREC_FP16 ? 256 : a.quant_rows;
+        if (cap <= 128 && (cap == 0 || n <= 128 || WAVES == 4)) return (n + 127) >> 7;
+        // (cap: 128, 192 or 256)
+        const int nch = cap == 192 ? (int)(__umulhi((uint32_t)n + 191, 0xAAAAAAABu) >> 7) : (n + cap - 1) >> (cap == 256 ? 8 : 7);
+        per = (((n + nch - 1) / nch) + 15) & ~15;
+        return nch;
     };
     int e, begin, cnt, per, chunk = blockIdx.y;
     TileCtx c;
     c.tokens = nullptr;
     if (a.direct_expert >= 0) {
-        e = a.direct_expert; begin = 0; cnt = a.direct_n; per = chunk_rows(e, cnt);
+        e = a.direct_expert; begin = 0; cnt = a.direct_n;
+        split(e, cnt, per);
     } else {
         // Chunks are handed out expert by expert, those whose workgroups run longest first: a launch ends when its last
         // workgroup does, so the long ones must not start last.  Microseconds of a workgroup with 4096 columns: 4-bit 56 and
@@ -450,15 +466,23 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a
             b = a.offsets[lane];
             n = a.offsets[lane + 1] - b;
         }
-        const int pr = chunk_rows(lane & 31, n), nch = (n + pr - 1) / pr;
+        int pr;
+        const int nch = split(lane & 31, n, pr);           // (the last one may be empty)
         const int tiles = (min(n, pr) + 15) >> 4, prec = prec_of(lane & 31);
         const int cost = prec == MOE_PREC_FP16 ? 1000 + n : (prec == MOE_PREC_INT8G64 ? 45 : 35) + 7 * tiles;
+        // chunks handed out before this expert's.  (Lane numbers as constants: a loop over them took 265 cycles a round, 4 of
+        // the 9 us that a workgroup of a launch with 32 experts spent before its first product.)
+        const int key = mine ? cost * 64 + 63 - lane : -1;
         int first = 0;
-        for (int i = 0; i < a.E; ++i) {
-            const int ci = __builtin_amdgcn_readlane(cost, i);
-            const int ni = __builtin_amdgcn_readlane(nch, i);
-            first += (ci > cost || (ci == cost && i < lane)) ? ni : 0;
-        }
+#pragma unroll
+        for (int g = 0; g < MOE_MAX_EXPERTS; g += 8)
+            if (g < a.E) {
+#pragma unroll
+                for (int i = g; i < g + 8; ++i) {
+                    const int ki = __builtin_amdgcn_readlane(key, i), ni = __builtin_amdgcn_readlane(nch, i);
+                    first += ki > key ? ni : 0;
+                }
+            }
         const unsigned long long owner = __ballot(mine && chunk >= first && chunk < first + nch);
         if (!owner) return;
         e = __builtin_ctzll(owner);
