@@ -676,6 +676,8 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //      beginning and end, and there are more of them; activations go into LDS twice.  Where 8 wavefronts would not give every
 //      compute unit a workgroup (600 tokens, 4 experts of 2048 x 2048, top-1, 4-bit 65 -> 60 us; 80 tokens on each of 4 experts
 //      of 1024 x 2816, 4-bit 45.7 -> 42.6, 16-bit 50.7 -> 47.9), not where they would (512 tokens, Mixtral shape, 505, 579).
+//      Also up to 76 rows per expert (68 rows, Mixtral shape, 4-bit 368 -> 351, 8-bit 438 -> 417, 16-bit 600 -> 562; 75 rows, 32 experts
+//      of 2048 x 1408, 4-bit 112 -> 105; 80 rows 367, 368, half 16-bit of 2048 x 5632 214, 220; 100 rows 405, 413).
 //      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64 and about half of the experts need two from
 //      some 52 on: 250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415, 16-bit 662 -> 557; 140 tokens 289, 290, 371 ->
 //      363, 552 -> 524; 200 tokens, 32 experts of 2048 x 1408, 4-bit 104 -> 98.5.  Quantized experts alone, long
@@ -686,7 +688,7 @@ int prefill_waves(const MfmaArgs& a, int ct, int columns) {
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
     const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
     if (ct == 4) return any16 || rows <= 32 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
-    return columns * E * ((rows + 127) / 128) <= (int)kComputeUnits ? 4 : 8;
+    return rows <= 76 || columns * E * ((rows + 127) / 128) <= (int)kComputeUnits ? 4 : 8;
 }
 
 // Most rows of a 4-bit or 8-bit expert's chunks in ffn_prefill.hip, 0: 128 and no even split (also where that kernel is not

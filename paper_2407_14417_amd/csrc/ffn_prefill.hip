@@ -1,8 +1,9 @@
-// Expert feed-forward layers on many rows, launches with more than 64 rows per expert (prefill): the grouped products of
-// ffn_mfma.hip with device memory brought straight into LDS.
+// Expert feed-forward layers on many rows (prefill; prefill_waves in ffn_mfma.hip says which launches): the grouped products
+// of ffn_mfma.hip with device memory brought straight into LDS.
 //
-// One workgroup = 8 wavefronts (two per SIMD, one workgroup per compute unit) = one (expert, tile of 128 rows of w1 and w3 or
-// 256 of w2, chunk of up to 256 activation rows, contraction split).  A wavefront multiplies 32 weight rows (two A operands of
+// One workgroup = 8 wavefronts = one (expert, tile of 128 rows of w1 and w3 or 256 of w2, chunk of up to 256 activation rows,
+// contraction split), one workgroup per compute unit; or 4 wavefronts, half the weight rows, half of LDS, chunks of up to 128
+// rows, two per compute unit.  Two wavefronts per SIMD either way.  A wavefront multiplies 32 weight rows (two A operands of
 // v_mfma_f32_16x16x32_f16) with all rows of the chunk.  The contraction goes in stages of 64 columns = one quantization group =
 // two sub-steps of 32.  What a stage needs lies in LDS rings filled by global-to-LDS transfers, several stages ahead and
 // without registers: activations [rows][128 bytes], brought by all wavefronts together; weights as they are stored, scales and
