@@ -680,15 +680,17 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //      of 2048 x 1408, 4-bit 112 -> 105; 80 rows 367, 368, half 16-bit of 2048 x 5632 214, 220; 100 rows 405, 413).
 //      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64 and about half of the experts need two from
 //      some 52 on: 250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415, 16-bit 662 -> 557; 140 tokens 289, 290, 371 ->
-//      363, 552 -> 524; 200 tokens, 32 experts of 2048 x 1408, 4-bit 104 -> 98.5.  Quantized experts alone, long
-//      contractions and fewer rows stay there: 200 tokens, Mixtral shape, 4-bit 312, 321, 8-bit 373, 389.
+//      363, 552 -> 524; 200 tokens, 32 experts of 2048 x 1408, 4-bit 104 -> 98.5.  Without 16-bit experts,
+//      long contractions and fewer rows stay there (200 tokens, Mixtral shape, 4-bit 312, 321, 8-bit 373, 389; two experts of 40
+//      rows each 103, 103 and 121, 123.5), but not one expert alone (40 rows, 4-bit 100 -> 73, 8-bit 111 -> 69).
 int prefill_waves(const MfmaArgs& a, int ct, int columns) {
     if (ct < 4 || a.K % kKTile || (uintptr_t)a.in % 16 || (uint64_t)a.P * a.K * 2 + 8192 >= (1ull << 32)) return 0;
     const int E = a.direct_expert >= 0 ? 1 : a.E, rows = (a.P + E - 1) / E;
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
     const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
-    if (ct == 4) return any16 || rows <= 32 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
-    return rows <= 76 || columns * E * ((rows + 127) / 128) <= (int)kComputeUnits ? 4 : 8;
+    const bool few = columns * E * ((rows + 127) / 128) <= (int)kComputeUnits;
+    if (ct == 4) return any16 || (few && E == 1) || rows <= 32 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
+    return few || rows <= 76 ? 4 : 8;
 }
 
 // Most rows of a 4-bit or 8-bit expert's chunks in ffn_prefill.hip, 0: 128 and no even split (also where that kernel is not
