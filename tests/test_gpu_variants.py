@@ -520,3 +520,10 @@ def test_prefill_tokens_off_16_byte_boundaries(orc, shift):
     ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2)
     assert np.array_equal(idx.cpu().numpy(), ref_idx)
     assert_ffn_close(out.cpu().numpy(), ref, cfg.name)
+
+
+# Rows per expert on either side of the lines between launches (13, 16, 27, 32, 50, 68, 80 on average): chunks of one and two
+# tiles, workgroups of 4 and of 8 wavefronts; loads spread about their mean, a skewed one; two steps up, 33 down.
+@pytest.mark.parametrize("T,zipf", [(52, None), (64, None), (108, None), (128, None), (200, None), (272, None), (320, None), (320, 1.2)])
+def test_block_at_the_lines_between_launches(orc, T, zipf):
+    _check_block(orc, common.Config(f"lines_{T}", 256, 4224, 8, 2, T, (0, 3, 6), zipf=zipf, int8_experts=(1, 4)))
