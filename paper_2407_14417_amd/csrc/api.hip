@@ -73,6 +73,14 @@ MfmaPlan plan_for(const moe_layer* L, int rows) {
     return plan_mfma(rows, L->d_model, L->d_ff, L->n_experts, L->top_k == L->n_experts);
 }
 
+// All n rows belong to one expert.  Few rows: the contraction of the down-projection is split over as many workgroups as the
+// workspace's partial-result region was sized for, and the partials are added in order.
+MfmaPlan lone_plan(const moe_layer* L, int n, const Workspace& w) {
+    MfmaPlan p = plan_mfma(n, L->d_model, L->d_ff, 1, true);
+    p.down_splits = p.down_splits < w.y_splits ? p.down_splits : w.y_splits;
+    return p;
+}
+
 int y_splits_for(const moe_layer* L, int T) {
     if (!use_mfma(L, T * L->top_k)) return 1;
     return plan_for(L, T * L->top_k).down_splits;
@@ -107,7 +115,7 @@ int check_ws(const moe_layer* L, int T, void* ws, size_t ws_bytes, Workspace* ou
     *out = carve_workspace(ws, T, L->d_model, L->d_ff, L->n_experts, L->top_k, splits);
     // (at these widths every workspace that holds the unsplit call has always been enough)
     while (out->bytes > ws_bytes && splits > 1 && half_step_width(L->d_model, L->d_ff)) {
-        splits = fewer_splits(L->d_ff, splits);
+        splits = fewer_splits(L->d_ff, splits, T * L->top_k);
         *out = carve_workspace(ws, T, L->d_model, L->d_ff, L->n_experts, L->top_k, splits);
     }
     if (ws_bytes < out->bytes)
@@ -248,15 +256,12 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
         launch_decode_up(table, w.idx, (const half_t*)x_rows, d, f, 1, w.h, w.status, kDecodeUpBlocks, st);
         launch_decode_down(table, w.idx, w.gate, w.h, d, f, 1, nullptr, nullptr, w.status, st, y);
     } else if (use_mfma(layer, n)) {
-        MfmaPlan p = plan_mfma(n, d, f, 1, true); // all n rows belong to the one expert
+        const MfmaPlan p = lone_plan(layer, n, w);
         launch_ffn_up_mfma(table, layer->n_experts, rows, n, (const half_t*)x_rows, d, f, w.h, p.ct, w.status, st);
-        // few rows: the contraction of the down-projection is split over as many workgroups as the workspace's
-        // partial-result region was sized for, and the partials are added in order
-        const int splits = p.down_splits < w.y_splits ? p.down_splits : w.y_splits;
-        if (splits > 1) {
+        if (p.down_splits > 1) {
             const size_t stride = (size_t)n * d;
-            launch_ffn_down_mfma(table, layer->n_experts, rows, n, w.h, d, f, w.y, p.ct, splits, stride, w.status, st);
-            launch_reduce_splits(w.y, splits, stride, stride, y, st);
+            launch_ffn_down_mfma(table, layer->n_experts, rows, n, w.h, d, f, w.y, p.ct, p.down_splits, stride, w.status, st);
+            launch_reduce_splits(w.y, p.down_splits, stride, stride, y, st);
         } else {
             launch_ffn_down_mfma(table, layer->n_experts, rows, n, w.h, d, f, y, p.ct, 1, 0, w.status, st);
         }
@@ -265,6 +270,25 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
         launch_ffn_down(table, layer->n_experts, rows, w.h, d, f, y, w.status, st);
     }
     return check_hip(st);
+}
+
+// For the tests, host-only: the launches on the matrix cores that moe_layer_forward (expert < 0, n tokens) or
+// moe_expert_ffn_mixed (n rows) would make with a workspace of ws_bytes.  MOE_ESHAPE if it would make none.
+int moemix_launch_form(const moe_layer* layer, int expert, const void* x, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down) {
+    if (int rc = check_layer(layer)) return rc;
+    const int k = layer->top_k, E = layer->n_experts, d = layer->d_model, f = layer->d_ff;
+    const bool alone = expert >= 0;
+    const int T = alone ? (n + k - 1) / k : n, P = alone ? n : n * k;
+    Workspace w;
+    if (int rc = check_ws(layer, T, (void*)256, ws_bytes, &w)) return rc;
+    if (use_decode(n) || !use_mfma(layer, P)) return fail(MOE_ESHAPE, "moemix_launch_form: not on the matrix cores");
+    const DevExperts table = device_table(layer);
+    const RowMap rows{nullptr, nullptr, k, alone ? expert : -1, alone ? n : 0};
+    MfmaPlan p = alone ? lone_plan(layer, n, w) : plan_for(layer, P);
+    if (!alone) p.down_splits = w.y_splits;
+    *up = up_form(table, E, rows, P, (const half_t*)x, d, f, p.ct);
+    *down = down_form(table, E, rows, P, d, f, p.ct, p.down_splits);
+    return MOE_OK;
 }
 
 int moe_layer_forward(const moe_layer* layer, const void* x, int T, void* out, int32_t* topk_idx_out,

@@ -636,12 +636,12 @@ bool one_step_per_stage(const MfmaArgs& a, dim3 grid) {
 }
 
 template <bool UP, bool WIDE, bool HALF>
-void launch_ct_w(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
-    switch (ct) {
+void launch_ct_w(const MfmaArgs& a, const LaunchForm& form, dim3 grid, hipStream_t st) {
+    switch (form.ct) {
         case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
         case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
         case 4:
-            if (!HALF && one_step_per_stage(a, grid)) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
+            if (!HALF && form.steps_per_stage == 1) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
             else launch_one<UP, 4, WIDE, HALF>(a, grid, st);
             break;
         default: launch_one<UP, 8, true, true>(a, grid, st); break;
@@ -730,12 +730,30 @@ int chunk_slots(const RowMap& rows, const MfmaArgs& a, int P, int ct) {
     return std::min(P, P / (a.quant_rows ? a.quant_rows : mc) + a.E);
 }
 
+struct Launch {
+    MfmaArgs a;
+    LaunchForm form;
+    dim3 grid;
+};
+
+LaunchForm form_of(const MfmaArgs& a, int ct, dim3 grid, int splits) {
+    LaunchForm m;
+    m.waves = a.waves;
+    m.ct = ct;
+    m.quant_rows = a.quant_rows;
+    m.half = !a.waves && (a.K % kKTile || ct == 8);
+    m.steps_per_stage = a.waves ? 0 : ct == 4 && !m.half && one_step_per_stage(a, grid) ? 1 : spb_for(ct);
+    m.splits = splits;
+    m.steps_per_split = a.k_per_split / kKTile;
+    return m;
+}
+
 template <bool UP>
-void launch_ct(const MfmaArgs& a, int ct, dim3 grid, hipStream_t st) {
-    if (a.waves) launch_prefill<UP>(a, grid, st);
-    else if (a.K % kKTile || ct == 8) launch_ct_w<UP, true, true>(a, ct, grid, st);
-    else if (any_int8(a.ex, a.E)) launch_ct_w<UP, true, false>(a, ct, grid, st);
-    else launch_ct_w<UP, false, false>(a, ct, grid, st);
+void launch_ct(const Launch& l, hipStream_t st) {
+    if (l.form.waves) launch_prefill<UP>(l.a, l.grid, st);
+    else if (l.form.half) launch_ct_w<UP, true, true>(l.a, l.form, l.grid, st);
+    else if (any_int8(l.a.ex, l.a.E)) launch_ct_w<UP, true, false>(l.a, l.form, l.grid, st);
+    else launch_ct_w<UP, false, false>(l.a, l.form, l.grid, st);
 }
 
 // Splits of a contraction of `f` columns into ranges of whole steps, all of one length but the last, which may be shorter.
@@ -767,7 +785,8 @@ bool mfma_rows_ok(int rows, int d, int f) {
 // unsplit, 27.4 here; 320 x 9280 49.6, 79.7, 24.5; 704 x 2432 30.9, 35.1, 23.9).  Every pair counts as a chunk there, up to the number
 // of experts: with the splits of one chunk, 10 pairs over 32 experts of 2880 x 2880, 4-bit, took 83 us, unsplit 59, with
 // those of ten 57.
-constexpr int kUnevenPairs = 16;   // (no more than a launch of 16-row chunks has)
+// (No more than a launch of 16-row chunks has: of the launches of whole steps only those look at where a range ends.)
+constexpr int kUnevenPairs = 16;
 
 MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
     MfmaPlan p;
@@ -799,20 +818,22 @@ MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
     // 4-bit 266 -> 260, 8-bit 357 -> 348, 16-bit 581 -> 505; 126 tokens 287 -> 268, 380 -> 352, 629 -> 507; 8 experts of 1024 x 2816
     // 46.1, 51.3 and 47.6, 48.8).
     if (p.ct == 2 && !even && avg > 26 && (f + 63) / 64 * E > 512 && !half_step_width(d, f)) p.ct = 4;
-    if (p.ct == 1 && !even && avg > ((f + 63) / 64 * E <= 512 ? 14 : 12)) p.ct = 2;
+    if (p.ct == 1 && !even && P > kUnevenPairs && avg > ((f + 63) / 64 * E <= 512 ? 14 : 12)) p.ct = 2;
     return p;
 }
 
-int fewer_splits(int f, int splits) {
+int fewer_splits(int f, int splits, int P) {
+    const int steps = contraction_steps(f);
     do --splits;
-    while (splits > 1 && !splits_ok(contraction_steps(f), splits));
+    while (splits > 1 && !(splits_ok(steps, splits) && (steps % splits == 0 || P <= kUnevenPairs)));
     return splits;
 }
 
-void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
-                        int ct, int32_t* status, hipStream_t st) {
-    TraceScope trace(kKernelUp, st);
-    MfmaArgs a;
+namespace {
+Launch up_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h, int ct,
+                 int32_t* status) {
+    Launch l;
+    MfmaArgs& a = l.a;
     a.ex = ex; a.offsets = rows.offsets; a.perm = rows.perm; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
     a.idx = rows.idx; a.P = P;
@@ -824,17 +845,30 @@ void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, 
     const int up_rows = a.waves ? 16 * a.waves : 32 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (f + up_rows - 1) / up_rows;
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles);
-    dim3 grid(a.tiles, chunk_slots(rows, a, P, ct), 1);
-    launch_ct<true>(a, ct, grid, st);
+    l.grid = dim3(a.tiles, chunk_slots(rows, a, P, ct), 1);
+    l.form = form_of(a, ct, l.grid, 1);
+    return l;
+}
+}  // namespace
+
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, int ct) {
+    return up_launch(ex, E, rows, P, x, d, f, nullptr, ct, nullptr).form;
+}
+
+void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
+                        int ct, int32_t* status, hipStream_t st) {
+    TraceScope trace(kKernelUp, st);
+    launch_ct<true>(up_launch(ex, E, rows, P, x, d, f, h, ct, status), st);
 }
 
 #endif
 #if !defined(MOEMIX_MFMA_UP)
 
-void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,
-                          int ct, int splits, size_t split_stride, int32_t* status, hipStream_t st) {
-    TraceScope trace(kKernelDown, st);
-    MfmaArgs a;
+namespace {
+Launch down_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y, int ct,
+                   int splits, size_t split_stride, int32_t* status) {
+    Launch l;
+    MfmaArgs& a = l.a;
     a.ex = ex; a.offsets = rows.offsets; a.perm = nullptr; a.top_k = rows.top_k;
     a.direct_expert = rows.direct_expert; a.direct_n = rows.direct_n;
     a.idx = rows.idx; a.P = P;
@@ -847,8 +881,20 @@ void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P
     const int down_rows = a.waves ? 32 * a.waves : 64 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (d + down_rows - 1) / down_rows;
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles * splits);
-    dim3 grid(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
-    launch_ct<false>(a, ct, grid, st);
+    l.grid = dim3(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
+    l.form = form_of(a, ct, l.grid, splits);
+    return l;
+}
+}  // namespace
+
+LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits) {
+    return down_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, splits, 0, nullptr).form;
+}
+
+void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,
+                          int ct, int splits, size_t split_stride, int32_t* status, hipStream_t st) {
+    TraceScope trace(kKernelDown, st);
+    launch_ct<false>(down_launch(ex, E, rows, P, h, d, f, y, ct, splits, split_stride, status), st);
 }
 
 #endif

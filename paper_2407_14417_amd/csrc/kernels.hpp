@@ -47,7 +47,8 @@ void launch_ffn_down(const DevExperts& ex, int E, const RowMap& rows, const half
 // chunk (1, 2, 4 or 8); the down-projection splits the contraction `splits` ways and writes one partial
 // y per split (`split_stride` elements apart), which launch_combine adds up.
 // Widths of odd multiples of 64 (half_step_width) take fewer splits where the workspace at hand has no room for the
-// plan's: fewer_splits gives the next smaller number that divides the contraction evenly.
+// plan's: fewer_splits gives the next smaller number that divides the contraction evenly (any that leaves ranges of two
+// steps where the P pairs are few enough for the plan to have such).
 struct MfmaPlan {
     int ct;
     int down_splits;
@@ -57,11 +58,23 @@ bool mfma_rows_ok(int rows, int d, int f);
 // `even`: every expert gets the same number of the P pairs.
 MfmaPlan plan_mfma(int P, int d, int f, int E, bool even);
 inline bool half_step_width(int d, int f) { return (d | f) % 128 != 0; }
-int fewer_splits(int f, int splits);
+int fewer_splits(int f, int splits, int P);
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
                         int ct, int32_t* status, hipStream_t st);
 void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,
                           int ct, int splits, size_t split_stride, int32_t* status, hipStream_t st);
+// How such a launch runs (asked for by the tests: moemix_launch_form in api.hip).
+struct LaunchForm {
+    int waves;             // ffn_prefill.hip: wavefronts per workgroup; 0: grouped_mfma_kernel
+    int ct;                // 16-row activation tiles per chunk of the plan
+    int quant_rows;        // ffn_prefill.hip, 8 wavefronts: most rows of a quantized expert's chunks, 0: 128
+    int steps_per_stage;   // grouped_mfma_kernel: 128-column steps per LDS stage
+    int half;              // ... the variant that takes contractions of any multiple of 64 and ranges of unequal length
+    int splits;            // ranges of the contraction
+    int steps_per_split;   // 128-column steps of each, the last one may have fewer where `half` or ct == 1
+};
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, int ct);
+LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits);
 
 // Batch-1 decode path (one token): shapes it covers, and its two kernels.
 bool decode_shape_ok(int d, int f);

@@ -4,6 +4,7 @@ HIP path; builders that need quantized experts use the oracle's quantizer."""
 from __future__ import annotations
 
 import bisect
+import ctypes
 from dataclasses import dataclass, field
 from fractions import Fraction
 from typing import List, Optional
@@ -177,6 +178,28 @@ def unsplit_workspace_bytes(d: int, f: int, E: int, k: int, T: int) -> int:
     P = T * k
     parts = [256, 4 * P, 4 * P, 4 * E, 4 * (E + 1), 4 * P, 4 * P, 256, 2 * T * d, 2 * P * f, 4 * P * d]
     return sum((n + 255) // 256 * 256 for n in parts)
+
+
+class LaunchForm(ctypes.Structure):
+    """How the library runs a launch of grouped products (csrc/kernels.hpp)."""
+    _fields_ = [(n, ctypes.c_int) for n in ("waves", "ct", "quant_rows", "steps_per_stage", "half", "splits", "steps_per_split")]
+
+
+def launch_forms(precs, d: int, f: int, k: int, n: int, expert: int = -1, ws_bytes: int = 1 << 40, x: int = 256):
+    """(up, down) as the library itself says: a block of n tokens over experts of the given precision codes, or one of
+    them alone with n rows, its tokens at address x.  Host only; nothing is launched."""
+    from paper_2407_14417_amd import binding as mm
+    experts = (mm.CExpert * len(precs))()
+    for e, prec in zip(experts, precs):
+        e.prec, e.resident = prec, 1
+        for m in (e.w1, e.w3, e.w2):
+            m.data = m.scale = m.zero = 4096
+    layer = mm.CLayer(d, f, len(precs), k, 4096, None, experts)
+    up, down = LaunchForm(), LaunchForm()
+    fn = mm.lib().moemix_launch_form
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    assert fn(ctypes.byref(layer), expert, x, n, ws_bytes, ctypes.byref(up), ctypes.byref(down)) == 0, mm.lib().moe_last_error()
+    return up, down
 
 
 @dataclass

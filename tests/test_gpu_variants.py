@@ -208,6 +208,35 @@ def test_static_scratch_at_its_limit_odd_multiples_of_64(orc):
     assert refused.value.code == mm.MOE_EWORKSPACE
 
 
+# Contractions of whole steps beside a d_model of an odd multiple of 64, a workspace for fewer splits than the plan has: the
+# ranges keep one length (20 rows alone and 40 tokens in chunks of up to 32 rows, the rest in prefill launches), an infinity at
+# the start of a row of w2 stays in its output.
+@pytest.mark.parametrize("T", [10, 40, 95])
+def test_smaller_workspace_whole_steps(orc, T):
+    d, f = 832, 2816
+    cfg = common.Config(f"fewer_{T}", d, f, 4, 2, T, (0, 2), int8_experts=(1,))
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    least, full = common.unsplit_workspace_bytes(d, f, 4, 2, T), mm.workspace_bytes(layer, T)
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2)
+    rows = np.concatenate([wl.x, wl.x])
+    alone = [orc.expert_ffn(e, rows) for e in wl.experts]
+    for n in sorted({least, full, *(least + s * 8 * T * d for s in (1, 2, 3, 5) if least + s * 8 * T * d < full)}):
+        room = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        out, idx, _ = _run_block(layer, wl.x, 2, room[:n])
+        assert np.array_equal(idx, ref_idx)
+        assert_ffn_close(out, ref, f"{cfg.name} ws={n}")
+        for e in range(4):
+            y = torch.full((2 * T, d), float("nan"), dtype=torch.float32, device="cuda")
+            mm.moe_expert_ffn_mixed(layer, e, dev(rows), y, room[:n])
+            assert_ffn_close(y.cpu().numpy(), alone[e], f"{cfg.name} expert {e} ws={n}")
+        layer.experts[3].w2.data[7, 0] = float("inf")
+        mm.moe_expert_ffn_mixed(layer, 3, dev(rows), y, room[:n])
+        layer.experts[3].w2.data[7, 0] = float(wl.experts[3].w2.data[7, 0])
+        assert not torch.isfinite(y[:, 7]).any() and torch.isfinite(y[:, torch.arange(d, device="cuda") != 7]).all()
+        assert bool((room[n:] == 0xFF).all())
+
+
 # Up to 16 pairs: ranges of unequal length where the number of steps has no divisor (17, 19, 23, 67 steps, with and without
 # half a step at the end, the last range of two and three steps), the same with a workspace for fewer splits and through
 # one expert alone.
