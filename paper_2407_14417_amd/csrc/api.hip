@@ -81,6 +81,15 @@ MfmaPlan lone_plan(const moe_layer* L, int n, const Workspace& w) {
     return p;
 }
 
+// The launches of ffn_prefill.hip bring tokens into LDS 16 bytes at a time, from 16-byte boundaries; all other kernels read
+// them from anywhere.  Tokens that lie elsewhere are copied for those launches: by the gating kernel, which holds the rows
+// anyway, or (one expert alone) into the room of the partial results, which the down-projection writes afterwards.  (Mixtral
+// shape, tokens 8 bytes past a boundary, without and with the copy: 300 tokens, 4-bit 482 -> 374 us, on one 378; 1000 tokens, 8-bit
+// 1025 -> 814, 814; one expert, 40 rows, 4-bit 71 -> 61, 61.)
+bool copies_tokens(const DevExperts& table, int E, const RowMap& rows, int P, const half_t* x, int d, int f, int ct) {
+    return (uintptr_t)x % 16 && up_form(table, E, rows, P, d, f, ct).waves;
+}
+
 int y_splits_for(const moe_layer* L, int T) {
     if (!use_mfma(L, T * L->top_k)) return 1;
     return plan_for(L, T * L->top_k).down_splits;
@@ -139,13 +148,14 @@ int layer_body(const moe_layer* L, const DevExperts& table, const half_t* x, int
         launch_decode_down(table, w.idx, w.gate, w.h, d, f, k, residual, out, w.status, st);
         return check_hip(st);
     }
-    launch_route(x, (const half_t*)L->w_gate, L->gate_bias, T, d, E, k, w.idx, w.gate, idx_out, gate_out,
-                 reset_status ? w.status : nullptr, st, rms_gain, eps, w.xn);
-    if (rms_gain) x = w.xn;
     const size_t split_stride = (size_t)T * k * d;
     const bool mfma = use_mfma(L, T * k);
     MfmaPlan p{1, 1};
     if (mfma) p = plan_for(L, T * k);
+    const bool to_xn = rms_gain || (mfma && copies_tokens(table, E, RowMap{w.offsets, w.perm, k, -1, 0}, T * k, x, d, f, p.ct));
+    launch_route(x, (const half_t*)L->w_gate, L->gate_bias, T, d, E, k, w.idx, w.gate, idx_out, gate_out,
+                 reset_status ? w.status : nullptr, st, rms_gain, eps, to_xn ? w.xn : nullptr);
+    if (to_xn) x = w.xn;
     // few pairs: no launch for the grouping, unless that is the kernel the caller wants to measure
     const bool inline_groups = mfma && group_inline_ok(T * k, p.ct) && !trace_armed(kKernelPermute);
     if (!inline_groups) launch_permute(w.idx, T * k, E, w.counts, w.offsets, w.perm, w.inv, w.status, st);
@@ -257,7 +267,12 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
         launch_decode_down(table, w.idx, w.gate, w.h, d, f, 1, nullptr, nullptr, w.status, st, y);
     } else if (use_mfma(layer, n)) {
         const MfmaPlan p = lone_plan(layer, n, w);
-        launch_ffn_up_mfma(table, layer->n_experts, rows, n, (const half_t*)x_rows, d, f, w.h, p.ct, w.status, st);
+        const half_t* x = (const half_t*)x_rows;
+        if (copies_tokens(table, layer->n_experts, rows, n, x, d, f, p.ct)) {
+            launch_copy_halves(x, (size_t)n * d, (half_t*)w.y, st);
+            x = (const half_t*)w.y;
+        }
+        launch_ffn_up_mfma(table, layer->n_experts, rows, n, x, d, f, w.h, p.ct, w.status, st);
         if (p.down_splits > 1) {
             const size_t stride = (size_t)n * d;
             launch_ffn_down_mfma(table, layer->n_experts, rows, n, w.h, d, f, w.y, p.ct, p.down_splits, stride, w.status, st);
@@ -274,7 +289,7 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
 
 // For the tests, host-only: the launches on the matrix cores that moe_layer_forward (expert < 0, n tokens) or
 // moe_expert_ffn_mixed (n rows) would make with a workspace of ws_bytes.  MOE_ESHAPE if it would make none.
-int moemix_launch_form(const moe_layer* layer, int expert, const void* x, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down) {
+int moemix_launch_form(const moe_layer* layer, int expert, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down) {
     if (int rc = check_layer(layer)) return rc;
     const int k = layer->top_k, E = layer->n_experts, d = layer->d_model, f = layer->d_ff;
     const bool alone = expert >= 0;
@@ -286,7 +301,7 @@ int moemix_launch_form(const moe_layer* layer, int expert, const void* x, int n,
     const RowMap rows{nullptr, nullptr, k, alone ? expert : -1, alone ? n : 0};
     MfmaPlan p = alone ? lone_plan(layer, n, w) : plan_for(layer, P);
     if (!alone) p.down_splits = w.y_splits;
-    *up = up_form(table, E, rows, P, (const half_t*)x, d, f, p.ct);
+    *up = up_form(table, E, rows, P, d, f, p.ct);
     *down = down_form(table, E, rows, P, d, f, p.ct, p.down_splits);
     return MOE_OK;
 }
@@ -451,8 +466,11 @@ int moe_layer_forward_swap(const moe_layer* layer, const moe_swap* swap, const v
     const half_t* xin = (const half_t*)x;
 
     // gating, then the one host round trip of this path: which experts were chosen?
+    const bool to_xn = !use_decode(T) && use_mfma(layer, T * k) &&
+                       copies_tokens(device_table(layer), E, RowMap{w.offsets, w.perm, k, -1, 0}, T * k, xin, d, f, plan_for(layer, T * k).ct);
     launch_route(xin, (const half_t*)layer->w_gate, layer->gate_bias, T, d, E, k, w.idx, w.gate, topk_idx_out, topk_gate_out,
-                 w.status, st);
+                 w.status, st, nullptr, 0.0f, to_xn ? w.xn : nullptr);
+    if (to_xn) xin = w.xn;
     hipError_t e = hipMemcpyAsync(swap->host_idx, w.idx, (size_t)T * k * sizeof(int32_t), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(MOE_EHIP, "HIP: %s", hipGetErrorString(e));

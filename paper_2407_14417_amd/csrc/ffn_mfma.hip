@@ -461,7 +461,8 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
 // kernel's register count is that of its largest body, so blocks without 8-bit experts get a kernel without it
 // (and keep four wavefronts per SIMD at few rows per expert).  In the wide kernel tile_body has variants for 1, 2, 4 and 8
 // tiles only.
-// HALF: contraction lengths that are odd multiples of 64 (and 128-row chunks that ffn_prefill.hip does not take), all precisions.  (A wavefront per weight row
+// HALF: contraction lengths that are odd multiples of 64 (and 128-row chunks whose rows end too close to the reach of 32-bit
+// offsets for ffn_prefill.hip), all precisions.  (A wavefront per weight row
 // with scalar products, which is what such widths had, took 296 + 190 us for 33 tokens, 4 of 32 experts, d_model and
 // d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
 // a time and 4-bit rows whose 128-byte requests straddle two lines.)
@@ -669,8 +670,8 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 }
 
 // Wavefronts per workgroup of ffn_prefill.hip for a launch of plan `ct` with `columns` tiles of 128 (down: 256) weight rows and
-// splits, 0: not for that kernel.  It takes contractions of whole steps, input rows that start on 16-byte boundaries (its
-// transfers into LDS are of 16 bytes; tokens may lie anywhere) and end a little before the reach of a 32-bit byte offset.
+// splits, 0: not for that kernel.  It takes contractions of whole steps and input rows that end a little before the reach of a
+// 32-bit byte offset (and that start on 16-byte boundaries, which the callers see to: copies_tokens in api.hip).
 //   8: chunks of up to 256 rows, one workgroup per compute unit.
 //   4: chunks of up to 128 rows, two workgroups per compute unit with half the weight rows each: they hide each other's
 //      beginning and end, and there are more of them; activations go into LDS twice.  Where 8 wavefronts would not give every
@@ -684,7 +685,7 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //      long contractions and fewer rows stay there (200 tokens, Mixtral shape, 4-bit 312, 321, 8-bit 373, 389; two experts of 40
 //      rows each 103, 103 and 121, 123.5), but not one expert alone (40 rows, 4-bit 100 -> 73, 8-bit 111 -> 69).
 int prefill_waves(const MfmaArgs& a, int ct, int columns) {
-    if (ct < 4 || a.K % kKTile || (uintptr_t)a.in % 16 || (uint64_t)a.P * a.K * 2 + 8192 >= (1ull << 32)) return 0;
+    if (ct < 4 || a.K % kKTile || (uint64_t)a.P * a.K * 2 + 8192 >= (1ull << 32)) return 0;
     const int E = a.direct_expert >= 0 ? 1 : a.E, rows = (a.P + E - 1) / E;
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
     const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
@@ -851,8 +852,8 @@ Launch up_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const h
 }
 }  // namespace
 
-LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, int ct) {
-    return up_launch(ex, E, rows, P, x, d, f, nullptr, ct, nullptr).form;
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct) {
+    return up_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, nullptr).form;
 }
 
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,

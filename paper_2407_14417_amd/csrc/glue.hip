@@ -114,6 +114,17 @@ void launch_reduce_splits(const float* y, int splits, size_t split_stride, size_
     reduce_splits_kernel<<<blocks, 256, 0, st>>>(y, splits, split_stride, n4, dst);
 }
 
+typedef uint4_t __attribute__((aligned(2))) uint4_half_aligned_t;
+__global__ __launch_bounds__(256) void copy_halves_kernel(const half_t* __restrict__ src, size_t n8, half_t* __restrict__ dst) {
+    for (size_t i = blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256)
+        ((uint4_t*)dst)[i] = ((const uint4_half_aligned_t*)src)[i];
+}
+
+void launch_copy_halves(const half_t* src, size_t n, half_t* dst, hipStream_t st) {
+    const size_t n8 = n / 8;
+    copy_halves_kernel<<<(int)((n8 + 255) / 256 < 2048 ? (n8 + 255) / 256 : 2048), 256, 0, st>>>(src, n8, dst);
+}
+
 // Fill kernel used instead of a memset node so that every launch sequence stays graph-capturable.
 __global__ void zero_words_kernel(int32_t* p, int n) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;

@@ -29,7 +29,7 @@ struct RowMap {
 constexpr int kInlinePairs = 256;
 inline bool group_inline_ok(int P, int ct) { return P <= kInlinePairs && ct <= 2; }
 
-// rms_gain != null: the gating input is RMSNorm(x) * rms_gain (fp16), which is also written to xn [T, d].
+// rms_gain != null: the gating input is RMSNorm(x) * rms_gain (fp16).  xn != null: the gating input is also written there [T, d].
 void launch_route(const half_t* x, const half_t* wg, const float* bias, int T, int d, int E, int k, int32_t* idx,
                   float* gate, int32_t* idx2, float* gate2, int32_t* status, hipStream_t st,
                   const half_t* rms_gain = nullptr, float eps = 0.0f, half_t* xn = nullptr);
@@ -59,6 +59,7 @@ bool mfma_rows_ok(int rows, int d, int f);
 MfmaPlan plan_mfma(int P, int d, int f, int E, bool even);
 inline bool half_step_width(int d, int f) { return (d | f) % 128 != 0; }
 int fewer_splits(int f, int splits, int P);
+// (x on a 16-byte boundary if up_form(..).waves)
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
                         int ct, int32_t* status, hipStream_t st);
 void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,
@@ -73,7 +74,7 @@ struct LaunchForm {
     int splits;            // ranges of the contraction
     int steps_per_split;   // 128-column steps of each, the last one may have fewer where `half` or ct == 1
 };
-LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, int ct);
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct);
 LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits);
 
 // Batch-1 decode path (one token): shapes it covers, and its two kernels.
@@ -116,6 +117,8 @@ void launch_combine(const float* y, int splits, size_t split_stride, const float
                     int k, const half_t* residual, half_t* out, hipStream_t st, const int32_t* idx = nullptr);
 // dst[i] = sum_p y[p][i] for i < n (n a multiple of 4), p over the `splits` partial results `split_stride` elements apart
 void launch_reduce_splits(const float* y, int splits, size_t split_stride, size_t n, float* dst, hipStream_t st);
+// dst[i] = src[i]; n a multiple of 8, dst on a 16-byte boundary, src anywhere
+void launch_copy_halves(const half_t* src, size_t n, half_t* dst, hipStream_t st);
 void launch_zero_words(int32_t* p, int n, hipStream_t st);
 
 void launch_dequant_int4(const DevMat& m, int out, int in, half_t* w, hipStream_t st);

@@ -27,12 +27,12 @@ __global__ __launch_bounds__(256) void route_kernel(const half_t* __restrict__ x
         // chained configuration: the block input is RMSNorm(x) * gain, rounded to fp16; it is written to xn for the
         // expert kernels and used for the logits in the same pass
         gate_rmsnorm<NCHUNK>(xv, rms_gain, d, eps, lane);
-        if (wave == 0) {
+    }
+    if (xn && wave == 0) {
 #pragma unroll
-            for (int j = 0; j < NCHUNK; ++j) {
-                const int c = (lane + 64 * j) * 8;
-                if (c < d) *(uint4_t*)(xn + (size_t)t * d + c) = xv[j];
-            }
+        for (int j = 0; j < NCHUNK; ++j) {
+            const int c = (lane + 64 * j) * 8;
+            if (c < d) *(uint4_t*)(xn + (size_t)t * d + c) = xv[j];
         }
     }
     constexpr int kAtOnce = NCHUNK <= 4 ? 4 : NCHUNK <= 8 ? 2 : 1;   // 64 registers of gate matrix rows

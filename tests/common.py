@@ -185,9 +185,9 @@ class LaunchForm(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("waves", "ct", "quant_rows", "steps_per_stage", "half", "splits", "steps_per_split")]
 
 
-def launch_forms(precs, d: int, f: int, k: int, n: int, expert: int = -1, ws_bytes: int = 1 << 40, x: int = 256):
+def launch_forms(precs, d: int, f: int, k: int, n: int, expert: int = -1, ws_bytes: int = 1 << 40):
     """(up, down) as the library itself says: a block of n tokens over experts of the given precision codes, or one of
-    them alone with n rows, its tokens at address x.  Host only; nothing is launched."""
+    them alone with n rows.  Host only; nothing is launched."""
     from paper_2407_14417_amd import binding as mm
     experts = (mm.CExpert * len(precs))()
     for e, prec in zip(experts, precs):
@@ -197,8 +197,8 @@ def launch_forms(precs, d: int, f: int, k: int, n: int, expert: int = -1, ws_byt
     layer = mm.CLayer(d, f, len(precs), k, 4096, None, experts)
     up, down = LaunchForm(), LaunchForm()
     fn = mm.lib().moemix_launch_form
-    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
-    assert fn(ctypes.byref(layer), expert, x, n, ws_bytes, ctypes.byref(up), ctypes.byref(down)) == 0, mm.lib().moe_last_error()
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    assert fn(ctypes.byref(layer), expert, n, ws_bytes, ctypes.byref(up), ctypes.byref(down)) == 0, mm.lib().moe_last_error()
     return up, down
 
 

@@ -534,7 +534,7 @@ def test_prefill_tiles_and_steps(orc, d, f, T):
 
 @pytest.mark.parametrize("shift", [1, 4])
 def test_prefill_tokens_off_16_byte_boundaries(orc, shift):
-    """Tokens may lie anywhere: those that no 16-byte transfer can fetch take the launch that loads them into registers."""
+    """Tokens may lie anywhere: those that no 16-byte transfer can fetch give the same result."""
     cfg = common.Config(f"prefill_shift{shift}", 512, 896, 3, 2, 150, (0,), int8_experts=(1,))
     wl = build_workload(cfg, orc)
     layer, n = device_layer(wl), cfg.T * cfg.d
@@ -549,6 +549,52 @@ def test_prefill_tokens_off_16_byte_boundaries(orc, shift):
     ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 2)
     assert np.array_equal(idx.cpu().numpy(), ref_idx)
     assert_ffn_close(out.cpu().numpy(), ref, cfg.name)
+
+
+# Where tokens lie decides neither the launch nor the order of its sums: blocks, the expert-miss path and one expert alone of
+# 33 to 64 rows, of more, and of few (which are read from where they are), tokens of eight steps (walked from different places).
+@pytest.mark.parametrize("T", [20, 60, 150, 400])
+@pytest.mark.parametrize("shift", [1, 2, 4, 7])
+def test_same_bits_wherever_tokens_lie(T, shift):
+    d, f, E = 1024, 4352, 3
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    draw = lambda shape, sigma: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(0.0, sigma, generator=gen)
+    experts, hosts = [], []
+    for bits in (16, 4, 8):
+        mats = []
+        for o, i in ((f, d), (f, d), (d, f)):
+            w = draw((o, i), 0.02)
+            if bits < 16:
+                codes = torch.empty((o, i * bits // 8), dtype=torch.uint8, device="cuda")
+                scale, zero = (torch.empty((o, i // 64), dtype=torch.float16, device="cuda") for _ in range(2))
+                (mm.moe_quantize_int4 if bits == 4 else mm.moe_quantize_int8)(w, codes, scale, zero)
+            mats.append(mm.Mat(w) if bits == 16 else mm.Mat(codes, scale, zero))
+        experts.append(mm.Expert({16: mm.PREC_FP16, 4: mm.PREC_INT4G64, 8: mm.PREC_INT8G64}[bits], *mats))
+    wg, x = draw((E, d), 0.02), draw((T, d), 1.0)
+    layer = mm.Layer(d, f, 2, wg, experts)
+    off = torch.empty(T * d + 8, dtype=torch.float16, device="cuda")[shift:shift + T * d].view(T, d)
+    off.copy_(x)
+    assert off.data_ptr() % 16 and not x.data_ptr() % 16
+
+    def block(tokens):
+        out, ws = torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda"), mm.alloc_workspace(layer, T)
+        mm.moe_layer_forward(layer, tokens, out, ws)
+        return out
+
+    assert torch.equal(block(x), block(off)) and bool(torch.isfinite(block(off)).all())
+    for e in range(E):
+        ws = mm.alloc_workspace(layer, (T + 1) // 2).fill_(0xFF)
+        a, b = (torch.full((T, d), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+        mm.moe_expert_ffn_mixed(layer, e, x, a, ws)
+        mm.moe_expert_ffn_mixed(layer, e, off, b, ws)
+        assert torch.equal(a, b) and bool(torch.isfinite(b).all()), e
+    pinned = [mm.Mat(*(None if t is None else t.cpu().pin_memory() for t in (m.data, m.scale, m.zero)))
+              for m in (experts[1].w1, experts[1].w3, experts[1].w2)]
+    part = mm.Layer(d, f, 2, wg, [experts[0], mm.Expert(mm.PREC_INT4G64, None, None, None, resident=False), experts[2]])
+    swap = mm.Swap(part, [None, mm.Expert(mm.PREC_INT4G64, *pinned, resident=False), None], 1, T)
+    out = torch.full((T, d), float("nan"), dtype=torch.float16, device="cuda")
+    assert mm.moe_layer_forward_swap(part, swap, off, out, mm.alloc_workspace(part, T)) == 1
+    assert torch.equal(out, block(x))
 
 
 # Rows per expert on either side of the lines between launches (13, 16, 27, 32, 50, 68, 80 on average): chunks of one and two
