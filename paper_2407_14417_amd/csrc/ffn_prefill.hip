@@ -36,15 +36,17 @@ constexpr int kLdsBytes = 163840;                          // of a compute unit
 // ---- device memory straight into LDS
 
 // 16 bytes per lane from p + v + OFFSET, lane l's to LDS byte lds + OFFSET + 16 l (the instruction's offset counts on both
-// sides; kBack makes up for it).  The wait state is the one that a write of M0 asks for.
+// sides; kBack makes up for it).  M0 is an operand of its own, so that the compiler knows what it holds; the wait state is the one
+// that a write of M0 asks for.  (A base from a lane read would ask for five: 1 % of a launch as s_nop 4; there is none, which a test
+// of the built code checks.)
 template <int OFFSET>
 __device__ __forceinline__ void bring(uint32_t lds, gptr_t p, uint32_t v) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds), "v"(v), "s"(p), "n"(OFFSET) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"{m0}"(lds), "v"(v), "s"(p), "n"(OFFSET) : "memory");
 }
 constexpr int kBack = 4096;   // base pointers point this far back, lane offsets are that much larger less OFFSET
 // 4 bytes per lane, lane l's to LDS byte lds + 4 l
 __device__ __forceinline__ void bring_words(uint32_t lds, gptr_t p, uint32_t v) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(v), "s"(p) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(lds), "v"(v), "s"(p) : "memory");
 }
 // At most COUNT of the wavefront's own transfers are under way, its LDS accesses are done; then all wavefronts meet.
 template <int COUNT>
