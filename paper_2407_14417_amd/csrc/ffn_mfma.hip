@@ -555,8 +555,8 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     // around: walking it in step, every workgroup of the launch would ask for the same columns of rows that lie a
     // power of two apart at the same time, which lands on a fraction of the memory channels (measured with a bare
     // read kernel of the same access pattern: 4.3 TB/s in step, 6.0 TB/s staggered).  The offset depends on the
-    // tile of weight rows, the expert and the split only, so a given output element is summed in the same order in
-    // every launch shape.
+    // tile of weight rows, the expert and the split only: an output element is summed in the same order in every launch
+    // with the same rows per tile and splits.
     // Up-projection: one starting place per tile.  Down-projection (rows 7 x 4 KB apart in the Mixtral shape, less
     // prone to the effect): one per expert and contraction split, so that the workgroups which share a slice of the
     // hidden rows walk it in step and find it in L2 (fetched bytes of the prefill down-projection: 1060 MB with one
