@@ -111,15 +111,14 @@ MEDIUM_ZIPF = Config("medium_zipf", 1024, 2816, 8, 2, 96, (2, 3, 4, 5, 6, 7), zi
 # f = 7 x 128) and a ragged last tile of 256 weight rows in the down-projection (640 = 2 x 256 + 128).
 ODD_STEPS = Config("odd_steps", 640, 896, 8, 2, 40, (0, 3, 4, 6))
 # Contraction ranges of a multiple of four 128-column steps in both projections (d = 8 steps, f = 16 steps, split
-# into ranges of 4 steps): what the pipelined matrix-core bodies for launches with 128-row chunks ask for.
+# into ranges of 4 steps), which are walked from different places; the zipf load runs in prefill launches of 4 wavefronts.
 STEPS4 = Config("steps4", 1024, 2048, 8, 2, 40, (1, 3, 4, 6))
 STEPS4_ZIPF = Config("steps4_zipf", 1024, 2048, 8, 2, 420, (2, 3, 4, 5, 6, 7), zipf=1.2)
-# The same with the 4-bit experts in front: experts 0 and 1 get 391 and 250 of the 840 rows, which run in chunks of 13,
-# 12 and 16 tiles (in launches of that many workgroups a 4-bit expert's chunks hold up to 256 rows, split evenly),
-# expert 2 in one of 7.
+# The same with the 4-bit experts in front and wide enough for 8 wavefronts: experts 0 and 1 get 391 and 250 of the 840 rows,
+# which run in chunks of 13, 12 and 16 tiles (chunks hold up to 256 rows there, split evenly), expert 2 in one of 7.
 STEPS4_ZIPF_Q = Config("steps4_zipf_4bit_heavy", 1024, 5120, 8, 2, 420, (0, 1, 2, 4, 5), zipf=1.2)
-# One 16-bit expert (250 rows, one chunk of 16 tiles) between 4-bit ones: its chunk is handed out before those of
-# expert 0 (the longest workgroups go first), so chunk index and expert order differ.
+# One 16-bit expert (250 rows) between 4-bit ones: its chunks are handed out before those of expert 0 (the longest
+# workgroups go first), so chunk index and expert order differ.
 STEPS4_ZIPF_MID = Config("steps4_zipf_16bit_second", 1024, 2048, 8, 2, 420, (0, 2, 3, 4, 5, 6, 7), zipf=1.2)
 # d below 256: served by the shape-agnostic kernels (more than one token).
 GENERIC = Config("generic", 192, 320, 4, 2, 9, (1, 2))

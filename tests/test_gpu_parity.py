@@ -10,8 +10,8 @@ from paper_2407_14417_amd import binding as mm
 from paper_2407_14417_amd import synth
 from tests import common
 from tests.common import (TINY, MEDIUM, MEDIUM_ZIPF, ODD_STEPS, GENERIC, STEPS4, STEPS4_ZIPF, STEPS4_ZIPF_Q, STEPS4_ZIPF_MID,
-                          build_workload, assert_ffn_close)
-from tests.gpu_common import dev, device_layer, device_mat
+                          build_workload, assert_ffn_close, launch_forms)
+from tests.gpu_common import dev, device_layer, device_mat, prec_of
 
 pytestmark = pytest.mark.gpu
 
@@ -207,11 +207,9 @@ def test_expert_ffn_odd_steps_ragged_tiles_many_chunks(orc, n):
 
 @pytest.mark.parametrize("n", [70, 90, 100, 128, 129, 148, 188, 200, 256, 257, 300, 400, 520])
 def test_expert_ffn_pipelined_bodies(orc, n):
-    """Matrix-core path, launches with 128-row chunks and ranges of a multiple of four steps: the pipelined bodies.
-    A 16-bit expert's chunks hold up to 256 rows, split evenly (70 .. 256 rows: one chunk of 5 .. 16 tiles; 257, 300,
-    400: two chunks; 520: three); a 4-bit expert alone, in a launch this small, runs in chunks of 128 rows (bodies for
-    2 .. 8 tiles: 148 = 128 + 20 rows, 188 = 128 + 60, 90, 200 = 128 + 72, ...; a last chunk of one tile runs the plain
-    body); its chunks of up to 256 rows are covered by test_layer_forward_4bit_chunks_of_more_than_8_tiles."""
+    """Matrix-core path, one 16-bit or 4-bit expert alone with more than 64 rows: chunks of up to 128 rows on workgroups of 4
+    wavefronts (launches this small), with full, ragged and one-tile last ones (148 = 128 + 20 rows, 188 = 128 + 60,
+    129 = 128 + 1, ...)."""
     cfg = STEPS4
     wl = build_workload(cfg, orc, experts_needed=(0, 1))
     assert not wl.experts[0].int4 and wl.experts[1].int4
@@ -219,6 +217,7 @@ def test_expert_ffn_pipelined_bodies(orc, n):
     x = synth.normal_f16((n, cfg.d), 1.0, 41, synth.x_stream(0))
     ws = mm.alloc_workspace(layer, (n + cfg.k - 1) // cfg.k)
     for e in (0, 1):
+        assert [m.waves for m in launch_forms([prec_of(x) for x in wl.experts[:2]], cfg.d, cfg.f, cfg.k, n, e)] == [4, 4]
         _say(f"expert_ffn cfg={cfg.name} n={n} expert={e}")
         y = torch.full((n, cfg.d), float("nan"), dtype=torch.float32, device="cuda")
         mm.moe_expert_ffn_mixed(layer, e, dev(x), y, ws)
@@ -302,11 +301,11 @@ def test_layer_forward(orc, cfg):
     assert_ffn_close(out, ref, cfg.name)
 
 
-@pytest.mark.parametrize("T,tiles", [(288, (9, 8, 11)), (320, (10, 9, 12)), (360, (11, 10, 14))])
+@pytest.mark.parametrize("T,tiles", [(288, (8, 8, 1, 8, 3)), (320, (10, 9, 12)), (360, (11, 10, 14))])
 def test_layer_forward_4bit_chunks_of_more_than_8_tiles(orc, T, tiles):
-    """The busiest 4-bit experts get between 129 and 384 rows: chunks of up to 256 rows, split evenly, on the two-unit
-    body (``tiles``: 16-row tiles of the chunks of experts 0 and 1, as the row counts asserted below imply).  With 40
-    workgroups per chunk in both projections the launches are past the size below which chunks keep to 128 rows."""
+    """The busiest 4-bit experts get between 129 and 384 rows: chunks of up to 256 rows, split evenly, on workgroups of 8
+    wavefronts (``tiles``: 16-row tiles of the chunks of experts 0 and 1, as the row counts asserted below imply); the
+    fewest tokens have 72 rows per expert, which run on workgroups of 4 in chunks of 128 rows and a rest."""
     cfg = common.Config(f"steps4_zipf_4bit_heavy_T{T}", 1024, 5120, 8, 2, T, STEPS4_ZIPF_Q.int4_experts, zipf=1.2)
     wl = build_workload(cfg, orc)
     _say(f"layer_forward cfg={cfg.name}")
@@ -315,9 +314,13 @@ def test_layer_forward_4bit_chunks_of_more_than_8_tiles(orc, T, tiles):
     counts = np.bincount(ref_idx.reshape(-1), minlength=cfg.E)
     _say(f"rows per expert: {counts.tolist()}")
 
+    forms = launch_forms([prec_of(e) for e in wl.experts], cfg.d, cfg.f, cfg.k, T)
+    assert [(m.waves, m.quant_rows) for m in forms] == [(4, 0) if T == 288 else (8, 256)] * 2
+
     def chunk_tiles(n):          # the library's rule for a 4-bit expert with more than 128 rows
         nch = -(-n // 256)
-        per = (-(-n // nch) + 15) // 16 * 16
+        per = (-(-n // nch) + 15) // 16 * 16 if T > 288 else 128
+        nch = -(-n // per)
         return tuple((min(per, n - i * per) + 15) // 16 for i in range(nch))
     assert chunk_tiles(int(counts[0])) + chunk_tiles(int(counts[1])) == tiles
     assert status == 0

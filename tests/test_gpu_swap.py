@@ -26,9 +26,8 @@ def _forward(layer, x, cfg):
     return out.cpu().numpy(), idx.cpu().numpy()
 
 
-# (STEPS4_ZIPF: launches with 128-row chunks; the 16-bit experts 0 and 1 hold most rows and run in chunks of up to
-# 256 rows on the pipelined bodies, whether they are resident or come through the swap space; STEPS4_ZIPF_Q: the same
-# for 4-bit experts in chunks of 12, 13 and 16 tiles)
+# (STEPS4_ZIPF: prefill launches of 4 wavefronts, most rows with the 16-bit experts 0 and 1, whether those are resident or come
+# through the swap space; STEPS4_ZIPF_Q: of 8 wavefronts, most rows with 4-bit experts, in chunks of 12, 13 and 16 tiles)
 @pytest.mark.parametrize("cfg", [TINY, MEDIUM, STEPS4_ZIPF, STEPS4_ZIPF_Q], ids=lambda c: c.name)
 @pytest.mark.parametrize("offloaded,n_slots", [((0, 3), 1), ((0, 3), 2), ((1, 2, 3), 2), ((0, 1, 2, 3), 4), ((), 1)])
 def test_swap_many_tokens_equals_all_resident_bit_for_bit(orc, cfg, offloaded, n_slots):

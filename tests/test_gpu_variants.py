@@ -8,7 +8,7 @@ import torch
 
 from paper_2407_14417_amd import binding as mm, synth
 from tests import common
-from tests.common import assert_ffn_close, build_workload
+from tests.common import assert_ffn_close, build_workload, launch_forms
 from tests.gpu_common import dev, device_layer
 
 pytestmark = pytest.mark.gpu
@@ -282,8 +282,7 @@ def test_half_step_keeps_neighbours_apart(orc, bits):
     assert np.array_equal(got[:, cols], clean[:, cols]) and not np.isfinite(got[:, 7]).any()
 
 
-# 8-bit experts in launches with 128-row chunks: every number of 16-row tiles the pipelined body has (2 .. 8 in one
-# unit, 9 .. 16 in two; a lone expert's chunks stay at 128 rows, so those come from blocks), ragged last tiles, the
+# One 8-bit expert alone with more than 64 rows, on workgroups of 4 wavefronts: chunks of up to 128 rows, ragged last tiles, the
 # one-tile rest, ranges of 8 steps (up) and of splits of 4 steps (down).
 @pytest.mark.parametrize("n", [70, 81, 96, 100, 128, 129, 150, 170, 185, 200, 225, 250, 257])
 def test_expert_ffn_8bit_pipelined_body(orc, n):
@@ -301,7 +300,8 @@ def test_expert_ffn_8bit_pipelined_body(orc, n):
 @pytest.mark.parametrize("T", [139, 150, 170, 185, 200, 215, 230, 256, 257])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_block_quantized_chunks_in_small_launches(orc, T, bits):
-    """Both experts take every token; 16 workgroups per chunk: chunks of up to 128 rows, split evenly (5 .. 8 tiles)."""
+    """Both experts take every token; few workgroups, of 4 wavefronts: chunks of 128 rows and a rest."""
+    assert [m.waves for m in launch_forms([mm.PREC_INT4G64 if bits == 4 else mm.PREC_INT8G64] * 2, 1024, 2048, 2, T)] == [4, 4]
     _check_block(orc, common.Config(f"steps4_{bits}bit_T{T}", 1024, 2048, 2, 2, T, (0, 1) if bits == 4 else (),
                                     int8_experts=(0, 1) if bits == 8 else ()))
 
@@ -329,6 +329,8 @@ def test_block_quantized_chunks_of_more_than_128_rows(d, f, T, rows, bits):
     with the dequantized ones."""
     splits = 11 if f == 11264 else 10
     assert _rows_per_chunk(T, 2, f // 128) == _rows_per_chunk(T, 2, d // 256 * splits) == rows
+    form = launch_forms([mm.PREC_INT4G64 if bits == 4 else mm.PREC_INT8G64] * 2, d, f, 2, T)
+    assert [(m.waves, m.quant_rows) for m in form] == [(8, rows)] * 2 and form[1].splits == splits
     gen = torch.Generator(device="cuda").manual_seed(T)
     draw = lambda shape, sigma: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(0.0, sigma, generator=gen)
     experts, dense = [], []
@@ -501,12 +503,15 @@ def test_chunks_handed_out_by_length(orc, E, k, T, bias, d, f):
     assert_ffn_close(out, ref, cfg.name)
 
 
-# 64-row chunks of blocks without 16-bit experts: one step per LDS stage (odd and even numbers of steps, ragged and full
-# chunks; two in the few workgroups of 1408 x 1536, one in the many of 1408 x 5632), the same bits as beside a 16-bit expert that no token reaches (two steps per stage).
+# 33 to 64 rows per expert, contractions of up to 24 steps: blocks without 16-bit experts run the launches that blocks with some
+# run (workgroups of 4 wavefronts), and give the same bits as beside a 16-bit expert that no token reaches.
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("d,f,T", [(640, 896, 140), (1024, 2048, 200), (384, 1536, 256), (1408, 1536, 140), (1408, 5632, 140)])
 def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
     every = tuple(range(8))
+    prec = mm.PREC_INT4G64 if bits == 4 else mm.PREC_INT8G64
+    for last in (prec, mm.PREC_FP16):
+        assert [(m.waves, m.ct) for m in launch_forms([prec] * 7 + [last], d, f, 2, T)] == [(4, 4)] * 2
     cfg = common.Config(f"rows64_{bits}_{d}_{T}", d, f, 8, 2, T, every if bits == 4 else (), int8_experts=every if bits == 8 else ())
     wl = build_workload(cfg, orc)
     wl.bias = np.array([0, 0, 0, 0, 0, 0, 0, -50.0], np.float32)
@@ -523,12 +528,13 @@ def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
 
 # ---------------------------------------------------------------- prefill launches
 
-# Every number of 16-row tiles of a chunk with its ragged last one, one-tile rests, tiles of weight rows that end past the
-# matrix, contractions from two steps (shorter than the LDS rings are deep) to eleven, several splits; every token reaches
-# an expert of each precision, and chunks of 16-bit experts hold up to 256 rows.
+# Workgroups of 4 wavefronts: chunks of 5 to 8 tiles with their ragged last one, rests of 1 to 8, tiles of weight rows that end
+# past the matrix, contractions from two steps (shorter than the LDS rings are deep) to eleven, several splits; every token
+# reaches an expert of each precision.  (8 wavefronts: test_gpu_prefill.py.)
 @pytest.mark.parametrize("T", [65, 80, 81, 97, 113, 127, 128, 129, 145, 161, 177, 193, 209, 225, 241, 256, 257])
 @pytest.mark.parametrize("d,f", [(256, 384), (640, 256), (384, 1408)])
 def test_prefill_tiles_and_steps(orc, d, f, T):
+    assert [m.waves for m in launch_forms([mm.PREC_INT4G64, mm.PREC_INT8G64, mm.PREC_FP16], d, f, 3, T)] == [4, 4]
     _check_block(orc, common.Config(f"prefill_{d}_{f}_{T}", d, f, 3, 3, T, (0,), int8_experts=(1,)))
 
 
