@@ -1,5 +1,7 @@
 // Gating network with top-k selection (paper §1, §2.1) and the grouping of (token, slot)
 // pairs by expert.
+#include <type_traits>
+
 #include "common.hpp"
 #include "gating.hpp"
 #include "kernels.hpp"
@@ -10,7 +12,9 @@ namespace moemix {
 // chunks L, L + 64, ...), normalises it when the block input is RMSNorm(x) * gain, and evaluates the experts
 // w, w + 4, ... of the gate matrix, each as one wavefront-wide dot product (gating.hpp), kAtOnce of them per trip to
 // memory; the first wavefront then selects the top_k and computes the softmax over the selected logits.
-template <int NCHUNK>
+// COPY: the token row goes to xn as it is.  (A kernel of its own: with the same line taken by all calls the one for 4096 columns
+// had 213 registers instead of 117, 1792 tokens, 32 experts of 2560 x 640, top-1, 104 -> 113 us a block.)
+template <int NCHUNK, bool COPY>
 __global__ __launch_bounds__(256) void route_kernel(const half_t* __restrict__ x, const half_t* __restrict__ wg,
                                                      const float* __restrict__ bias, int d, int E, int k,
                                                      int32_t* __restrict__ idx, float* __restrict__ gate,
@@ -23,17 +27,22 @@ __global__ __launch_bounds__(256) void route_kernel(const half_t* __restrict__ x
     if (t == 0 && tid == 0 && status) *status = 0;   // status word describes the call that starts here
     uint4_t xv[NCHUNK];
     gate_load_row<NCHUNK>(x + (size_t)t * d, d, lane, xv);
-    if (rms_gain) {
+    const auto write_row = [&] {
+        if (wave == 0) {
+#pragma unroll
+            for (int j = 0; j < NCHUNK; ++j) {
+                const int c = (lane + 64 * j) * 8;
+                if (c < d) *(uint4_t*)(xn + (size_t)t * d + c) = xv[j];
+            }
+        }
+    };
+    if (COPY) {
+        write_row();
+    } else if (rms_gain) {
         // chained configuration: the block input is RMSNorm(x) * gain, rounded to fp16; it is written to xn for the
         // expert kernels and used for the logits in the same pass
         gate_rmsnorm<NCHUNK>(xv, rms_gain, d, eps, lane);
-    }
-    if (xn && wave == 0) {
-#pragma unroll
-        for (int j = 0; j < NCHUNK; ++j) {
-            const int c = (lane + 64 * j) * 8;
-            if (c < d) *(uint4_t*)(xn + (size_t)t * d + c) = xv[j];
-        }
+        write_row();
     }
     constexpr int kAtOnce = NCHUNK <= 4 ? 4 : NCHUNK <= 8 ? 2 : 1;   // 64 registers of gate matrix rows
     for (int e = wave; e < E; e += 4 * kAtOnce) {
@@ -67,13 +76,18 @@ void launch_route(const half_t* x, const half_t* wg, const float* bias, int T, i
                   float* gate, int32_t* idx2, float* gate2, int32_t* status, hipStream_t st, const half_t* rms_gain,
                   float eps, half_t* xn) {
     TraceScope trace(kKernelRoute, st);
-    if (d <= 2048)
-        route_kernel<4><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status, rms_gain, eps, xn);
-    else if (d <= 4096)
-        route_kernel<8><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status, rms_gain, eps, xn);
-    else
-        route_kernel<kGateMaxChunks><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status, rms_gain, eps,
-                                                          xn);
+    const auto launch = [&](auto copy) {
+        constexpr bool COPY = decltype(copy)::value;
+        if (d <= 2048)
+            route_kernel<4, COPY><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status, rms_gain, eps, xn);
+        else if (d <= 4096)
+            route_kernel<8, COPY><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status, rms_gain, eps, xn);
+        else
+            route_kernel<kGateMaxChunks, COPY><<<T, 256, 0, st>>>(x, wg, bias, d, E, k, idx, gate, idx2, gate2, status,
+                                                                   rms_gain, eps, xn);
+    };
+    if (xn && !rms_gain) launch(std::true_type{});
+    else launch(std::false_type{});
 }
 
 // One workgroup of 16 wavefronts; wavefront w owns the w-th of 16 contiguous runs of pairs and walks it 64 at a time.
