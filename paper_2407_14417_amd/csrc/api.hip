@@ -70,13 +70,15 @@ bool use_mfma(const moe_layer* L, int rows) {
 }
 
 MfmaPlan plan_for(const moe_layer* L, int rows) {
-    return plan_mfma(rows, L->d_model, L->d_ff, L->n_experts, L->top_k == L->n_experts);
+    bool any16 = false;   // (resident or not: a call that runs some experts later takes the same launches)
+    for (int e = 0; e < L->n_experts; ++e) any16 |= L->experts[e].prec == MOE_PREC_FP16;
+    return plan_mfma(rows, L->d_model, L->d_ff, L->n_experts, L->top_k, any16);
 }
 
 // All n rows belong to one expert.  Few rows: the contraction of the down-projection is split over as many workgroups as the
 // workspace's partial-result region was sized for, and the partials are added in order.
 MfmaPlan lone_plan(const moe_layer* L, int n, const Workspace& w) {
-    MfmaPlan p = plan_mfma(n, L->d_model, L->d_ff, 1, true);
+    MfmaPlan p = plan_mfma(n, L->d_model, L->d_ff, 1, 1, false);
     p.down_splits = p.down_splits < w.y_splits ? p.down_splits : w.y_splits;
     return p;
 }
@@ -92,7 +94,8 @@ bool copies_tokens(const DevExperts& table, int E, const RowMap& rows, int P, co
 
 int y_splits_for(const moe_layer* L, int T) {
     if (!use_mfma(L, T * L->top_k)) return 1;
-    return plan_for(L, T * L->top_k).down_splits;
+    // (of the shape alone: the experts need not be known when a workspace is sized)
+    return plan_mfma(T * L->top_k, L->d_model, L->d_ff, L->n_experts, L->top_k, false).down_splits;
 }
 
 // Splits that moe_workspace_bytes asks for.  The one-token kernels write no partial results; the widths of whole steps ask

@@ -789,7 +789,7 @@ bool mfma_rows_ok(int rows, int d, int f) {
 // (No more than a launch of 16-row chunks has: of the launches of whole steps only those look at where a range ends.)
 constexpr int kUnevenPairs = 16;
 
-MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
+MfmaPlan plan_mfma(int P, int d, int f, int E, int k, bool any16) {
     MfmaPlan p;
     const int avg = (P + E - 1) / E;              // rows per expert if the load were even
     p.ct = avg <= 16 ? 1 : avg <= 32 ? 2 : avg <= 64 ? 4 : 8;
@@ -810,16 +810,22 @@ MfmaPlan plan_mfma(int P, int d, int f, int E, bool even) {
     // launches with 128-row chunks: ranges of a multiple of 4 steps can be walked from different places (TileCtx::rot), so a
     // split that gives such ranges is preferred if it keeps at least half the workgroups
     p.down_splits = (p.ct == 8 && best4 * 2 >= best) ? best4 : best;
-    // Loads spread about their mean: from a mean of 13 rows on so many experts have more than 16 that two tiles per chunk
-    // cost less than their second chunks (64 tokens, Mixtral shape, 4-bit 236 -> 199 us, 8-bit 357 -> 276, 16-bit 596 -> 447;
-    // 52 tokens 200 -> 188, 314 -> 270, 500 -> 446; 40 tokens 177, 180; 268, 265; 429, 439), from 15 on where all chunks run side
-    // by side (8 experts of 1024 x 2816: 52 tokens 39.4, 41.3, 64 tokens 44.3 -> 42.0).  (The splits, and with them the
-    // workspace, stay those of one tile.)
-    // Likewise the launches of 33 to 64 rows from a mean of 27 on, unless all chunks run side by side (Mixtral shape, 110 tokens,
-    // 4-bit 266 -> 260, 8-bit 357 -> 348, 16-bit 581 -> 505; 126 tokens 287 -> 268, 380 -> 352, 629 -> 507; 8 experts of 1024 x 2816
-    // 46.1, 51.3 and 47.6, 48.8).
-    if (p.ct == 2 && !even && avg > 26 && (f + 63) / 64 * E > 512 && !half_step_width(d, f)) p.ct = 4;
-    if (p.ct == 1 && !even && P > kUnevenPairs && avg > ((f + 63) / 64 * E <= 512 ? 14 : 12)) p.ct = 2;
+    // Loads spread about their mean, by the square root of avg (1 - k / E): where at least one expert in ten has more rows than
+    // a chunk, two tiles per chunk cost less than second chunks (64 tokens, Mixtral shape, 4-bit 236 -> 199 us, 8-bit 357 -> 276,
+    // 16-bit 596 -> 447; 52 tokens 200 -> 188, 314 -> 270, 500 -> 446; 40 tokens 177, 180; 268, 265; 429, 439; half of the
+    // experts per token: 26 tokens, 8 experts of 3840 x 4480, 16-bit 153, 162).  From a mean of 15 on where all chunks run side by
+    // side (8 experts of 1024 x 2816: 52 tokens 39.4, 41.3, 64 tokens 44.3 -> 42.0), never where twice as many would (32 tokens,
+    // 4 experts of 640 x 1024, 4-bit 21.1, 22.3).  (The splits, and with them the workspace, stay those of one tile.)
+    // Likewise from 32 to 64 rows, unless all chunks run side by side (Mixtral shape, 110 tokens, 4-bit 266 -> 260, 8-bit 357 -> 348,
+    // 16-bit 581 -> 505; 126 tokens 287 -> 268, 380 -> 352, 629 -> 507; 8 experts of 1024 x 2816 46.1, 51.3 and 47.6, 48.8); without
+    // 16-bit experts only if the workgroups of both projections fill the chip (124 tokens, 8 experts of 2432 x 4864, 8-bit
+    // 98.6, 109.9; 112 of 16 x 768 x 3968 76, 76).
+    const int columns = (f + 63) / 64 * E;
+    const auto overflows = [&](int rows) { return avg <= rows && 10 * E * (rows + 1 - avg) * (rows + 1 - avg) <= 17 * avg * (E - k); };
+    if (p.ct == 2 && overflows(32) && columns > 512 && !half_step_width(d, f) &&
+        (any16 || (columns >= 1200 && (d + 127) / 128 * p.down_splits * E >= 384)))
+        p.ct = 4;
+    if (p.ct == 1 && P > kUnevenPairs && overflows(16) && columns > (avg > 14 ? 128 : 512)) p.ct = 2;
     return p;
 }
 

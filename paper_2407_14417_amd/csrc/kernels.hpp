@@ -55,8 +55,8 @@ struct MfmaPlan {
 };
 bool mfma_shape_ok(int d, int f);
 bool mfma_rows_ok(int rows, int d, int f);
-// `even`: every expert gets the same number of the P pairs.
-MfmaPlan plan_mfma(int P, int d, int f, int E, bool even);
+// P pairs over E experts, k of them per token; any16: one of them is held in 16 bits.  (The splits do not depend on the last two.)
+MfmaPlan plan_mfma(int P, int d, int f, int E, int k, bool any16);
 inline bool half_step_width(int d, int f) { return (d | f) % 128 != 0; }
 int fewer_splits(int f, int splits, int P);
 // (x on a 16-byte boundary if up_form(..).waves)

@@ -81,6 +81,19 @@ def test_smaller_workspaces_leave_equal_ranges(L, d, f, E, k):
         assert 1 in seen
 
 
+@pytest.mark.parametrize("bits,d,f,k,T,ct", [
+    ("h" * 16, 5760, 2688, 8, 26, 1),      # 13 rows per expert on average, half of the experts per token: few have more than 16
+    ("q" * 8, 4096, 14336, 2, 52, 2),      # the same mean, a quarter of them
+    ("q" * 8, 4096, 14336, 2, 48, 1), ("h" * 4, 1024, 512, 4, 16, 1), ("q" * 4, 1024, 8192, 4, 16, 1),
+    ("q" * 2, 2560, 1408, 1, 30, 1),       # twice the chunks would run side by side as well
+    ("qe" * 4, 2304, 4480, 1, 256, 2),     # 32 rows: the workgroups of the down-projection do not fill the chip
+    ("q" * 8, 4096, 14336, 2, 126, 4), ("h" * 8, 3072, 10752, 2, 126, 4), ("h" * 8, 3072, 10752, 4, 56, 2),
+])
+def test_chunk_length_follows_the_spread_of_loads(L, bits, d, f, k, T, ct):
+    precs = [{"h": mm.PREC_FP16, "q": mm.PREC_INT4G64, "e": mm.PREC_INT8G64}[b] for b in bits]
+    assert [m.ct for m in launch_forms(precs, d, f, k, T)] == [ct] * 2
+
+
 @pytest.mark.parametrize("kwargs,code", [
     (dict(d=250), mm.MOE_ESHAPE), (dict(f=100), mm.MOE_ESHAPE), (dict(E=33), mm.MOE_ESHAPE),
     (dict(k=5), mm.MOE_ESHAPE), (dict(k=0), mm.MOE_ESHAPE), (dict(gate=None), mm.MOE_EINVAL),
