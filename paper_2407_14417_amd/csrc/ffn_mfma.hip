@@ -466,11 +466,10 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
 // with scalar products, which is what such widths had, took 296 + 190 us for 33 tokens, 4 of 32 experts, d_model and
 // d_ff 2880, three quarters of the experts 4-bit; 105 + 54 us here, 4.6 TB/s of stored weights; the rest of the way to the 7 TB/s of a plain read is scales asked for 4 bytes at
 // a time and 4-bit rows whose 128-byte requests straddle two lines.)
-// SPB: 128-column steps per LDS stage.  Launches with 64-row chunks of blocks without 16-bit experts take one instead of
-// two (one_step_per_stage): their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two
+// SPB: 128-column steps per LDS stage.  Launches with 64-row chunks at whole steps, which hold no 16-bit experts, take one instead
+// of two (one_step_per_stage): their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two
 // wavefronts per SIMD are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us,
-// 8-bit 408 -> 372; 4-bit 2048 x 5632, 160 tokens 117 -> 95.  With 16-bit experts (99 KB) there is no second workgroup and
-// one step per stage loses up to 4 %; contractions that end with half a step lose 7 %.
+// 8-bit 408 -> 372; 4-bit 2048 x 5632, 160 tokens 117 -> 95.  (Contractions that end with half a step lose 7 %.)
 template <bool UP, int CT, bool WIDE, bool HALF, int SPB>
 __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int MC = 16 * CT;                  // activation rows per chunk
@@ -581,13 +580,14 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     }
     const int prec = ee.prec;
     const int nct = (c.rows + 15) >> 4;          // 16-row tiles that hold any rows
+    constexpr bool k16 = CT != 4 || HALF;        // (64-row chunks at whole steps: blocks with 16-bit experts take ffn_prefill.hip)
     // the straight-line body for exactly the chunk's tiles where the launch can have that many (the clamp keeps
     // the smaller launches from instantiating bodies they never run)
 #define MOEMIX_BODY(n)                                                                                          \
     do {                                                                                                        \
         if (prec == MOE_PREC_INT4G64) tile_body<UP, MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
-        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
-        else tile_body<UP, MOE_PREC_FP16, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base);                    \
+        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
+        else if (k16) tile_body<UP, k16 ? MOE_PREC_FP16 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
     } while (0)
     if (WIDE) {
         if (CT >= 8 && nct > 4) MOEMIX_BODY(8);
@@ -622,6 +622,12 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
 }
 
+bool any_int8(const DevExperts& ex, int E) {
+    for (int e = 0; e < E; ++e)
+        if (ex.e[e].prec == MOE_PREC_INT8G64) return true;
+    return false;
+}
+
 // Chunks of at most `cap` rows that P pairs over E experts make: half a chunk more per expert than full ones would be.
 int likely_chunks(int P, int E, int cap) { return (2 * P / cap + E + 1) / 2; }
 
@@ -630,8 +636,9 @@ int likely_chunks(int P, int E, int cap) { return (2 * P / cap + E + 1) / 2; }
 // steps: 79 columns of workgroups x 4 chunks, 12 steps 43.0, 54.7 us; 6 x 4, 79 steps 142.5, 123.6; 32 x 4, 32 steps 55.9, 51.9;
 // 11 x 10, 11 steps 27.1, 26.7; 10 x 2, 19 steps 34.2, 31.8; 38 x 2, 9 steps 20.6, 21.7; 8 x 10, 4 steps 14.4, 15.7; of 52
 // launches of 60 to 240 tokens the faster one is taken in all but two, where they differ by 1 %.
-bool one_step_per_stage(const MfmaArgs& a, dim3 grid) {
-    if (a.unit_bytes != 2048) return false;
+// (Up-projections and blocks with 4-bit experts come here with more workgroups than compute units only: prefill_waves.)
+bool one_step_per_stage(const MfmaArgs& a, dim3 grid, bool up) {
+    if (up || !any_int8(a.ex, a.E)) return true;
     const int chunks = a.direct_expert >= 0 ? (int)grid.y : std::min(a.P, likely_chunks(a.P, a.E, 64));
     return grid.x * chunks > kComputeUnits || a.k_per_split / kKTile <= 10;
 }
@@ -642,8 +649,8 @@ void launch_ct_w(const MfmaArgs& a, const LaunchForm& form, dim3 grid, hipStream
         case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
         case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
         case 4:
-            if (!HALF && form.steps_per_stage == 1) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
-            else launch_one<UP, 4, WIDE, HALF>(a, grid, st);
+            if (!HALF && (UP || !WIDE || form.steps_per_stage == 1)) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
+            else launch_one<UP, 4, WIDE || !HALF, HALF>(a, grid, st);
             break;
         default: launch_one<UP, 8, true, true>(a, grid, st); break;
     }
@@ -653,12 +660,6 @@ uint32_t prec_mask(const DevExperts& ex, int E, int prec) {
     uint32_t m = 0;
     for (int e = 0; e < E; ++e) m |= (uint32_t)(ex.e[e].prec == prec) << e;
     return m;
-}
-
-bool any_int8(const DevExperts& ex, int E) {
-    for (int e = 0; e < E; ++e)
-        if (ex.e[e].prec == MOE_PREC_INT8G64) return true;
-    return false;
 }
 
 // Weight staging needs 4 KB of LDS per A operand for 16-bit experts, 2 KB for 4-bit ones.
@@ -679,19 +680,30 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //      of 1024 x 2816, 4-bit 45.7 -> 42.6, 16-bit 50.7 -> 47.9), not where they would (512 tokens, Mixtral shape, 505, 579).
 //      Also up to 76 rows per expert (68 rows, Mixtral shape, 4-bit 368 -> 351, 8-bit 438 -> 417, 16-bit 600 -> 562; 75 rows, 32 experts
 //      of 2048 x 1408, 4-bit 112 -> 105; 80 rows 367, 368, half 16-bit of 2048 x 5632 214, 220; 100 rows 405, 413).
-//      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64 and about half of the experts need two from
-//      some 52 on: 250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415, 16-bit 662 -> 557; 140 tokens 289, 290, 371 ->
-//      363, 552 -> 524; 200 tokens, 32 experts of 2048 x 1408, 4-bit 104 -> 98.5.  Without 16-bit experts,
-//      long contractions and fewer rows stay there (200 tokens, Mixtral shape, 4-bit 312, 321, 8-bit 373, 389; two experts of 40
-//      rows each 103, 103 and 121, 123.5), but not one expert alone (40 rows, 4-bit 100 -> 73, 8-bit 111 -> 69).
-int prefill_waves(const MfmaArgs& a, int ct, int columns) {
+//      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64: beside 16-bit experts (250 tokens,
+//      Mixtral shape, 662 -> 557; 140 tokens 552 -> 524) and from 53 rows on, where about half of the experts need two such chunks
+//      (250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415).  Else by w, its workgroups at a chunk per expert; all but
+//        - up-projections of one and a half to two rounds of 512, or more than 2.7.  The other kernel, half as many workgroups of
+//          twice the work, fills one round with the former, and just past two rounds begins its second.  80 launches, the other
+//          kernel's time over this one's, whole blocks: w up to 768 1.04, 1.5 to 2 rounds 0.97, up to 2.7 1.05, beyond 0.99.
+//        - down-projections of one and a half to two rounds (0.99; 1.06 elsewhere, 1.1 to 1.5 below half a round, where contractions
+//          are long), without 4-bit experts half to two if ranges are long (136 tokens, 8 experts of 4992 x 11648, 8-bit 386,
+//          397, 4-bit 344, 325), and those of 600 workgroups and more with ranges of up to 3 steps, which end before the
+//          rings pay (0.98; 280 tokens, 32 experts of 1536 x 1280, top-4, 4-bit 86, 90).
+//      240 random blocks of 33 to 64 rows without 16-bit experts, the other kernel, all on this one, as it is: 1, 0.882, 0.878 in
+//      the geometric mean.
+int prefill_waves(const MfmaArgs& a, int ct, int columns, bool up) {
     if (ct < 4 || a.K % kKTile || (uint64_t)a.P * a.K * 2 + 8192 >= (1ull << 32)) return 0;
-    const int E = a.direct_expert >= 0 ? 1 : a.E, rows = (a.P + E - 1) / E;
+    const bool alone = a.direct_expert >= 0;
+    const int E = alone ? 1 : a.E, rows = (a.P + E - 1) / E;
+    if (ct > 4) return columns * E * ((rows + 127) / 128) <= (int)kComputeUnits || rows <= 76 ? 4 : 8;
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
-    const bool any16 = a.direct_expert >= 0 ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
-    const bool few = columns * E * ((rows + 127) / 128) <= (int)kComputeUnits;
-    if (ct == 4) return any16 || (few && E == 1) || rows <= 32 || rows > 52 || a.k_per_split <= 24 * kKTile ? 4 : 0;
-    return few || rows <= 76 ? 4 : 8;
+    if (rows > 52 || (alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0)) return 4;
+    const bool all8 = alone ? (a.prec8 >> a.direct_expert) & 1 : a.prec8 == (uint32_t)((1ull << a.E) - 1);
+    const int w = 2 * columns * E;
+    const int from = !up && all8 && a.k_per_split > 24 * kKTile ? 256 : 768;
+    if ((w > from && w <= 1024) || (up && w > 1376)) return 0;
+    return !up && w >= 600 && a.k_per_split <= 3 * kKTile ? 0 : 4;
 }
 
 // Most rows of a 4-bit or 8-bit expert's chunks in ffn_prefill.hip, 0: 128 and no even split (also where that kernel is not
@@ -737,13 +749,13 @@ struct Launch {
     dim3 grid;
 };
 
-LaunchForm form_of(const MfmaArgs& a, int ct, dim3 grid, int splits) {
+LaunchForm form_of(const MfmaArgs& a, int ct, dim3 grid, int splits, bool up) {
     LaunchForm m;
     m.waves = a.waves;
     m.ct = ct;
     m.quant_rows = a.quant_rows;
     m.half = !a.waves && (a.K % kKTile || ct == 8);
-    m.steps_per_stage = a.waves ? 0 : ct == 4 && !m.half && one_step_per_stage(a, grid) ? 1 : spb_for(ct);
+    m.steps_per_stage = a.waves ? 0 : ct == 4 && !m.half && one_step_per_stage(a, grid, up) ? 1 : spb_for(ct);
     m.splits = splits;
     m.steps_per_split = a.k_per_split / kKTile;
     return m;
@@ -848,12 +860,12 @@ Launch up_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const h
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
-    a.waves = prefill_waves(a, ct, (f + 127) / 128);
+    a.waves = prefill_waves(a, ct, (f + 127) / 128, true);
     const int up_rows = a.waves ? 16 * a.waves : 32 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (f + up_rows - 1) / up_rows;
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles);
     l.grid = dim3(a.tiles, chunk_slots(rows, a, P, ct), 1);
-    l.form = form_of(a, ct, l.grid, 1);
+    l.form = form_of(a, ct, l.grid, 1, true);
     return l;
 }
 }  // namespace
@@ -884,12 +896,12 @@ Launch down_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const
     a.unit_bytes = staging_unit_bytes(ex, E, rows);
     a.prec16 = prec_mask(ex, E, MOE_PREC_FP16);
     a.prec8 = prec_mask(ex, E, MOE_PREC_INT8G64);
-    a.waves = prefill_waves(a, ct, (d + 255) / 256 * splits);
+    a.waves = prefill_waves(a, ct, (d + 255) / 256 * splits, false);
     const int down_rows = a.waves ? 32 * a.waves : 64 * (ct <= 2 ? kNASmall : 4);
     a.tiles = (d + down_rows - 1) / down_rows;
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles * splits);
     l.grid = dim3(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
-    l.form = form_of(a, ct, l.grid, splits);
+    l.form = form_of(a, ct, l.grid, splits, false);
     return l;
 }
 }  // namespace

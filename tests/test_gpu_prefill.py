@@ -165,21 +165,34 @@ def test_prefill_one_expert_alone(weights, d, f, n, waves, quant):
         assert_ffn_close(y.cpu().numpy(), _reference(x, dense[e]), f"expert {e}")
 
 
-# Blocks without 16-bit experts with 33 to 52 rows per expert and long contractions stay with the kernel for few rows: one
-# 128-column step per LDS stage in launches of many workgroups, two in those of few, chunks of every number of tiles; the
-# same tokens give the same bits in both.
-@pytest.mark.parametrize("bits", ["q" * 16, "e" * 16, "qe" * 8])
-def test_64_row_chunks_outside_the_prefill_kernel(weights, bits):
-    d, f = 4096, 3712
+# Blocks without 16-bit experts with 33 to 52 rows per expert: the projections that stay with the kernel for few rows, up and
+# down, long and short ranges, chunks of every number of tiles.
+ROWS = [30, 50, 64, 65, 1, 16, 17, 33, 48, 49, 0, 100, 80, 5, 128, 2]
+
+
+@pytest.mark.parametrize("d,f,bits,up,down", [(4096, 3712, "q" * 16, 0, 4), (4096, 3712, "qe" * 8, 0, 4), (4096, 3712, "e" * 16, 0, 0),
+                                              (1536, 1280, "q" * 16, 4, 0), (1536, 1280, "qe" * 8, 4, 0), (1536, 1280, "e" * 16, 4, 0),
+                                              (3584, 1408, "q" * 32, 4, 0), (3584, 1408, "qe" * 16, 4, 0)])
+def test_64_row_chunks_outside_the_prefill_kernel(weights, d, f, bits, up, down):
     experts, dense = weights(d, f, bits)
-    rows = [30, 50, 64, 65, 1, 16, 17, 33, 48, 49, 0, 100, 80, 5, 128, 2]
-    many = launch_forms([PREC[b] for b in bits], d, f, 1, sum(rows))
-    few = launch_forms([PREC[b] for b in bits[:2]], d, f, 1, rows[0] + rows[1])
-    for form, steps in ((many, 1), (few, 2)):
-        assert [(m.waves, m.ct, m.half, m.steps_per_stage, m.splits) for m in form] == [(0, 4, 0, steps, 1)] * 2
-    x, to, gate = _routed(torch.Generator(device="cuda").manual_seed(5), d, 16, rows)
+    rows = ROWS * (len(bits) // 16)
+    form = launch_forms([PREC[b] for b in bits], d, f, 1, sum(rows))
+    assert [(m.waves, m.ct, m.half, m.steps_per_stage) for m in form] == [(w, 4, 0, 0 if w else 1) for w in (up, down)]
+    x, to, gate = _routed(torch.Generator(device="cuda").manual_seed(5), d, len(bits), rows)
+    _check(d, f, gate, experts, dense, x, to)
+
+
+def test_64_row_chunks_two_steps_per_stage(weights):
+    """Long down-projections of few workgroups, all 8-bit: two 128-column steps per LDS stage; the same bits as in a block of
+    more experts, which takes one."""
+    d, f = 5376, 3712
+    experts, dense = weights(d, f, "e" * 12)
+    few, many = (launch_forms([mm.PREC_INT8G64] * E, d, f, 1, sum(ROWS[:E])) for E in (8, 12))
+    assert [few[0].waves, many[0].waves] == [4, 4]
+    assert [(m[1].waves, m[1].half, m[1].steps_per_stage, m[1].splits) for m in (few, many)] == [(0, 0, 2, 1), (0, 0, 1, 1)]
+    x, to, gate = _routed(torch.Generator(device="cuda").manual_seed(5), d, 12, ROWS[:12])
     _check(d, f, gate, experts, dense, x, to)
     out, _ = _block(d, f, gate, experts, x)
-    first = to < 2
-    some, _ = _block(d, f, gate[:2].contiguous(), experts[:2], x[first].contiguous())
+    first = to < 8
+    some, _ = _block(d, f, gate[:8].contiguous(), experts[:8], x[first].contiguous())
     assert torch.equal(some, out[first])
