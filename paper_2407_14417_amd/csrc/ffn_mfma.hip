@@ -681,8 +681,10 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //      Also up to 76 rows per expert (68 rows, Mixtral shape, 4-bit 368 -> 351, 8-bit 438 -> 417, 16-bit 600 -> 562; 75 rows, 32 experts
 //      of 2048 x 1408, 4-bit 112 -> 105; 80 rows 367, 368, half 16-bit of 2048 x 5632 214, 220; 100 rows 405, 413).
 //      And with 33 to 64 rows per expert, where a chunk of ffn_mfma.hip holds 64: beside 16-bit experts (250 tokens,
-//      Mixtral shape, 662 -> 557; 140 tokens 552 -> 524) and from 53 rows on, where about half of the experts need two such chunks
-//      (250 tokens, Mixtral shape, 4-bit 414 -> 350, 8-bit 478 -> 415).  Else by w, its workgroups at a chunk per expert; all but
+//      Mixtral shape, 662 -> 557; 140 tokens 552 -> 524) and where so many experts have more than 64 that they need two such chunks:
+//      loads spread by the square root of rows (1 - k / E), and the line lies 1.7 times that below 65 (250 tokens, Mixtral shape,
+//      4-bit 414 -> 350, 8-bit 478 -> 415; half of the experts per token, 110 tokens, 8 experts of 1024 x 7168 78, 86).  Else
+//      by w, its workgroups at a chunk per expert; all but
 //        - up-projections of one and a half to two rounds of 512, or more than 2.7.  The other kernel, half as many workgroups of
 //          twice the work, fills one round with the former, and just past two rounds begins its second.  80 launches, the other
 //          kernel's time over this one's, whole blocks: w up to 768 1.04, 1.5 to 2 rounds 0.97, up to 2.7 1.05, beyond 0.99.
@@ -698,7 +700,8 @@ int prefill_waves(const MfmaArgs& a, int ct, int columns, bool up) {
     const int E = alone ? 1 : a.E, rows = (a.P + E - 1) / E;
     if (ct > 4) return columns * E * ((rows + 127) / 128) <= (int)kComputeUnits || rows <= 76 ? 4 : 8;
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
-    if (rows > 52 || (alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0)) return 4;
+    if (alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0) return 4;
+    if (rows > 64 || E * (65 - rows) * (65 - rows) < 3 * rows * (E - (alone ? 1 : a.top_k))) return 4;
     const bool all8 = alone ? (a.prec8 >> a.direct_expert) & 1 : a.prec8 == (uint32_t)((1ull << a.E) - 1);
     const int w = 2 * columns * E;
     const int from = !up && all8 && a.k_per_split > 24 * kKTile ? 256 : 768;

@@ -94,6 +94,19 @@ def test_chunk_length_follows_the_spread_of_loads(L, bits, d, f, k, T, ct):
     assert [m.ct for m in launch_forms(precs, d, f, k, T)] == [ct] * 2
 
 
+@pytest.mark.parametrize("bits,d,f,k,T,up,down", [
+    ("qe" * 4, 1024, 7168, 4, 110, 0, 0),  # 55 rows per expert, half of the experts per token: few have more than 64
+    ("qe" * 4, 1024, 7168, 2, 220, 4, 4),  # the same mean, a quarter of them
+    ("qe" * 4, 1024, 7168, 2, 200, 0, 0),  # one and a half to two rounds of workgroups in both projections
+    ("qe" * 4, 1024, 5120, 2, 200, 4, 4), ("h" + "q" * 7, 1024, 7168, 2, 200, 4, 4),
+    ("q" * 2, 5632, 3712, 1, 68, 4, 4),    # long ranges, few workgroups
+    ("q" * 8, 4096, 14336, 2, 180, 0, 0),
+])
+def test_64_rows_per_expert_by_rounds_of_workgroups(L, bits, d, f, k, T, up, down):
+    precs = [{"h": mm.PREC_FP16, "q": mm.PREC_INT4G64, "e": mm.PREC_INT8G64}[b] for b in bits]
+    assert [(m.ct, m.waves) for m in launch_forms(precs, d, f, k, T)] == [(4, up), (4, down)]
+
+
 @pytest.mark.parametrize("kwargs,code", [
     (dict(d=250), mm.MOE_ESHAPE), (dict(f=100), mm.MOE_ESHAPE), (dict(E=33), mm.MOE_ESHAPE),
     (dict(k=5), mm.MOE_ESHAPE), (dict(k=0), mm.MOE_ESHAPE), (dict(gate=None), mm.MOE_EINVAL),
