@@ -477,20 +477,8 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     constexpr int NT = UP ? 32 * NA : 64 * NA;   // weight rows per workgroup
     extern __shared__ __align__(16) uint8_t lds[];   // [2][MC][SPB * 256 + 16]
     const int tid = threadIdx.x;
-    // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk
-    // Workgroups go to the 8 XCDs (each with an L2 of its own) in turn, in launch order: with 2, 4 or 8 contraction
-    // splits those of one chunk and split, which read the same slice of the activations, get the indices that
-    // land on the same 4, 2 or 1 XCDs.
     int tile_x, split_z;
-    {
-        const int sp = gridDim.x / a.tiles, i = blockIdx.x, xcd = i & 7, slot = i >> 3;
-        if (sp > 1 && (a.tiles * sp) % 8 == 0 && 8 % sp == 0) {
-            const int q = 8 / sp;                                  // XCDs per split
-            split_z = xcd / q; tile_x = slot * q + xcd % q;
-        } else {
-            tile_x = i % a.tiles; split_z = i / a.tiles;
-        }
-    }
+    place_workgroup(a.tiles, tile_x, split_z);
 
     // ---- which expert, which rows
     const int k_begin = split_z * a.k_per_split;
@@ -568,14 +556,7 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     void* out_base = UP ? a.out : (void*)((float*)a.out + split_z * a.split_stride);
     if (ee.resident == kDeferred) return;
     if (!(ee.resident && ee.w1.data && ee.w3.data && ee.w2.data)) {
-        if (tid == 0 && tile_x == 0) atomicOr(a.status, kStatusNotResident);
-        if (!UP) {   // rows of an expert that cannot run contribute nothing
-            float* y = (float*)out_base;
-            for (int i = tid; i < c.rows * NT; i += 256) {
-                const int rr = i / NT, cc = c.n0 + i % NT;
-                if (cc < c.N) y[(size_t)(begin + c.m0 + rr) * c.N + cc] = 0.0f;
-            }
-        }
+        leave_out<UP>(c, out_base, a.status, tile_x, NT, 256);
         return;
     }
     const int prec = ee.prec;
@@ -608,17 +589,8 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     // activation stages + 4 wavefronts x NA operands of weight staging
     const size_t lds_max = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * 4096;
     const size_t lds_bytes = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
-    // the attribute belongs to (kernel, device): set it once per device of the process (bit d of the mask; devices
-    // past the 64th set it on every launch)
     static std::atomic<unsigned long long> configured{0};
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
-    if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
-        (void)hipFuncSetAttribute((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds_max);
-        configured.fetch_or(bit, std::memory_order_relaxed);
-    }
+    allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB>, lds_max, configured);
     grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
 }
 

@@ -418,20 +418,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a
     constexpr int kThreads = 64 * WAVES, NT = (UP ? 16 : 32) * WAVES;   // weight rows per workgroup
     extern __shared__ __align__(16) uint8_t lds[];
     const int tid = threadIdx.x;
-    // grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk.
-    // Workgroups go to the 8 XCDs (each with an L2 of its own) in turn, in launch order: with 2, 4 or 8 contraction
-    // splits those of one chunk and split, which read the same slice of the activations, get the indices that
-    // land on the same 4, 2 or 1 XCDs.
     int tile_x, split_z;
-    {
-        const int sp = gridDim.x / a.tiles, i = blockIdx.x, xcd = i & 7, slot = i >> 3;
-        if (sp > 1 && (a.tiles * sp) % 8 == 0 && 8 % sp == 0) {
-            const int q = 8 / sp;
-            split_z = xcd / q; tile_x = slot * q + xcd % q;
-        } else {
-            tile_x = i % a.tiles; split_z = i / a.tiles;
-        }
-    }
+    place_workgroup(a.tiles, tile_x, split_z);
     const int k_begin = split_z * a.k_per_split;
     const int n_steps = a.k_per_split / kKTile;
     // ---- which expert, which rows.  (The precisions as two words: read lane by lane out of the expert table they would be
@@ -517,14 +505,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a
     void* out_base = UP ? a.out : (void*)((float*)a.out + split_z * a.split_stride);
     if (ee.resident == kDeferred) return;
     if (!(ee.resident && ee.w1.data && ee.w3.data && ee.w2.data)) {
-        if (tid == 0 && tile_x == 0) atomicOr(a.status, kStatusNotResident);
-        if (!UP) {   // rows of an expert that cannot run contribute nothing
-            float* y = (float*)out_base;
-            for (int i = tid; i < c.rows * NT; i += kThreads) {
-                const int rr = i / NT, cc = c.n0 + i % NT;
-                if (cc < c.N) y[(size_t)(begin + c.m0 + rr) * c.N + cc] = 0.0f;
-            }
-        }
+        leave_out<UP>(c, out_base, a.status, tile_x, NT, kThreads);
         return;
     }
     const int prec = ee.prec;
@@ -536,16 +517,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void prefill_kernel(const MfmaArgs a
 template <int WAVES, bool UP, bool WIDE>
 void launch_prefill_w(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr size_t lds_bytes = kLdsBytes * WAVES / 8;
-    // the attribute belongs to (kernel, device): set it once per device of the process (bit d of the mask; devices
-    // past the 64th set it on every launch)
     static std::atomic<unsigned long long> configured{0};
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
-    if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
-        (void)hipFuncSetAttribute((const void*)prefill_kernel<WAVES, UP, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        configured.fetch_or(bit, std::memory_order_relaxed);
-    }
+    allow_lds((const void*)prefill_kernel<WAVES, UP, WIDE>, lds_bytes, configured);
     prefill_kernel<WAVES, UP, WIDE><<<grid, 64 * WAVES, lds_bytes, st>>>(a);
 }
 

@@ -2,6 +2,8 @@
 // what a workgroup works on, addressing, products, and the expansion of 4-bit and 8-bit codes.
 #pragma once
 
+#include <atomic>
+
 #include "common.hpp"
 
 namespace moemix {
@@ -59,7 +61,6 @@ __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t b
     return r;
 }
 
-// fp16 pairs (1024, 1024) and (64, 64) held in vector registers (not volatile: identical copies are merged).
 // A 32-bit lane offset as a value the compiler has not seen before: its widening to 64 bits then stays next to the
 // load that uses it (scalar base + 32-bit lane offset in one instruction) instead of being hoisted out of the loop
 // as a register pair per offset.
@@ -67,6 +68,7 @@ __device__ __forceinline__ uint32_t fresh_offset(uint32_t v) {
     asm volatile("" : "+v"(v));
     return v;
 }
+// A constant (fp16 pairs such as 1024, 1024) held in a vector register (not volatile: identical copies are merged).
 __device__ __forceinline__ uint32_t vreg_const(uint32_t v) {
     uint32_t m;
     asm("v_mov_b32 %0, %1" : "=v"(m) : "s"(v));
@@ -116,6 +118,45 @@ struct TileCtx {
     uint8_t* lds;
     uint32_t lds_base;       // the same as an LDS byte address
 };
+
+// Grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk.
+// Workgroups go to the 8 XCDs (each with an L2 of its own) in turn, in launch order: with 2, 4 or 8 contraction
+// splits those of one chunk and split, which read the same slice of the activations, get the indices that
+// land on the same 4, 2 or 1 XCDs.
+__device__ __forceinline__ void place_workgroup(int tiles, int& tile_x, int& split_z) {
+    const int sp = gridDim.x / tiles, i = blockIdx.x, xcd = i & 7, slot = i >> 3;
+    if (sp > 1 && (tiles * sp) % 8 == 0 && 8 % sp == 0) {
+        const int q = 8 / sp;                              // XCDs per split
+        split_z = xcd / q; tile_x = slot * q + xcd % q;
+    } else {
+        tile_x = i % tiles; split_z = i / tiles;
+    }
+}
+
+// The workgroup's expert cannot run: its rows contribute nothing, and the status word says so.
+template <bool UP>
+__device__ __forceinline__ void leave_out(const TileCtx& c, void* out_base, int32_t* status, int tile_x, int n_rows, int threads) {
+    if (threadIdx.x == 0 && tile_x == 0) atomicOr(status, kStatusNotResident);
+    if (!UP) {
+        float* y = (float*)out_base;
+        for (int i = threadIdx.x; i < c.rows * n_rows; i += threads) {
+            const int rr = i / n_rows, cc = c.n0 + i % n_rows;
+            if (cc < c.N) y[(size_t)(c.begin + c.m0 + rr) * c.N + cc] = 0.0f;
+        }
+    }
+}
+
+// Lets a kernel be launched with up to `bytes` of LDS.  The attribute belongs to (kernel, device): it is set once per device of
+// the process (bit d of `configured`, one per kernel; devices past the 64th set it on every launch).
+inline void allow_lds(const void* kernel, size_t bytes, std::atomic<unsigned long long>& configured) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
+    if (!(configured.load(std::memory_order_relaxed) & bit) || !bit) {
+        (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        configured.fetch_or(bit, std::memory_order_relaxed);
+    }
+}
 
 // Launches with a.waves != 0 (ffn_prefill.hip).
 template <bool UP>
