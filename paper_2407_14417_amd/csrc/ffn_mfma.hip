@@ -664,6 +664,8 @@ int staging_unit_bytes(const DevExperts& ex, int E, const RowMap& rows) {
 //          are long), without 4-bit experts half to two if ranges are long (136 tokens, 8 experts of 4992 x 11648, 8-bit 386,
 //          397, 4-bit 344, 325), and those of 600 workgroups and more with ranges of up to 3 steps, which end before the
 //          rings pay (0.98; 280 tokens, 32 experts of 1536 x 1280, top-4, 4-bit 86, 90).
+//        Of 27 to 32 rows (plan_mfma) only the up-projections, and of those ones of short contractions: there the loads past 64 that
+//        long chunks are taken for cost least (480 tokens, 32 experts of 768 x 2816, 4-bit 79 -> 73.5; of 3456 x 3840, skewed, 281, 331).
 //      240 random blocks of 33 to 64 rows without 16-bit experts, the other kernel, all on this one, as it is: 1, 0.882, 0.878 in
 //      the geometric mean.
 int prefill_waves(const MfmaArgs& a, int ct, int columns, bool up) {
@@ -674,6 +676,7 @@ int prefill_waves(const MfmaArgs& a, int ct, int columns, bool up) {
     // (by the experts' precisions, resident or not: a call that runs some of them later sums in the same order)
     if (alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0) return 4;
     if (rows > 64 || E * (65 - rows) * (65 - rows) < 3 * rows * (E - (alone ? 1 : a.top_k))) return 4;
+    if (rows <= 32 && !(up && a.K <= 12 * kKTile)) return 4;
     const bool all8 = alone ? (a.prec8 >> a.direct_expert) & 1 : a.prec8 == (uint32_t)((1ull << a.E) - 1);
     const int w = 2 * columns * E;
     const int from = !up && all8 && a.k_per_split > 24 * kKTile ? 256 : 768;
@@ -805,12 +808,11 @@ MfmaPlan plan_mfma(int P, int d, int f, int E, int k, bool any16) {
     // 4 experts of 640 x 1024, 4-bit 21.1, 22.3).  (The splits, and with them the workspace, stay those of one tile.)
     // Likewise from 32 to 64 rows, unless all chunks run side by side (Mixtral shape, 110 tokens, 4-bit 266 -> 260, 8-bit 357 -> 348,
     // 16-bit 581 -> 505; 126 tokens 287 -> 268, 380 -> 352, 629 -> 507; 8 experts of 1024 x 2816 46.1, 51.3 and 47.6, 48.8); without
-    // 16-bit experts only if the workgroups of both projections fill the chip (124 tokens, 8 experts of 2432 x 4864, 8-bit
-    // 98.6, 109.9; 112 of 16 x 768 x 3968 76, 76).
+    // 16-bit experts only if the workgroups of the down-projection fill the chip too (124 tokens, 8 experts of 2432 x 4864, 8-bit
+    // 98.6, 109.9; 232 tokens, 8 of 2176 x 5376, top-1, 8-bit 109 -> 98).
     const int columns = (f + 63) / 64 * E;
     const auto overflows = [&](int rows) { return avg <= rows && 10 * E * (rows + 1 - avg) * (rows + 1 - avg) <= 17 * avg * (E - k); };
-    if (p.ct == 2 && overflows(32) && columns > 512 && !half_step_width(d, f) &&
-        (any16 || (columns >= 1200 && (d + 127) / 128 * p.down_splits * E >= 384)))
+    if (p.ct == 2 && overflows(32) && columns > 512 && !half_step_width(d, f) && (any16 || (d + 127) / 128 * p.down_splits * E >= 384))
         p.ct = 4;
     if (p.ct == 1 && P > kUnevenPairs && overflows(16) && columns > (avg > 14 ? 128 : 512)) p.ct = 2;
     return p;
