@@ -13,8 +13,10 @@
 // expansion of the codes and waiting.  Measured here: a product occupies the SIMD's issue for 8 of its 16 cycles, so two
 // vector instructions per product are free and every further one costs 4 cycles, whichever wavefront it comes from; LDS
 // delivers 256 bytes per cycle to conflict-free 16-byte reads, so reading each B operand for two products only is no burden,
-// while the expansion is done once per weight.  The chip runs at its power limit in these launches (1.5 - 2.1 GHz of 2.4; bare
-// products of random data reach 1973 TFLOP/s, of zeros 2443): what is left is energy, not latency.
+// while the expansion is done once per weight.  What bounds the launches now: the clock, which falls to 1.8 - 2.0 GHz of 2.4 in
+// those of many rows (the same launches with weights of zero keep 2.3 - 2.4 and take 0.76 - 0.89 of the time, few and short
+// ones 0.95 - 1), and instructions and waiting beside the products: matrix cores busy 0.41 (512 tokens, Mixtral shape, skewed,
+// up-projection) and 0.49 (1000 tokens, 8-bit) of the cycles, wavefronts at a wait 0.32 and 0.41 of theirs, LDS busy 0.28.
 // Blocks, before and after (both libraries in turn): 1000 tokens, 8 experts of 4096 x 14336, all 8-bit 842 -> 797 us; 500
 // tokens, 32 experts of 2048 x 1408, half 16-bit 192 -> 160; 80 tokens on every expert, 16-bit 638 -> 568; 600 tokens,
 // 2816 x 2816, 16-bit 173 -> 131; 256 tokens on every expert, 4-bit 741 -> 670.
