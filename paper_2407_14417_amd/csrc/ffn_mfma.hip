@@ -814,6 +814,7 @@ MfmaPlan plan_mfma(int P, int d, int f, int E, int k, bool any16) {
     const auto overflows = [&](int rows) { return avg <= rows && 10 * E * (rows + 1 - avg) * (rows + 1 - avg) <= 17 * avg * (E - k); };
     if (p.ct == 2 && overflows(32) && columns > 512 && !half_step_width(d, f) && (any16 || (d + 127) / 128 * p.down_splits * E >= 384))
         p.ct = 4;
+    // (chunks of more than one tile take ranges of one length; so few pairs over one expert never get here)
     if (p.ct == 1 && P > kUnevenPairs && overflows(16) && columns > (avg > 14 ? 128 : 512)) p.ct = 2;
     return p;
 }

@@ -503,8 +503,8 @@ def test_chunks_handed_out_by_length(orc, E, k, T, bias, d, f):
     assert_ffn_close(out, ref, cfg.name)
 
 
-# 33 to 64 rows per expert, contractions of up to 24 steps: blocks without 16-bit experts run the launches that blocks with some
-# run (workgroups of 4 wavefronts), and give the same bits as beside a 16-bit expert that no token reaches.
+# 33 to 64 rows per expert, launches of up to one and a half rounds of workgroups: blocks without 16-bit experts run what blocks
+# with some run (workgroups of 4 wavefronts), and give the same bits as beside a 16-bit expert that no token reaches.
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("d,f,T", [(640, 896, 140), (1024, 2048, 200), (384, 1536, 256), (1408, 1536, 140), (1408, 5632, 140)])
 def test_block_64_row_chunks_without_16bit_experts(orc, bits, d, f, T):
