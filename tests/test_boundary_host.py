@@ -57,19 +57,19 @@ def test_workspace_of_odd_multiples_of_64(L):
             assert unsplit <= need and (need == unsplit or (T > 1 and need <= own)), (d, f, T)
 
 
-@pytest.mark.parametrize("d,f", [(832, 2816), (320, 2304), (64 * 5, 1408), (1088, 3008), (2880, 2048), (2944, 2880), (448, 16384)])
+@pytest.mark.parametrize("d,f", [(832, 2816), (1472, 1152), (320, 2304), (64 * 5, 1408), (1088, 3008), (2880, 2048), (2944, 2880), (448, 16384)])
 @pytest.mark.parametrize("E,k", [(4, 2), (32, 8), (1, 1), (7, 3)])
 def test_smaller_workspaces_leave_equal_ranges(L, d, f, E, k):
     """Ranges of a split contraction may differ in length only in the launches that look at each range's end: 16-row chunks
     and the variant for odd multiples of 64.  Every workspace from the unsplit call's up, block and one expert alone."""
     steps = (f + 127) // 128
-    for T in [2, 3, 5, 8, 9, 16, 17, 20, 33, 40, 64, 65, 95, 130, 300, 700]:
+    for T in [2, 3, 5, 8, 9, 16, 17, 20, 33, 40, 64, 65, 95, 130, 257, 300, 700]:
         lay, _ = _layer(d=d, f=f, E=E, k=k)
         least, full = unsplit_workspace_bytes(d, f, E, k, T), L.moe_workspace_bytes(ctypes.byref(lay), T)
         seen = set()
         for ws in sorted({least, full, *(least + s * 4 * T * k * d for s in range(1, 17)), *(least + (full - least) * i // 9 for i in range(9))}):
             for prec in (mm.PREC_FP16, mm.PREC_INT4G64):
-                for expert, n in ((-1, T), (0, T * k), (0, T * k - k + 1)):
+                for expert, n in ((-1, T), (0, T), (0, T * k), (0, T * k - k + 1)):
                     if (n if expert == 0 else T * k) < 2 or n == 1:
                         continue
                     _, down = launch_forms([prec] * E, d, f, k, n, expert, ws)
