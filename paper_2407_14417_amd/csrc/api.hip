@@ -292,7 +292,7 @@ int moe_expert_ffn_mixed(const moe_layer* layer, int expert, const void* x_rows,
 
 // For the tests, host-only: the launches on the matrix cores that moe_layer_forward (expert < 0, n tokens) or
 // moe_expert_ffn_mixed (n rows) would make with a workspace of ws_bytes.  MOE_ESHAPE if it would make none.
-int moemix_launch_form(const moe_layer* layer, int expert, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down) {
+static int launch_form(const moe_layer* layer, int expert, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down, int teams[2]) {
     if (int rc = check_layer(layer)) return rc;
     const int k = layer->top_k, E = layer->n_experts, d = layer->d_model, f = layer->d_ff;
     const bool alone = expert >= 0;
@@ -304,9 +304,20 @@ int moemix_launch_form(const moe_layer* layer, int expert, int n, size_t ws_byte
     const RowMap rows{nullptr, nullptr, k, alone ? expert : -1, alone ? n : 0};
     MfmaPlan p = alone ? lone_plan(layer, n, w) : plan_for(layer, P);
     if (!alone) p.down_splits = w.y_splits;
-    *up = up_form(table, E, rows, P, d, f, p.ct);
-    *down = down_form(table, E, rows, P, d, f, p.ct, p.down_splits);
+    *up = up_form(table, E, rows, P, d, f, p.ct, &teams[0]);
+    *down = down_form(table, E, rows, P, d, f, p.ct, p.down_splits, &teams[1]);
     return MOE_OK;
+}
+
+int moemix_launch_form(const moe_layer* layer, int expert, int n, size_t ws_bytes, LaunchForm* up, LaunchForm* down) {
+    int teams[2];
+    return launch_form(layer, expert, n, ws_bytes, up, down, teams);
+}
+
+// The same for the teams of wavefronts that share a workgroup's contraction range: teams[0] up-, teams[1] down-projection.
+int moemix_launch_teams(const moe_layer* layer, int expert, int n, size_t ws_bytes, int* teams) {
+    LaunchForm up, down;
+    return launch_form(layer, expert, n, ws_bytes, &up, &down, teams);
 }
 
 int moe_layer_forward(const moe_layer* layer, const void* x, int T, void* out, int32_t* topk_idx_out,

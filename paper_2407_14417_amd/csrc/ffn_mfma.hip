@@ -34,11 +34,11 @@ constexpr int kSPBMax = 2;         // most 128-column steps per LDS stage
 constexpr int spb_for(int ct) { return (8 / ct) < kSPBMax ? (8 / ct) : kSPBMax; }
 
 // Results of one workgroup: lane (r16, c4) holds, for activation row 16 j + r16, weight rows
-// 16 tile + 4 c4 + (0..3) of the wavefront's NT/4 rows.
+// 16 tile + 4 c4 + (0..3) of the wavefront's rows.
 template <bool UP, int NCT, int NA>
 __device__ __forceinline__ void store_results(const TileCtx& c, const float4_t (&acc)[NA][NCT], void* out_base, int wave,
                                               int r16, int c4) {
-    constexpr int NT = UP ? 32 * NA : 64 * NA;
+    constexpr int RW = UP ? 8 * NA : 16 * NA;          // weight rows per wavefront
     const int N = c.N;
 #pragma unroll
     for (int j = 0; j < NCT; ++j) {
@@ -49,7 +49,7 @@ __device__ __forceinline__ void store_results(const TileCtx& c, const float4_t (
                 half_t* h = (half_t*)out_base + g * N;
 #pragma unroll
                 for (int tile = 0; tile < NA / 2; ++tile) {
-                    const int col = c.n0 + wave * (NT / 4) + tile * 16 + c4 * 4;
+                    const int col = c.n0 + wave * RW + tile * 16 + c4 * 4;
                     if (col < N) {
                         half4_t o;
 #pragma unroll
@@ -61,12 +61,33 @@ __device__ __forceinline__ void store_results(const TileCtx& c, const float4_t (
                 float* y = (float*)out_base + g * N;
 #pragma unroll
                 for (int tile = 0; tile < NA; ++tile) {
-                    const int col = c.n0 + wave * (NT / 4) + tile * 16 + c4 * 4;
+                    const int col = c.n0 + wave * RW + tile * 16 + c4 * 4;
                     if (col < N) *(float4_t*)(y + col) = acc[tile][j];
                 }
             }
         }
     }
+}
+
+// The first team's sums become those of all teams, added in the order of the teams.  The others hand theirs over in their
+// activation stages (no wavefront reads those any more: every team has passed the last barrier of the range).
+template <int KS, int NCT, int NA>
+__device__ __forceinline__ void share_sums(const TileCtx& c, float4_t (&acc)[NA][NCT], int wave, int lane) {
+    const auto slot = [&](uint8_t* lds, int t, int j) { return (float4_t*)(lds + (((wave * NA + t) * NCT + j) * 64 + lane) * 16); };
+    if (c.team) {
+#pragma unroll
+        for (int t = 0; t < NA; ++t)
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) *slot(c.lds, t, j) = acc[t][j];
+    }
+    __syncthreads();
+    if (c.team) return;
+#pragma unroll
+    for (int s = 1; s < KS; ++s)
+#pragma unroll
+        for (int t = 0; t < NA; ++t)
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) acc[t][j] += *slot(c.lds + s * c.team_bytes, t, j);
 }
 
 // A wavefront holds NA A operands (16-row tiles of weights) per step.  UP: two matrices (w1, w3), NA/2 tiles each
@@ -82,15 +103,20 @@ __device__ __forceinline__ void store_results(const TileCtx& c, const float4_t (
 // zero too (quantized weights: the scale and zero of the absent group are zero words out of the byte permute, which
 // costs nothing) or the products are left out (16-bit weights: the last two of four sub-steps), so that neither an
 // infinity next door nor one in the repeated piece reaches a sum.
-template <bool UP, int PREC, int NCT, int SPB, int NA, bool HALF = false>   // PREC: moe_prec of the expert
+//
+// KS: the 4 wavefronts are KS teams of 4 / KS, each with a part of the contraction range and LDS of its own, all on the same
+// weight rows, 1 / KS as many; c is the team's.  The teams meet at every barrier (c.barriers of them, for the longest part), and
+// the first adds up the sums.
+template <bool UP, int PREC, int NCT, int SPB, int NA, bool HALF = false, int KS = 1>   // PREC: moe_prec of the expert
 __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee, void* out_base) {
     constexpr bool INT4 = PREC == MOE_PREC_INT4G64, INT8 = PREC == MOE_PREC_INT8G64, QUANT = INT4 || INT8;
-    constexpr int NT = UP ? 32 * NA : 64 * NA;     // weight rows per workgroup: 16 NA / (matrices) per wavefront
+    constexpr int RW = UP ? 8 * NA : 16 * NA;      // weight rows per wavefront: 16 NA / (matrices)
+    constexpr int TW = 4 / KS;                     // wavefronts per team
     constexpr int kStride = SPB * kKTile * 2 + 16;     // bytes per activation row of an LDS stage (16 bytes of padding)
     constexpr int PPR = 16 * SPB;                      // 16-byte pieces per row of a stage
-    constexpr int RPP = 256 / PPR;                     // rows the 256 threads cover in one pass
-    constexpr int NP = NCT * SPB;                      // pieces per thread and stage
-    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, c4 = lane >> 4;
+    constexpr int RPP = 64 * TW / PPR;                 // rows the threads of a team cover in one pass
+    constexpr int NP = NCT * SPB * KS;                 // pieces per thread and stage
+    const int tid = threadIdx.x % (64 * TW), lane = tid & 63, r16 = lane & 15, c4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int K = c.K, N = c.N, n_steps = c.n_steps;
     const int last = n_steps - 1;    // loads that would run past the contraction range repeat the last step instead
@@ -138,7 +164,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         }
     };
 
-    // ---- scales and zeros of this lane's weight rows (4-bit): the wavefront owns NT/4 rows from n0 + wave * NT/4,
+    // ---- scales and zeros of this lane's weight rows (4-bit): the wavefront owns RW rows from n0 + wave * RW,
     // in tiles of 16; lane (r16, c4) looks after row r16 of each tile
     gptr_t sbase[NA], zbase[NA];                       // uniform bases, one lane offset for both
     uint32_t soff[NA];
@@ -146,13 +172,14 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     for (int t = 0; t < NA; ++t) {
         const int tile = UP ? (t >> 1) : t;                        // up: operands (w1 tile0, w3 tile0, w1 tile1, w3 tile1)
         const DevMat& m = UP ? ((t & 1) ? ee.w3 : ee.w1) : ee.w2;
-        int row = c.n0 + wave * (NT / 4) + tile * 16 + r16;
+        int row = c.n0 + wave * RW + tile * 16 + r16;
         row = row < N ? row : N - 1;                               // rows past the end repeat the last row, never stored
         sbase[t] = QUANT ? scalar_ptr(m.scale + (c.k_begin >> 6)) : nullptr;
         zbase[t] = QUANT ? scalar_ptr(m.zero + (c.k_begin >> 6)) : nullptr;
         soff[t] = (uint32_t)row * (uint32_t)(K >> 6) * 2;
     }
-    bool sz_aligned16 = true;                          // (what the 128-bit scale loads below ask of the arrays)
+    // (what the 128-bit scale loads below ask of the arrays, and of the rows: a part of an uneven range may hold whole fours)
+    bool sz_aligned16 = KS == 1 || K % 512 == 0;
 #pragma unroll
     for (int t = 0; t < NA; ++t)
         sz_aligned16 = sz_aligned16 && !(((uintptr_t)sbase[t] | (uintptr_t)zbase[t]) & 15);
@@ -256,7 +283,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         cbase[t] = scalar_ptr(m.data + (INT4 ? (c.k_begin >> 1) : INT8 ? c.k_begin : c.k_begin * 2));
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
-            int row = c.n0 + wave * (NT / 4) + tile * 16 + 8 * hb + (lane >> 3);
+            int row = c.n0 + wave * RW + tile * 16 + 8 * hb + (lane >> 3);
             row = row < N ? row : N - 1;                           // rows past the end repeat the last row, never stored
             goff[t][hb] = (uint32_t)row * (uint32_t)(INT4 ? (K >> 1) : INT8 ? K : 2 * K) + (lane & 7) * 16;
         }
@@ -454,6 +481,11 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         }
     }
 
+    if constexpr (KS > 1) {
+        for (int i = (n_steps + SPB - 1) / SPB; i < c.barriers; ++i) __syncthreads();
+        share_sums<KS, NCT, NA>(c, acc, wave, lane);
+        if (c.team) return;
+    }
     store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
 }
 
@@ -470,20 +502,30 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
 // of two (one_step_per_stage): their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two
 // wavefronts per SIMD are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us,
 // 8-bit 408 -> 372; 4-bit 2048 x 5632, 160 tokens 117 -> 95.  (Contractions that end with half a step lose 7 %.)
-template <bool UP, int CT, bool WIDE, bool HALF, int SPB>
+// Steps of each of `teams` parts of a range, the last of which may be shorter: whole fours where that comes out even (the wide
+// loads of scales), else whole pairs (units of 4-bit codes).
+__host__ __device__ inline int team_steps(int steps, int teams) {
+    const int unit = steps % (4 * teams) == 0 ? 4 : 2;
+    return (steps + teams * unit - 1) / (teams * unit) * unit;
+}
+
+// KS: teams that the 4 wavefronts make, which share the contraction range (teams_for).  Launches of few workgroups are bound by
+// the chain of steps of each, not by memory: three 4-bit experts of 6784 x 512, 42 tokens, block 63.9 -> 47.3 us with two teams; five
+// 16-bit ones of 512 x 7808, 8 tokens, 76.6 -> 43.0 with four.
+template <bool UP, int CT, bool WIDE, bool HALF, int SPB, int KS>
 __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
     constexpr int MC = 16 * CT;                  // activation rows per chunk
     constexpr int NA = CT <= 2 ? kNASmall : 4;   // A operands per wavefront
-    constexpr int NT = UP ? 32 * NA : 64 * NA;   // weight rows per workgroup
+    constexpr int NT = (UP ? 32 * NA : 64 * NA) / KS;   // weight rows per workgroup
     extern __shared__ __align__(16) uint8_t lds[];   // [2][MC][SPB * 256 + 16]
     const int tid = threadIdx.x;
     int tile_x, split_z;
     place_workgroup(a.tiles, tile_x, split_z);
 
     // ---- which expert, which rows
-    const int k_begin = split_z * a.k_per_split;
+    int k_begin = split_z * a.k_per_split;
     // (the last range of uneven splits is shorter; launches of few pairs only)
-    const int n_steps = HALF || CT == 1 ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
+    int n_steps = HALF || CT == 1 ? (min(a.k_per_split, a.K - k_begin) + kKTile - 1) / kKTile : a.k_per_split / kKTile;
     int e, begin, cnt, chunk = blockIdx.y;
     TileCtx c;
     c.tokens = nullptr;
@@ -535,6 +577,18 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     c.begin = begin;
     c.rows = min(MC, cnt - c.m0);
     c.n0 = tile_x * NT;
+    c.mc = MC;
+    c.unit_bytes = a.unit_bytes;
+    c.lds = lds;
+    if constexpr (KS > 1) {
+        const int part = team_steps(n_steps, KS);
+        c.team = __builtin_amdgcn_readfirstlane(tid / (256 / KS));
+        c.team_bytes = 2 * MC * (SPB * kKTile * 2 + 16) + 4 / KS * NA * a.unit_bytes;
+        c.barriers = (part + SPB - 1) / SPB;
+        c.lds = lds + c.team * c.team_bytes;
+        k_begin += c.team * part * kKTile;
+        n_steps = min(part, n_steps - c.team * part);
+    }
     c.k_begin = k_begin;
     c.n_steps = n_steps;
     c.tail = HALF && k_begin + n_steps * kKTile > a.K;
@@ -549,9 +603,6 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     // hidden rows walk it in step and find it in L2 (fetched bytes of the prefill down-projection: 1060 MB with one
     // starting place per tile, 781 MB per slice, 637 MB with the slice's workgroups on two XCDs as well).
     c.rot = (HALF || (c.n_steps & 3)) ? 0 : 4 * ((UP ? tile_x * 5 : e * 3 + split_z * 5) % (c.n_steps >> 2));
-    c.mc = MC;
-    c.unit_bytes = a.unit_bytes;
-    c.lds = lds;
     const DevExpert& ee = a.ex.e[e];
     void* out_base = UP ? a.out : (void*)((float*)a.out + split_z * a.split_stride);
     if (ee.resident == kDeferred) return;
@@ -566,9 +617,9 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     // the smaller launches from instantiating bodies they never run)
 #define MOEMIX_BODY(n)                                                                                          \
     do {                                                                                                        \
-        if (prec == MOE_PREC_INT4G64) tile_body<UP, MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
-        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
-        else if (k16) tile_body<UP, k16 ? MOE_PREC_FP16 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF>(c, ee, out_base); \
+        if (prec == MOE_PREC_INT4G64) tile_body<UP, MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF, KS>(c, ee, out_base); \
+        else if (WIDE && prec == MOE_PREC_INT8G64) tile_body<UP, WIDE ? MOE_PREC_INT8G64 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF, KS>(c, ee, out_base); \
+        else if (k16) tile_body<UP, k16 ? MOE_PREC_FP16 : MOE_PREC_INT4G64, ((n) <= CT ? (n) : CT), SPB, NA, HALF, KS>(c, ee, out_base); \
     } while (0)
     if (WIDE) {
         if (CT >= 8 && nct > 4) MOEMIX_BODY(8);
@@ -583,15 +634,15 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
 #undef MOEMIX_BODY
 }
 
-template <bool UP, int CT, bool WIDE, bool HALF, int SPB = spb_for(CT)>
+template <bool UP, int CT, bool WIDE, bool HALF, int SPB = spb_for(CT), int KS = 1>
 void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr int NA = CT <= 2 ? kNASmall : 4;
-    // activation stages + 4 wavefronts x NA operands of weight staging
-    const size_t lds_max = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * 4096;
-    const size_t lds_bytes = 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
+    // activation stages per team + 4 wavefronts x NA operands of weight staging
+    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * 4096;
+    const size_t lds_bytes = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
     static std::atomic<unsigned long long> configured{0};
-    allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB>, lds_max, configured);
-    grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB><<<grid, 256, lds_bytes, st>>>(a);
+    allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS>, lds_max, configured);
+    grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS><<<grid, 256, lds_bytes, st>>>(a);
 }
 
 bool any_int8(const DevExperts& ex, int E) {
@@ -599,6 +650,9 @@ bool any_int8(const DevExperts& ex, int E) {
         if (ex.e[e].prec == MOE_PREC_INT8G64) return true;
     return false;
 }
+
+// 128-column steps of a contraction, the last of which may be half a one.
+int contraction_steps(int f) { return (f + kKTile - 1) / kKTile; }
 
 // Chunks of at most `cap` rows that P pairs over E experts make: half a chunk more per expert than full ones would be.
 int likely_chunks(int P, int E, int cap) { return (2 * P / cap + E + 1) / 2; }
@@ -615,11 +669,42 @@ bool one_step_per_stage(const MfmaArgs& a, dim3 grid, bool up) {
     return grid.x * chunks > kComputeUnits || a.k_per_split / kKTile <= 10;
 }
 
+// Teams of wavefronts in a workgroup of a launch with a grid for one: `teams` times as many workgroups then walk 1 / teams of the
+// range each.  A workgroup alone on its compute unit takes 0.7 to 1 us per step, whatever it reads (it has one wavefront per SIMD, each a
+// chain of LDS round trips and expansion), so where compute units have none, chains get shorter; past that every workgroup more
+// stages the same activations again and starts again.  150 random blocks of up to 32 rows per expert, both projections, W =
+// workgroups with one team, W x steps, block with one, two and four teams (us):
+//   four: 16 x 61 76.6, 54.8, 43.0; 24 x 22 32.0, 25.8, 22.5; 36 x 29 40.7, 32.6, 26.8; 44 x 37 57.0, 44.4, 37.0; from some 50
+//     on either may be faster (56 x 59 72.3, 51.6, 41.5; 56 x 61 106.1, 85.3, 90.2; 60 x 23 45.5, 39.7, 44.1), 72 x 33 44.7, 35.5, 42.0.
+//   two: 60 x 17 40.2, 34.9; 120 x 48 72.5, 60.2; 160 x 18 35.5, 30.5; without 16-bit experts up to 340 (224 x 38 88.6, 77.7;
+//     340 x 52 113.0, 103.0; 378 x 9 36.8, 42.5), with them 192 (160 x 17 39.9, 36.8; 220 x 29 93.9, 98.6), chunks of two tiles,
+//     whose stages take twice the LDS, 170 (160 x 23 59.5, 51.7; 266 x 4 30.5, 37.5).
+// (By the experts' precisions, resident or not: a call that runs some of them later sums in the same order.)
+int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
+    if (a.waves || ct > 2) return 1;
+    const auto fits = [&](int teams) {   // every part of every range holds two steps at least
+        const auto ok = [&](int steps) { return steps - (teams - 1) * team_steps(steps, teams) >= 2; };
+        const int steps = a.k_per_split / kKTile, all = contraction_steps(a.K);
+        return ok(steps) && ok(all - (splits - 1) * steps);
+    };
+    const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
+    const int wgs = grid.x * (alone ? (int)grid.y : std::min(a.P, likely_chunks(a.P, a.E, 16 * ct)));
+    if (ct == 1 && 5 * wgs <= (int)kComputeUnits && fits(4)) return 4;
+    return wgs <= (ct == 2 ? 170 : any16 ? 192 : 340) && fits(2) ? 2 : 1;
+}
+
 template <bool UP, bool WIDE, bool HALF>
-void launch_ct_w(const MfmaArgs& a, const LaunchForm& form, dim3 grid, hipStream_t st) {
+void launch_ct_w(const MfmaArgs& a, const LaunchForm& form, int teams, dim3 grid, hipStream_t st) {
     switch (form.ct) {
-        case 1: launch_one<UP, 1, WIDE, HALF>(a, grid, st); break;
-        case 2: launch_one<UP, 2, WIDE, HALF>(a, grid, st); break;
+        case 1:
+            if (teams == 4) launch_one<UP, 1, WIDE, HALF, spb_for(1), 4>(a, grid, st);
+            else if (teams == 2) launch_one<UP, 1, WIDE, HALF, spb_for(1), 2>(a, grid, st);
+            else launch_one<UP, 1, WIDE, HALF>(a, grid, st);
+            break;
+        case 2:
+            if (teams == 2) launch_one<UP, 2, WIDE, HALF, spb_for(2), 2>(a, grid, st);
+            else launch_one<UP, 2, WIDE, HALF>(a, grid, st);
+            break;
         case 4:
             if (!HALF && (UP || !WIDE || form.steps_per_stage == 1)) launch_one<UP, 4, WIDE, HALF, HALF ? spb_for(4) : 1>(a, grid, st);
             else launch_one<UP, 4, WIDE || !HALF, HALF>(a, grid, st);
@@ -725,6 +810,7 @@ struct Launch {
     MfmaArgs a;
     LaunchForm form;
     dim3 grid;
+    int teams;    // grouped_mfma_kernel: teams per workgroup
 };
 
 LaunchForm form_of(const MfmaArgs& a, int ct, dim3 grid, int splits, bool up) {
@@ -742,13 +828,12 @@ LaunchForm form_of(const MfmaArgs& a, int ct, dim3 grid, int splits, bool up) {
 template <bool UP>
 void launch_ct(const Launch& l, hipStream_t st) {
     if (l.form.waves) launch_prefill<UP>(l.a, l.grid, st);
-    else if (l.form.half) launch_ct_w<UP, true, true>(l.a, l.form, l.grid, st);
-    else if (any_int8(l.a.ex, l.a.E)) launch_ct_w<UP, true, false>(l.a, l.form, l.grid, st);
-    else launch_ct_w<UP, false, false>(l.a, l.form, l.grid, st);
+    else if (l.form.half) launch_ct_w<UP, true, true>(l.a, l.form, l.teams, l.grid, st);
+    else if (any_int8(l.a.ex, l.a.E)) launch_ct_w<UP, true, false>(l.a, l.form, l.teams, l.grid, st);
+    else launch_ct_w<UP, false, false>(l.a, l.form, l.teams, l.grid, st);
 }
 
 // Splits of a contraction of `f` columns into ranges of whole steps, all of one length but the last, which may be shorter.
-int contraction_steps(int f) { return (f + kKTile - 1) / kKTile; }
 int steps_per_split(int steps, int splits) { return (steps + splits - 1) / splits; }
 // every range holds two steps at least, the last one included
 bool splits_ok(int steps, int splits) { return steps - (splits - 1) * steps_per_split(steps, splits) >= 2; }
@@ -844,12 +929,16 @@ Launch up_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const h
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles);
     l.grid = dim3(a.tiles, chunk_slots(rows, a, P, ct), 1);
     l.form = form_of(a, ct, l.grid, 1, true);
+    l.teams = teams_for(a, ct, l.grid, 1);
+    if (l.teams > 1) l.grid.x = a.tiles = (f + up_rows / l.teams - 1) / (up_rows / l.teams);
     return l;
 }
 }  // namespace
 
-LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct) {
-    return up_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, nullptr).form;
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int* teams) {
+    const Launch l = up_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, nullptr);
+    if (teams) *teams = l.teams;
+    return l.form;
 }
 
 void launch_ffn_up_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* x, int d, int f, half_t* h,
@@ -880,12 +969,19 @@ Launch down_launch(const DevExperts& ex, int E, const RowMap& rows, int P, const
     a.quant_rows = quant_chunk_rows(rows, a, P, a.tiles * splits);
     l.grid = dim3(a.tiles * splits, chunk_slots(rows, a, P, ct), 1);
     l.form = form_of(a, ct, l.grid, splits, false);
+    l.teams = teams_for(a, ct, l.grid, splits);
+    if (l.teams > 1) {
+        a.tiles = (d + down_rows / l.teams - 1) / (down_rows / l.teams);
+        l.grid.x = a.tiles * splits;
+    }
     return l;
 }
 }  // namespace
 
-LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits) {
-    return down_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, splits, 0, nullptr).form;
+LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits, int* teams) {
+    const Launch l = down_launch(ex, E, rows, P, nullptr, d, f, nullptr, ct, splits, 0, nullptr);
+    if (teams) *teams = l.teams;
+    return l.form;
 }
 
 void launch_ffn_down_mfma(const DevExperts& ex, int E, const RowMap& rows, int P, const half_t* h, int d, int f, float* y,

@@ -74,8 +74,9 @@ struct LaunchForm {
     int splits;            // ranges of the contraction
     int steps_per_split;   // 128-column steps of each, the last one may have fewer where `half` or ct == 1
 };
-LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct);
-LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits);
+// (teams: grouped_mfma_kernel, teams of wavefronts that share the contraction range of a workgroup)
+LaunchForm up_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int* teams = nullptr);
+LaunchForm down_form(const DevExperts& ex, int E, const RowMap& rows, int P, int d, int f, int ct, int splits, int* teams = nullptr);
 
 // Batch-1 decode path (one token): shapes it covers, and its two kernels.
 bool decode_shape_ok(int d, int f);

@@ -117,6 +117,7 @@ struct TileCtx {
     int unit_bytes;          // LDS bytes per A operand of the weight staging regions (2048: 4-bit only, 4096)
     uint8_t* lds;
     uint32_t lds_base;       // the same as an LDS byte address
+    int team, team_bytes, barriers;   // grouped_mfma_kernel with several teams: which one, LDS of each, barriers of the longest part
 };
 
 // Grid: x = tile of weight rows + tiles * contraction split, y = chunk: workgroups are handed out chunk by chunk.

@@ -1,0 +1,83 @@
+"""Launches of grouped products in which the wavefronts of a workgroup share its contraction range in teams, each asked from
+the library before it is run, against the oracle."""
+from __future__ import annotations
+
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_14417_amd import binding as mm
+from tests import common
+from tests.common import assert_ffn_close, build_workload
+from tests.gpu_common import dev, device_layer
+
+PREC = {"h": mm.PREC_FP16, "q": mm.PREC_INT4G64, "e": mm.PREC_INT8G64}
+
+
+def launch_teams(bits, d, f, k, n, expert=-1, ws_bytes=1 << 40):
+    """Teams per workgroup in the up- and the down-projection, as the library itself says (host only)."""
+    experts = (mm.CExpert * len(bits))()
+    for e, b in zip(experts, bits):
+        e.prec, e.resident = PREC[b], 1
+        for m in (e.w1, e.w3, e.w2):
+            m.data = m.scale = m.zero = 4096
+    layer = mm.CLayer(d, f, len(bits), k, 4096, None, experts)
+    teams = (ctypes.c_int * 2)()
+    fn = mm.lib().moemix_launch_teams
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_void_p]
+    assert fn(ctypes.byref(layer), expert, n, ws_bytes, teams) == 0, mm.lib().moe_last_error()
+    return tuple(teams)
+
+
+def _config(bits, d, f, k, T):
+    pick = lambda c: tuple(i for i, b in enumerate(bits) if b == c)
+    return common.Config(f"teams_{bits}_{d}_{f}_{k}_{T}", d, f, len(bits), k, T, pick("q"), int8_experts=pick("e"))
+
+
+# Contractions whose parts are whole fours of steps, pairs with a shorter or an odd last one, and end with half a step; tiles of
+# weight rows that end past the matrix; chunks of one and two tiles, full and ragged; the three precisions, alone and mixed.
+CASES = [
+    ("qqq", 2048, 256, 2, 6, (4, 1)), ("hqe", 1792, 384, 2, 5, (4, 1)), ("eee", 2944, 320, 1, 9, (4, 1)),
+    ("hhh", 2624, 512, 2, 7, (4, 1)), ("hhh", 1344, 512, 2, 7, (2, 1)), ("qqe", 1088, 704, 3, 4, (2, 1)),
+    ("qhqe", 256, 2944, 2, 13, (1, 4)), ("qqqq", 320, 2880, 1, 17, (1, 4)), ("qqqq", 256, 3968, 1, 34, (1, 4)),
+    ("eeh", 576, 2944, 3, 15, (1, 4)), ("hh", 512, 6016, 1, 9, (2, 4)), ("qqqq", 512, 512, 2, 2, (2, 1)),
+    ("hhhh", 640, 1408, 2, 8, (1, 2)), ("hhh", 256, 2176, 2, 20, (1, 2)), ("qqq", 256, 2944, 3, 24, (1, 2)),
+    ("hhe", 320, 2368, 3, 22, (1, 2)), ("qqq", 1152, 640, 2, 40, (2, 1)), ("heq", 960, 832, 2, 47, (2, 2)),
+    ("qqqqqqqq", 1024, 1408, 2, 24, (2, 2)),
+]
+
+
+@pytest.mark.parametrize("bits,d,f,k,T,teams", CASES)
+def test_rule(bits, d, f, k, T, teams):
+    assert launch_teams(bits, d, f, k, T) == teams
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,d,f,k,T,teams", CASES)
+def test_block(orc, bits, d, f, k, T, teams):
+    assert launch_teams(bits, d, f, k, T) == teams
+    cfg = _config(bits, d, f, k, T)
+    wl = build_workload(cfg, orc)
+    layer = device_layer(wl)
+    x, idx = dev(wl.x), torch.empty((T, k), dtype=torch.int32, device="cuda")
+    out, gate = torch.empty_like(x), torch.empty((T, k), dtype=torch.float32, device="cuda")
+    ws = mm.alloc_workspace(layer, T)
+    for _ in range(2):
+        out.fill_(float("nan"))
+        mm.moe_layer_forward(layer, x, out, ws, idx, gate)
+        ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, k)
+        assert np.array_equal(idx.cpu().numpy(), ref_idx)
+        assert_ffn_close(out.cpu().numpy(), ref, cfg.name)
+    assert mm.moe_read_status(ws) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,d,f,n,teams", [("qqq", 2048, 256, 6, (4, 1)), ("hhh", 2048, 2944, 12, (4, 4)), ("eee", 1856, 1408, 20, (2, 2))])
+def test_one_expert_alone(orc, bits, d, f, n, teams):
+    assert launch_teams(bits, d, f, 2, n, expert=1) == teams
+    wl = build_workload(_config(bits, d, f, 2, n), orc)
+    layer, y = device_layer(wl), torch.full((n, d), float("nan"), device="cuda")
+    mm.moe_expert_ffn_mixed(layer, 1, dev(wl.x), y, mm.alloc_workspace(layer, n))
+    assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[1], wl.x), f"{bits} n={n}")
