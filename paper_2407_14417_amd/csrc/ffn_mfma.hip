@@ -510,7 +510,7 @@ __host__ __device__ inline int team_steps(int steps, int teams) {
 }
 
 // KS: teams that the 4 wavefronts make, which share the contraction range (teams_for).  Launches of few workgroups are bound by
-// the chain of steps of each, not by memory: three 4-bit experts of 6784 x 512, 42 tokens, block 63.9 -> 47.3 us with two teams; five
+// the chain of steps of each, not by memory: three 4-bit experts of 6784 x 512, 42 tokens, block 64.4 -> 47.5 us with two teams, 38.9 with four; five
 // 16-bit ones of 512 x 7808, 8 tokens, 76.6 -> 43.0 with four.
 template <bool UP, int CT, bool WIDE, bool HALF, int SPB, int KS>
 __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma_kernel(const MfmaArgs a) {
@@ -638,7 +638,8 @@ template <bool UP, int CT, bool WIDE, bool HALF, int SPB = spb_for(CT), int KS =
 void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr int NA = CT <= 2 ? kNASmall : 4;
     // activation stages per team + 4 wavefronts x NA operands of weight staging
-    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * 4096;
+    // (four teams with chunks of two tiles: launches without 16-bit experts only, whose staging no longer fits)
+    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (CT * KS == 8 ? 2048 : 4096);
     const size_t lds_bytes = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
     static std::atomic<unsigned long long> configured{0};
     allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS>, lds_max, configured);
@@ -677,8 +678,11 @@ bool one_step_per_stage(const MfmaArgs& a, dim3 grid, bool up) {
 //   four: 16 x 61 76.6, 54.8, 43.0; 24 x 22 32.0, 25.8, 22.5; 36 x 29 40.7, 32.6, 26.8; 44 x 37 57.0, 44.4, 37.0; from some 50
 //     on either may be faster (56 x 59 72.3, 51.6, 41.5; 56 x 61 106.1, 85.3, 90.2; 60 x 23 45.5, 39.7, 44.1), 72 x 33 44.7, 35.5, 42.0.
 //   two: 60 x 17 40.2, 34.9; 120 x 48 72.5, 60.2; 160 x 18 35.5, 30.5; without 16-bit experts up to 340 (224 x 38 88.6, 77.7;
-//     340 x 52 113.0, 103.0; 378 x 9 36.8, 42.5), with them 192 (160 x 17 39.9, 36.8; 220 x 29 93.9, 98.6), chunks of two tiles,
-//     whose stages take twice the LDS, 170 (160 x 23 59.5, 51.7; 266 x 4 30.5, 37.5).
+//     340 x 52 113.0, 103.0; 378 x 9 36.8, 42.5), with them 192 (160 x 17 39.9, 36.8; 220 x 29 93.9, 98.6).
+// Chunks of two tiles: the stages of two teams leave room for one workgroup per compute unit, so two while each has one of its own,
+// also if one expert has a chunk more than expected (110 x 16 39.9, 34.0; 130 x 15 42.0, 43.8; 182 x 4 30.5, 37.5; 126 x 27, all 16-bit, with
+// a chunk per expert 54.5, 46.6, with one more 58.5, 64.7), four, which fit beside the staging of codes only, as above
+// without 16-bit experts (32 x 53 64.4, 47.5, 38.9; 30 x 57 69.5, 51.0, 42.4; 32 x 32 45.1, 34.2, 29.5).
 // (By the experts' precisions, resident or not: a call that runs some of them later sums in the same order.)
 int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     if (a.waves || ct > 2) return 1;
@@ -689,8 +693,10 @@ int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     };
     const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
     const int wgs = grid.x * (alone ? (int)grid.y : std::min(a.P, likely_chunks(a.P, a.E, 16 * ct)));
-    if (ct == 1 && 5 * wgs <= (int)kComputeUnits && fits(4)) return 4;
-    return wgs <= (ct == 2 ? 170 : any16 ? 192 : 340) && fits(2) ? 2 : 1;
+    if ((ct == 1 || !any16) && 5 * wgs <= (int)kComputeUnits && fits(4)) return 4;
+    // (chunks of two tiles: one per expert, and one expert with two)
+    const int pairs = grid.x * (alone ? (int)grid.y : std::min(a.P, a.E) + 1);
+    return (ct == 2 ? pairs <= (int)kComputeUnits / 2 : wgs <= (any16 ? 192 : 340)) && fits(2) ? 2 : 1;
 }
 
 template <bool UP, bool WIDE, bool HALF>
@@ -702,7 +708,8 @@ void launch_ct_w(const MfmaArgs& a, const LaunchForm& form, int teams, dim3 grid
             else launch_one<UP, 1, WIDE, HALF>(a, grid, st);
             break;
         case 2:
-            if (teams == 2) launch_one<UP, 2, WIDE, HALF, spb_for(2), 2>(a, grid, st);
+            if (teams == 4) launch_one<UP, 2, WIDE, HALF, spb_for(2), 4>(a, grid, st);
+            else if (teams == 2) launch_one<UP, 2, WIDE, HALF, spb_for(2), 2>(a, grid, st);
             else launch_one<UP, 2, WIDE, HALF>(a, grid, st);
             break;
         case 4:

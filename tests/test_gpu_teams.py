@@ -43,9 +43,11 @@ CASES = [
     ("hhh", 2624, 512, 2, 7, (4, 1)), ("hhh", 1344, 512, 2, 7, (2, 1)), ("qqe", 1088, 704, 3, 4, (2, 1)),
     ("qhqe", 256, 2944, 2, 13, (1, 4)), ("qqqq", 320, 2880, 1, 17, (1, 4)), ("qqqq", 256, 3968, 1, 34, (1, 4)),
     ("eeh", 576, 2944, 3, 15, (1, 4)), ("hh", 512, 6016, 1, 9, (2, 4)), ("qqqq", 512, 512, 2, 2, (2, 1)),
-    ("hhhh", 640, 1408, 2, 8, (1, 2)), ("hhh", 256, 2176, 2, 20, (1, 2)), ("qqq", 256, 2944, 3, 24, (1, 2)),
+    ("hhhh", 640, 1408, 2, 8, (1, 2)), ("hhh", 256, 2176, 2, 20, (1, 2)), ("qqq", 256, 2944, 3, 24, (1, 4)),
     ("hhe", 320, 2368, 3, 22, (1, 2)), ("qqq", 1152, 640, 2, 40, (2, 1)), ("heq", 960, 832, 2, 47, (2, 2)),
-    ("qqqqqqqq", 1024, 1408, 2, 24, (2, 2)),
+    ("qqqqqqqq", 1024, 1408, 2, 24, (2, 2)), ("qqq", 2048, 256, 3, 25, (4, 1)), ("ee", 1856, 384, 2, 31, (4, 1)),
+    ("eqe", 1920, 256, 1, 60, (4, 1)), ("qq", 256, 3968, 2, 20, (1, 4)), ("qqqqq", 2048, 1280, 4, 28, (2, 1)),
+    ("qqqqq", 1920, 1664, 4, 28, (1, 2)),
 ]
 
 
@@ -74,7 +76,7 @@ def test_block(orc, bits, d, f, k, T, teams):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("bits,d,f,n,teams", [("qqq", 2048, 256, 6, (4, 1)), ("hhh", 2048, 2944, 12, (4, 4)), ("eee", 1856, 1408, 20, (2, 2))])
+@pytest.mark.parametrize("bits,d,f,n,teams", [("qqq", 2048, 256, 6, (4, 1)), ("hhh", 2048, 2944, 12, (4, 4)), ("eee", 1856, 1408, 20, (4, 2)), ("hhh", 1856, 1408, 20, (2, 2))])
 def test_one_expert_alone(orc, bits, d, f, n, teams):
     assert launch_teams(bits, d, f, 2, n, expert=1) == teams
     wl = build_workload(_config(bits, d, f, 2, n), orc)
