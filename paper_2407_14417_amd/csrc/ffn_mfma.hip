@@ -688,7 +688,7 @@ int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     if (a.waves || ct > 2) return 1;
     const auto fits = [&](int teams) {   // every part of every range holds two steps at least
         const auto ok = [&](int steps) { return steps - (teams - 1) * team_steps(steps, teams) >= 2; };
-        const int steps = a.k_per_split / kKTile, all = contraction_steps(a.K);
+        const int steps = contraction_steps(a.k_per_split), all = contraction_steps(a.K);   // (unsplit: k_per_split is K)
         return ok(steps) && ok(all - (splits - 1) * steps);
     };
     const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;

@@ -48,6 +48,9 @@ CASES = [
     ("qqqqqqqq", 1024, 1408, 2, 24, (2, 2)), ("qqq", 2048, 256, 3, 25, (4, 1)), ("ee", 1856, 384, 2, 31, (4, 1)),
     ("eqe", 1920, 256, 1, 60, (4, 1)), ("qq", 256, 3968, 2, 20, (1, 4)), ("qqqqq", 2048, 1280, 4, 28, (2, 1)),
     ("qqqqq", 1920, 1664, 4, 28, (1, 2)),
+    # odd multiples of 64 take as many teams as the whole steps they round up to; the last team's part is a step and a half
+    ("qqq", 704, 256, 2, 4, (2, 1)), ("qqq", 768, 256, 2, 4, (2, 1)), ("heq", 960, 256, 2, 4, (4, 1)), ("heq", 1024, 256, 2, 4, (4, 1)),
+    ("hhe", 704, 256, 2, 20, (2, 1)), ("qqe", 960, 256, 2, 22, (4, 1)),
 ]
 
 
