@@ -17,6 +17,7 @@
 // one barrier per stage.  The launches with 128-row chunks of whole steps are in ffn_prefill.hip.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -670,33 +671,54 @@ bool one_step_per_stage(const MfmaArgs& a, dim3 grid, bool up) {
     return grid.x * chunks > kComputeUnits || a.k_per_split / kKTile <= 10;
 }
 
+// Chunks of at most `cap` rows that an even load of P pairs over E experts, k of them per token, makes on average: experts
+// that get any rows, and those with more than one, two, .. chunks, rows per expert taken as normal about their mean.  (1500 random
+// blocks: within 0.91 to 1.12 of the chunks there were in nine of ten; skewed loads of Zipf 0.6 and 1.2 have up to 1.45 times as many in
+// chunks of 32, fewer in chunks of 16.)
+double expected_chunks(int P, int E, int k, int cap) {
+    const double mean = (double)P / E, share = (double)k / E, sd = std::max(std::sqrt(mean * (1.0 - share)), 1e-6);
+    const int T = P / k;                                            // most rows of an expert
+    double n = 1.0 - std::pow(1.0 - share, T);
+    for (int rows = cap; rows < T; rows += cap) {
+        const double more = 0.5 * std::erfc((rows + 0.5 - mean) / (sd * std::sqrt(2.0)));
+        if (more < 1e-3) break;
+        n += more;
+    }
+    return E * n;
+}
+
 // Teams of wavefronts in a workgroup of a launch with a grid for one: `teams` times as many workgroups then walk 1 / teams of the
 // range each.  A workgroup alone on its compute unit takes 0.7 to 1 us per step, whatever it reads (it has one wavefront per SIMD, each a
 // chain of LDS round trips and expansion), so where compute units have none, chains get shorter; past that every workgroup more
-// stages the same activations again and starts again.  150 random blocks of up to 32 rows per expert, both projections, W =
-// workgroups with one team, W x steps, block with one, two and four teams (us):
-//   four: 16 x 61 76.6, 54.8, 43.0; 24 x 22 32.0, 25.8, 22.5; 36 x 29 40.7, 32.6, 26.8; 44 x 37 57.0, 44.4, 37.0; from some 50
-//     on either may be faster (56 x 59 72.3, 51.6, 41.5; 56 x 61 106.1, 85.3, 90.2; 60 x 23 45.5, 39.7, 44.1), 72 x 33 44.7, 35.5, 42.0.
-//   two: 60 x 17 40.2, 34.9; 120 x 48 72.5, 60.2; 160 x 18 35.5, 30.5; without 16-bit experts up to 340 (224 x 38 88.6, 77.7;
-//     340 x 52 113.0, 103.0; 378 x 9 36.8, 42.5), with them 192 (160 x 17 39.9, 36.8; 220 x 29 93.9, 98.6).
-// Chunks of two tiles: the stages of two teams leave room for one workgroup per compute unit, so two while each has one of its own,
-// also if one expert has a chunk more than expected (110 x 16 39.9, 34.0; 130 x 15 42.0, 43.8; 182 x 4 30.5, 37.5; 126 x 27, all 16-bit, with
-// a chunk per expert 54.5, 46.6, with one more 58.5, 64.7), four, which fit beside the staging of codes only, as above
-// without 16-bit experts (32 x 53 64.4, 47.5, 38.9; 30 x 57 69.5, 51.0, 42.4; 32 x 32 45.1, 34.2, 29.5).
+// stages the same activations again and starts again.  1500 random blocks of up to 32 rows per expert, more than half with an even load, the
+// others skewed (gating biases of Zipf 0.6 and 1.2); W = workgroups with one team at the expected chunks, W x steps; time of the whole block
+// over that with one team (geometric mean, worst), examples with one, two and four teams (us):
+//   one tile, four: while every workgroup has a compute unit, W <= 64, 0.67, 0.94 (two: 0.84); up to 80 0.87, 1.10 (two: 0.86).  60 x 44 61.7,
+//     45.1, 38.8; 66 x 49 67.0, 49.1, 55.4.
+//   one tile, two: while all run at once, three per compute unit without 16-bit experts (2 W <= 768), two with them (2 W <= 512), short of
+//     that by what the chunks may be off, less for long chains, which gain more.  Without: chains of up to 12 steps 0.97, 1.03 up to W 350
+//     and 1.05, 1.15 up to 450, longer ones 0.93, 1.01 up to 380 and 1.05, 1.15 up to 450 (304 x 33 77.9, 70.7; 380 x 22 60.7, 55.3;
+//     400 x 4 34.6, 37.1).  With: 0.94, 1.01 up to 240 and 1.01, 1.13 up to 300 (160 x 33 56.8, 50.0; 300 x 22 60.7, 65.6).
+// Chunks of two tiles: W with at least a chunk per expert and one expert with two.
+//   four: they fit beside the staging of codes only.  W <= 64 0.74, 0.95 (two: 0.81); up to 80 0.88, 1.13 (two: 0.82).  64 x 60 81.6, 62.5, 54.5.
+//   two: the stages of two teams leave room for one workgroup per compute unit, and a second round costs 10 to 20 %.  So while each has one
+//     of its own, W <= 128, and if the chain is short (it gains some 5 % then) also with a chunk more than expected: 0.87, even loads at worst
+//     1.02, skewed ones 1.14 (they may have more chunks); up to 150 1.02, 1.19; up to 200 1.10, 1.22.  126 x 40 68.8, 53.7; 150 x 18 42.3, 46.3.
 // (By the experts' precisions, resident or not: a call that runs some of them later sums in the same order.)
 int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     if (a.waves || ct > 2) return 1;
+    const int steps = contraction_steps(a.k_per_split), units = kComputeUnits;   // (unsplit: k_per_split is K)
     const auto fits = [&](int teams) {   // every part of every range holds two steps at least
-        const auto ok = [&](int steps) { return steps - (teams - 1) * team_steps(steps, teams) >= 2; };
-        const int steps = contraction_steps(a.k_per_split), all = contraction_steps(a.K);   // (unsplit: k_per_split is K)
-        return ok(steps) && ok(all - (splits - 1) * steps);
+        const auto ok = [&](int n) { return n - (teams - 1) * team_steps(n, teams) >= 2; };
+        return ok(steps) && ok(contraction_steps(a.K) - (splits - 1) * steps);
     };
+    if (!fits(2)) return 1;
     const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
-    const int wgs = grid.x * (alone ? (int)grid.y : std::min(a.P, likely_chunks(a.P, a.E, 16 * ct)));
-    if ((ct == 1 || !any16) && 5 * wgs <= (int)kComputeUnits && fits(4)) return 4;
-    // (chunks of two tiles: one per expert, and one expert with two)
-    const int pairs = grid.x * (alone ? (int)grid.y : std::min(a.P, a.E) + 1);
-    return (ct == 2 ? pairs <= (int)kComputeUnits / 2 : wgs <= (any16 ? 192 : 340)) && fits(2) ? 2 : 1;
+    const double expected = alone ? grid.y : expected_chunks(a.P, a.E, a.top_k, 16 * ct);
+    const double chunks = ct == 2 && !alone ? std::max(expected, std::min(a.P, a.E) + 1.0) : expected;
+    if ((ct == 1 || !any16) && 4 * grid.x * chunks <= units && fits(4)) return 4;
+    if (ct == 1) return grid.x * chunks <= (any16 ? 240 : steps > 12 ? 380 : 350) ? 2 : 1;
+    return 2 * grid.x * (!alone && steps <= 10 ? std::max(chunks, expected + 1) : chunks) <= units ? 2 : 1;
 }
 
 template <bool UP, bool WIDE, bool HALF>

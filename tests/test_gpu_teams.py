@@ -59,6 +59,18 @@ def test_rule(bits, d, f, k, T, teams):
     assert launch_teams(bits, d, f, k, T) == teams
 
 
+# Teams of the up-projection on either side of the rule's lines, which count chunks as an even load makes them: of two tiles, where the
+# mean is near a chunk and many experts have two (8 experts, mean of 31 rows: 11 chunks); of one tile, where few rows
+# reach nearly every expert (36 pairs over 10 experts: 10 chunks).  And one workgroup per compute unit.
+@pytest.mark.parametrize("bits,d,f,k,T,up", [
+    ("q" * 8, 2048, 896, 1, 248, 1), ("q" * 8, 2048, 640, 1, 248, 2), ("q" * 8, 2048, 896, 1, 152, 2), ("q" * 16, 2048, 448, 2, 240, 1),
+    ("h" * 8, 2048, 768, 1, 248, 1), ("q" * 10, 896, 2688, 4, 9, 1), ("q" * 10, 896, 2176, 4, 9, 2), ("h" * 10, 896, 1600, 4, 9, 1),
+    ("h" * 10, 896, 1536, 4, 9, 2), ("q" * 8, 2048, 512, 2, 32, 4), ("q" * 8, 2048, 576, 2, 32, 2),
+])
+def test_rule_counts_chunks(bits, d, f, k, T, up):
+    assert launch_teams(bits, d, f, k, T)[0] == up
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits,d,f,k,T,teams", CASES)
 def test_block(orc, bits, d, f, k, T, teams):
