@@ -179,8 +179,9 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
         zbase[t] = QUANT ? scalar_ptr(m.zero + (c.k_begin >> 6)) : nullptr;
         soff[t] = (uint32_t)row * (uint32_t)(K >> 6) * 2;
     }
-    // (what the 128-bit scale loads below ask of the arrays, and of the rows: a part of an uneven range may hold whole fours)
-    bool sz_aligned16 = KS == 1 || K % 512 == 0;
+    // (what the 128-bit scale loads below ask of the arrays, and of the rows: a range of uneven splits, or a team's part of one, may
+    // hold whole fours of steps where rows do not)
+    bool sz_aligned16 = K % 512 == 0;
 #pragma unroll
     for (int t = 0; t < NA; ++t)
         sz_aligned16 = sz_aligned16 && !(((uintptr_t)sbase[t] | (uintptr_t)zbase[t]) & 15);

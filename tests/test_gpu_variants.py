@@ -261,6 +261,20 @@ def test_uneven_splits(orc, d, f, T):
         assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[e], wl.x), f"{cfg.name} expert {e}")
 
 
+# Ranges of four steps of 7 and 19, which ask for scales 128 bits at a time where rows of scales start on 16-byte boundaries:
+# these are 28 and 76 bytes apart.
+@pytest.mark.parametrize("d,f,T,splits", [(320, 896, 4, 2), (576, 2432, 3, 5)])
+def test_uneven_splits_of_whole_fours(orc, d, f, T, splits):
+    down = common.launch_forms([mm.PREC_INT4G64] * 3, d, f, 1, T)[1]
+    assert (down.half, down.ct, down.splits, down.steps_per_split) == (0, 1, splits, 4)
+    cfg = common.Config(f"fours_d{d}_f{f}_T{T}", d, f, 3, 1, T, (0, 1, 2))
+    wl = build_workload(cfg, orc)
+    ref, ref_idx, _ = orc.layer_forward(wl.x, wl.wg, wl.experts, 1)
+    out, idx, _ = _run_block(device_layer(wl), wl.x, 1)
+    assert np.array_equal(idx, ref_idx)
+    assert_ffn_close(out, ref, cfg.name)
+
+
 @pytest.mark.parametrize("bits", [4, 8, 16])
 def test_half_step_keeps_neighbours_apart(orc, bits):
     """A row's end is the next row's start in memory: infinities at the start of a token, of a hidden row and of a
