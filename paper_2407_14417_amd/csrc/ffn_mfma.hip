@@ -641,7 +641,7 @@ void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
     constexpr int NA = CT <= 2 ? kNASmall : 4;
     // activation stages per team + 4 wavefronts x NA operands of weight staging
     // (four teams with chunks of two tiles: launches without 16-bit experts only, whose staging no longer fits)
-    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (CT * KS == 8 ? 2048 : 4096);
+    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (CT == 2 && KS == 4 ? 2048 : 4096);
     const size_t lds_bytes = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
     static std::atomic<unsigned long long> configured{0};
     allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS>, lds_max, configured);
