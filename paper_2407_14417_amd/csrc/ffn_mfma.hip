@@ -491,6 +491,24 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
     store_results<UP, NCT, NA>(c, acc, out_base, wave, r16, c4);
 }
 
+// Steps of each of `teams` parts of a range, the last of which may be shorter: whole fours where that comes out even (the wide
+// loads of scales), else whole pairs (units of 4-bit codes).
+__host__ __device__ inline int team_steps(int steps, int teams) {
+    const int unit = steps % (4 * teams) == 0 ? 4 : 2;
+    return (steps + teams * unit - 1) / (teams * unit) * unit;
+}
+
+// LDS of a workgroup of grouped_mfma_kernel: two activation stages for each team, then weight staging, `unit` bytes for each A operand of
+// the 4 wavefronts (c.unit_bytes; a team's part holds its own).
+constexpr size_t lds_bytes_for(int ct, int spb, int teams, int unit) {
+    return (size_t)teams * 2 * 16 * ct * (spb * kKTile * 2 + 16) + 4 * (ct <= 2 ? kNASmall : 4) * unit;
+}
+// Four teams with chunks of two tiles leave no room for the staging of 16-bit weights: such launches hold no 16-bit experts (teams_for) and
+// have no code for them.
+constexpr bool room_for_16bit(int ct, int spb, int teams) {
+    return lds_bytes_for(ct, spb, teams, 4096) + (ct <= 2 ? 4 * 16 * ct * sizeof(uint16_t) : 0) <= 160 * 1024;
+}
+
 // WIDE: the block holds 8-bit experts as well.  The 8-bit body needs more registers than the other two, and a
 // kernel's register count is that of its largest body, so blocks without 8-bit experts get a kernel without it
 // (and keep four wavefronts per SIMD at few rows per expert).  In the wide kernel tile_body has variants for 1, 2, 4 and 8
@@ -504,13 +522,7 @@ __device__ __forceinline__ void tile_body(const TileCtx& c, const DevExpert& ee,
 // of two (one_step_per_stage): their stages and weight staging then fit LDS twice (67 KB where two steps want 100), and two
 // wavefronts per SIMD are worth more than half the barriers.  Block with 200 tokens, Mixtral shape: 4-bit 359 -> 306 us,
 // 8-bit 408 -> 372; 4-bit 2048 x 5632, 160 tokens 117 -> 95.  (Contractions that end with half a step lose 7 %.)
-// Steps of each of `teams` parts of a range, the last of which may be shorter: whole fours where that comes out even (the wide
-// loads of scales), else whole pairs (units of 4-bit codes).
-__host__ __device__ inline int team_steps(int steps, int teams) {
-    const int unit = steps % (4 * teams) == 0 ? 4 : 2;
-    return (steps + teams * unit - 1) / (teams * unit) * unit;
-}
-
+//
 // KS: teams that the 4 wavefronts make, which share the contraction range (teams_for).  Launches of few workgroups are bound by
 // the chain of steps of each, not by memory: three 4-bit experts of 6784 x 512, 42 tokens, block 64.4 -> 47.5 us with two teams, 38.9 with four; five
 // 16-bit ones of 512 x 7808, 8 tokens, 76.6 -> 43.0 with four.
@@ -519,7 +531,7 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     constexpr int MC = 16 * CT;                  // activation rows per chunk
     constexpr int NA = CT <= 2 ? kNASmall : 4;   // A operands per wavefront
     constexpr int NT = (UP ? 32 * NA : 64 * NA) / KS;   // weight rows per workgroup
-    extern __shared__ __align__(16) uint8_t lds[];   // [2][MC][SPB * 256 + 16]
+    extern __shared__ __align__(16) uint8_t lds[];   // per team: stages [2][MC][SPB * 256 + 16], weight staging (lds_bytes_for)
     const int tid = threadIdx.x;
     int tile_x, split_z;
     place_workgroup(a.tiles, tile_x, split_z);
@@ -614,7 +626,8 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
     }
     const int prec = ee.prec;
     const int nct = (c.rows + 15) >> 4;          // 16-row tiles that hold any rows
-    constexpr bool k16 = CT != 4 || HALF;        // (64-row chunks at whole steps: blocks with 16-bit experts take ffn_prefill.hip)
+    // (64-row chunks at whole steps: blocks with 16-bit experts take ffn_prefill.hip)
+    constexpr bool k16 = (CT != 4 || HALF) && room_for_16bit(CT, SPB, KS);
     // the straight-line body for exactly the chunk's tiles where the launch can have that many (the clamp keeps
     // the smaller launches from instantiating bodies they never run)
 #define MOEMIX_BODY(n)                                                                                          \
@@ -638,11 +651,8 @@ __global__ __launch_bounds__(256, CT == 4 && SPB == 1 ? 2 : 1) void grouped_mfma
 
 template <bool UP, int CT, bool WIDE, bool HALF, int SPB = spb_for(CT), int KS = 1>
 void launch_one(const MfmaArgs& a, dim3 grid, hipStream_t st) {
-    constexpr int NA = CT <= 2 ? kNASmall : 4;
-    // activation stages per team + 4 wavefronts x NA operands of weight staging
-    // (four teams with chunks of two tiles: launches without 16-bit experts only, whose staging no longer fits)
-    const size_t lds_max = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (CT == 2 && KS == 4 ? 2048 : 4096);
-    const size_t lds_bytes = KS * 2u * 16 * CT * (SPB * kKTile * 2 + 16) + 4 * NA * (size_t)a.unit_bytes;
+    const size_t lds_max = lds_bytes_for(CT, SPB, KS, room_for_16bit(CT, SPB, KS) ? 4096 : 2048);
+    const size_t lds_bytes = lds_bytes_for(CT, SPB, KS, a.unit_bytes);
     static std::atomic<unsigned long long> configured{0};
     allow_lds((const void*)grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS>, lds_max, configured);
     grouped_mfma_kernel<UP, CT, WIDE, HALF, SPB, KS><<<grid, 256, lds_bytes, st>>>(a);
@@ -717,7 +727,7 @@ int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
     const double expected = alone ? grid.y : expected_chunks(a.P, a.E, a.top_k, 16 * ct);
     const double chunks = ct == 2 && !alone ? std::max(expected, std::min(a.P, a.E) + 1.0) : expected;
-    if ((ct == 1 || !any16) && 4 * grid.x * chunks <= units && fits(4)) return 4;
+    if ((!any16 || room_for_16bit(ct, spb_for(ct), 4)) && 4 * grid.x * chunks <= units && fits(4)) return 4;
     if (ct == 1) return grid.x * chunks <= (any16 ? 240 : steps > 12 ? 380 : 350) ? 2 : 1;
     return 2 * grid.x * (!alone && steps <= 10 ? std::max(chunks, expected + 1) : chunks) <= units ? 2 : 1;
 }
