@@ -704,8 +704,8 @@ double expected_chunks(int P, int E, int k, int cap) {
 // stages the same activations again and starts again.  1500 random blocks of up to 32 rows per expert, more than half with an even load, the
 // others skewed (gating biases of Zipf 0.6 and 1.2); W = workgroups with one team at the expected chunks, W x steps; time of the whole block
 // over that with one team (geometric mean, worst), examples with one, two and four teams (us):
-//   one tile, four: while every workgroup has a compute unit, W <= 64, 0.67, 0.94 (two: 0.84); up to 80 0.87, 1.10 (two: 0.86).  60 x 44 61.7,
-//     45.1, 38.8; 66 x 49 67.0, 49.1, 55.4.
+//   one tile, four: while every workgroup has a compute unit, W (whole chunks) <= 64, 0.67, 0.94 (two: 0.84); up to 80 0.87, 1.10 (two: 0.86).
+//     60 x 44 61.7, 45.1, 38.8; 66 x 49 67.0, 49.1, 55.4; 13 columns of 4.9 chunks, 33 steps 38.0, 31.8, 37.7.
 //   one tile, two: while all run at once, three per compute unit without 16-bit experts (2 W <= 768), two with them (2 W <= 512), short of
 //     that by what the chunks may be off, less for long chains, which gain more.  Without: chains of up to 12 steps 0.97, 1.03 up to W 350
 //     and 1.05, 1.15 up to 450, longer ones 0.93, 1.01 up to 380 and 1.05, 1.15 up to 450 (304 x 33 77.9, 70.7; 380 x 22 60.7, 55.3;
@@ -727,7 +727,7 @@ int teams_for(const MfmaArgs& a, int ct, dim3 grid, int splits) {
     const bool alone = a.direct_expert >= 0, any16 = alone ? (a.prec16 >> a.direct_expert) & 1 : a.prec16 != 0;
     const double expected = alone ? grid.y : expected_chunks(a.P, a.E, a.top_k, 16 * ct);
     const double chunks = ct == 2 && !alone ? std::max(expected, std::min(a.P, a.E) + 1.0) : expected;
-    if ((!any16 || room_for_16bit(ct, spb_for(ct), 4)) && 4 * grid.x * chunks <= units && fits(4)) return 4;
+    if ((!any16 || room_for_16bit(ct, spb_for(ct), 4)) && 4 * grid.x * std::round(chunks) <= units && fits(4)) return 4;
     if (ct == 1) return grid.x * chunks <= (any16 ? 240 : steps > 12 ? 380 : 350) ? 2 : 1;
     return 2 * grid.x * (!alone && steps <= 10 ? std::max(chunks, expected + 1) : chunks) <= units ? 2 : 1;
 }

@@ -66,6 +66,7 @@ def test_rule(bits, d, f, k, T, teams):
     ("q" * 8, 2048, 896, 1, 248, 1), ("q" * 8, 2048, 640, 1, 248, 2), ("q" * 8, 2048, 896, 1, 152, 2), ("q" * 16, 2048, 448, 2, 240, 1),
     ("h" * 8, 2048, 768, 1, 248, 1), ("q" * 10, 896, 2688, 4, 9, 1), ("q" * 10, 896, 2176, 4, 9, 2), ("h" * 10, 896, 1600, 4, 9, 1),
     ("h" * 10, 896, 1536, 4, 9, 2), ("q" * 8, 2048, 512, 2, 32, 4), ("q" * 8, 2048, 576, 2, 32, 2),
+    ("q" * 5, 4160, 832, 2, 8, 2),   # (13 columns of 4.9 chunks: 65 workgroups)
 ])
 def test_rule_counts_chunks(bits, d, f, k, T, up):
     assert launch_teams(bits, d, f, k, T)[0] == up
