@@ -11,7 +11,7 @@ import torch
 from paper_2407_14417_amd import binding as mm
 from tests import common
 from tests.common import assert_ffn_close, build_workload
-from tests.gpu_common import dev, device_layer
+from tests.gpu_common import dev, device_layer, device_layer_with_offloaded
 
 PREC = {"h": mm.PREC_FP16, "q": mm.PREC_INT4G64, "e": mm.PREC_INT8G64}
 
@@ -99,3 +99,77 @@ def test_one_expert_alone(orc, bits, d, f, n, teams):
     layer, y = device_layer(wl), torch.full((n, d), float("nan"), device="cuda")
     mm.moe_expert_ffn_mixed(layer, 1, dev(wl.x), y, mm.alloc_workspace(layer, n))
     assert_ffn_close(y.cpu().numpy(), orc.expert_ffn(wl.experts[1], wl.x), f"{bits} n={n}")
+
+
+def _forward(layer, x, k, ws=None):
+    out = torch.full_like(x, float("nan"))
+    idx = torch.empty((x.shape[0], k), dtype=torch.int32, device="cuda")
+    ws = mm.alloc_workspace(layer, x.shape[0]) if ws is None else ws
+    ws.fill_(0xFF)                                                # NaN wherever it is floats
+    mm.moe_layer_forward(layer, x, out, ws, idx)
+    return out.cpu().numpy(), idx.cpu().numpy(), mm.moe_read_status(ws)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,d,f,k,T,teams", [("qheq", 1024, 2944, 2, 6, (2, 4)), ("qqqq", 2048, 256, 2, 6, (4, 1)), ("qeqe", 2048, 1408, 1, 70, (2, 2)),
+                                                ("qqee", 1024, 3968, 2, 34, (1, 4))])
+def test_missing_expert_is_left_out(orc, bits, d, f, k, T, teams):
+    """Every tile of a missing expert's rows is zero, whatever the workspace held, in tiles of a half and a quarter of the rows."""
+    assert launch_teams(bits, d, f, k, T) == teams
+    cfg = _config(bits, d, f, k, T)
+    wl = build_workload(cfg, orc)
+    ref_idx, ref_gate = orc.route(wl.x, wl.wg, k)
+    victim = int(np.bincount(ref_idx.reshape(-1)).argmax())
+    layer = device_layer(wl)
+    layer.experts[victim].resident = False
+    layer = mm.Layer(d, f, k, layer.w_gate, layer.experts)
+    out, idx, status = _forward(layer, dev(wl.x), k)
+    assert status == mm.STATUS_NOT_RESIDENT and np.array_equal(idx, ref_idx)
+    ref = np.zeros((T, d))
+    for e in set(range(len(bits))) - {victim}:
+        t, s = np.nonzero(ref_idx == e)
+        if t.size:
+            ref[t] += ref_gate[t, s][:, None].astype(np.float64) * orc.expert_ffn(wl.experts[e], wl.x[t])
+    assert_ffn_close(out, ref, cfg.name)
+    assert not out[(ref_idx == victim).all(axis=1)].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,d,f,k,T,teams", [("qheq", 1024, 2944, 2, 6, (2, 4)), ("heqh", 1024, 1024, 2, 6, (4, 1)), ("qeqe", 1856, 2944, 2, 10, (2, 4)),
+                                                ("qeqe", 2048, 576, 1, 70, (4, 1))])
+@pytest.mark.parametrize("offloaded,n_slots", [((0, 3), 1), ((0, 1, 2, 3), 2)])
+def test_swapped_experts_sum_in_the_same_order(orc, bits, d, f, k, T, teams, offloaded, n_slots):
+    """Bit for bit the block with every expert resident, also where all experts of a precision come later."""
+    assert launch_teams(bits, d, f, k, T) == teams
+    wl = build_workload(_config(bits, d, f, k, T), orc)
+    x = dev(wl.x)
+    want, want_idx, status = _forward(device_layer(wl), x, k)
+    assert status == 0
+    layer, hosts = device_layer_with_offloaded(wl, set(offloaded))
+    ws, out = mm.alloc_workspace(layer, T), torch.full_like(x, float("nan"))
+    ws.fill_(0xFF)
+    missed = mm.moe_layer_forward_swap(layer, mm.Swap(layer, hosts, n_slots, T), x, out, ws)
+    assert mm.moe_read_status(ws) == 0 and missed == len({int(e) for e in want_idx.reshape(-1)} & set(offloaded))
+    assert np.array_equal(out.cpu().numpy().view(np.uint16), want.view(np.uint16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits,d,f,T,teams", [("q", 1984, 448, 6, (4, 1)), ("e", 1984, 448, 6, (4, 1)), ("h", 1984, 448, 6, (4, 1)),
+                                              ("q", 320, 3904, 20, (1, 4)), ("e", 320, 3904, 20, (1, 4)), ("h", 320, 3904, 20, (1, 2))])
+def test_half_step_of_the_last_team_keeps_neighbours_apart(orc, bits, d, f, T, teams):
+    """A row's end is the next row's start in memory: infinities at the start of a token, of a hidden row and of a weight row stay
+    with their token and their output column."""
+    assert launch_teams(bits, d, f, 1, T) == teams
+    wl = build_workload(_config(bits, d, f, 1, T), orc)
+    layer = device_layer(wl)
+    clean, _, _ = _forward(layer, dev(wl.x), 1)
+    x = wl.x.copy()
+    x[3, 0] = np.inf
+    got, _, _ = _forward(layer, dev(x), 1)
+    keep = np.arange(T) != 3
+    assert np.array_equal(got[keep], clean[keep]) and not np.isfinite(got[3]).all()
+    w2 = layer.experts[0].w2
+    (w2.data if bits == "h" else w2.scale)[7, 0] = float("inf")
+    got, _, _ = _forward(layer, dev(wl.x), 1)
+    cols = np.arange(d) != 7
+    assert np.array_equal(got[:, cols], clean[:, cols]) and not np.isfinite(got[:, 7]).any()
