@@ -94,8 +94,8 @@ __device__ __forceinline__ void share_sums(const TileCtx& c, float4_t (&acc)[NA]
 // A wavefront holds NA A operands (16-row tiles of weights) per step.  UP: two matrices (w1, w3), NA/2 tiles each
 // (workgroup of 4 wavefronts: 32 NA rows); down: one matrix (w2), NA tiles (workgroup: 64 NA rows).  NA = 4 for
 // chunks of many activation rows (each B operand read from LDS feeds 4 products), NA = 2 when a chunk holds at
-// most 32 rows: the kernel is then bound by the expansion of the codes, and half the registers per wavefront
-// buy twice the wavefronts per SIMD to hide its latencies.
+// most 32 rows: the kernel is then bound by its weight stream and a chain of latencies, and half the registers per
+// wavefront buy twice the wavefronts per SIMD to hide them.
 // NCT = 16-row activation tiles computed (exactly the tiles that hold rows), so the inner loops are
 // straight-line code.  SPB = 128-column steps per LDS stage (and per barrier): a launch with few activation
 // rows per chunk stages more columns at a time, so that the LDS buffers always hold 128 x 128 elements.
